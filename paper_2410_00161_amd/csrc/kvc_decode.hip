@@ -271,6 +271,7 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   } else {
     const int total_items = A.header[HW_TOTAL_ITEMS];
     const int short_items = A.header[HW_SHORT_ITEMS];
+    const int base = A.header[HW_PLAN_BASE];   // (0 where no plan was made)
     if (NW == 4 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
     if (NW == 4 && A.plan && (int)blockIdx.x < A.gsel) {
       // a list kept from kvc_decode_plan was made without the output at hand: the zero rows of a
@@ -282,7 +283,8 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
     if (total_items > A.cap || short_items < 0 || short_items > total_items) return;
     const int n_long = total_items - short_items;
     if ((int)blockIdx.x >= (NW == 4 ? n_long : short_items)) return;
-    it = A.items[NW == 4 ? blockIdx.x : n_long + blockIdx.x];   // the short items end the list
+    if (A.plan && (base < 0 || base > A.plan_cap - total_items)) return;
+    it = A.items[base + (NW == 4 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
     Tc = A.header[HW_CHUNK_T];
   }
   const int g = it.g, t0 = it.t0, n_tok = it.n_tok, nch = it.nch;
@@ -733,10 +735,12 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
     it = sl.it;
     Tc = sl.T;
   } else {
-    if (p >= A.header[HW_TOTAL_PARTIALS] || p >= A.cap) return;
-    const int item = A.slot_item[p];
-    if (item < 0 || item >= A.header[HW_TOTAL_ITEMS] || item >= A.cap) return;
-    it = A.items[item];
+    const int total_items = A.header[HW_TOTAL_ITEMS], base = A.header[HW_PLAN_BASE];
+    if (p >= A.header[HW_TOTAL_PARTIALS] || p >= total_items || p >= A.cap) return;
+    if (A.plan && (base < 0 || base > A.plan_cap - total_items)) return;
+    const int item = A.slot_item[base + p];
+    if (item < 0 || item >= total_items || item >= A.cap) return;
+    it = A.items[base + item];
     Tc = A.header[HW_CHUNK_T];
   }
   const int nch = it.nch;
@@ -1141,6 +1145,7 @@ static int decode_args_check(const kvc_config* cfg, const kvc_state* st, const v
 // plan_mode 0: an ordinary call (work list, chunks, combine).  1: only the work lists, one per
 // layer, kept in the workspace (q and out are not looked at).  2: layer `layer_begin` from its kept list.
 enum { PLAN_NONE = 0, PLAN_BUILD = 1, PLAN_USE = 2 };
+constexpr size_t kPlanRowChunk = 256;
 static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const void* q, float* out,
                              int layer_begin, int layer_end, int accumulate_metric, void* ws, void* stream,
                              int plan_mode = PLAN_NONE, int ctx_plus = 0) {
@@ -1165,7 +1170,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   A.items = (DecodeItem*)W.items; A.slot_item = W.slot_item; A.part_ml = W.part_ml; A.part_acc = W.part_acc; A.stash = W.stash;
   A.header = W.header;
   A.status = W.header;
-  A.plan = 0; A.plan_stride = 0; A.ctx_plus = 0; A.self_list = 0;
+  A.plan = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
   A.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D.d));
 
   int T = 0;
@@ -1201,15 +1206,17 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   // full chunks either way, and one shorter item per head.
   const size_t most_tokens = std::min((size_t)D.N * D.b, (size_t)A.gsel * D.maxb * D.b);   // pool, or the rows of the heads called for
   const size_t bound_pool = (A.adapt_T ? std::max(most_tokens / T, (size_t)410) : most_tokens / T) + (size_t)A.gsel;
-  const size_t Tmin = A.adapt_T ? (size_t)kSmallCallChunk : (size_t)T;
-  const size_t bound_row = (size_t)A.gsel * (((size_t)D.maxb * D.b + Tmin - 1) / Tmin);
-  const size_t grid = bound_pool < bound_row ? bound_pool : bound_row;
+  auto items_of_rows = [&](size_t chunk) { return std::min(bound_pool, (size_t)A.gsel * (((size_t)D.maxb * D.b + chunk - 1) / chunk)); };
+  const size_t grid = items_of_rows(A.adapt_T ? (size_t)kSmallCallChunk : (size_t)T);
   if (grid > 0x7fffffffull) return KVC_ERR_UNSUPPORTED;   // before anything is launched: the work list stays clean
   if (plan_mode != PLAN_NONE) {
-    // every layer's list has `grid` records of its own (the most its call could need)
-    if (grid * (size_t)D.Lyr > (size_t)A.cap) return KVC_ERR_UNSUPPORTED;
+    // Rows with far more room than the pool can fill have no lists: every layer's launch is as large as
+    // full rows would need, and nearly all of it would be empty.  (Lists of chunks of kPlanRowChunk for
+    // all layers' full rows have to fit the records that the workspace has.)
+    if (items_of_rows(kPlanRowChunk) * (size_t)D.Lyr > (size_t)A.cap) return KVC_ERR_UNSUPPORTED;
     A.plan = 1;
-    A.plan_stride = (int)grid;
+    A.plan_cap = A.cap;
+    A.cap = (int)std::min(grid, (size_t)A.cap);
     A.ctx_plus = ctx_plus;
     A.header = W.plan_hdr;
     if (plan_mode == PLAN_BUILD) {
@@ -1219,9 +1226,6 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
       return KVC_OK;
     }
     A.header += (size_t)layer_begin * HW_WORDS;
-    A.items += (size_t)layer_begin * grid;
-    A.slot_item += (size_t)layer_begin * grid;
-    A.cap = (int)grid;
   } else if (small_call && A.gsel <= kSelfListHeads) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {

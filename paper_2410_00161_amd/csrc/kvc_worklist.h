@@ -40,8 +40,9 @@ struct DecodeArgs {
   float* stash;
   int32_t* header;
   // Work lists kept from one launch for every layer (kvc_decode_plan): layer l has its own header
-  // block at header + l * HW_WORDS and its own stretch of plan_stride records of items / slot_item.
-  int plan, plan_stride;  // plan: the work-list kernel runs one workgroup per layer; a decode reads one layer's list
+  // block at header + l * HW_WORDS and its own stretch of the records of items / slot_item.
+  int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
+  int plan_cap;           // records of all layers the workspace holds
   int self_list;          // no work list: every workgroup finds its own item from the lengths (at most kSelfListHeads heads)
   int ctx_plus;           // the plan is made for heads ctx_plus tokens longer than they are now
   int32_t* status;        // the workspace's own header (status word), whatever `header` points at
@@ -192,14 +193,15 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   __shared__ int bins[16], base[16], cur[17], ptot;
   __shared__ unsigned long long tokens;
   __shared__ int live, longest;
+  __shared__ unsigned long long before;
   const int tid = threadIdx.x;
   // a plan: workgroup l lists layer A.l0 + l into that layer's header block and stretch of records
   const int layer = A.plan ? (int)blockIdx.x : 0;
   int32_t* header = A.header + (size_t)layer * (A.plan ? HW_WORDS : 0);
-  DecodeItem* items = A.items + (size_t)layer * A.plan_stride;
-  int32_t* slot_item = A.slot_item + (size_t)layer * A.plan_stride;
-  const int cap = A.plan ? A.plan_stride : A.cap;
-  if (tid == 0) { ptot = 0; tokens = 0; live = 0; longest = 0; }
+  DecodeItem* items = A.items;
+  int32_t* slot_item = A.slot_item;
+  int cap = A.cap;
+  if (tid == 0) { ptot = 0; tokens = 0; live = 0; longest = 0; before = 0; }
   if (tid < 16) bins[tid] = 0;
   if (tid < 17) cur[tid] = 0;
   __syncthreads();
@@ -207,6 +209,21 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   if (tid < A.gsel) {
     g = sel_to_g(A.D, A.l0 + layer, A.nl, tid);
     C = A.ctx[g] + A.ctx_plus;
+  }
+  // The layer's records start behind the most the layers before it can need: a full chunk holds at
+  // least kSmallCallChunk of their tokens, and a head has one shorter chunk.  All layers together
+  // need no more records than the workspace has for one call over them all.  (A stretch of equal
+  // length for every layer would have to hold what full rows hold.)
+  if (A.plan) {
+    const int per = layer * A.D.Hk;
+    unsigned long long t = 0;
+    for (int i = tid; i < A.D.S * per; i += 1024) {
+      const int s = i / per;
+      t += (unsigned long long)max(A.ctx[(size_t)s * A.D.Lyr * A.D.Hk + (i - s * per)] + A.ctx_plus, 0);
+    }
+    for (int m = 32; m >= 1; m >>= 1) t += __shfl_xor(t, m);
+    if ((tid & 63) == 0 && t) atomicAdd(&before, t);
+    // (a plan picks its chunk length on the device: the barrier below serves)
   }
   int T = A.T;
   if (A.adapt_T) {
@@ -217,6 +234,14 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     if ((tid & 63) == 0 && t) { atomicAdd(&tokens, t); atomicAdd(&live, lv); atomicMax(&longest, lm); }
     __syncthreads();
     T = small_call_chunk(A.T, tokens, live, longest);
+  }
+  if (A.plan) {
+    const unsigned long long at = before / kSmallCallChunk + (unsigned long long)layer * A.gsel;
+    const int start = (int)(at < (unsigned long long)A.plan_cap ? at : (unsigned long long)A.plan_cap);
+    items += start;
+    slot_item += start;
+    cap = min(cap, A.plan_cap - start);
+    if (tid == 0) header[HW_PLAN_BASE] = start;
   }
   if (tid == 0) header[HW_CHUNK_T] = T;
   if (tid < A.gsel) {
@@ -237,7 +262,8 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
       run += bins[k];
       if (k >= A.short_class) shorts += bins[k];
     }
-    header[HW_TOTAL_ITEMS] = run;
+    // (a list that does not fit, which lengths the pool can hold never make, is one no decode takes)
+    header[HW_TOTAL_ITEMS] = A.plan && run > cap ? 0x7fffffff : run;
     header[HW_SHORT_ITEMS] = shorts;
   }
   __syncthreads();
