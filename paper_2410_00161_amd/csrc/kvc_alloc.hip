@@ -713,7 +713,7 @@ int kvc_append(const kvc_config* cfg, const kvc_state* st, const void* k_new, co
   A.kc = (char*)st->k_cache; A.vc = (char*)st->v_cache; A.metric = st->metric; A.pos = st->pos;
   A.table = st->block_table; A.ctx = st->ctx_len; A.free_map = st->free_map;
   A.k_new = (const char*)k_new; A.v_new = (const char*)v_new; A.new_pos = new_pos;
-  A.header = W.header; A.part = W.alloc_part; A.list = W.off_b;
+  A.header = W.header; A.part = W.seg_hist; A.list = W.off_b;
   // a workgroup per 1024 heads or 16 KB of the map, whichever asks for more, at most kAppendWgs
   const int by_heads = (A.nsel + kAppendThreads - 1) / kAppendThreads;
   const int by_map = (int)(((size_t)D.N + 16 * kAppendThreads - 1) / (16 * kAppendThreads));
@@ -721,6 +721,7 @@ int kvc_append(const kvc_config* cfg, const kvc_state* st, const void* k_new, co
   if (n_wg > kAppendWgs) n_wg = kAppendWgs;
   const int heads_per_wg = (A.nsel + n_wg - 1) / n_wg;
   const int map_per_wg = (int)(align_up(((size_t)D.N + n_wg - 1) / n_wg, 16));
+  static_assert(kAppendWgs * 3 <= 256, "the counts fit one segment's histogram");
   const int fused = A.nsel <= kAppendFused;
   hipLaunchKernelGGL(append_reserve_kernel, dim3(n_wg), dim3(kAppendThreads), 0, s, A, n_wg, heads_per_wg, map_per_wg, fused);
   KVC_LAUNCH_CHECK();

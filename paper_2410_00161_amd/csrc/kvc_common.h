@@ -64,7 +64,6 @@ struct Workspace {
   int32_t* header;     // [HW_WORDS]
   int32_t* plan_hdr;   // [Lyr][HW_WORDS]     header block of every layer's kept work list (kvc_decode_plan)
   int32_t* tile_sums;  // [ntile_max + 1]
-  int32_t* alloc_part; // [kAppendWgs][3]     what each workgroup of an append counted
   int32_t* off_a;      // [G + 1]  scan over head instances (requests / chunks / ties)
   int32_t* off_b;      // [G + 1]
   int32_t* held;       // [G]      blocks held per head instance
@@ -73,7 +72,7 @@ struct Workspace {
   float*   part_ml;    // [max_items][r][2]   chunk max and sum per query head
   float*   part_acc;   // [max_items][r][d]   chunk un-normalised output
   float*   stash;      // [N*b][r]            chunk-relative exp of every logit
-  int32_t* seg_hist;   // [S][256]            radix histograms per segment
+  int32_t* seg_hist;   // [S][256]            radix histograms per segment; in an append, what its workgroups counted ([kAppendWgs][3])
   int32_t* seg_state;  // [S][8]              prefix, remaining, ties wanted, ...
   int32_t* flag_scan;  // [G][maxb]           per-head prefix count of flagged blocks
   size_t bytes;
@@ -95,7 +94,6 @@ inline Workspace carve(const Dims& D, void* base) {
   w.header = (int32_t*)take(HW_WORDS * 4);
   w.plan_hdr = (int32_t*)take((size_t)D.Lyr * HW_WORDS * 4);
   w.tile_sums = (int32_t*)take(ntile * 4);
-  w.alloc_part = (int32_t*)take((size_t)kAppendWgs * 3 * 4);
   w.off_a = (int32_t*)take(((size_t)D.G + 1) * 4);
   w.off_b = (int32_t*)take(((size_t)D.G + 1) * 4);
   w.held = (int32_t*)take((size_t)D.G * 4);

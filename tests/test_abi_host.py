@@ -130,3 +130,9 @@ def test_binding_refuses_wrong_dtypes_and_strides():
         B._ptr(t, torch.int32)
     with pytest.raises(ValueError):
         B._ptr(t.t())
+
+
+def test_small_pools_need_no_more_workspace_than_their_block_list_did():
+    """A cache at the limit of the fixed scratch array: one head, 64 blocks, a table that fills the rest."""
+    cfg = good_cfg(num_seqs=1, num_layers=1, num_kv_heads=1, group_size=1, num_blocks=64, max_blocks_per_head=8383940)
+    assert B.kvc_workspace_bytes(cfg) <= 33554176 < B.KVC_STATIC_SCRATCH_BYTES
