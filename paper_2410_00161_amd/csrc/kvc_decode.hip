@@ -271,7 +271,8 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   } else {
     const int total_items = A.header[HW_TOTAL_ITEMS];
     const int short_items = A.header[HW_SHORT_ITEMS];
-    const int base = A.header[HW_PLAN_BASE];   // (0 where no plan was made)
+    const bool placed = A.plan && A.plan_stride == 0;
+    const int base = placed ? A.header[HW_PLAN_BASE] : 0;
     if (NW == 4 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
     if (NW == 4 && A.plan && (int)blockIdx.x < A.gsel) {
       // a list kept from kvc_decode_plan was made without the output at hand: the zero rows of a
@@ -283,7 +284,7 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
     if (total_items > A.cap || short_items < 0 || short_items > total_items) return;
     const int n_long = total_items - short_items;
     if ((int)blockIdx.x >= (NW == 4 ? n_long : short_items)) return;
-    if (A.plan && (base < 0 || base > A.plan_cap - total_items)) return;
+    if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
     it = A.items[base + (NW == 4 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
     Tc = A.header[HW_CHUNK_T];
   }
@@ -735,9 +736,10 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
     it = sl.it;
     Tc = sl.T;
   } else {
-    const int total_items = A.header[HW_TOTAL_ITEMS], base = A.header[HW_PLAN_BASE];
+    const bool placed = A.plan && A.plan_stride == 0;
+    const int total_items = A.header[HW_TOTAL_ITEMS], base = placed ? A.header[HW_PLAN_BASE] : 0;
     if (p >= A.header[HW_TOTAL_PARTIALS] || p >= total_items || p >= A.cap) return;
-    if (A.plan && (base < 0 || base > A.plan_cap - total_items)) return;
+    if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
     const int item = A.slot_item[base + p];
     if (item < 0 || item >= total_items || item >= A.cap) return;
     it = A.items[base + item];
@@ -1170,7 +1172,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   A.items = (DecodeItem*)W.items; A.slot_item = W.slot_item; A.part_ml = W.part_ml; A.part_acc = W.part_acc; A.stash = W.stash;
   A.header = W.header;
   A.status = W.header;
-  A.plan = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
+  A.plan = 0; A.plan_stride = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
   A.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D.d));
 
   int T = 0;
@@ -1216,6 +1218,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     if (items_of_rows(kPlanRowChunk) * (size_t)D.Lyr > (size_t)A.cap) return KVC_ERR_UNSUPPORTED;
     A.plan = 1;
     A.plan_cap = A.cap;
+    A.plan_stride = grid * (size_t)D.Lyr <= (size_t)A.cap ? (int)grid : 0;   // (a start of its own costs every launch a dependent load)
     A.cap = (int)std::min(grid, (size_t)A.cap);
     A.ctx_plus = ctx_plus;
     A.header = W.plan_hdr;
@@ -1226,6 +1229,8 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
       return KVC_OK;
     }
     A.header += (size_t)layer_begin * HW_WORDS;
+    A.items += (size_t)layer_begin * A.plan_stride;
+    A.slot_item += (size_t)layer_begin * A.plan_stride;
   } else if (small_call && A.gsel <= kSelfListHeads) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {

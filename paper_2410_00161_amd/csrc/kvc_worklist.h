@@ -42,6 +42,7 @@ struct DecodeArgs {
   // Work lists kept from one launch for every layer (kvc_decode_plan): layer l has its own header
   // block at header + l * HW_WORDS and its own stretch of the records of items / slot_item.
   int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
+  int plan_stride;        // records of a layer's stretch; 0: it starts where its header block says
   int plan_cap;           // records of all layers the workspace holds
   int self_list;          // no work list: every workgroup finds its own item from the lengths (at most kSelfListHeads heads)
   int ctx_plus;           // the plan is made for heads ctx_plus tokens longer than they are now
@@ -198,8 +199,8 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   // a plan: workgroup l lists layer A.l0 + l into that layer's header block and stretch of records
   const int layer = A.plan ? (int)blockIdx.x : 0;
   int32_t* header = A.header + (size_t)layer * (A.plan ? HW_WORDS : 0);
-  DecodeItem* items = A.items;
-  int32_t* slot_item = A.slot_item;
+  DecodeItem* items = A.items + (size_t)layer * A.plan_stride;
+  int32_t* slot_item = A.slot_item + (size_t)layer * A.plan_stride;
   int cap = A.cap;
   if (tid == 0) { ptot = 0; tokens = 0; live = 0; longest = 0; before = 0; }
   if (tid < 16) bins[tid] = 0;
@@ -210,11 +211,12 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     g = sel_to_g(A.D, A.l0 + layer, A.nl, tid);
     C = A.ctx[g] + A.ctx_plus;
   }
-  // The layer's records start behind the most the layers before it can need: a full chunk holds at
-  // least kSmallCallChunk of their tokens, and a head has one shorter chunk.  All layers together
-  // need no more records than the workspace has for one call over them all.  (A stretch of equal
-  // length for every layer would have to hold what full rows hold.)
-  if (A.plan) {
+  // Where stretches of equal length, for what full rows hold, do not fit: the layer's records start
+  // behind the most that the layers before it can need from their lengths (a full chunk holds at least
+  // kSmallCallChunk tokens, and a head has one shorter chunk).  That always fits: all layers together
+  // need no more records than the workspace has for one call over them all.
+  const bool placed = A.plan && A.plan_stride == 0;
+  if (placed) {
     const int per = layer * A.D.Hk;
     unsigned long long t = 0;
     for (int i = tid; i < A.D.S * per; i += 1024) {
@@ -235,7 +237,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     __syncthreads();
     T = small_call_chunk(A.T, tokens, live, longest);
   }
-  if (A.plan) {
+  if (placed) {
     const unsigned long long at = before / kSmallCallChunk + (unsigned long long)layer * A.gsel;
     const int start = (int)(at < (unsigned long long)A.plan_cap ? at : (unsigned long long)A.plan_cap);
     items += start;
