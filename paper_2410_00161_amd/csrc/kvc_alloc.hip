@@ -245,19 +245,67 @@ struct AppendArgs {
   const char* v_new;
   const int32_t* new_pos;
   int32_t* header;
-  int32_t* part;           // [workgroups][3] requests, free blocks, error bits
-  int32_t* list;           // [nsel] requesters of workgroup w from its first head's place on
+  int n_wg, heads_per_wg, map_per_wg;   // workgroups of the reservation, and their shares (map_per_wg in whole tiles)
+  int32_t* part;           // [workgroups][3] requests, free blocks, error bits; then [2][kAppendWgs] requests, free blocks ahead of each
+  int32_t* rank;           // [nsel] rank of a head's request among its workgroup's, -1 = none (many heads)
+  uint32_t* bits;          // [tiles][32] the free map as it was, a bit per block
+  int32_t* tile_free;      // [tiles] free blocks per tile
 };
+constexpr int kAppendTile = 1024;   // blocks per tile of the map: what a wavefront reads at a time
 
 __device__ __forceinline__ int append_head(const AppendArgs& A, int idx) {
   const int s = idx / (A.nl * A.D.Hk);
   return (s * A.D.Lyr + A.l0 + (idx / A.D.Hk) % A.nl) * A.D.Hk + idx % A.D.Hk;
 }
 
-__device__ __forceinline__ void append_one(const AppendArgs& A, int idx, int gl) {
-  const int g = append_head(A, idx);
-  const int C = A.ctx[g];
-  const int blk = A.table[(size_t)g * A.D.maxb + (C >> A.lb)];
+// Inclusive prefix sums over a wavefront (row shifts, then the rows' last lanes broadcast).
+__device__ __forceinline__ int wave_prefix_i(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// Block that is free block number k of the map (k below the number of them), by all lanes of a
+// wavefront: the share, the tile, the word and the bit that hold it.  ahead: free blocks ahead of
+// share `lane`.  FRESH: what this launch's other workgroups left (else an earlier launch's).
+template <bool FRESH>
+__device__ __forceinline__ int nth_free_block(const AppendArgs& A, int ahead, int k, int lane) {
+  auto get = [&](const int32_t* p) { return FRESH ? published_i32(p) : *p; };
+  const int share = __popcll(__ballot(ahead <= k)) - 1;   // the last one: shares without a free block have the next one's number
+  int rest = k - __builtin_amdgcn_readlane(ahead, share);
+  const int per = A.map_per_wg / kAppendTile, n_tiles = (int)(((size_t)A.D.N + kAppendTile - 1) / kAppendTile);
+  const int t1 = min(n_tiles, (share + 1) * per);
+  int tile = share * per;
+  for (;; tile += 64) {
+    if (tile >= t1) return -1;   // (fewer free blocks than were counted: cannot be)
+    const int c = tile + lane < t1 ? get(&A.tile_free[tile + lane]) : 0;
+    const int inc = wave_prefix_i(c);
+    const unsigned long long past = __ballot(inc > rest);
+    if (past) {
+      const int l = __builtin_ctzll(past);
+      rest -= __builtin_amdgcn_readlane(inc - c, l);
+      tile += l;
+      break;
+    }
+    rest -= __builtin_amdgcn_readlane(inc, 63);
+  }
+  const uint32_t word = lane < 32 ? (uint32_t)get((const int32_t*)A.bits + (size_t)tile * 32 + lane) : 0;
+  const int c = __popc(word), inc = wave_prefix_i(c);
+  const unsigned long long past = __ballot(inc > rest);
+  if (!past) return -1;
+  const int l = __builtin_ctzll(past);
+  rest -= __builtin_amdgcn_readlane(inc - c, l);
+  uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)word, l);
+  for (; rest > 0; --rest) w &= w - 1;
+  return tile * kAppendTile + l * 32 + __builtin_ctz(w);
+}
+
+// The new token of head instance g, which holds C tokens, into block blk.
+__device__ __forceinline__ void append_one(const AppendArgs& A, int g, int C, int blk, int gl) {
   const size_t row_bytes = (size_t)A.D.d * kv_esz(A.D.dtype);
   const size_t slot = ((size_t)blk << A.lb) + (C & (A.D.b - 1));
   const int pieces = (int)(row_bytes / 16);
@@ -284,78 +332,148 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x) {
 // 16 bytes of the free map from `at` on (bytes past `end` read as 0)
 __device__ __forceinline__ uint4 free_bytes16(const uint8_t* map, size_t at, size_t end, bool wide) {
   if (wide && at + 16 <= end) return *(const uint4*)(map + at);
-  uint32_t w[4] = {0, 0, 0, 0};
-  for (int k = 0; k < 16; ++k)
-    if (at + k < end) w[k >> 2] |= (uint32_t)map[at + k] << (8 * (k & 3));
-  return make_uint4(w[0], w[1], w[2], w[3]);
+  uint64_t lo = 0, hi = 0;
+#pragma unroll 1
+  for (int k = 0; k < 16 && at + k < end; ++k) {   // (rare, and in every place that reads the map: kept short)
+    const uint64_t byte = (uint64_t)map[at + k] << (8 * (k & 7));
+    if (k < 8) lo |= byte; else hi |= byte;
+  }
+  return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
-// The whole reservation of an append in one launch: which heads need a block (their length fills
-// the blocks they hold), the lowest free blocks for them in ascending head order, the error
-// checks before anything is written; for few heads also the append itself.
+// The reservation of an append in one launch: which heads need a block (their length fills the
+// blocks they hold), the lowest free blocks for them in ascending head order, the error checks before
+// anything is written; for few heads also the append itself.
 //
-// Workgroup w of n looks at its share of the heads and of the free map, leaves its counts and the
-// list of its requesters, and announces itself; the last one to arrive reads all the counts (one
-// wavefront: n <= 64), settles the status and hands the blocks out, walking only the shares of
-// the map that hold the first blocks it needs.  In place of a launch each for counting, for a
-// scan in one workgroup over all heads, and for a second walk over the whole map: a launch costs
-// ~4.5 us in a busy stream whatever it does (with the rows: 16 384 heads, 1.35 M blocks 23.2 ->
-// 12.8 us; one layer of one sequence 16.4 -> 6.6 us).
+// Workgroup w of n looks at its share of the heads and of the free map, leaves the counts, the ranks
+// of its requesters and its share of the map as bits with a count per tile, and announces itself; the
+// last one to arrive reads all the counts (one wavefront: n <= 64) and settles the status.  Every
+// requester then finds its own block (nth_free_block), in the launch that writes the rows, or here for
+// few heads: wherever the free blocks lie, nobody walks the map for them.  In place of a launch each for
+// counting, for a scan in one workgroup over all heads, and for a second walk over the whole map: a
+// launch costs ~4.5 us in a busy stream whatever it does.  Replayed from a graph, four launches against
+// this: 16 384 heads, 1.35 M blocks of which a fifth or a thousandth is free 24.1 and 20.4 -> 12.1 and
+// 12.2 us (23.5 and 265 when the last workgroup walked the map for all requests); a layer of one
+// sequence 11.6 -> 3.8 without a request, 14.7 -> 6.1 with one from every head.
 constexpr int kAppendThreads = 1024;
-// Heads appended by the same launch.  One CU writing rows all over the pool pays for them one
-// round of 32 heads after the other: 128 heads 12.3 us in one launch against 10.5 in two, 256 heads
-// 19.6 against 10.0 (all rows of a round asked for at once), 8 heads 6.6 against 10.
-constexpr int kAppendFused = 64;
-__global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendArgs A, int n_wg, int heads_per_wg,
-                                                                        int map_per_wg, int fused) {
-  __shared__ int smem[kAppendThreads / 64 + 1];
-  __shared__ int req0[kAppendWgs + 1], free0[kAppendWgs + 1];
-  __shared__ int bits_s, free_s, last_s, ok_s;
+// Heads appended by the same launch.  One CU finds their blocks sixteen at a time and writes all their
+// rows: 8 heads without a request 3.8 us, 6.2 with a launch for the rows, with one from every head
+// 6.1 and 7.3; 32 heads 7.6 and 7.7; 64 heads 8.7 and 7.9, with a request from every head 11.2 and 8.8.
+constexpr int kAppendFused = 32;
+constexpr int kWaitLoads = 0x0f70;   // s_waitcnt vmcnt(0)
+template <bool FUSED>
+__global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendArgs A) {
+  __shared__ __align__(16) int asks_s[kAppendThreads / 64];
+  __shared__ int bits_s, free_s, req_s, last_s, ok_s;
+  __shared__ int want_g[kAppendFused], ahead_s[kAppendWgs];
   const Dims& D = A.D;
-  const int tid = threadIdx.x, w = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, w = blockIdx.x;
+  const int n_wg = A.n_wg;
   const bool wide = ((uintptr_t)A.free_map & 15) == 0;   // (map_per_wg is a multiple of 16)
+  auto wants = [&](int g, bool* full) {
+    const int C = A.ctx[g], u = C >> A.lb;
+    if (C & (D.b - 1)) return false;
+    *full = u >= D.maxb;
+    return *full || A.table[(size_t)g * D.maxb + u] < 0;
+  };
+  // this share of the map, a tile per wavefront and round, kRounds asked for together
+  const size_t m0 = (size_t)w * A.map_per_wg, m1 = min((size_t)D.N, m0 + A.map_per_wg);
+  constexpr int kRounds = 2;
+  size_t tile0 = m0 + (size_t)wv * kAppendTile;
+  uint4 v[kRounds];
+  auto ask = [&]() {
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+      const size_t at = tile0 + (size_t)u * 16 * kAppendThreads + (size_t)lane * 16;
+      v[u] = at < m1 ? free_bytes16(A.free_map, at, m1, wide) : make_uint4(0, 0, 0, 0);
+    }
+  };
+  if (!FUSED) ask();   // (it hangs on nothing; few heads often ask for no block at all)
   if (tid == 0) { bits_s = 0; free_s = 0; }
   __syncthreads();
-  // requesters of this share, listed in ascending order
-  const int i0 = w * heads_per_wg, i1 = min(A.nsel, i0 + heads_per_wg);
+  // requesters, in ascending order: of this share of the heads; of all of few heads, in every
+  // workgroup, so that without any nobody looks at the map
   int n_req = 0;
-  for (int base = i0; base < i1; base += kAppendThreads) {
-    const int idx = base + tid;
-    int g = 0, want = 0;
-    if (idx < i1) {
-      g = append_head(A, idx);
-      const int C = A.ctx[g];
-      if ((C & (D.b - 1)) == 0) {
-        const int u = C >> A.lb;
-        if (u >= D.maxb) { want = 1; atomicOr(&bits_s, EB_TABLE); }
-        else want = A.table[(size_t)g * D.maxb + u] < 0;
+  if (FUSED) {
+    if (wv == 0) {
+      bool full = false;
+      const int g = lane < A.nsel ? append_head(A, lane) : 0;
+      const unsigned long long asks = __ballot(lane < A.nsel && wants(g, &full));
+      if (asks >> lane & 1) want_g[__popcll(asks & ((1ull << lane) - 1))] = g;
+      const bool any_full = __any(full);
+      if (lane == 0) { req_s = __popcll(asks); bits_s = any_full ? EB_TABLE : 0; }
+    }
+    __syncthreads();
+    n_req = req_s;
+  } else {
+    const int i0 = w * A.heads_per_wg, i1 = min(A.nsel, i0 + A.heads_per_wg);
+    for (int base = i0; base < i1; base += kAppendThreads) {
+      const int idx = base + tid;
+      bool full = false;
+      const int want = idx < i1 && wants(append_head(A, idx), &full);
+      if (full) atomicOr(&bits_s, EB_TABLE);
+      const unsigned long long asks = __ballot(want);
+      if (base > i0) __syncthreads();   // the counts of the round before have been read
+      if (lane == 0) asks_s[wv] = __popcll(asks);
+      __syncthreads();
+      int ahead = __popcll(asks & ((1ull << lane) - 1)), tot = 0;
+#pragma unroll
+      for (int k = 0; k < kAppendThreads / 64; ++k) {
+        const int c = asks_s[k];
+        if (k < wv) ahead += c;
+        tot += c;
       }
+      if (idx < i1) A.rank[idx] = want ? n_req + ahead : -1;
+      n_req += tot;
     }
-    int tot;
-    const int ex = block_exclusive_scan<kAppendThreads>(want, smem, &tot);
-    if (want) publish_i32(&A.list[i0 + n_req + ex], g);
-    n_req += tot;
   }
-  // free blocks of this share of the map (a single workgroup counts them only when they are wanted)
-  const size_t m0 = (size_t)w * map_per_wg, m1 = min((size_t)D.N, m0 + map_per_wg);
-  if (n_wg > 1 || n_req) {
+  // its free blocks (a single workgroup counts them only when they are wanted)
+  const bool alone = n_wg == 1, counted = n_req > 0 || (!FUSED && !alone);
+  if (FUSED && counted) ask();
+  // The loads are done, in words the compiler counts by: it would wait for them further down, and with
+  // them for the stores below.
+  __builtin_amdgcn_s_waitcnt(kWaitLoads);
+  if (counted) {
     int s = 0;
-    for (size_t at = m0 + (size_t)tid * 16; at < m1; at += (size_t)kAppendThreads * 16) {
-      const uint4 v = free_bytes16(A.free_map, at, m1, wide);
-      s += __popc(nonzero_bytes(v.x)) + __popc(nonzero_bytes(v.y)) + __popc(nonzero_bytes(v.z)) + __popc(nonzero_bytes(v.w));
+    while (tile0 < m1) {
+#pragma unroll
+      for (int u = 0; u < kRounds; ++u) {
+        const size_t first = tile0 + (size_t)u * 16 * kAppendThreads;   // the tile's first block
+        if (first >= m1) break;
+        // a bit per byte: the top bits of a word's four bytes, brought together by a product
+        auto four = [](uint32_t x) { return ((nonzero_bytes(x) >> 7) * 0x10204080u) >> 28; };
+        const uint32_t mine = four(v[u].x) | four(v[u].y) << 4 | four(v[u].z) << 8 | four(v[u].w) << 12;
+        const uint32_t pair = mine | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xb1, 0xf, 0xf, false) << 16;
+        const int n = wave_prefix_i(__popc(mine));   // lane 63: of the tile
+        int32_t* word = (int32_t*)A.bits + first / 32 + (lane >> 1);
+        int32_t* count = &A.tile_free[first / kAppendTile];
+        if (FUSED) {   // read by this launch's last workgroup, else by the next launch
+          if (!(lane & 1)) publish_i32(word, (int)pair);
+          if (lane == 63) publish_i32(count, n);
+        } else {
+          if (!(lane & 1)) *word = (int)pair;
+          if (lane == 63) *count = n;
+        }
+        s += n;
+      }
+      tile0 += (size_t)kRounds * 16 * kAppendThreads;
+      if (tile0 >= m1) break;
+      ask();
+      __builtin_amdgcn_s_waitcnt(kWaitLoads);
     }
-    s = wave_sum_i(s);
-    if ((tid & 63) == 0 && s) atomicAdd(&free_s, s);
+    if (lane == 63 && s) atomicAdd(&free_s, s);
+    if (FUSED) publish_wait();   // what this thread left is out
   }
-  publish_wait();      // this thread's part of the list is out
   __syncthreads();
   if (tid == 0) {
     bool last = true;
-    if (n_wg > 1) {
-      publish_i32(&A.part[3 * w], n_req);
-      publish_i32(&A.part[3 * w + 1], free_s);
-      publish_i32(&A.part[3 * w + 2], bits_s);
-      publish_wait();
+    if (!alone) {   // (all of them, also without a request: nothing is written while one may still look)
+      if (counted) {
+        publish_i32(&A.part[3 * w], n_req);
+        publish_i32(&A.part[3 * w + 1], free_s);
+        publish_i32(&A.part[3 * w + 2], bits_s);
+        publish_wait();
+      }
       last = __hip_atomic_fetch_add(&A.header[HW_ARRIVED], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_wg - 1;
     }
     last_s = last;
@@ -364,78 +482,74 @@ __global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendAr
   if (!last_s) return;
   // ---- the last workgroup ----
   if (tid < 64) {
-    int r = 0, f = 0, bits = 0;
-    if (n_wg == 1) {
+    int r = 0, f = 0, bits = 0, st = A.header[HW_STATUS];
+    if (alone || !counted) {
       if (tid == 0) { r = n_req; f = free_s; bits = bits_s; }
     } else if (tid < n_wg) {
       r = published_i32(&A.part[3 * tid]);
       f = published_i32(&A.part[3 * tid + 1]);
       bits = published_i32(&A.part[3 * tid + 2]);
     }
-    int ri = r, fi = f;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int a = __shfl_up(ri, o), c = __shfl_up(fi, o);
-      if (tid >= o) { ri += a; fi += c; }
-    }
-    req0[tid] = ri - r;
-    free0[tid] = fi - f;
+    const int ri = wave_prefix_i(r), fi = wave_prefix_i(f);
+    if (FUSED) ahead_s[tid] = fi - f;
+    else { A.part[tid] = ri - r; A.part[kAppendWgs + tid] = fi - f; }   // (the counts have been read, by this wavefront)
     const bool table_full = __any(bits & EB_TABLE);
     if (tid == 63) {
-      req0[64] = ri;
-      free0[64] = fi;
-      if (n_wg > 1) A.header[HW_ARRIVED] = 0;
-      int st = A.header[HW_STATUS];
+      if (!alone) A.header[HW_ARRIVED] = 0;
       if (st == KVC_OK) {
-        st = table_full ? KVC_ERR_TABLE_FULL : ri > fi ? KVC_ERR_OOM : KVC_OK;
+        st = table_full ? KVC_ERR_TABLE_FULL : (FUSED ? n_req : ri) > fi ? KVC_ERR_OOM : KVC_OK;
         if (st != KVC_OK) A.header[HW_STATUS] = st;
       }
       ok_s = st == KVC_OK;
     }
   }
+  if (!FUSED) return;
   __syncthreads();
   if (!ok_s) return;
-  const int total = req0[64];
-  for (int w2 = 0; w2 < n_wg && free0[w2] < total; ++w2) {
-    if (free0[w2 + 1] == free0[w2]) continue;   // nothing free in this share (the same for every thread)
-    const size_t a0 = (size_t)w2 * map_per_wg, a1 = min((size_t)D.N, a0 + map_per_wg);
-    int rank0 = free0[w2];
-    for (size_t base = a0; base < a1 && rank0 < total; base += (size_t)kAppendThreads * 16) {
-      const size_t at = base + (size_t)tid * 16;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (at < a1) v = free_bytes16(A.free_map, at, a1, wide);
-      uint32_t m[4] = {nonzero_bytes(v.x), nonzero_bytes(v.y), nonzero_bytes(v.z), nonzero_bytes(v.w)};
-      int tot;
-      int k = rank0 + block_exclusive_scan<kAppendThreads>(__popc(m[0]) + __popc(m[1]) + __popc(m[2]) + __popc(m[3]), smem, &tot);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        while (m[q] && k < total) {
-          const int id = (int)at + 4 * q + (__builtin_ctz(m[q]) >> 3);
-          m[q] &= m[q] - 1;
-          int lo = 0, hi = 64;   // share that holds the k-th requester
-          while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (req0[mid] <= k) lo = mid; else hi = mid; }
-          const int g = published_i32(&A.list[lo * heads_per_wg + (k - req0[lo])]);
-          A.table[(size_t)g * D.maxb + (A.ctx[g] >> A.lb)] = id;
-          A.free_map[id] = 0;
-          ++k;
-        }
-      }
-      rank0 += tot;
+  // few heads: a wavefront per request, then the rows
+  const int ahead = ahead_s[lane];
+  for (int k = wv; k < n_req; k += kAppendThreads / 64) {
+    const int g = want_g[k];
+    const int id = nth_free_block<true>(A, ahead, k, lane);
+    if (lane == 0 && id >= 0) {
+      A.table[(size_t)g * D.maxb + (A.ctx[g] >> A.lb)] = id;
+      A.free_map[id] = 0;
     }
   }
-  if (!fused) return;
   __syncthreads();   // the table cells written above are read below, by this workgroup
   const int groups = kAppendThreads / A.lanes_per_head;
-  for (int idx = tid / A.lanes_per_head; idx < A.nsel; idx += groups) append_one(A, idx, tid % A.lanes_per_head);
+  for (int idx = tid / A.lanes_per_head; idx < A.nsel; idx += groups) {
+    const int g = append_head(A, idx), C = A.ctx[g];
+    const int blk = A.table[(size_t)g * D.maxb + (C >> A.lb)];
+    if (blk >= 0) append_one(A, g, C, blk, tid % A.lanes_per_head);
+  }
 }
 
 // The append of many heads, as a launch of its own: as many lanes per head as the new key and
 // value have 16-byte pieces (rounded up to a power of two, at most a wavefront; 32 for 256-byte
-// rows).  A chain of three dependent loads per head, so heads in flight are what counts.
+// rows).  A chain of three dependent loads per head, so heads in flight are what counts.  The requests
+// of a wavefront's heads find their blocks first, one after the other.
 __global__ void __launch_bounds__(256) append_write_kernel(AppendArgs A) {
-  if (A.header[HW_STATUS] != KVC_OK) return;
   const int idx = blockIdx.x * (256 / A.lanes_per_head) + threadIdx.x / A.lanes_per_head;
-  if (idx < A.nsel) append_one(A, idx, threadIdx.x % A.lanes_per_head);
+  const int lane = threadIdx.x & 63, gl = threadIdx.x % A.lanes_per_head;
+  const bool real = idx < A.nsel;
+  // (everything that hangs on nothing else is asked for together)
+  const int g = real ? append_head(A, idx) : 0;
+  const int rank = real ? A.rank[idx] : -1, C = A.ctx[g];
+  const int before = A.part[lane], ahead = A.part[kAppendWgs + lane];
+  if (A.header[HW_STATUS] != KVC_OK) return;
+  int32_t* cell = &A.table[(size_t)g * A.D.maxb + (C >> A.lb)];
+  int blk = real && rank < 0 ? *cell : -1;
+  for (unsigned long long asks = __ballot(gl == 0 && rank >= 0); asks; asks &= asks - 1) {
+    const int src = __builtin_ctzll(asks);
+    const int share = __builtin_amdgcn_readlane(idx, src) / A.heads_per_wg;
+    const int k = __builtin_amdgcn_readlane(before, share) + __builtin_amdgcn_readlane(rank, src);
+    const int id = nth_free_block<false>(A, ahead, k, lane);
+    if (lane / A.lanes_per_head == src / A.lanes_per_head) blk = id;
+  }
+  if (blk < 0) return;
+  if (gl == 0 && rank >= 0) { *cell = blk; A.free_map[blk] = 0; }
+  append_one(A, g, C, blk, gl);
 }
 
 // Count, rank the free map, resolve errors, hand out (n: see AllocMode).
@@ -713,19 +827,25 @@ int kvc_append(const kvc_config* cfg, const kvc_state* st, const void* k_new, co
   A.kc = (char*)st->k_cache; A.vc = (char*)st->v_cache; A.metric = st->metric; A.pos = st->pos;
   A.table = st->block_table; A.ctx = st->ctx_len; A.free_map = st->free_map;
   A.k_new = (const char*)k_new; A.v_new = (const char*)v_new; A.new_pos = new_pos;
-  A.header = W.header; A.part = W.seg_hist; A.list = W.off_b;
+  A.header = W.header; A.part = W.seg_hist; A.rank = W.off_b;
   // a workgroup per 1024 heads or 16 KB of the map, whichever asks for more, at most kAppendWgs
   const int by_heads = (A.nsel + kAppendThreads - 1) / kAppendThreads;
   const int by_map = (int)(((size_t)D.N + 16 * kAppendThreads - 1) / (16 * kAppendThreads));
   int n_wg = by_heads > by_map ? by_heads : by_map;
   if (n_wg > kAppendWgs) n_wg = kAppendWgs;
-  const int heads_per_wg = (A.nsel + n_wg - 1) / n_wg;
-  const int map_per_wg = (int)(align_up(((size_t)D.N + n_wg - 1) / n_wg, 16));
+  A.n_wg = n_wg;
+  A.heads_per_wg = (A.nsel + n_wg - 1) / n_wg;
+  A.map_per_wg = (int)align_up(((size_t)D.N + n_wg - 1) / n_wg, kAppendTile);
+  // [tiles][32] bits and [tiles] counts, 132 bytes per 1024 blocks, fit where the decode keeps N * b * r floats
+  A.bits = (uint32_t*)W.stash;
+  A.tile_free = (int32_t*)W.stash + ((size_t)D.N + kAppendTile - 1) / kAppendTile * 32;
   static_assert(kAppendWgs * 3 <= 256, "the counts fit one segment's histogram");
-  const int fused = A.nsel <= kAppendFused;
-  hipLaunchKernelGGL(append_reserve_kernel, dim3(n_wg), dim3(kAppendThreads), 0, s, A, n_wg, heads_per_wg, map_per_wg, fused);
-  KVC_LAUNCH_CHECK();
-  if (!fused) {
+  if (A.nsel <= kAppendFused) {
+    hipLaunchKernelGGL(append_reserve_kernel<true>, dim3(n_wg), dim3(kAppendThreads), 0, s, A);
+    KVC_LAUNCH_CHECK();
+  } else {
+    hipLaunchKernelGGL(append_reserve_kernel<false>, dim3(n_wg), dim3(kAppendThreads), 0, s, A);
+    KVC_LAUNCH_CHECK();
     const int heads_per_launch_wg = 256 / A.lanes_per_head;
     hipLaunchKernelGGL(append_write_kernel, dim3((A.nsel + heads_per_launch_wg - 1) / heads_per_launch_wg), dim3(256), 0, s, A);
     KVC_LAUNCH_CHECK();

@@ -1,0 +1,131 @@
+"""Appends into pools with few free blocks left, spread over the whole map: every requester gets the
+block that is its own by rank (the lowest free blocks in ascending head order), and the call takes no
+longer than one into a pool with plenty."""
+import statistics
+
+import pytest
+import torch
+
+from paper_2410_00161_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+class Pool:
+    """G heads of two blocks each; `free` marks the free blocks, `req` the heads whose blocks are full."""
+
+    def __init__(self, S, Lyr, Hk, N, b, free, req, seed, align=0, d=8):
+        G = S * Lyr * Hk
+        g = torch.Generator(device=DEV)
+        g.manual_seed(seed)
+        taken = torch.nonzero(~free)[:, 0]
+        taken = taken[torch.randperm(len(taken), generator=g, device=DEV)[:2 * G]]
+        self.table = torch.full((G, 4), -1, dtype=torch.int32, device=DEV)
+        self.table[:, :2] = taken.view(G, 2).int()
+        self.ctx = torch.where(req, 2 * b, 2 * b - 1).int()   # (a length of one token per block asks when it equals the blocks held)
+        self.free, self.req = free.to(torch.uint8), req
+        self.buf = torch.empty(N + align, dtype=torch.uint8, device=DEV)
+        self.now = [self.table.clone(), self.ctx.clone(), self.buf[align:]]
+        kv = torch.zeros((2, N, b, d), dtype=torch.bfloat16, device=DEV)
+        self.k, self.v = kv[0], kv[1]
+        self.metric = torch.ones((N, b), device=DEV)
+        self.pos = torch.full((N, b), -1, dtype=torch.int32, device=DEV)
+        self.cfg = B.make_config(S, Lyr, Hk, 1, d, b, N, 4, "bf16", B.KVC_L2)
+        self.st = B.make_state(self.k, self.v, self.metric, self.pos, self.now[0], self.now[1], self.now[2])
+        self.ws = B.new_workspace(self.cfg, torch.device(DEV))
+        self.new = torch.arange(G, device=DEV).view(G, 1).remainder(251).add(1).to(torch.bfloat16).expand(G, d).contiguous()
+        self.Lyr, self.b = Lyr, b
+
+    def reset(self):
+        for t, was in zip(self.now, (self.table, self.ctx, self.free)):
+            t.copy_(was)
+
+    def append(self, flags=B.KVC_ASYNC):
+        B.kvc_append(self.cfg, self.st, self.new, self.new, None, 0, self.Lyr, self.ws, flags=flags)
+
+    def check(self):
+        torch.cuda.synchronize()
+        assert B.kvc_poll_status(self.cfg, self.ws) == B.KVC_OK
+        n = int(self.req.sum())
+        ids = torch.nonzero(self.free)[:n, 0]
+        want = self.table.clone()
+        want[self.req, self.ctx[self.req].long() // self.b] = ids.int()
+        assert torch.equal(self.now[0], want)
+        assert torch.equal(self.now[1], self.ctx + 1)
+        left = self.free.clone()
+        left[ids] = 0
+        assert torch.equal(self.now[2], left)
+        G = len(self.ctx)
+        slot = want[torch.arange(G, device=DEV), self.ctx.long() // self.b].long() * self.b + self.ctx.long() % self.b
+        for t in (self.k, self.v):
+            assert torch.equal(t.view(-1, t.shape[-1])[slot], self.new)
+        assert (self.metric.view(-1)[slot] == 0).all() and torch.equal(self.pos.view(-1)[slot], self.ctx)
+
+
+def spread(N, n, seed):
+    """n free blocks anywhere in the map, its first and last among them."""
+    inner = 1 + torch.randperm(N - 2, generator=torch.Generator().manual_seed(seed))[:max(0, n - 2)]
+    free = torch.zeros(N, dtype=torch.bool, device=DEV)
+    free[inner.to(DEV)] = True
+    free[N - 1] = True
+    if n >= 2:
+        free[0] = True
+    return free
+
+
+@pytest.mark.parametrize("S,Lyr,Hk,N,b,n_free,n_req,align", [
+    (1, 1, 1, 9, 4, 1, 1, 0),
+    (1, 1, 8, 1023, 16, 8, 8, 0), (1, 1, 8, 1024, 16, 9, 8, 3), (1, 2, 32, 1025, 2, 64, 64, 0),   # tiles of the map
+    (1, 1, 8, 16384, 16, 3, 2, 0), (2, 1, 32, 16385, 16, 70, 64, 1),                              # one workgroup, two
+    (1, 1, 8, 340001, 16, 8, 8, 0), (8, 1, 8, 1100000, 2, 64, 64, 0), (1, 1, 8, 340001, 16, 8, 0, 0),
+    (1, 4, 8, 5000, 4, 32, 32, 0), (3, 1, 11, 5000, 4, 33, 33, 0),                                # by the reservation's launch, by one of their own
+    (1, 5, 13, 1025, 4, 65, 65, 0), (1, 4, 32, 16385, 16, 5, 5, 1),                              
+    (16, 1, 8, 340001, 16, 200, 128, 0), (64, 4, 8, 65537, 4, 2048, 2048, 0),
+    (41, 5, 5, 3000000, 1, 1030, 1025, 0), (41, 5, 5, 40000, 1, 30000, 1025, 0),
+])
+def test_every_requester_gets_its_own_block(S, Lyr, Hk, N, b, n_free, n_req, align):
+    G = S * Lyr * Hk
+    req = torch.zeros(G, dtype=torch.bool, device=DEV)
+    req[torch.randperm(G, generator=torch.Generator().manual_seed(1))[:n_req].to(DEV)] = True
+    p = Pool(S, Lyr, Hk, N, b, spread(N, n_free, 2), req, 3, align)
+    for _ in range(2):
+        p.reset()
+        p.append()
+        p.check()
+    if n_req:   # one block short: an error, and nothing has changed
+        p.reset()
+        p.now[2][torch.nonzero(p.free)[n_req - 1:, 0]] = 0
+        before = [t.clone() for t in p.now]
+        with pytest.raises(B.KvcError) as e:
+            p.append(flags=0)
+        assert e.value.code == B.KVC_ERR_OOM
+        assert all(torch.equal(a, t) for a, t in zip(before, p.now))
+        p.reset()
+        p.append()
+        p.check()
+
+
+def test_a_nearly_full_pool_takes_no_longer():
+    """16 384 heads, 1.35 M blocks: 1024 requests and 1080 free blocks spread over the map, against a fifth
+    of the map free.  (A walk of the map by one workgroup took ten times as long.)"""
+    G, N = 16384, 1350000
+    req = torch.zeros(G, dtype=torch.bool, device=DEV)
+    req[torch.randperm(G, generator=torch.Generator().manual_seed(1))[:1024].to(DEV)] = True
+    took = []
+    for n_free in (N // 5, 1080):
+        p = Pool(64, 32, 8, N, 16, spread(N, n_free, 2), req, 3)
+        times = []
+        for _ in range(30):
+            p.reset()
+            torch.cuda._sleep(20000)   # the launches queue up behind it
+            a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            p.append()
+            e.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(e) * 1e3)
+        p.check()
+        took.append(statistics.median(times))
+    assert took[1] <= 3 * took[0], took
