@@ -356,10 +356,13 @@ __device__ __forceinline__ uint4 free_bytes16(const uint8_t* map, size_t at, siz
 // 12.2 us (23.5 and 265 when the last workgroup walked the map for all requests); a layer of one
 // sequence 11.6 -> 3.8 without a request, 14.7 -> 6.1 with one from every head.
 constexpr int kAppendThreads = 1024;
-// Heads appended by the same launch.  One CU finds their blocks sixteen at a time and writes all their
-// rows: 8 heads without a request 3.8 us, 6.2 with a launch for the rows, with one from every head
-// 6.1 and 7.3; 32 heads 7.6 and 7.7; 64 heads 8.7 and 7.9, with a request from every head 11.2 and 8.8.
-constexpr int kAppendFused = 32;
+// Heads appended by the same launch, a wavefront's lanes of them at most.  One CU finds their blocks
+// sixteen at a time and writes all their rows; a launch for the rows costs more wherever few ask.
+// Together and apart: 8 heads without a request 3.8 and 6.8 us, with one from every head 6.1 and 7.4;
+// 56 heads of 12 000 blocks 3.9 and 5.0, with four requests 5.9 and 6.5; 64 heads of 170 000 blocks with
+// four requests 8.8 and 7.8, with 64 11.1 and 8.8 (from a graph; issued by the host, the launch saved
+// is worth more: three layers of 38 heads 9 us).
+constexpr int kAppendFused = 64;
 constexpr int kWaitLoads = 0x0f70;   // s_waitcnt vmcnt(0)
 template <bool FUSED>
 __global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendArgs A) {

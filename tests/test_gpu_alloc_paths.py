@@ -59,9 +59,8 @@ def test_prompts_admitted_and_preempted(S, Lyr, Hk, b, tokens):
 @pytest.mark.parametrize("S,Lyr,Hk,b,slack_blocks,layers,odd_map", [
     (1, 1, 1, 1, 3, None, False),          # one head, one workgroup; then out of blocks
     (4, 2, 16, 2, 700, None, True),        # 128 heads: a workgroup of rows after the reservation; a map at an odd address
-    (1, 2, 32, 2, 900, (1, 2), False),     # 32 heads of one layer: appended by the reservation's launch
-    (2, 2, 32, 2, 900, (1, 2), False),     # 64 heads: rows written by a launch of their own
-    (5, 2, 13, 2, 900, (1, 2), False),     # 65 heads, in 13s
+    (2, 2, 32, 2, 900, (1, 2), False),     # 64 heads of one layer: appended by the reservation's launch
+    (5, 2, 13, 2, 900, (1, 2), False),     # 65 heads: rows written by a launch of their own
     (41, 5, 5, 1, 20000, None, False),     # 1025 heads: two workgroups of heads, two of the map
     (2, 4, 3, 1, 1200000, (0, 3), False),  # more of the map than 64 workgroups' first rounds
 ])

@@ -80,8 +80,8 @@ def spread(N, n, seed):
     (1, 1, 8, 1023, 16, 8, 8, 0), (1, 1, 8, 1024, 16, 9, 8, 3), (1, 2, 32, 1025, 2, 64, 64, 0),   # tiles of the map
     (1, 1, 8, 16384, 16, 3, 2, 0), (2, 1, 32, 16385, 16, 70, 64, 1),                              # one workgroup, two
     (1, 1, 8, 340001, 16, 8, 8, 0), (8, 1, 8, 1100000, 2, 64, 64, 0), (1, 1, 8, 340001, 16, 8, 0, 0),
-    (1, 4, 8, 5000, 4, 32, 32, 0), (3, 1, 11, 5000, 4, 33, 33, 0),                                # by the reservation's launch, by one of their own
-    (1, 5, 13, 1025, 4, 65, 65, 0), (1, 4, 32, 16385, 16, 5, 5, 1),                              
+    (1, 4, 8, 5000, 4, 32, 32, 0), (3, 1, 11, 5000, 4, 33, 33, 0),
+    (1, 5, 13, 1025, 4, 65, 65, 0), (1, 4, 32, 16385, 16, 5, 5, 1),                               # rows in a launch of their own
     (16, 1, 8, 340001, 16, 200, 128, 0), (64, 4, 8, 65537, 4, 2048, 2048, 0),
     (41, 5, 5, 3000000, 1, 1030, 1025, 0), (41, 5, 5, 40000, 1, 30000, 1025, 0),
 ])
