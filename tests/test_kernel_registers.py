@@ -1,0 +1,51 @@
+"""Registers per lane of kernels whose speed hangs on how many workgroups share a CU, from the metadata
+of the library's own code object."""
+import re
+import struct
+
+import pytest
+
+from paper_2410_00161_amd import binding as B
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def kernels():
+    """{kernel name: metadata} of every gfx950 code object in the library."""
+    blob = open(B.LIB_PATH, "rb").read()
+    out = {}
+    for m in re.finditer(rb"\x7fELF\x02\x01", blob):
+        at = m.start()
+        if struct.unpack_from("<H", blob, at + 18)[0] != 224:   # EM_AMDGPU
+            continue
+        shoff, = struct.unpack_from("<Q", blob, at + 40)
+        shentsize, shnum = struct.unpack_from("<HH", blob, at + 58)
+        for i in range(shnum):
+            kind, = struct.unpack_from("<I", blob, at + shoff + i * shentsize + 4)
+            off, size = struct.unpack_from("<QQ", blob, at + shoff + i * shentsize + 24)
+            if kind != 7:   # SHT_NOTE
+                continue
+            p, end = at + off, at + off + size
+            while p + 12 <= end:
+                namesz, descsz, typ = struct.unpack_from("<III", blob, p)
+                desc = p + 12 + (namesz + 3) // 4 * 4
+                if typ == 32:   # NT_AMDGPU_METADATA
+                    for k in msgpack.unpackb(blob[desc:desc + descsz])["amdhsa.kernels"]:
+                        out[k[".name"]] = k
+                p = desc + (descsz + 3) // 4 * 4
+    return out
+
+
+def test_window_sums_leave_room_for_their_workgroups():
+    """A SIMD has 512 registers per lane: 128 let four workgroups of 256 share a CU (what the LDS holds of
+    32 to 128 query rows), 168 let three (256 rows of 64 dimensions)."""
+    seen = 0
+    for name, k in kernels().items():
+        m = re.search(r"window_sum_kernelILi\dELi(\d+)ELi(\d+)ELi\d", name)
+        if not m:
+            continue
+        seen += 1
+        most = 128 if m[2] == "16" else 168 if m[1] == "64" else 256
+        assert k[".vgpr_count"] <= most, (name, k[".vgpr_count"])
+        assert k[".vgpr_spill_count"] == 0, name
+    assert seen == 32
