@@ -40,7 +40,17 @@ def prompt(S, Lyr, Hk, r, d, b, lengths, dtype, seed, slack=1.3):
     per = Lyr * Hk
     ctx = torch.tensor(lengths, dtype=torch.int32).repeat_interleave(per)
     shape = W.Shape(S, Lyr, Hk, r, d, b, W.pool_size(ctx, b, slack, 5), -(-max(lengths) // b) + 1, dtype)
-    return W.make_cache(shape, ctx, seed, placement="fragmented").to(DEV)
+    cache = W.make_cache(shape, ctx, seed, placement="fragmented").to(DEV)
+    used = torch.zeros(shape.num_blocks * b, dtype=torch.bool, device=DEV)   # the rest must never leak in
+    for g, C in enumerate(ctx.tolist()):
+        j = torch.arange(C, device=DEV)
+        used[cache.block_table.view(len(ctx), -1)[g, j // b].long() * b + j % b] = True
+    rows = cache.k_cache.view(-1, d)
+    if dtype == "fp8":
+        rows.view(torch.uint8)[~used] = 0x7F
+    else:
+        rows[~used] = float("nan")
+    return cache
 
 
 def queries(shape, w, scale=1.0, seed=5):
@@ -151,3 +161,69 @@ def test_references_follow_the_logits(d, dtype, b):
         assert float((got[slots] - inc).norm() / inc.norm()) <= 2 * 0.6931 * size * 2.0 ** -23, g
         assert torch.equal(got[slots][inc == 0], inc[inc == 0])
     assert seen_large > 100
+
+
+# (S, Lyr, Hk, r, d, b, lengths, dtype, w, first, exclude, lse, mode, chunk)
+BLOCKS = [
+    (3, 1, 2, 4, 128, 16, [3000, 1500, 700], "bf16", 256, 1200, 10, False, "l2", 1024),    # ragged, up to three chunks
+    (1, 2, 2, 4, 128, 16, [5000], "bf16", 128, 4800, 0, False, "l2", 1024),                # tiles without a mask, the queries at the end
+    (1, 2, 2, 4, 128, 16, [5000], "bf16", 128, 4990, 0, True, "l2", 1024),                 # queries past the last key
+    (1, 1, 3, 8, 128, 64, [2049], "bf16", 57, 1000, 100, False, "l2", 1024),               # few of a tile's rows padded; far back keys only
+    (1, 1, 3, 8, 64, 32, [2049], "bf16", 57, 1000, 0, False, "l1", 1024),
+    (2, 1, 2, 4, 64, 8, [1300, 0], "bf16", 192, 0, 0, False, "l2", 1024),                  # blocks of half a load; no KV; a prompt's first queries
+    (2, 1, 2, 4, 128, 1, [1300, 64], "bf16", 190, 500, 3, False, "l2", 1024),              # a block per token; a head that ends in front of the queries
+    (1, 1, 2, 2, 128, 1024, [2500], "bf16", 256, 2000, 0, False, "l1", 1024),
+    (2, 1, 2, 4, 128, 16, [3000, 2000], "fp8", 256, 1500, 10, False, "l2", 1024),
+    (2, 1, 2, 8, 64, 4, [3000, 1100], "fp8", 128, 1000, 0, True, "l1", 1024),
+    (1, 1, 2, 1, 128, 16, [1500], "bf16", 512, 900, 64, True, "l2", 1024),                 # one query head
+    (1, 2, 8, 8, 128, 16, [8300], "bf16", 1024, 7200, 10, False, "l2", 2048),
+    (1, 4, 8, 8, 64, 16, [8300], "bf16", 512, 7700, 0, False, "l2", 2048),
+    (1, 4, 8, 8, 128, 16, [8300], "bf16", 1024, 7276, 0, False, "l2", 4096),
+    (1, 4, 8, 8, 128, 16, [8300], "fp8", 1024, 7276, 10, True, "l1", 4096),
+]
+
+
+@pytest.mark.parametrize("S,Lyr,Hk,r,d,b,lengths,dtype,w,first,exclude,lse,mode,chunk", BLOCKS)
+def test_streamed_blocks(S, Lyr, Hk, r, d, b, lengths, dtype, w, first, exclude, lse, mode, chunk):
+    from paper_2410_00161_amd.session import KvcSession
+    cache = prompt(S, Lyr, Hk, r, d, b, lengths, dtype, 41)
+    assert streamed_chunk(cache.shape, w, first, lse) == chunk
+    cache.metric.zero_()
+    q = queries(cache.shape, w)
+    want = torch.zeros(cache.shape.num_blocks * b, dtype=torch.float64, device=DEV)
+    row_lse = torch.empty((S, Lyr, Hk * r, w), device=DEV)
+    size = 1.0
+    for g, slots, inc, l in in_64_bits(cache, q, w, first, exclude, mode):
+        want[slots] += inc
+        row_lse.view(cache.shape.G, r, w)[g] = l.float()
+        if len(slots):
+            size = max(size, float(l.abs().max()) * 1.4427)
+    sess = KvcSession(cache, metric_mode=B.KVC_L1 if mode == "l1" else B.KVC_L2)
+    sess.query_block_metric(q, w, first, exclude, row_lse=row_lse if lse else None)
+    got = sess.cache.metric.double().view(-1)
+    # rounding of a row's constant and of an exp's argument, each half a last bit at the size of the
+    # largest logits and doubled by the square, and a few last bits of the sums
+    bound = 2 * 0.6931 * size * 2.0 ** -23 + 4 * 2.0 ** -23
+    assert float((got - want).norm() / want.norm()) <= bound
+    large = want > 1e-3 * want.max()
+    assert float(((got - want)[large] / want[large]).abs().max()) <= 4 * bound
+    assert torch.equal(got[want == 0], want[want == 0])
+
+
+def test_a_streamed_block_of_some_layers():
+    """Layers 1 and 2 of 4; the metrics of the others stay, and what was there is added to."""
+    from paper_2410_00161_amd.session import KvcSession
+    cache = prompt(2, 4, 2, 4, 128, 16, [2600, 1400], "bf16", 43)
+    w, first = 256, 1100
+    assert streamed_chunk(cache.shape, w, first, False, layers=2)
+    before = cache.metric.uniform_(0.5, 1.0).double().view(-1).clone()
+    q = queries(cache.shape, w)
+    want = before.clone()
+    for g, slots, inc, _ in in_64_bits(cache, q, w, first, 0):
+        if (g // 2) % 4 in (1, 2):
+            want[slots] += inc
+    sess = KvcSession(cache)
+    sess.query_block_metric(q, w, first, 0, layer_begin=1, layer_end=3)
+    got = sess.cache.metric.double().view(-1)
+    assert float(((got - want) / want).abs().max()) <= 4e-6
+    assert torch.equal(got[want == before], before[want == before])

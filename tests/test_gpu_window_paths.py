@@ -1,7 +1,7 @@
 """Prefill-end metrics at the edges of the kernels' row and chunk sizes, against the CPU oracle:
 row counts around 32, 64, 128 and 256 (a kernel variant each), blocks of queries that are worked
-off in several passes and that end inside a tile, tables with far more room than the heads hold (a
-work list instead of an index grid), logits that outgrow the first ones by far."""
+off in several passes, tables with far more room than the heads hold, long rows without a work list,
+logits that outgrow the first ones by far."""
 import numpy as np
 import pytest
 import torch
@@ -70,12 +70,12 @@ def test_windows(r, w, d, b, dtype, room):
 
 
 @pytest.mark.parametrize("r,w,first,exclude,d,b,dtype,room", [
-    (4, 65, 300, 0, 128, 16, "bf16", 0),       # 260 rows: the block sums, one query in a second tile
-    (4, 64, 1000, 3, 128, 16, "bf16", 0),      # 256 rows: held
-    (8, 127, 0, 10, 64, 16, "fp8", 0),         # the prompt's first queries
-    (3, 300, 900, 64, 128, 4, "bf16", 0),
-    (4, 700, 200, 10, 128, 16, "bf16", 0),     # several passes: what they leave does not fit the workspace at once
-    (4, 130, 500, 10, 128, 16, "fp8", 50000),  # a work list
+    (4, 65, 300, 0, 128, 16, "bf16", 0),       # 260 rows: a second pass of one query
+    (4, 64, 1000, 3, 128, 16, "bf16", 0),      # 256 rows: one pass
+    (8, 127, 0, 10, 64, 16, "fp8", 0),         # the prompt's first queries, all rows at once
+    (3, 300, 900, 64, 128, 4, "bf16", 0),      # rows that no pass divides
+    (4, 700, 200, 10, 128, 16, "bf16", 0),     # several passes: what all rows at once would leave does not fit the workspace
+    (4, 130, 500, 10, 128, 16, "fp8", 50000),  # several passes over a work list, for rows with far more room
     (1, 513, 10, 0, 64, 1, "bf16", 0),
 ])
 def test_blocks_of_queries(r, w, first, exclude, d, b, dtype, room):
@@ -90,9 +90,46 @@ def test_blocks_of_queries(r, w, first, exclude, d, b, dtype, room):
     check(sess, st, real, before)
 
 
+@pytest.mark.parametrize("r,w,lse,d,dtype,lengths", [
+    (4, 32, False, 128, "bf16", [5200, 4097]), (4, 32, True, 128, "fp8", [5200, 0]),        # 128 rows, six chunks a row
+    (8, 32, False, 64, "bf16", [5120, 1024]), (2, 16, False, 128, "bf16", [4200, 5200]),    # 256 and 32 rows
+])
+def test_windows_over_long_rows(r, w, lse, d, dtype, lengths):
+    """Rows of more than four chunks that the heads nearly fill: items from an index grid."""
+    from paper_2410_00161_amd.session import KvcSession
+    shape, cache, real = make(2, 1, 2, r, d, 16, [n for n in lengths for _ in range(2)], dtype, 0)
+    chunks = -(-shape.max_blocks_per_head * 16 // 1024)
+    pool = shape.num_blocks * 16 // 1024 + 4
+    assert chunks >= 5 and 4 * chunks <= 2 * min(pool, 4 * chunks)
+    st = oracle_state(cache)
+    before = cache.metric.numpy().astype(np.float64)
+    q = queries(shape, w)
+    row_lse = None
+    if lse:
+        row_lse = np.zeros((2, 1, 2 * r, w))
+        for g in range(4):
+            n, o = O.slots_of(st, g)
+            C = len(n)
+            for hq in range(r if C else 0):
+                sc = q.double().numpy()[g // 2, 0, (g % 2) * r + hq] @ st.k_cache[n, o].T / np.sqrt(d)
+                sc[np.arange(C)[None, :] > (C - w + np.arange(w))[:, None]] = -np.inf
+                top = sc.max(1)
+                row_lse[g // 2, 0, (g % 2) * r + hq] = top + np.log(np.exp(sc - top[:, None]).sum(1))
+        row_lse = row_lse.astype(np.float32)
+    O.window_metric(st, q.double().numpy(), w, 7, row_lse=row_lse)
+    sess = KvcSession(cache)
+    sess.window_metric(q.to(sess.device), w, 7, row_lse=None if row_lse is None else torch.from_numpy(row_lse).to(sess.device))
+    torch.cuda.synchronize()
+    m = sess.cache.metric.cpu().numpy().astype(np.float64)
+    big = real & (st.metric > 1e-6)
+    np.testing.assert_allclose(m[big], st.metric[big], rtol=1e-4, atol=0)
+    np.testing.assert_array_equal(m[~real], before[~real])
+
+
 def test_logits_that_outgrow_the_first_tiles():
     """Keys grow along the sequence until their logits stand hundreds of powers of two above the
-    first ones, and shrink again: the statistics' reference has to follow."""
+    first ones, and shrink again: the running maxima of a block in several passes and of a window
+    have to follow."""
     from paper_2410_00161_amd.session import KvcSession
     shape, cache, real = make(1, 1, 2, 4, 128, 16, [1500, 900], "bf16", 0)
     st = oracle_state(cache)
