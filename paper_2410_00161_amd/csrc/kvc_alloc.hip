@@ -760,7 +760,7 @@ int kvc_check_state(const kvc_config* cfg, const kvc_state* st, void* ws, void* 
   hipLaunchKernelGGL(check_state_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, st->block_table, st->ctx_len,
                      st->free_map, owner, W.header);
   KVC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+  hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
   KVC_LAUNCH_CHECK();
   return (flags & KVC_ASYNC) ? KVC_OK : finish_sync(W, s);
 }
@@ -792,7 +792,7 @@ int kvc_block_free(const kvc_config* cfg, const kvc_state* st, const int32_t* n_
   hipLaunchKernelGGL(count_drop_kernel, dim3(gb), dim3(256), 0, s, D, st->block_table, st->ctx_len, n_drop,
                      W.held, W.off_b, W.header);
   KVC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+  hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
   KVC_LAUNCH_CHECK();
   hipLaunchKernelGGL(drop_kernel, dim3(gb), dim3(256), 0, s, D, st->block_table, st->ctx_len,
                      st->free_map, W.held, W.off_b, W.header);

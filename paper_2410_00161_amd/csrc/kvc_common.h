@@ -224,7 +224,7 @@ __device__ __forceinline__ void settle_status(int32_t* header) {
 // exactly the blocks it loses), or 0 when the call failed.  One workgroup adds the counts up:
 // a counter bumped by every head would see thousands of adds to one word, which the chip runs
 // one after the other (that counter alone took 0.13 ms per round at 16 384 heads).
-// With `resolve` set the launch also does what resolve_kernel(header, 0) does, first: a compaction
+// With `resolve` set the launch also does what resolve_kernel does, first: a compaction
 // that reports its count settles its status and publishes in one launch, ahead of the moves.
 static __global__ void __launch_bounds__(1024) publish_freed_kernel(int32_t* __restrict__ header,
                                                                     const int32_t* __restrict__ counts, int G,
@@ -232,15 +232,7 @@ static __global__ void __launch_bounds__(1024) publish_freed_kernel(int32_t* __r
   __shared__ long long part[1024 / 64];
   __shared__ int status_s;
   if (threadIdx.x == 0) {
-    if (resolve) {
-      const int bits = header[HW_SCRATCH0];
-      int st = KVC_OK;
-      if (bits & EB_ARG) st = KVC_ERR_ARG;
-      else if (bits & EB_TABLE) st = KVC_ERR_TABLE_FULL;
-      else if (bits & EB_NUMERIC) st = KVC_ERR_NUMERIC;
-      if (st != KVC_OK && header[HW_STATUS] == KVC_OK) header[HW_STATUS] = st;
-      header[HW_SCRATCH0] = 0;
-    }
+    if (resolve) settle_status(header);
     status_s = header[HW_STATUS];
   }
   long long s = 0;
@@ -356,18 +348,8 @@ static __global__ void zero_words_kernel(int32_t* p, int n) {
   if (i < n) p[i] = 0;
 }
 
-// Turns the error bits and the two totals into the status word, in a fixed
-// priority: argument, table full, numeric, out of blocks (check_oom == 1 only).
-static __global__ void resolve_kernel(int32_t* header, int check_oom) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int bits = header[HW_SCRATCH0];
-  int st = KVC_OK;
-  if (bits & EB_ARG) st = KVC_ERR_ARG;
-  else if (bits & EB_TABLE) st = KVC_ERR_TABLE_FULL;
-  else if (bits & EB_NUMERIC) st = KVC_ERR_NUMERIC;
-  else if (check_oom == 1 && header[HW_TOTAL_REQ] > header[HW_TOTAL_FREE]) st = KVC_ERR_OOM;
-  if (st != KVC_OK && header[HW_STATUS] == KVC_OK) header[HW_STATUS] = st;
-  header[HW_SCRATCH0] = 0;
+static __global__ void resolve_kernel(int32_t* header) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) settle_status(header);
 }
 
 // Per-segment state of a selection (block mode and rank-block mode share it): eight words.

@@ -262,9 +262,12 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   if (NW == 4 && A.self_list) {
     SelfList sl;
     const bool found = self_item(A, blockIdx.x, false, sl);
-    // a head without a KV: the lane that looked at it in the first workgroup writes its zero rows
-    if (blockIdx.x == 0 && w == 0 && sl.g >= 0 && sl.C == 0)
-      for (int i = 0; i < R * HD; ++i) A.out[(size_t)sl.g * R * HD + i] = 0.0f;
+    // heads without a KV (lane = head, the same in every wavefront): the first workgroup writes their zero rows
+    if (blockIdx.x == 0)
+      for (unsigned long long empty = __ballot(sl.g >= 0 && sl.C == 0); empty; empty &= empty - 1) {
+        float* o = A.out + (size_t)__builtin_amdgcn_readlane(sl.g, __builtin_ctzll(empty)) * R * HD;
+        for (int i = tid; i < R * HD; i += NT) o[i] = 0.0f;
+      }
     if (!found) return;
     it = sl.it;
     Tc = sl.T;
@@ -819,8 +822,9 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
         unsafeAtomicAdd(&A.metric[slot[u]], inc);
       }
     }
-  }  // output pieces e0 .. e1 - 1 of this chunk's workgroup; np threads (a power of two) side by
-  // side on pieces, 256 / np sharing the chunks of each
+  }
+  // output pieces e0 .. e1 - 1 of this chunk's workgroup; np threads (a power of two) side by side on
+  // pieces, 256 / np sharing the chunks of each
   const int pieces = R * HD / 4;
   const int e0 = (int)((long long)pieces * c / nch), e1 = (int)((long long)pieces * (c + 1) / nch);
   for (int ebase = e0; ebase < e1; ebase += 256) {
@@ -857,7 +861,8 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
       *(float4*)&A.out[(size_t)g * R * HD + i] = make_float4(t.x * il, t.y * il, t.z * il, t.w * il);
     }
     __syncthreads();
-  }}
+  }
+}
 
 // Fallback for shapes the tiled kernel does not cover (blocks of more than 64 tokens, any d that
 // is a multiple of 16 bytes, any r <= 16): one workgroup per head instance, logits

@@ -747,7 +747,7 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
     hipLaunchKernelGGL(select_segment_kernel, dim3(D.S), dim3(kSegThreads), lds, s, D, protect_tail_blocks, kSegLdsKeys,
                        block_key, st->ctx_len, budget, evict_flag, evict_count, selected, W.seg_state, W.off_a, W.header);
     KVC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+    hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
     KVC_LAUNCH_CHECK();
     hipLaunchKernelGGL(select_mark_kernel, dim3(gw), dim3(256), 0, s, D, protect_tail_blocks, block_key,
                        st->ctx_len, (const int32_t*)nullptr, W.seg_state, W.off_a, evict_flag, evict_count, selected,
@@ -772,7 +772,7 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
                        W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
     if (pass == 0) {  // keys checked, budgets checked: settle the status before any output is written
-      hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+      hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
       KVC_LAUNCH_CHECK();
     }
   }
@@ -803,7 +803,7 @@ int kvc_compact(const kvc_config* cfg, const kvc_state* st, const uint8_t* evict
   // the status is settled before anything moves; a caller that wants the count gets it from the
   // same launch (the counts are this call's input, the moves do not change them)
   if (blocks_freed) hipLaunchKernelGGL(publish_freed_kernel, dim3(1), dim3(1024), 0, s, W.header, evict_count, D.G, blocks_freed, 1);
-  else hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+  else hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
   KVC_LAUNCH_CHECK();
   const size_t stage_bytes = (size_t)D.maxb * 8;   // prefix counts and block ids of one head
   char* kcp = (char*)st->k_cache;

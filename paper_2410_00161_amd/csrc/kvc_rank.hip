@@ -714,7 +714,7 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
                        W.header);
     KVC_LAUNCH_CHECK();
     if (pass == 0 && nseg > 1) {
-      hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
+      hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
       KVC_LAUNCH_CHECK();
     }
   }
@@ -752,16 +752,15 @@ int kvc_compact_rank(const kvc_config* cfg, const kvc_state* st, const int32_t* 
   const bool few = D.G <= kRankSmallHeads;
   if (few) {
     hipLaunchKernelGGL(rank_check_small_kernel, dim3(1), dim3(1024), 0, s, D, st->ctx_len, evict_rows, blocks_freed, W.header);
+    KVC_LAUNCH_CHECK();
   } else {
     hipLaunchKernelGGL(rank_check_kernel, dim3((D.G + 255) / 256), dim3(256), 0, s, D, st->ctx_len, evict_rows,
                        W.header);
+    KVC_LAUNCH_CHECK();
+    if (blocks_freed) hipLaunchKernelGGL(publish_freed_kernel, dim3(1), dim3(1024), 0, s, W.header, evict_rows, D.G, blocks_freed, 1);
+    else hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
+    KVC_LAUNCH_CHECK();
   }
-  KVC_LAUNCH_CHECK();
-  if (few) {
-    // (settled)
-  } else if (blocks_freed) hipLaunchKernelGGL(publish_freed_kernel, dim3(1), dim3(1024), 0, s, W.header, evict_rows, D.G, blocks_freed, 1);
-  else hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header, 0);
-  KVC_LAUNCH_CHECK();
   if (D.G <= 1024) {
     // few, possibly long heads: a workgroup of 1024 threads per head, the head's metrics kept in
     // LDS (up to 36864 tokens; one such workgroup per CU is all there is to run anyway)
