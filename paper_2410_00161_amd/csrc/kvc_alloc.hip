@@ -86,8 +86,10 @@ constexpr int kScanWide = 1024 * kScanRun;     // elements per tile
 // consecutive elements (four 16-byte loads and, for the results, four 16-byte stores when the
 // arrays are 16-byte aligned, which workspace arrays are: a thread's run is 64 bytes, so with
 // 4-byte accesses every instruction of a wavefront touched 64 different lines), one workgroup
-// scan joins the runs.  out[i] = exclusive prefix (out may be `in`).
-__device__ __forceinline__ int wide_exclusive_scan(const int32_t* in, int n, int32_t* out, int* smem) {
+// scan joins the runs.  out[i] = exclusive prefix (out may be `in`).  owner (or NULL): owner[out[i]] = i
+// for every element that is not zero.
+__device__ __forceinline__ int wide_exclusive_scan(const int32_t* in, int n, int32_t* out, int* smem,
+                                                   int32_t* owner = nullptr, int owner_n = 0) {
   __shared__ int carry_s;
   if (threadIdx.x == 0) carry_s = 0;
   __syncthreads();
@@ -123,6 +125,11 @@ __device__ __forceinline__ int wide_exclusive_scan(const int32_t* in, int n, int
 #pragma unroll
       for (int k = 0; k < kScanRun; ++k) if (first + k < n) out[first + k] = o[k];
     }
+    if (owner) {
+#pragma unroll
+      for (int k = 0; k < kScanRun; ++k)
+        if (v[k] && (unsigned)o[k] < (unsigned)owner_n) owner[o[k]] = first + k;
+    }
     __syncthreads();
     if (threadIdx.x == 0) carry_s += tot;
     __syncthreads();
@@ -130,14 +137,16 @@ __device__ __forceinline__ int wide_exclusive_scan(const int32_t* in, int n, int
   return carry_s;
 }
 
-// Launch 2, one workgroup: exclusive scan of the requests (off[g], off[G] = total), exclusive
-// scan of the free-tile counts, and the status word.
+// Launch 2, one workgroup: exclusive scan of the requests (off[g], off[G] = total) with the owner of
+// every head's first request (owner[off[g]] = g), exclusive scan of the free-tile counts, and the status
+// word.
 __global__ void __launch_bounds__(1024) alloc_scan_kernel(Dims D, const int32_t* __restrict__ req,
                                                           int32_t* __restrict__ off,
+                                                          int32_t* __restrict__ owner,
                                                           int32_t* __restrict__ tile_sums, int ntiles,
                                                           int32_t* __restrict__ header) {
   __shared__ int smem[1024 / 64 + 1];
-  const int total_req = wide_exclusive_scan(req, D.G, off, smem);
+  const int total_req = wide_exclusive_scan(req, D.G, off, smem, owner, D.N);
   const int total_free = wide_exclusive_scan(tile_sums, ntiles, tile_sums, smem);
   if (threadIdx.x == 0) {
     off[D.G] = total_req;
@@ -153,22 +162,39 @@ __global__ void __launch_bounds__(1024) alloc_scan_kernel(Dims D, const int32_t*
   }
 }
 
+// Last head instance of [lo, hi) with off[g] <= k (off[lo] <= k), by all lanes of a wavefront.
+__device__ __forceinline__ int wave_find_head(const int32_t* off, int lo, int hi, int k, int lane) {
+  while (hi - lo > 1) {
+    const int step = (int)(((long long)hi - lo + 63) / 64);
+    const long long at = (long long)lo + (long long)lane * step;
+    const int below = __popcll(__ballot(at < hi && off[at < hi ? at : lo] <= k));   // the first lanes
+    lo += (below - 1) * step;
+    hi = hi - lo < step ? hi : lo + step;
+  }
+  return lo;
+}
+
 // Third phase of the scan over the free map, fused with the hand-out: the free block of
 // rank k (ascending id) goes to the head instance g with off[g] <= k < off[g + 1], as its
-// (k - off[g])-th new block.  A thread's free blocks are consecutive in rank: it searches for the
-// head of its first one and looks at that head again before it searches for the next.  (The
-// scan's single workgroup writing every request's head into a list instead was one thread's
-// serial run per head: 595 us for a prompt of 1024 blocks a head, 8 us for the whole launch here.)
+// (k - off[g])-th new block.  A rank that starts a head finds it in the list (an entry counts when its
+// head starts there, so nothing has to be cleared); every other rank goes where the one before it
+// went, whichever thread has that, and the workgroup's first one is searched for.  (All owners in the
+// list were one thread's serial run per head, without a list every thread searched for every head.
+// Whole call, all owners listed, searched, and this way: 16 384 heads, 1000 of them asking for a block
+// 23, 43 and 22 us, for one each 28, 35 and 28, for up to eight 52, 36 and 28; 2560 heads, five each 26, 30
+// and 20; 64 prompts of 7000 tokens in 32 layers of 8 heads 3776, 57 and 64.)
 // seq_tokens (a prefill): the lengths of the heads follow in the same launch.
 __global__ void __launch_bounds__(kScanThreads) pick_scatter_kernel(Dims D, int32_t* __restrict__ table,
                                                                     uint8_t* __restrict__ free_map,
                                                                     const int32_t* __restrict__ tile_sums,
                                                                     const int32_t* __restrict__ held,
                                                                     const int32_t* __restrict__ off,
+                                                                    const int32_t* __restrict__ owner,
                                                                     const int32_t* __restrict__ seq_tokens,
                                                                     int32_t* __restrict__ ctx,
                                                                     const int32_t* __restrict__ header) {
   __shared__ int smem[kScanThreads / 64 + 1];
+  __shared__ int head_s[kScanThreads / 64 + 1];   // last head that starts in every wavefront's ranks; [4]: the first rank's
   const int total_req = header[HW_TOTAL_REQ];
   if (header[HW_STATUS] != KVC_OK) return;
   if (seq_tokens)
@@ -181,22 +207,60 @@ __global__ void __launch_bounds__(kScanThreads) pick_scatter_kernel(Dims D, int3
   const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
   int v[kScanItems];
   int s = 0;
+  if (((uintptr_t)free_map & 7) == 0 && base + kScanItems <= D.N) {   // (a load of eight bytes, not eight)
+    const uint2 m = *(const uint2*)(free_map + base);
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k) { v[k] = (base + k < D.N) ? (free_map[base + k] != 0) : 0; s += v[k]; }
+    for (int k = 0; k < kScanItems; ++k) { v[k] = ((k < 4 ? m.x : m.y) >> (8 * (k & 3)) & 0xff) != 0; s += v[k]; }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) { v[k] = (base + k < D.N) ? (free_map[base + k] != 0) : 0; s += v[k]; }
+  }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (wv == 0) {
+    const int ga = tile0 > 0 ? wave_find_head(off, 0, D.G, tile0, lane) : 0;   // (rank 0 starts a head: nothing goes by this one)
+    if (lane == 0) head_s[kScanThreads / 64] = ga;
+  }
   int ex = block_exclusive_scan<kScanThreads>(s, smem, nullptr) + tile0;
-  int g = -1, first = 0, end = 0;   // head instance in hand, its requests' ranks first .. end - 1
+  int own[kScanItems], own_first[kScanItems], own_end[kScanItems], own_held[kScanItems];   // asked for together
+  int e = ex;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    own[k] = v[k] && e < total_req ? owner[e] : -1;
+    if ((unsigned)own[k] >= (unsigned)D.G) own[k] = -1;
+    e += v[k];
+  }
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    own_first[k] = own[k] >= 0 ? off[own[k]] : -1;
+    own_end[k] = own[k] >= 0 ? off[own[k] + 1] : 0;
+    own_held[k] = own[k] >= 0 ? held[own[k]] : 0;
+  }
+  int last = -1;   // last head that starts in this thread's ranks
+  e = ex;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (own_first[k] != e || own_end[k] <= e) own[k] = -1;
+    if (own[k] >= 0) last = own[k];
+    e += v[k];
+  }
+  const unsigned long long starts = __ballot(last >= 0);
+  const unsigned long long ahead = starts & ((1ull << lane) - 1);
+  int g = __shfl(last, ahead ? 63 - __builtin_clzll(ahead) : 0);   // head in hand: of the rank before this thread's first
+  if (!ahead) g = -1;
+  const int wave_last = __shfl(last, starts ? 63 - __builtin_clzll(starts) : 0);
+  if (lane == 0) head_s[wv] = starts ? wave_last : -1;
+  __syncthreads();
+  if (g < 0) {
+    g = head_s[kScanThreads / 64];
+    for (int w = 0; w < wv; ++w) if (head_s[w] >= 0) g = head_s[w];
+  }
+  int first = off[g], had = held[g];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (v[k]) {
       if (ex < total_req) {
-        if (ex >= end) {   // the last head with off[g] <= ex: its own requests are not empty
-          int lo = g < 0 ? 0 : g, hi = D.G;
-          while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (off[mid] <= ex) lo = mid; else hi = mid; }
-          g = lo;
-          first = off[g];
-          end = off[g + 1];
-        }
-        table[(size_t)g * D.maxb + held[g] + (ex - first)] = base + k;
+        if (own[k] >= 0) { g = own[k]; first = own_first[k]; had = own_held[k]; }
+        table[(size_t)g * D.maxb + had + (ex - first)] = base + k;
         free_map[base + k] = 0;
       }
       ++ex;
@@ -560,14 +624,15 @@ static int alloc_common(const Dims& D, const kvc_state* st, const Workspace& W, 
                         int mode, hipStream_t s) {
   const int gb = (D.G + 255) / 256;
   const int ntiles = (D.N + kScanTile - 1) / kScanTile;
+  int32_t* owner = (int32_t*)W.stash;   // [N] fits where the decode keeps N * b * r floats
   hipLaunchKernelGGL(count_and_free_tiles_kernel, dim3(gb + ntiles), dim3(256), 0, s, D, st->block_table,
                      st->ctx_len, n, mode, gb, st->free_map, W.held, W.off_b, W.tile_sums, W.header);
   KVC_LAUNCH_CHECK();
-  hipLaunchKernelGGL(alloc_scan_kernel, dim3(1), dim3(1024), 0, s, D, W.off_b, W.off_a, W.tile_sums,
+  hipLaunchKernelGGL(alloc_scan_kernel, dim3(1), dim3(1024), 0, s, D, W.off_b, W.off_a, owner, W.tile_sums,
                      ntiles, W.header);
   KVC_LAUNCH_CHECK();
   hipLaunchKernelGGL(pick_scatter_kernel, dim3(ntiles), dim3(kScanThreads), 0, s, D, st->block_table,
-                     st->free_map, W.tile_sums, W.held, W.off_a, mode == ALLOC_PREFILL ? n : (const int32_t*)nullptr,
+                     st->free_map, W.tile_sums, W.held, W.off_a, owner, mode == ALLOC_PREFILL ? n : (const int32_t*)nullptr,
                      st->ctx_len, W.header);
   KVC_LAUNCH_CHECK();
   return KVC_OK;
