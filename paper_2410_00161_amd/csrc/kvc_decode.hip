@@ -1229,7 +1229,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     A.header = W.plan_hdr;
     if (plan_mode == PLAN_BUILD) {
       A.out = nullptr;    // (the zero rows of heads without a KV are written when the layer is decoded)
-      hipLaunchKernelGGL(decode_worklist_small_kernel, dim3(D.Lyr), dim3(1024), 0, s, A);
+      hipLaunchKernelGGL(decode_worklist_small_kernel<true>, dim3(D.Lyr), dim3(1024), 0, s, A);
       KVC_LAUNCH_CHECK();
       return KVC_OK;
     }
@@ -1239,7 +1239,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   } else if (small_call && A.gsel <= kSelfListHeads) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {
-    hipLaunchKernelGGL(decode_worklist_small_kernel, dim3(1), dim3(1024), 0, s, A);
+    hipLaunchKernelGGL(decode_worklist_small_kernel<false>, dim3(1), dim3(1024), 0, s, A);
     KVC_LAUNCH_CHECK();
   } else {
     hipLaunchKernelGGL(decode_count_kernel, dim3((A.gsel + 255) / 256), dim3(256), 0, s, A);

@@ -190,6 +190,7 @@ __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long to
 // layer of a model, one prompt): one launch instead of two.  Leaves the header words as the
 // two-pass pair does.  (Measured with two heads per thread, 2048 heads: no faster than the pair.)
 constexpr int kSmallWorklistHeads = 1024;
+template <bool PLAN>
 static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(DecodeArgs A) {
   __shared__ int bins[16], base[16], cur[17], ptot;
   __shared__ unsigned long long tokens;
@@ -197,8 +198,8 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   __shared__ unsigned long long before;
   const int tid = threadIdx.x;
   // a plan: workgroup l lists layer A.l0 + l into that layer's header block and stretch of records
-  const int layer = A.plan ? (int)blockIdx.x : 0;
-  int32_t* header = A.header + (size_t)layer * (A.plan ? HW_WORDS : 0);
+  const int layer = PLAN ? (int)blockIdx.x : 0;
+  int32_t* header = A.header + (size_t)layer * (PLAN ? HW_WORDS : 0);
   DecodeItem* items = A.items + (size_t)layer * A.plan_stride;
   int32_t* slot_item = A.slot_item + (size_t)layer * A.plan_stride;
   int cap = A.cap;
@@ -215,7 +216,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   // behind the most that the layers before it can need from their lengths (a full chunk holds at least
   // kSmallCallChunk tokens, and a head has one shorter chunk).  That always fits: all layers together
   // need no more records than the workspace has for one call over them all.
-  const bool placed = A.plan && A.plan_stride == 0;
+  const bool placed = PLAN && A.plan_stride == 0;
   if (placed) {
     const int per = layer * A.D.Hk;
     unsigned long long t = 0;
@@ -265,7 +266,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
       if (k >= A.short_class) shorts += bins[k];
     }
     // (a list that does not fit, which lengths the pool can hold never make, is one no decode takes)
-    header[HW_TOTAL_ITEMS] = A.plan && run > cap ? 0x7fffffff : run;
+    header[HW_TOTAL_ITEMS] = PLAN && run > cap ? 0x7fffffff : run;
     header[HW_SHORT_ITEMS] = shorts;
   }
   __syncthreads();
