@@ -329,9 +329,12 @@ int kvc_window_metric(const kvc_config* cfg, const kvc_state* st, const void* q_
  * Always accumulates; no pooling.  Calling it for consecutive blocks of a prompt's queries
  * builds M_full[j] = sum over i >= j + v and the group's heads of A_ij^2.  row_lse
  * [S, Lyr, Hq, w] or NULL, shapes and errors as kvc_window_metric, except that w may be any
- * length (the paper aggregates 1024 queries at a time): more than 256 query rows are worked off
- * in one pass where they round well to the kernels' tiles, else 64 queries, or 256 query rows,
- * at a time.  Asynchronous.                            */
+ * length (the paper aggregates 1024 queries at a time).  More than 256 query rows are worked off all
+ * at once (the keys are read twice, once with row_lse) where w rounds to tiles of 64 queries and
+ * w * group_size to 256 rows by at most an eighth, the tables have at most twice the room that the pool
+ * can fill, and what the launches leave each other (8 bytes per row and chunk of 1024 to 4096 keys,
+ * none with row_lse, and 4 per row) fits the workspace's partial outputs; else 64 queries, or 256
+ * query rows, at a time.  Asynchronous.                                                         */
 int kvc_query_block_metric(const kvc_config* cfg, const kvc_state* st, const void* q_blk, const float* row_lse,
                            int w, int first_pos, int exclude, int layer_begin, int layer_end, void* ws,
                            void* stream);
