@@ -455,7 +455,8 @@ __global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendAr
       v[u] = at < m1 ? free_bytes16(A.free_map, at, m1, wide) : make_uint4(0, 0, 0, 0);
     }
   };
-  if (!FUSED) ask();   // (it hangs on nothing; few heads often ask for no block at all)
+  const bool early = !FUSED && n_wg > 1;
+  if (early) ask();   // (it hangs on nothing; few heads, and small pools, often need no look at the map)
   if (tid == 0) { bits_s = 0; free_s = 0; }
   __syncthreads();
   // requesters, in ascending order: of this share of the heads; of all of few heads, in every
@@ -496,9 +497,9 @@ __global__ void __launch_bounds__(kAppendThreads) append_reserve_kernel(AppendAr
   }
   // its free blocks (a single workgroup counts them only when they are wanted)
   const bool alone = n_wg == 1, counted = n_req > 0 || (!FUSED && !alone);
-  if (FUSED && counted) ask();
-  // The loads are done, in words the compiler counts by: it would wait for them further down, and with
-  // them for the stores below.
+  if (counted && !early) ask();
+  // The loads are done (or there are none), in words the compiler counts by: it would wait for them
+  // further down, and with them for the stores below.
   __builtin_amdgcn_s_waitcnt(kWaitLoads);
   if (counted) {
     int s = 0;
