@@ -98,4 +98,6 @@ def test_few_requests_among_many_heads_cost_little_more_than_none():
             times.append(a.elapsed_time(e))
         p.check(n)
         took.append(statistics.median(times))
+    # 16.0 and 21.3 us, a ratio of 1.33 to 1.34 in five runs; with the search 15.4 and 43.3 us, 2.8: the line is
+    # between the two, near their geometric mean (1.9)
     assert took[1] <= 2 * took[0], took
