@@ -1,0 +1,89 @@
+"""Windows whose query rows stay in registers (one run of keys per wavefront), against the CPU oracle:
+heads that begin and end inside a run, runs of several heads, tiles of 16, 32 and 64 tokens, blocks
+shorter than a load, the max-pool across runs at its widest and one wider (the other kernels), runs long
+enough for the pool to be taken in several pieces."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvc_oracle as O
+from paper_2410_00161_amd import workloads as W
+from helpers import oracle_state
+from test_gpu_window_paths import make, queries
+from test_gpu_window_metric import row_lse
+
+pytestmark = pytest.mark.gpu
+LENGTHS = [1, 15, 16, 17, 0, 127, 128, 129, 31, 300, 2049, 64, 1000, 5, 513, 640]
+
+
+def close(got, want, real):
+    """f32 sums of at most 256 exact products per score, exps good to 2^-18: 1e-5 of a metric; what lies
+    1e6 below the largest is not told from the rounding of its neighbours in the exp's argument."""
+    big = real & (want > 1e-6)
+    assert np.isfinite(got[real]).all()
+    np.testing.assert_allclose(got[big], want[big], rtol=1e-4, atol=0)
+    np.testing.assert_allclose(got[real], want[real], rtol=0, atol=1e-4 * want[real].max())
+
+
+@pytest.mark.parametrize("r,w,d,b,dtype,pool,lse,add", [
+    (4, 8, 128, 16, "bf16", 7, False, False),     # 32 rows
+    (4, 16, 128, 16, "bf16", 33, False, False),   # 64 rows, the widest pool
+    (4, 16, 128, 16, "bf16", 35, False, False),   # wider than a run's halo
+    (4, 32, 128, 16, "bf16", 7, True, False),     # 128 rows
+    (3, 21, 128, 32, "bf16", 5, True, True),      # 63 rows, added to the metric
+    (5, 25, 128, 8, "bf16", 7, True, False),      # 125 rows, two blocks to a group
+    (1, 64, 128, 4, "bf16", 1, False, False),     # a block per load
+    (2, 16, 128, 2, "bf16", 7, True, False),      # blocks shorter than a load
+    (1, 5, 128, 1, "bf16", 7, False, True),
+    (8, 16, 128, 16, "fp8", 7, True, False),      # tiles of 32 tokens
+    (2, 32, 128, 8, "fp8", 3, False, False),
+    (4, 32, 64, 16, "bf16", 7, False, False),
+    (4, 8, 64, 4, "bf16", 7, False, False),
+    (8, 16, 64, 64, "fp8", 7, False, False),      # tiles of 64 tokens
+    (1, 32, 64, 8, "fp8", 1, False, False),
+])
+def test_runs_and_heads(r, w, d, b, dtype, pool, lse, add):
+    from paper_2410_00161_amd.session import KvcSession
+    shape, cache, real = make(2, 2, 4, r, d, b, LENGTHS, dtype, 0)
+    st = oracle_state(cache)
+    before = cache.metric.numpy().astype(np.float64)
+    q = queries(shape, w)
+    given = row_lse(st, q.double().numpy(), w) if lse else None
+    O.window_metric(st, q.double().numpy(), w, pool, accumulate=add, row_lse=given)
+    sess = KvcSession(cache)
+    sess.window_metric(q.to(sess.device), w, pool, accumulate=add,
+                       row_lse=None if given is None else torch.from_numpy(given).to(sess.device))
+    torch.cuda.synchronize()
+    m = sess.cache.metric.cpu().numpy().astype(np.float64)
+    close(m, st.metric, real)
+    np.testing.assert_array_equal(m[~real], before[~real])
+
+
+@pytest.mark.parametrize("Lyr,Hk,r,w,d,b,dtype,L", [
+    (32, 8, 4, 32, 128, 16, "bf16", 4200),    # 128 rows without the log-sum-exp: at least 32 tiles per wavefront
+    (21, 8, 4, 8, 64, 16, "fp8", 3900),       # five tiles of 64
+    (30, 8, 2, 16, 128, 8, "bf16", 3001),
+])
+def test_long_runs_sampled(Lyr, Hk, r, w, d, b, dtype, L):
+    """Every wavefront takes the pool of its run in more than one piece; sampled heads."""
+    from paper_2410_00161_amd.session import KvcSession
+    dev = torch.device("cuda:0")
+    ctx = torch.full((Lyr * Hk,), L, dtype=torch.int32)
+    ctx[1::3] -= 77
+    shape = W.Shape(1, Lyr, Hk, r, d, b, W.pool_size(ctx, b, 1.0, 5), -(-L // b) + 1, dtype)
+    tile = 4096 // (d * (1 if dtype == "fp8" else 2))
+    assert -(-int(ctx.sum()) // (2048 * tile)) * tile > 288      # positions of a run
+    cache = W.make_cache(shape, ctx, 23, device=dev, placement="fragmented", init_metric="prefill")
+    q = queries(shape, w).to(dev)
+    sess = KvcSession(cache, device=dev)
+    heads = [0, 1, Lyr * Hk // 2, Lyr * Hk - 1]
+    small, _ = W.gather_heads(sess.cache, heads)
+    st = oracle_state(small)
+    q_small = q.reshape(Lyr * Hk, r, w, d)[heads].double().cpu().numpy().reshape(st.S, st.Lyr, st.Hk * r, w, d)
+    O.window_metric(st, q_small, w, 7)
+    sess.window_metric(q, w, 7)
+    torch.cuda.synchronize()
+    after, _ = W.gather_heads(sess.cache, heads)
+    for i in range(len(heads)):
+        n, o = O.slots_of(st, i)
+        close(after.metric.double().numpy()[n, o], st.metric[n, o], np.ones(len(n), dtype=bool))
