@@ -177,25 +177,23 @@ __device__ __forceinline__ void stash_load(const float* stash, size_t slot, floa
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / 64;
 
-// A shape takes Q K^T to the matrix cores where the plain ALUs are the bound: 16-bit or 8-bit
+// A shape takes both products to the matrix cores where the plain ALUs are the bound: 16-bit or 8-bit
 // rows (the latter widened to bf16 on their way into the operand tile) with eight query heads per
-// KV head, 8-bit rows with four (half the bytes per logit: with the dot products on the plain ALUs
-// that launch ran 8 % longer), d = 128, blocks of a multiple of 16 tokens.
-__host__ __device__ constexpr bool decode_uses_mfma(int esz, int R, int HD, int b) {
-  return esz <= 2 && (R == 8 || (R == 4 && esz == 1)) && HD == 128 && b % 16 == 0;
-}
-
-// P V goes to the matrix cores wherever Q K^T does.
-__host__ __device__ constexpr bool decode_pv_mfma(int esz, int R, int HD, int b) {
-  return decode_uses_mfma(esz, R, HD, b);
+// KV head, 8-bit rows of d = 128 with four (half the bytes per logit: with the dot products on the plain
+// ALUs that launch ran 8 % longer).  On the plain ALUs and here, decode steps over 32 layers x 8 KV heads
+// at a quarter of 8192 tokens: d = 128 in blocks of 8 tokens, 16 sequences of bf16 with eight heads
+// 1250 and 843 us, of fp8 with eight 1224 and 576, 24 of fp8 with four 766 and 705; d = 64, 32 sequences
+// of bf16 with eight 1134 and 912, of fp8 with eight 1061 and 766, of fp8 with four 647 and 656 (left out).
+__host__ __device__ constexpr bool decode_uses_mfma(int esz, int R, int HD) {
+  return (HD == 128 || HD == 64) && ((R == 8 && esz <= 2) || (R == 4 && esz == 1 && HD == 128));
 }
 
 // Register buffers of K and V groups a wavefront rotates through (one less is in flight behind
 // the group being worked on): three for rows of at most 16 bits when four wavefronts share a
 // long chunk (up to four query heads, or the matrix-core shapes), else two.
-__host__ __device__ constexpr int decode_depth(int esz, int R, int HD, bool b16, int nw) {
+__host__ __device__ constexpr int decode_depth(int esz, int R, int HD, int nw) {
   if (nw != 4 || esz > 2) return 2;
-  return (R <= 4 || (b16 && decode_uses_mfma(esz, R, HD, 16))) ? 3 : 2;
+  return (R <= 4 || decode_uses_mfma(esz, R, HD)) ? 3 : 2;
 }
 
 __host__ __device__ inline size_t decode_lds_bytes(int T, int R, int HD, int b, int waves = kDecodeWaves,
@@ -230,7 +228,7 @@ __host__ __device__ inline size_t decode_lds_bytes(int T, int R, int HD, int b, 
 template <int ESZ, int HD, int R, bool B16, int NW>
 __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   constexpr int NT = NW * 64;
-  constexpr int DEPTH = decode_depth(ESZ, R, HD, B16, NW);
+  constexpr int DEPTH = decode_depth(ESZ, R, HD, NW);
   constexpr int EPL = Row<ESZ>::EPL;
   constexpr int PB = Row<ESZ>::PB;     // bytes a lane loads at once
   typedef typename Row<ESZ>::P Piece;
@@ -248,9 +246,8 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   // order through 4 KiB of LDS, cells XOR-swizzled so that neither side has a bank conflict.
   // Head h sits in operand row 4 (h % 4) + h / 4, which leaves lane 16 a + t with the logits of
   // token t against heads a and a + 4.
-  constexpr bool MF = B16 && decode_uses_mfma(ESZ, R, HD, 16);
-  constexpr bool PVM = B16 && decode_pv_mfma(ESZ, R, HD, 16);   // P V on the matrix cores (with or without Q K^T)
-  constexpr int RW = PVM ? 8 : R;      // output rows a wavefront's LDS region has room for
+  constexpr bool MF = decode_uses_mfma(ESZ, R, HD);
+  constexpr int RW = MF ? 8 : R;      // output rows a wavefront's LDS region has room for
   constexpr int NVH = (R + 3) / 4;     // MF: logits per lane
   constexpr int OWN = MF ? NVH : PER;
 
@@ -309,7 +306,15 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   // [waves][R][HD]; on the matrix-core path a wavefront's 4 KiB of it are its operand tile until
   // its main loop ends (R * HD * 4 = 16 * HD * 2 there, so no wavefront touches another's tile)
   float* s_acc = (float*)smem_raw;
-  static_assert(!PVM || (size_t)RW * HD * 4 == (size_t)16 * HD * 2, "output rows alias the operand tile wavefront by wavefront");
+  constexpr int PARTS = HD == 128 && B16 ? 2 : 3;   // MF: parts of 16 bits of a probability (see P V)
+  constexpr int PROWS = R == 4 && PARTS == 3 ? 4 : 8;   // MF: operand rows between a head's parts
+  constexpr int CELLS = HD / 8;        // MF: 16-byte cells of a token's row in the operand tile
+  // position of cell c of token t's row: such that the 16 lanes that read one cell of 16 keys, and the 8
+  // tokens x 32 bytes that half a wavefront reads of V, touch every bank once
+  auto k_at = [](int t, int c) { return t * CELLS + (c ^ (CELLS == 16 ? t : t >> 1)); };
+  auto v_swizzle = [](int t) { return CELLS == 16 ? 2 * (t & 7) : 2 * ((t >> 1) & 3); };
+  static_assert(!MF || U == HD / 32, "a product of 32 dimensions per load");
+  static_assert(!MF || (size_t)RW * HD * 4 == (size_t)16 * HD * 2, "output rows alias the operand tile wavefront by wavefront");
   float* s_e = s_acc + NW * RW * HD;         // [waves][16][R]
   float* s_red = s_e + NW * 16 * R;          // [2][waves][R]
   float* s_gm = s_red + 2 * NW * R;          // [T / 16][R]
@@ -375,14 +380,15 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
 #pragma unroll
     for (int k = 0; k < EPL; ++k) acc[hh][k] = 0.0f;
   // MFMA path: P V as v_mfma_f32_16x16x16_bf16 per 16 dimensions (rows = heads, columns =
-  // dimensions, k = the 16 tokens of a group).  A probability goes in as two bf16 halves,
-  // hi = its upper 16 bits in row h, lo = (p - hi) in row h + 8, so that the product carries
-  // 16 bits of p (one half alone misses the output tolerance when one key dominates).
+  // dimensions, k = the 16 tokens of a group).  A probability goes in as parts of 16 bits each, its
+  // upper 16 bits, those of the remainder, and, where PARTS is 3, the rest: with two parts the product
+  // carries 16 bits of p (one alone misses the output tolerance when one key dominates), with three
+  // all 24.
   constexpr int NDT = HD / 16;
-  static_assert(!PVM || R == 8 || R == 4, "operand rows: heads 0..7 as upper halves, then as remainders");
-  f32x4_t pacc[PVM ? NDT : 1];
+  static_assert(!MF || R == 8 || R == 4, "operand rows");
+  f32x4_t pacc[MF ? NDT : 1];
 #pragma unroll
-  for (int i = 0; i < (PVM ? NDT : 1); ++i) pacc[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int i = 0; i < (MF ? NDT : 1); ++i) pacc[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   float m_run[R];            // running max per query head, the same in every lane
   float m_own[OWN], l_own[OWN];  // this lane's head(s): running max and partial sum
 #pragma unroll
@@ -397,21 +403,44 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
       float m_new[R];
       bool moved = false;
       if constexpr (MF) {
-        // this wavefront's K tile into operand order: cell (token, 16-byte piece c) sits at
-        // position c ^ token of the token's row
-        uint4* kt = s_kt + w * 256;
+        // this wavefront's K tile into operand order
+        uint4* kt = s_kt + w * 16 * CELLS;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int t = u * TPI + sub;
-          kt[t * 16 + (seg ^ t)] = Row<ESZ>::as_bf16x8(kcur[u]);
+          kt[k_at(t, seg)] = Row<ESZ>::as_bf16x8(kcur[u]);
         }
         const int tl = lane & 15, hrow = lane >> 4;
-        f32x4_t sacc = {0.0f, 0.0f, 0.0f, 0.0f};
+        float sacc[NVH];
+        if constexpr (PARTS == 2) {
+          f32x4_t acc4 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int st = 0; st < U; ++st) {
-          const uint4 kb = kt[tl * 16 + ((4 * st + hrow) ^ tl)];
-          sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qv[st]),
-                                                         __builtin_bit_cast(bf16x8_t, kb), sacc, 0, 0, 0);
+          for (int st = 0; st < U; ++st) {
+            const uint4 kb = kt[k_at(tl, 4 * st + hrow)];
+            acc4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qv[st]), __builtin_bit_cast(bf16x8_t, kb), acc4, 0, 0, 0);
+          }
+#pragma unroll
+          for (int v = 0; v < NVH; ++v) sacc[v] = acc4[v];
+        } else {
+          // products of 16 dimensions each, added up in pairs: as near to 64 bits as the plain dot products
+          f32x4_t dots[2 * U];
+#pragma unroll
+          for (int st = 0; st < U; ++st) {
+            const uint4 kb = kt[k_at(tl, 4 * st + hrow)];
+            const i16x4_t q2[2] = {__builtin_bit_cast(i16x4_t, make_uint2(qv[st].x, qv[st].y)), __builtin_bit_cast(i16x4_t, make_uint2(qv[st].z, qv[st].w))};
+            const i16x4_t k2[2] = {__builtin_bit_cast(i16x4_t, make_uint2(kb.x, kb.y)), __builtin_bit_cast(i16x4_t, make_uint2(kb.z, kb.w))};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              dots[2 * st + i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(q2[i], k2[i], f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+          }
+#pragma unroll
+          for (int v = 0; v < NVH; ++v) {
+#pragma unroll
+            for (int half = U; half >= 1; half /= 2)
+#pragma unroll
+              for (int i = 0; i < half; ++i) dots[i][v] += dots[i + half][v];
+            sacc[v] = dots[0][v];
+          }
         }
         const bool live = grp * 16 + tl < n_tok;
         float x[NVH], gm[NVH], e[NVH];
@@ -476,7 +505,7 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
           const float e = __builtin_amdgcn_exp2f(part[i] - gm[i]);
           l_own[i] = l_own[i] * __builtin_amdgcn_exp2f(m_own[i] - gm[i]) + e;
           m_own[i] = gm[i];
-          my_e[PVM ? hh * 16 + tl : tl * R + hh] = e;   // [head][token] for the matrix-core P V
+          my_e[MF ? hh * 16 + tl : tl * R + hh] = e;   // [head][token] for the matrix-core P V
           s_q[(grp * 16 + tl) * R + hh] = (uint16_t)q16(e);
           if (gm_writer) s_gm[grp * R + hh] = gm[i];
         }
@@ -488,57 +517,64 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
         }
       }
       const bool tail = B16 && grp * 16 + 16 > n_tok;
-      if constexpr (PVM) {
+      if constexpr (MF) {
         if (moved) {
-          // this lane's product rows 4 (lane / 16) + v belong to heads 4 ((lane / 16) % 2) + v
+          // this lane's product rows 4 (lane / 16) + v belong to heads 4 ((lane / 16) % 2) + v (PROWS = 4: to heads v)
           const bool upper = (lane & 16) != 0;
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const float a_lo = __builtin_amdgcn_exp2f(m_run[v] - m_new[v]);
-            const float a_hi = R > 4 ? __builtin_amdgcn_exp2f(m_run[(4 + v) % R] - m_new[(4 + v) % R]) : 1.0f;
-            const float a = upper ? a_hi : a_lo;
+            const float a_hi = R > 4 ? __builtin_amdgcn_exp2f(m_run[(4 + v) % R] - m_new[(4 + v) % R]) : a_lo;
+            const float a = upper && R > 4 ? a_hi : a_lo;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) pacc[dt][v] *= a;
           }
 #pragma unroll
           for (int hh = 0; hh < R; ++hh) m_run[hh] = m_new[hh];
         }
-        // The K tile (if Q K^T went through it) has been consumed: its 4 KiB take the V tile, row-major [token][d] in
-        // bf16, the 16-byte cell c of token t at position c ^ 2 (t % 8) of the row, which keeps
-        // the transposing reads below (8 tokens x 32 bytes per half wavefront) off each other's banks.
-        uint4* vt = s_kt + w * 256;
+        // The K tile has been consumed: its bytes take the V tile, row-major [token][d] in bf16.
+        uint4* vt = s_kt + w * 16 * CELLS;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int t = u * TPI + sub;
           const bool dead = tail && grp * 16 + t >= n_tok;   // empty slot: may hold anything
-          vt[t * 16 + (seg ^ (2 * (t & 7)))] = Row<ESZ>::as_bf16x8(dead ? Row<ESZ>::zero() : vcur[u]);
+          vt[t * CELLS + (seg ^ v_swizzle(t))] = Row<ESZ>::as_bf16x8(dead ? Row<ESZ>::zero() : vcur[u]);
         }
-        // A operand: lane = (row lane % 16, tokens 4 (lane / 16) .. + 3)
-        const int rho = lane & 15, kap = lane >> 4;
+        // A operand: lane = (row lane % 16, tokens 4 (lane / 16) .. + 3), row = part * PROWS + head
+        const int rho = lane & 15, kap = lane >> 4, part = rho / PROWS;
         float4 pe = *(const float4*)(my_e + (rho & (R - 1)) * 16 + 4 * kap);
-        if (R < 8 && (rho & 7) >= R) pe = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // operand rows without a head
-        const bool hi_row = rho < 8;
-        auto half_of = [&](float p) {   // the float whose upper 16 bits are this row's half of p
-          const uint32_t bits = __float_as_uint(p);
-          const float lo = p - __uint_as_float(bits & 0xffff0000u);   // exact
-          return hi_row ? bits : __float_as_uint(lo);
+        if (R < 8 && (rho % PROWS >= R || part >= PARTS)) pe = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // rows without a head or a part
+        auto top16 = [](float p) { return __uint_as_float(__float_as_uint(p) & 0xffff0000u); };
+        auto part_of = [&](float p) {   // a float whose upper 16 bits are this row's part of p
+          const float mid = p - top16(p);   // exact
+          if (PROWS == 4) return part == 0 ? p : part == 1 ? mid : mid - top16(mid);
+          return part == 0 ? p : mid;
         };
-        const uint32_t hb0 = half_of(pe.x), hb1 = half_of(pe.y), hb2 = half_of(pe.z), hb3 = half_of(pe.w);
-        const uint2 apack = make_uint2(__builtin_amdgcn_perm(hb1, hb0, 0x07060302u),
-                                       __builtin_amdgcn_perm(hb3, hb2, 0x07060302u));
-        const i16x4_t aop = __builtin_bit_cast(i16x4_t, apack);
+        auto pack = [](float p0, float p1, float p2, float p3) {
+          const uint2 u = make_uint2(__builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u),
+                                     __builtin_amdgcn_perm(__float_as_uint(p3), __float_as_uint(p2), 0x07060302u));
+          return __builtin_bit_cast(i16x4_t, u);
+        };
+        const i16x4_t aop = pack(part_of(pe.x), part_of(pe.y), part_of(pe.z), part_of(pe.w));
+        // the third part of eight heads does not fit: a second operand, the same rows
+        i16x4_t aop3 = {0, 0, 0, 0};
+        if constexpr (PARTS == 3 && R == 8) {
+          auto last = [&](float p) { const float mid = p - top16(p); return part == 0 ? mid - top16(mid) : 0.0f; };
+          aop3 = pack(last(pe.x), last(pe.y), last(pe.z), last(pe.w));
+        }
         // B operand of dimension tile dt: lane = (column lane % 16, tokens 4 (lane / 16) .. + 3).
         // The transposing read delivers it when lane j of a group of 16 points at token
         // 4 (lane / 16) + j / 4, dimensions 16 dt + 4 (j % 4) .. + 3.
         const int tt = 4 * kap + (rho >> 2);
-        const char* vrow = (const char*)vt + tt * 256 + 8 * (rho & 1);
-        const int csw = 2 * (tt & 7), chalf = (rho & 3) >> 1;
+        const char* vrow = (const char*)vt + tt * (HD * 2) + 8 * (rho & 1);
+        const int csw = v_swizzle(tt), chalf = (rho & 3) >> 1;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
           const int c = (2 * dt + chalf) ^ csw;
           const i16x4_t bop = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
               (i16x4_t __attribute__((address_space(3)))*)(vrow + c * 16));
           pacc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aop, bop, pacc[dt], 0, 0, 0);
+          if constexpr (PARTS == 3 && R == 8) pacc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aop3, bop, pacc[dt], 0, 0, 0);
         }
       } else {
         if (moved) {
@@ -631,13 +667,14 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
       }
     }
   }
-  if constexpr (PVM) {
-    // rows h and h + 8 of the product (lanes 32 apart) are the two halves of head h
+  if constexpr (MF) {
+    // rows PROWS apart of the product are the parts of a head: rows h and h + 8 are 32 lanes apart
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float a = pacc[dt][v] + __shfl_xor(pacc[dt][v], 32);
+        float a = pacc[dt][v] + __shfl_xor(pacc[dt][v], 32);
+        if (PROWS == 4) a += __shfl_xor(a, 16);
         if (lane < (R > 4 ? 32 : 16)) s_acc[(w * RW + 4 * (lane >> 4) + v) * HD + 16 * dt + (lane & 15)] = a;
       }
   } else {
@@ -969,7 +1006,7 @@ static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_shor
   if (pp) { KVC_HIP(hipEventRecord(pp->a1, s)); KVC_HIP(hipEventRecord(pp->s0, s)); }
   if (A.short_class < 16) {
     hipLaunchKernelGGL(kern_short, dim3(grid_short), dim3(64),
-                       decode_lds_bytes(A.Ts, R, HD, A.D.b, 1, decode_pv_mfma(ESZ, R, HD, A.D.b)), s, A);
+                       decode_lds_bytes(A.Ts, R, HD, A.D.b, 1, decode_uses_mfma(ESZ, R, HD)), s, A);
     KVC_LAUNCH_CHECK();
   }
   if (pp) { KVC_HIP(hipEventRecord(pp->s1, s)); KVC_HIP(hipEventRecord(pp->b0, s)); }
@@ -1026,11 +1063,11 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
     // just what the tables have room for, and picks the length (at most the default) on the device
     if (shrunk && gsel <= kSmallWorklistHeads) { T = T_default; device_side = true; }
   }
-  const bool mf = decode_pv_mfma(esz, D.r, D.d, D.b);   // a per-wavefront operand tile in LDS
-  // the default is sized so that two workgroups share a CU's LDS with blocks of 16 tokens; blocks
-  // of one or two tokens put a block id per token or two next to the exps: a shorter chunk keeps
-  // the second workgroup on the CU
-  if (!g_chunk_tokens.load(std::memory_order_relaxed) && D.b < 4 &&
+  const bool mf = decode_uses_mfma(esz, D.r, D.d);   // a per-wavefront operand tile in LDS
+  // the default is sized so that two workgroups share a CU's LDS with blocks of 16 tokens; shorter
+  // blocks put more block ids next to the exps (eight heads, d = 128, blocks of 8: 82 628 bytes): a shorter
+  // chunk keeps the second workgroup on the CU
+  if (!g_chunk_tokens.load(std::memory_order_relaxed) && D.b < 16 &&
       decode_lds_bytes(T, D.r, D.d, 16, kDecodeWaves, mf) <= kLdsLimit / 2)
     while (T > 1024 && decode_lds_bytes(T, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsLimit / 2) T -= 64;
   while (T > kMinChunk && decode_lds_bytes(T, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsLimit) T -= 64;
