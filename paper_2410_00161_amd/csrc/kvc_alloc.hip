@@ -322,17 +322,6 @@ __device__ __forceinline__ int append_head(const AppendArgs& A, int idx) {
   return (s * A.D.Lyr + A.l0 + (idx / A.D.Hk) % A.nl) * A.D.Hk + idx % A.D.Hk;
 }
 
-// Inclusive prefix sums over a wavefront (row shifts, then the rows' last lanes broadcast).
-__device__ __forceinline__ int wave_prefix_i(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-  return v;
-}
-
 // Block that is free block number k of the map (k below the number of them), by all lanes of a
 // wavefront: the share, the tile, the word and the bit that hold it.  ahead: free blocks ahead of
 // share `lane`.  FRESH: what this launch's other workgroups left (else an earlier launch's).

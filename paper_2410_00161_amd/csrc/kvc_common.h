@@ -164,19 +164,69 @@ __device__ __forceinline__ int32_t published_i32(const int32_t* p) {
 }
 __device__ __forceinline__ void publish_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-  return v;
+// ---- across the lanes of a wavefront ----
+// Without LDS: a shuffle is an LDS access of ~110 clocks, and a reduction is a chain of six.  Lanes of
+// a row of 16 by data-parallel moves, rows and halves by the swaps of gfx950.
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+// The values of lanes l and l ^ MASK, in this order for every lane l without that bit and, for MASK of
+// 16 and 32, for every lane (below: the lane's own first): for sums and maxima, which take either order.
+template <int MASK> struct LanePair { int a, b; };
+template <int MASK>
+__device__ __forceinline__ LanePair<MASK> lane_pair(int v) {
+  if constexpr (MASK == 32) { const auto t = __builtin_amdgcn_permlane32_swap(v, v, false, false); return {(int)t[0], (int)t[1]}; }
+  else if constexpr (MASK == 16) { const auto t = __builtin_amdgcn_permlane16_swap(v, v, false, false); return {(int)t[0], (int)t[1]}; }
+  else if constexpr (MASK == 8) return {v, dpp_move<0x128>(v)};                  // a rotation by 8
+  else if constexpr (MASK == 4) return {v, dpp_move<0x141>(dpp_move<0x1B>(v))};   // a quad reverse, then a half-row mirror: i ^ 3 ^ 7
+  else if constexpr (MASK == 2) return {v, dpp_move<0x4E>(v)};                   // quad permutes
+  else return {v, dpp_move<0xB1>(v)};
 }
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-  return v;
+template <int MASK>
+__device__ __forceinline__ int sum_xor(int v) { const auto p = lane_pair<MASK>(v); return p.a + p.b; }
+template <int MASK>
+__device__ __forceinline__ int max_xor(int v) { const auto p = lane_pair<MASK>(v); return max(p.a, p.b); }
+template <int MASK>
+__device__ __forceinline__ float sum_xor(float v) {
+  const auto p = lane_pair<MASK>(__builtin_bit_cast(int, v));
+  return __builtin_bit_cast(float, p.a) + __builtin_bit_cast(float, p.b);
 }
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m));
+template <int MASK>
+__device__ __forceinline__ float max_xor(float v) {
+  const auto p = lane_pair<MASK>(__builtin_bit_cast(int, v));
+  return fmaxf(__builtin_bit_cast(float, p.a), __builtin_bit_cast(float, p.b));
+}
+// Value held by lane (l ^ MASK).
+template <int MASK>
+__device__ __forceinline__ float lane_xor(float v) {
+  const auto p = lane_pair<MASK>(__builtin_bit_cast(int, v));
+  if constexpr (MASK >= 16) return __builtin_bit_cast(float, (threadIdx.x & MASK) ? p.a : p.b);
+  else return __builtin_bit_cast(float, p.b);
+}
+template <class T>
+__device__ __forceinline__ T wave_sum(T v) {
+  v = sum_xor<32>(v); v = sum_xor<16>(v); v = sum_xor<8>(v);
+  v = sum_xor<4>(v); v = sum_xor<2>(v); return sum_xor<1>(v);
+}
+template <class T>
+__device__ __forceinline__ T wave_max(T v) {
+  v = max_xor<32>(v); v = max_xor<16>(v); v = max_xor<8>(v);
+  v = max_xor<4>(v); v = max_xor<2>(v); return max_xor<1>(v);
+}
+__device__ __forceinline__ int wave_sum_i(int v) { return wave_sum(v); }
+__device__ __forceinline__ float wave_sum_f(float v) { return wave_sum(v); }
+__device__ __forceinline__ float wave_max_f(float v) { return wave_max(v); }
+// Sum over the wavefront of 64 values of at most 31 bits.
+__device__ __forceinline__ unsigned long long wave_sum_long(int v) {
+  return ((unsigned long long)wave_sum(v >> 16) << 16) + (unsigned long long)wave_sum(v & 0xffff);
+}
+// Inclusive prefix sums over a wavefront (row shifts, then the rows' last lanes broadcast).
+__device__ __forceinline__ int wave_prefix_i(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
   return v;
 }
 
@@ -185,12 +235,7 @@ __device__ __forceinline__ float wave_max_f(float v) {
 template <int NT>
 __device__ __forceinline__ int block_exclusive_scan(int v, int* smem, int* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(inc, o);
-    if (lane >= o) inc += t;
-  }
+  const int inc = wave_prefix_i(v);
   if (lane == 63) smem[wid] = inc;
   __syncthreads();
   if (threadIdx.x == 0) {

@@ -255,8 +255,8 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   extern __shared__ __align__(16) char smem_raw[];
   DecodeItem it;
   int Tc;                                // tokens the work list was cut at (<= A.T)
-  const int T = NW == 4 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
-  if (NW == 4 && A.self_list) {
+  const int T = NW > 1 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
+  if (NW > 1 && A.self_list) {
     SelfList sl;
     const bool found = self_item(A, blockIdx.x, false, sl);
     // heads without a KV (lane = head, the same in every wavefront): the first workgroup writes their zero rows
@@ -273,33 +273,28 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
     const int short_items = A.header[HW_SHORT_ITEMS];
     const bool placed = A.plan && A.plan_stride == 0;
     const int base = placed ? A.header[HW_PLAN_BASE] : 0;
-    if (NW == 4 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
-    if (NW == 4 && A.plan && (int)blockIdx.x < A.gsel) {
+    if (NW > 1 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
+    if (NW > 1 && A.plan && (int)blockIdx.x < A.gsel) {
       // a list kept from kvc_decode_plan was made without the output at hand: the zero rows of a
       // head that holds no KV are written here, by the workgroup with the head's index
       const int ge = sel_to_g(A.D, A.l0, A.nl, blockIdx.x);
       if (A.ctx[ge] == 0)
         for (int i = tid; i < R * HD; i += NT) A.out[(size_t)ge * R * HD + i] = 0.0f;
     }
+    Tc = A.header[HW_CHUNK_T];
+    // (a long item's record is where the workgroup's index says: asked for together with the header words)
+    if (NW > 1 && !placed && (int)blockIdx.x < A.cap) it = A.items[blockIdx.x];
     if (total_items > A.cap || short_items < 0 || short_items > total_items) return;
     const int n_long = total_items - short_items;
-    if ((int)blockIdx.x >= (NW == 4 ? n_long : short_items)) return;
+    if ((int)blockIdx.x >= (NW > 1 ? n_long : short_items)) return;
     if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
-    it = A.items[base + (NW == 4 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
-    Tc = A.header[HW_CHUNK_T];
+    if (NW == 1 || placed) it = A.items[base + (NW > 1 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
   }
   const int g = it.g, t0 = it.t0, n_tok = it.n_tok, nch = it.nch;
   if ((unsigned)g >= (unsigned)A.D.G || n_tok <= 0 || n_tok > T || t0 < 0 || nch <= 0 || Tc < 64 || Tc > A.T ||
       (nch > 1 && (it.pbase < 0 || it.pbase + nch > A.cap)))
     return;  // not a record this call wrote
-  if (A.plan) {
-    // the head must still be as long as the plan took it to be (the record carries that length).
-    // A stale plan is an argument error, found here and left in the status word.
-    if (A.ctx[g] != it.pad[0]) {
-      if (tid == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
-      return;
-    }
-  }
+  const int C_now = A.plan ? A.ctx[g] : 0;   // (looked at below, behind the other loads)
   const int b = A.D.b, lb = A.log2b;
 
   uint4* s_kt = (uint4*)smem_raw;                      // MF: [waves][16 tokens][16 cells of 16 bytes]
@@ -342,6 +337,12 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   } else {
 #pragma unroll
     for (int hh = 0; hh < R; ++hh) qv[hh] = Row<ESZ>::load_q(A.q + ((size_t)g * R + hh) * QROWB, seg);
+  }
+  // A head of a kept list must still be as long as the plan took it to be (the record carries that length).
+  // A stale plan is an argument error, found here and left in the status word.
+  if (A.plan && C_now != it.pad[0]) {
+    if (tid == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
+    return;
   }
   __syncthreads();
 
@@ -448,10 +449,10 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
         for (int v = 0; v < NVH; ++v) {
           x[v] = live ? sacc[v] * A.scale_log2 : -INFINITY;
           float m = x[v];   // max over the 16 tokens = over the 16 lanes of this row of lanes
-          m = fmaxf(m, lane_xor<1>(m));
-          m = fmaxf(m, lane_xor<2>(m));
-          m = fmaxf(m, lane_xor<4>(m));
-          m = fmaxf(m, lane_xor<8>(m));
+          m = max_xor<1>(m);
+          m = max_xor<2>(m);
+          m = max_xor<4>(m);
+          m = max_xor<8>(m);
           gm[v] = fmaxf(m, m_own[v]);
         }
 #pragma unroll
@@ -490,10 +491,10 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
           part[i] = tok < n_tok ? part[i] * A.scale_log2 : -INFINITY;
           // max over the group's tokens: the lanes that hold one head differ in lane bits 2..5
           float m = part[i];
-          m = fmaxf(m, lane_xor<4>(m));
-          m = fmaxf(m, lane_xor<8>(m));
-          m = fmaxf(m, __shfl_xor(m, 16));
-          m = fmaxf(m, __shfl_xor(m, 32));
+          m = max_xor<4>(m);
+          m = max_xor<8>(m);
+          m = max_xor<16>(m);
+          m = max_xor<32>(m);
           gm[i] = fmaxf(m, m_own[i]);
         }
         // exp of the group against the new running max; partial sums rescaled
@@ -630,11 +631,10 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
 #pragma unroll
     for (int v = 0; v < NVH; ++v) {   // sums over the 16 token lanes of a row of lanes
       float l = l_own[v];
-      l += lane_xor<1>(l);
-      l += lane_xor<2>(l);
-      l += lane_xor<4>(l);
-      l += lane_xor<8>(l);
-      l_own[v] = l;
+      l = sum_xor<1>(l);
+      l = sum_xor<2>(l);
+      l = sum_xor<4>(l);
+      l_own[v] = sum_xor<8>(l);
     }
     if ((lane & 15) == 0) {
 #pragma unroll
@@ -650,11 +650,10 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       float l = l_own[i];
-      l += lane_xor<4>(l);
-      l += lane_xor<8>(l);
-      l += __shfl_xor(l, 16);
-      l += __shfl_xor(l, 32);
-      l_own[i] = l;
+      l = sum_xor<4>(l);
+      l = sum_xor<8>(l);
+      l = sum_xor<16>(l);
+      l_own[i] = sum_xor<32>(l);
     }
     if (lane < 4) {
 #pragma unroll
@@ -673,17 +672,20 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        float a = pacc[dt][v] + __shfl_xor(pacc[dt][v], 32);
-        if (PROWS == 4) a += __shfl_xor(a, 16);
+        float a = sum_xor<32>(pacc[dt][v]);
+        if (PROWS == 4) a = sum_xor<16>(a);
         if (lane < (R > 4 ? 32 : 16)) s_acc[(w * RW + 4 * (lane >> 4) + v) * HD + 16 * dt + (lane & 15)] = a;
       }
   } else {
 #pragma unroll
-    for (int m = LPT; m < 64; m <<= 1)
+    for (int hh = 0; hh < R; ++hh)   // the lanes that hold the same dimensions
 #pragma unroll
-      for (int hh = 0; hh < R; ++hh)
-#pragma unroll
-        for (int k = 0; k < EPL; ++k) acc[hh][k] += __shfl_xor(acc[hh][k], m);
+      for (int k = 0; k < EPL; ++k) {
+        if constexpr (LPT <= 4) acc[hh][k] = sum_xor<4>(acc[hh][k]);
+        if constexpr (LPT <= 8) acc[hh][k] = sum_xor<8>(acc[hh][k]);
+        if constexpr (LPT <= 16) acc[hh][k] = sum_xor<16>(acc[hh][k]);
+        acc[hh][k] = sum_xor<32>(acc[hh][k]);
+      }
     if (sub == 0) {
 #pragma unroll
       for (int hh = 0; hh < R; ++hh)
@@ -777,13 +779,16 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
     Tc = sl.T;
   } else {
     const bool placed = A.plan && A.plan_stride == 0;
-    const int total_items = A.header[HW_TOTAL_ITEMS], base = placed ? A.header[HW_PLAN_BASE] : 0;
-    if (p >= A.header[HW_TOTAL_PARTIALS] || p >= total_items || p >= A.cap) return;
+    if (p >= A.cap) return;
+    const int total_items = A.header[HW_TOTAL_ITEMS], total_partials = A.header[HW_TOTAL_PARTIALS];
+    const int base = placed ? A.header[HW_PLAN_BASE] : 0;
+    Tc = A.header[HW_CHUNK_T];
+    int item = placed ? 0 : A.slot_item[p];   // (asked for together with the header words)
+    if (p >= total_partials || p >= total_items) return;
     if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
-    const int item = A.slot_item[base + p];
+    if (placed) item = A.slot_item[base + p];
     if (item < 0 || item >= total_items || item >= A.cap) return;
     it = A.items[base + item];
-    Tc = A.header[HW_CHUNK_T];
   }
   const int nch = it.nch;
   if (nch <= 1) return;
@@ -792,7 +797,7 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
     return;  // not a record this call wrote
   const int g = it.g, t0 = it.t0, n_tok = it.n_tok;
   if (Tc < 64 || Tc > A.T) return;
-  if (A.plan && A.ctx[g] != it.pad[0]) return;   // a kept list that no longer fits the head: its chunks did nothing either
+  const int C_now = A.plan ? A.ctx[g] : 0;   // (looked at below, behind the other loads)
   const int c = t0 / Tc;
   if (c >= nch) return;
   const int first = it.pbase;                // partial-result slots first .. first + nch - 1
@@ -826,6 +831,7 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
       s_w[hh] = mine / l;
     }
   }
+  if (A.plan && C_now != it.pad[0]) return;   // a kept list that no longer fits the head: its chunks did nothing either
   __syncthreads();
   if (A.accumulate) {
     float wv_h[R];

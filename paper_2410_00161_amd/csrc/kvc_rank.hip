@@ -251,12 +251,7 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
     // running counts over the digits in order: four per lane, then over the lanes
     const int4 c = *(const int4*)(hist + 4 * lane);
     const int mine = c.x + c.y + c.z + c.w;
-    int inc = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(inc, o);
-      if (lane >= o) inc += t;
-    }
+    const int inc = wave_prefix_i(mine);
     int ex = below + inc - mine;
     const int cc[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
@@ -572,12 +567,7 @@ __global__ void __launch_bounds__(NTH) rank_compact_kernel(Dims D, char* __restr
     if (wv == 0) {
       const int c4[4] = {hist[4 * lane], hist[4 * lane + 1], hist[4 * lane + 2], hist[4 * lane + 3]};
       const int mine = c4[0] + c4[1] + c4[2] + c4[3];
-      int inc = mine;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-      }
+      const int inc = wave_prefix_i(mine);
       int ex = inc - mine;
       const int remain = remain_s;
 #pragma unroll

@@ -178,7 +178,8 @@ constexpr int kSmallCallChunk = 128;
 __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long tokens, int live, int longest) {
   const unsigned long long want = tokens + tokens / 4;
   auto length = [&](int den) {
-    const unsigned long long t = want / den;
+    // (a 64-bit division by a variable is ~150 instructions, in front of everything a small call does)
+    const unsigned long long t = want >> 32 ? want / den : (unsigned long long)((unsigned)want / (unsigned)den);
     const int t64 = (int)((t < (unsigned long long)T_max ? t : (unsigned long long)T_max) + 63) & ~63;
     return min(T_max, max(kSmallCallChunk, t64));
   };
@@ -230,9 +231,8 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   }
   int T = A.T;
   if (A.adapt_T) {
-    unsigned long long t = (unsigned long long)max(C, 0);
-    int lm = C;
-    for (int m = 32; m >= 1; m >>= 1) { t += __shfl_xor(t, m); lm = max(lm, __shfl_xor(lm, m)); }
+    const unsigned long long t = wave_sum_long(max(C, 0));
+    const int lm = wave_max(C);
     const int lv = __popcll(__ballot(C > 0));
     if ((tid & 63) == 0 && t) { atomicAdd(&tokens, t); atomicAdd(&live, lv); atomicMax(&longest, lm); }
     __syncthreads();
@@ -252,22 +252,30 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     rem = C - nfull * T;
     nch = nfull + (rem ? 1 : 0);
     cls = rem ? size_class(rem, T) : 0;
-    if (nfull) atomicAdd(&bins[0], nfull);
     if (rem) atomicAdd(&bins[cls], 1);
-    if (nch > 1 || (A.all_partials && nch > 0)) atomicAdd(&ptot, nch);
   }
+  // full chunks and partial-result slots are claimed per wavefront (a thousand adds to one LDS word are
+  // run one after the other)
+  const bool slotted = nch > 1 || (A.all_partials && nch > 0);
+  const int lane = tid & 63, full_to = wave_prefix_i(nfull), slots_to = wave_prefix_i(slotted ? nch : 0);
+  int full_at = 0, slots_at = 0;
+  if (lane == 63) {
+    if (full_to) { atomicAdd(&bins[0], full_to); full_at = atomicAdd(&cur[0], full_to); }
+    if (slots_to) { atomicAdd(&ptot, slots_to); slots_at = atomicAdd(&cur[16], slots_to); }
+  }
+  full_at = __builtin_amdgcn_readlane(full_at, 63) + full_to - nfull;
+  const int pbase = slotted ? __builtin_amdgcn_readlane(slots_at, 63) + slots_to - nch : 0;
   __syncthreads();
-  if (tid == 0) {
-    header[HW_TOTAL_PARTIALS] = ptot;
-    int run = 0, shorts = 0;
-    for (int k = 0; k < 16; ++k) {
-      base[k] = run;
-      run += bins[k];
-      if (k >= A.short_class) shorts += bins[k];
+  if (tid < 64) {
+    const int n = tid < 16 ? bins[tid] : 0, to = wave_prefix_i(n);
+    if (tid < 16) base[tid] = to - n;
+    const int run = __builtin_amdgcn_readlane(to, 63), longs = A.short_class > 0 ? __builtin_amdgcn_readlane(to, A.short_class - 1) : 0;
+    if (tid == 0) {
+      header[HW_TOTAL_PARTIALS] = ptot;
+      // (a list that does not fit, which lengths the pool can hold never make, is one no decode takes)
+      header[HW_TOTAL_ITEMS] = PLAN && run > cap ? 0x7fffffff : run;
+      header[HW_SHORT_ITEMS] = run - longs;
     }
-    // (a list that does not fit, which lengths the pool can hold never make, is one no decode takes)
-    header[HW_TOTAL_ITEMS] = PLAN && run > cap ? 0x7fffffff : run;
-    header[HW_SHORT_ITEMS] = shorts;
   }
   __syncthreads();
   if (tid >= A.gsel) return;
@@ -278,11 +286,9 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     }
     return;
   }
-  const bool slotted = nch > 1 || A.all_partials;
-  const int pbase = slotted ? atomicAdd(&cur[16], nch) : 0;
   if (pbase < 0 || pbase + nch > cap) return;
   if (nfull) {
-    const int at = base[0] + atomicAdd(&cur[0], nfull);
+    const int at = base[0] + full_at;
     if (at < 0 || at + nfull > cap) return;
     for (int c = 0; c < nfull; ++c) {
       DecodeItem it = {g, c * T, T, nch, pbase, {C, 0, 0}};
@@ -319,22 +325,11 @@ __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, bool parti
   }
   int T = A.T;
   if (A.adapt_T) {
-    unsigned long long t = (unsigned long long)C;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) t += __shfl_xor(t, m);
-    int longest = C;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) longest = max(longest, __shfl_xor(longest, m));
-    T = small_call_chunk(A.T, t, __popcll(__ballot(C > 0)), longest);
+    T = small_call_chunk(A.T, wave_sum_long(C), __popcll(__ballot(C > 0)), wave_max(C));
   }
   const int nfull = C / T, rem = C - nfull * T, nch = nfull + (rem ? 1 : 0);
   const int split = nch > 1 ? nch : 0;
-  int fi = nfull, si = split;   // inclusive prefixes
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int a = __shfl_up(fi, o), b = __shfl_up(si, o);
-    if (lane >= o) { fi += a; si += b; }
-  }
+  const int fi = wave_prefix_i(nfull), si = wave_prefix_i(split);   // inclusive
   const int F = __builtin_amdgcn_readlane(fi, 63);
   const unsigned long long rm = __ballot(rem > 0);
   int t0 = -1;   // the item's first token, in the lane of its head
@@ -353,22 +348,6 @@ __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, bool parti
                       __builtin_amdgcn_readlane(nch, src), __builtin_amdgcn_readlane(si - split, src), {0, 0, 0}};
   out.it.n_tok = min(T, __builtin_amdgcn_readlane(C, src) - out.it.t0);
   return true;
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-// Value held by lane (l ^ MASK).  Masks below 16 stay inside a row of 16 lanes and use
-// data-parallel primitives: quad permutes for 1 and 2, a quad reverse followed by a half-row
-// mirror for 4 (i ^ 3 ^ 7 = i ^ 4), a rotation by 8 for 8.
-template <int MASK>
-__device__ __forceinline__ float lane_xor(float v) {
-  if constexpr (MASK == 1) return dpp_move<0xB1>(v);
-  else if constexpr (MASK == 2) return dpp_move<0x4E>(v);
-  else if constexpr (MASK == 4) return dpp_move<0x141>(dpp_move<0x1B>(v));
-  else if constexpr (MASK == 8) return dpp_move<0x128>(v);
-  else return __shfl_xor(v, MASK);
 }
 
 template <int N, int MASK>
