@@ -435,6 +435,26 @@ static __global__ void __launch_bounds__(256) segments_init_kernel(Dims D, const
   if (i < D.G) per_head[i] = 0;
 }
 
+// The end of a head's moves when several workgroups of 256 threads share them: the last of the `expected`
+// ones gives the tail blocks back and sets the new length T (was C).  By all threads; the workgroup's
+// reads of the head's row and length are done.
+__device__ __forceinline__ void finish_head(const Dims& D, int32_t* table, int32_t* ctx, uint8_t* free_map, int32_t* arrived,
+                                            int g, int expected, int C, int T) {
+  __shared__ int last_s;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last_s = __hip_atomic_fetch_add(&arrived[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expected - 1;
+  __syncthreads();
+  if (!last_s) return;
+  int32_t* row = table + (size_t)g * D.maxb;
+  const int nb = (C + D.b - 1) / D.b, nb2 = (T + D.b - 1) / D.b;
+  for (int u = nb2 + (int)threadIdx.x; u < nb; u += 256) {
+    free_map[row[u]] = 1;
+    row[u] = -1;
+  }
+  if (threadIdx.x == 0) ctx[g] = T;
+}
+
 // How much dynamic LDS a kernel may take above the default 64 KB is an attribute of the kernel on
 // a device: remembered per device (the first 64 of a process), raised when a call needs more.
 // Host threads may race here; telling the runtime twice is harmless.

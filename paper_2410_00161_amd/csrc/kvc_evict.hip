@@ -7,6 +7,8 @@
 // the threshold key and how many ties at the threshold are still wanted; ties
 // are then granted in ascending (s, l, h, u).  All counting is integer, so the
 // result is the one a stable sort by (key, s, l, h, u) would give.
+#include <algorithm>
+
 #include "kvc_common.h"
 #include <atomic>
 
@@ -442,10 +444,12 @@ __global__ void __launch_bounds__(256) compact_scan_kernel(Dims D, const uint8_t
                                                            const int32_t* __restrict__ evict_count,
                                                            const int32_t* __restrict__ ctx,
                                                            int32_t* __restrict__ flag_scan,
+                                                           int32_t* __restrict__ arrived,
                                                            int32_t* __restrict__ header) {
   const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (g >= D.G) return;
   const int lane = threadIdx.x & 63;
+  if (lane == 0) arrived[g] = 0;   // workgroups of the head's sliced moves that are done
   const int nb = (ctx[g] + D.b - 1) / D.b;
   const uint8_t* frow = flag + (size_t)g * D.maxb;
   int32_t* srow = flag_scan + (size_t)g * D.maxb;
@@ -556,41 +560,46 @@ __global__ void __launch_bounds__(256) compact_move_kernel(Dims D, char* __restr
   if (threadIdx.x == 0) ctx[g] = T;   // nb - nb2 = e blocks went back
 }
 
-// Tables sized for long prompts: workgroup (g, y) moves the kept KVs of logical slots
-// T + y * kSlice .. + kSlice - 1 of head g, and the tables are left to compact_free_kernel.
-// (One workgroup per head with the head's whole table in LDS: a 131072-token head that loses a
-// tenth of its blocks is 12 MB of moves behind one workgroup, two such workgroups fit a CU, and
-// a round of a million blocks took 7.4 ms.)  The movers of a slice are consecutive in rank, so
+// Few heads, or long ones: workgroup (g, y) moves the kept KVs of logical slots T + y * slice .. + slice
+// - 1 of head g, and the last of a head's workgroups to be done gives its tail blocks back and shortens
+// it (nothing of the head is read after that).  One workgroup per head is one CU per head: 80 heads of up
+// to 19756 tokens brought down to a sixteenth 272 us of moves in 479 for the prompt, 240 in all this way; 192
+// heads that lose 30 % of 8650 tokens 743 -> 319; a 131072-token head that loses a tenth of its blocks is 12
+// MB of moves behind one workgroup.  The movers of a slice are consecutive in rank, so
 // their holes are consecutive flagged blocks: the workgroup finds the first of them with a
 // 256-way search over the prefix counts, walks on from there gathering block ids, and keeps only
 // its own stretch of the table in LDS (a few KB).
 constexpr int kSlice = 2048;
 __global__ void __launch_bounds__(256) compact_move_sliced_kernel(Dims D, char* __restrict__ kc, char* __restrict__ vc,
                                                                   float* __restrict__ metric, int32_t* __restrict__ pos,
-                                                                  const int32_t* __restrict__ table,
-                                                                  const int32_t* __restrict__ ctx,
+                                                                  int32_t* __restrict__ table,
+                                                                  int32_t* __restrict__ ctx,
+                                                                  uint8_t* __restrict__ free_map,
                                                                   const int32_t* __restrict__ evict_count,
                                                                   const int32_t* __restrict__ flag_scan,
-                                                                  const int32_t* __restrict__ header) {
-  if (header[HW_STATUS] != KVC_OK) return;
+                                                                  int32_t* __restrict__ arrived,
+                                                                  const int32_t* __restrict__ header, int slice) {
   const int g = blockIdx.x;
   const int e = evict_count[g];
-  if (e <= 0) return;
+  if (header[HW_STATUS] != KVC_OK || e <= 0) return;
   const int b = D.b;
-  if ((long long)blockIdx.y * kSlice >= (long long)e * b) return;   // the range of movers is at most e * b slots long
+  // The range of movers is at most e * b slots long.  Exactly the workgroups within it look at the head's
+  // length and row, and are waited for before these change.
+  if ((long long)blockIdx.y * slice >= (long long)e * b) return;
+  const int expected = (int)(((long long)e * b + slice - 1) / slice);
   int lb = 0;
   while ((1 << lb) < b) ++lb;   // block sizes are powers of two
   const int C = ctx[g];
   const int nb = (C + b - 1) >> lb;
-  const int32_t* row = table + (size_t)g * D.maxb;
+  int32_t* row = table + (size_t)g * D.maxb;
   const int32_t* pi = flag_scan + (size_t)g * D.maxb;  // inclusive prefix of flags
   const int last_flag = pi[nb - 1] - (nb > 1 ? pi[nb - 2] : 0);
   const int n_ev = e * b - (last_flag ? nb * b - C : 0);
   const int T = C - n_ev;
-  const int j_lo = T + (int)blockIdx.y * kSlice;
-  if (j_lo >= C) return;
-  const int j_hi = min(C, j_lo + kSlice);
+  const int j_lo = T + (int)blockIdx.y * slice;
+  const int j_hi = min(C, j_lo + slice);
   const int tid = threadIdx.x;
+  if (j_lo < j_hi) {   // (a last block that is evicted and not full: the range is shorter than e * b)
   constexpr int kMaxBlk = kSlice + 2;                 // blocks of a slice at b = 1, and one before
   __shared__ int s_pi[kMaxBlk], s_id[kMaxBlk], s_hole[kMaxBlk];
   __shared__ int s_first;
@@ -653,48 +662,39 @@ __global__ void __launch_bounds__(256) compact_move_sliced_kernel(Dims D, char* 
     dst = ((size_t)s_hole[(k >> lb) - r_lo] << lb) + (k & (b - 1));   // k-th hole: offset k % b of the (k / b)-th flagged block
     return true;
   };
-  for (int j = j_lo + grp; j < j_hi; j += 16) {
-    size_t src = 0, dst = 0;
-    if (!route(j, src, dst)) continue;
-    for (int c = gl; c < pieces; c += 16) {
-      ((uint4*)(kc + dst * row_bytes))[c] = ((const uint4*)(kc + src * row_bytes))[c];
-      ((uint4*)(vc + dst * row_bytes))[c] = ((const uint4*)(vc + src * row_bytes))[c];
+  // two KVs of a group at a time: a KV is a chain of loads and stores
+  for (int j = j_lo + grp; j < j_hi; j += 32) {
+    size_t s0 = 0, d0 = 0, s1 = 0, d1 = 0;
+    const bool one = route(j, s0, d0), two = route(j + 16, s1, d1);
+    if (!one && !two) continue;
+    if (!one) { s0 = s1; d0 = d1; }
+    if (one && two) {
+      for (int c = gl; c < pieces; c += 16) {
+        const uint4 k0 = ((const uint4*)(kc + s0 * row_bytes))[c], v0 = ((const uint4*)(vc + s0 * row_bytes))[c];
+        const uint4 k1 = ((const uint4*)(kc + s1 * row_bytes))[c], v1 = ((const uint4*)(vc + s1 * row_bytes))[c];
+        ((uint4*)(kc + d0 * row_bytes))[c] = k0;
+        ((uint4*)(vc + d0 * row_bytes))[c] = v0;
+        ((uint4*)(kc + d1 * row_bytes))[c] = k1;
+        ((uint4*)(vc + d1 * row_bytes))[c] = v1;
+      }
+    } else {
+      for (int c = gl; c < pieces; c += 16) {
+        const uint4 k0 = ((const uint4*)(kc + s0 * row_bytes))[c], v0 = ((const uint4*)(vc + s0 * row_bytes))[c];
+        ((uint4*)(kc + d0 * row_bytes))[c] = k0;
+        ((uint4*)(vc + d0 * row_bytes))[c] = v0;
+      }
     }
     if (gl == 0) {
-      metric[dst] = metric[src];
-      if (pos) pos[dst] = pos[src];
+      metric[d0] = metric[s0];
+      if (pos) pos[d0] = pos[s0];
+      if (one && two) {
+        metric[d1] = metric[s1];
+        if (pos) pos[d1] = pos[s1];
+      }
     }
   }
-}
-
-// The free step after a sliced move: one wavefront per head instance gives the tail blocks back
-// and shortens the head.
-__global__ void __launch_bounds__(256) compact_free_kernel(Dims D, int32_t* __restrict__ table,
-                                                           int32_t* __restrict__ ctx,
-                                                           uint8_t* __restrict__ free_map,
-                                                           const int32_t* __restrict__ evict_count,
-                                                           const int32_t* __restrict__ flag_scan,
-                                                           const int32_t* __restrict__ header) {
-  if (header[HW_STATUS] != KVC_OK) return;
-  const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (g >= D.G) return;
-  const int lane = threadIdx.x & 63;
-  const int e = evict_count[g];
-  if (e <= 0) return;
-  const int b = D.b;
-  const int C = ctx[g];
-  const int nb = (C + b - 1) / b;
-  const int32_t* pi = flag_scan + (size_t)g * D.maxb;
-  const int last_flag = pi[nb - 1] - (nb > 1 ? pi[nb - 2] : 0);
-  const int n_ev = e * b - (last_flag ? nb * b - C : 0);
-  const int T = C - n_ev;
-  int32_t* row = table + (size_t)g * D.maxb;
-  const int nb2 = (T + b - 1) / b;
-  for (int u = nb2 + lane; u < nb; u += 64) {
-    free_map[row[u]] = 1;
-    row[u] = -1;
   }
-  if (lane == 0) ctx[g] = T;
+  finish_head(D, table, ctx, free_map, arrived, g, expected, C, T);
 }
 
 }  // namespace kvc
@@ -798,7 +798,7 @@ int kvc_compact(const kvc_config* cfg, const kvc_state* st, const uint8_t* evict
   Workspace W = carve(D, ws);
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(compact_scan_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, evict_flag, evict_count,
-                     st->ctx_len, W.flag_scan, W.header);
+                     st->ctx_len, W.flag_scan, W.off_a, W.header);
   KVC_LAUNCH_CHECK();
   // the status is settled before anything moves; a caller that wants the count gets it from the
   // same launch (the counts are this call's input, the moves do not change them)
@@ -808,19 +808,21 @@ int kvc_compact(const kvc_config* cfg, const kvc_state* st, const uint8_t* evict
   const size_t stage_bytes = (size_t)D.maxb * 8;   // prefix counts and block ids of one head
   char* kcp = (char*)st->k_cache;
   char* vcp = (char*)st->v_cache;
-  // Tables sized for long prompts (more than 65536 tokens a head, where a head's table no longer
-  // fits the LDS several times over): a head's movers are spread over workgroups of kSlice logical
-  // slots each, and the tables change in a launch of their own.  (Below that the empty workgroups
-  // of the slice grid cost more than the slices gain: 65536 heads with tables for 32768 tokens,
-  // 0.70 ms per head-sized workgroup against 1.36 ms sliced.)
+  // A head's movers are spread over workgroups of `slice` logical slots each where heads are few, so
+  // that all of them make about kSlicedWgs (rounds that move a tenth: 1024 heads of 8192 tokens at 8x 140 ->
+  // 120 us, 4096 225 -> 211; 104 heads of 480, 6 KB of moves each, 68 both ways), and where tables are
+  // sized for more than 65536 tokens a head, which no longer fit the LDS several times over.  Else the empty
+  // workgroups of the slice grid cost more than the slices gain (65536 heads with tables for 32768
+  // tokens: 0.70 ms per head-sized workgroup against 1.36 ms sliced; 16384 heads level).
+  constexpr size_t kSlicedWgs = 8192;
   const size_t row_tokens = (size_t)D.maxb * D.b;
-  const size_t slices = (row_tokens + kSlice - 1) / kSlice;
-  if (row_tokens > 65536 && slices <= 65535) {
+  const int slice = row_tokens > 65536 ? kSlice
+                                       : (int)std::min((size_t)kSlice, std::max((size_t)256, (row_tokens * D.G / kSlicedWgs + 63) / 64 * 64));
+  const size_t slices = (row_tokens + slice - 1) / slice;
+  const bool few = D.G <= 4096 && row_tokens >= 512 && slices * D.G <= 4 * kSlicedWgs;
+  if ((row_tokens > 65536 || few) && slices <= 65535) {
     hipLaunchKernelGGL(compact_move_sliced_kernel, dim3(D.G, (unsigned)slices), dim3(256), 0, s, D, kcp, vcp, st->metric,
-                       st->pos, st->block_table, st->ctx_len, evict_count, W.flag_scan, W.header);
-    KVC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(compact_free_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, st->block_table, st->ctx_len,
-                       st->free_map, evict_count, W.flag_scan, W.header);
+                       st->pos, st->block_table, st->ctx_len, st->free_map, evict_count, W.flag_scan, W.off_a, W.header, slice);
   } else if (stage_bytes <= 64 * 1024) {
     hipLaunchKernelGGL(compact_move_kernel<true>, dim3(D.G), dim3(256), stage_bytes, s, D, kcp, vcp, st->metric,
                        st->pos, st->block_table, st->ctx_len, st->free_map, evict_count, W.flag_scan, W.header);
