@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(256) block_key_kernel(Dims D, int key_mode, co
   const int nb = (C + D.b - 1) / D.b;
   const int32_t* row = table + (size_t)g * D.maxb;
   float* krow = key + (size_t)g * D.maxb;
-  for (int u = lane; u < nb; u += 64) {   // cells of blocks the head does not hold are left alone
+  for (int u = blockIdx.y * 64 + lane; u < nb; u += 64 * gridDim.y) {   // cells of blocks the head does not hold are left alone
     float acc = 0.0f;
     {
       const float* m = metric + (size_t)row[u] * D.b;
@@ -60,6 +60,14 @@ __global__ void __launch_bounds__(256) block_key_kernel(Dims D, int key_mode, co
 // ---------------------------------------------------------------------------
 // selection
 // ---------------------------------------------------------------------------
+
+// Wavefronts that share a head's row in the passes over keys and metrics: so many that few heads make
+// `want` of them in all, none with less than one load of 64 blocks.  (80 heads of up to 1235 blocks, one
+// wavefront a head: keys 19.9 us, the first digit's histogram, eight heads to a wavefront then, 50.7; shared
+// 4.8 and 7.6.  Twice as many heads as wavefronts wanted, or more: one share, as before.)
+static inline unsigned row_shares(const Dims& D, int want) {
+  return (unsigned)std::max(1, std::min(want / std::max(D.G, 1), (D.maxb + 63) / 64));
+}
 
 __global__ void __launch_bounds__(256) zero_bytes_kernel(uint8_t* p, size_t n) {
   size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 16;
@@ -102,7 +110,7 @@ __global__ void __launch_bounds__(256) select_hist_kernel(Dims D, int pass, int 
       const int c = my[i];
       if (c) { atomicAdd(&seg_hist[cur_sg * 256 + i], c); my[i] = 0; }
     }
-    if (pass == 0 && lane == 0 && cand_acc) atomicAdd(&seg_state[cur_sg * 8 + SS_CAND], cand_acc);
+    if (pass == 0 && blockIdx.y == 0 && lane == 0 && cand_acc) atomicAdd(&seg_state[cur_sg * 8 + SS_CAND], cand_acc);
     cand_acc = 0;
   };
   for (int g = g_first; g < g_end; ++g) {
@@ -115,7 +123,7 @@ __global__ void __launch_bounds__(256) select_hist_kernel(Dims D, int pass, int 
     const bool live = pass == 0 || seg_state[sg * 8 + SS_TAKE] > 0;
     const float* krow = key + (size_t)g * D.maxb;
     if (live) {
-      for (int u = lane; u < ncand; u += 64) {
+      for (int u = blockIdx.y * 64 + lane; u < ncand; u += 64 * gridDim.y) {
         const uint32_t k = key_bits(krow[u]);
         if (pass == 0) bad |= k >= 0x7f800000u;
         if (pass == 0 || (k >> (shift + 8)) == prefix) atomicAdd(&my[(k >> shift) & 255], 1);
@@ -214,17 +222,22 @@ __global__ void __launch_bounds__(256) select_mark_kernel(Dims D, int protect, c
   const float* krow = key + (size_t)g * D.maxb;
   uint8_t* frow = flag + (size_t)g * D.maxb;
   int cnt = 0;
-  for (int base = 0; base < ncand; base += 64) {
-    const int u = base + lane;
-    uint32_t k = 0xffffffffu;
-    if (u < ncand) k = key_bits(krow[u]);
-    const bool tie = k == thr;
-    const unsigned long long tm = __ballot(tie);
-    const int my_rank = ties_before + __popcll(tm & ((1ull << lane) - 1ull));
-    const bool ev = (u < ncand) && (k < thr || (tie && my_rank < want));
-    if (ev) frow[u] = 1;
-    cnt += __popcll(__ballot(ev));
-    ties_before += __popcll(tm);
+  for (int base = 0; base < ncand; base += 4 * 64) {   // four rounds' keys asked for together
+    float key4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) key4[i] = krow[min(base + i * 64 + lane, ncand - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = base + i * 64 + lane;
+      const uint32_t k = u < ncand ? key_bits(key4[i]) : 0xffffffffu;
+      const bool tie = k == thr;
+      const unsigned long long tm = __ballot(tie);
+      const int my_rank = ties_before + __popcll(tm & ((1ull << lane) - 1ull));
+      const bool ev = (u < ncand) && (k < thr || (tie && my_rank < want));
+      if (ev) frow[u] = 1;
+      cnt += __popcll(__ballot(ev));
+      ties_before += __popcll(tm);
+    }
   }
   if (lane == 0) evict_count[g] = cnt;
 }
@@ -455,13 +468,18 @@ __global__ void __launch_bounds__(256) compact_scan_kernel(Dims D, const uint8_t
   int32_t* srow = flag_scan + (size_t)g * D.maxb;
   int run = 0;
   bool bad = false;
-  for (int base = 0; base < nb; base += 64) {
-    const int u = base + lane;
-    const bool f = (u < nb) && frow[u] != 0;
-    const unsigned long long m = __ballot(f);
-    const int inc = run + __popcll(m & ((2ull << lane) - 1ull));
-    if (u < nb) srow[u] = inc;
-    run += __popcll(m);
+  for (int base = 0; base < nb; base += 4 * 64) {   // four rounds' flags asked for together
+    uint8_t f[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = frow[min(base + i * 64 + lane, nb - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = base + i * 64 + lane;
+      const unsigned long long m = __ballot(u < nb && f[i] != 0);
+      const int inc = run + __popcll(m & ((2ull << lane) - 1ull));
+      if (u < nb) srow[u] = inc;
+      run += __popcll(m);
+    }
   }
   // no flag may be set past the blocks the head holds: that stretch (most of the row when heads
   // are compressed far below the length the table is sized for) is only looked at, 16 bytes a
@@ -711,7 +729,7 @@ int kvc_metric_reduce(const kvc_config* cfg, const kvc_state* st, float* block_k
   if (key_mode != KVC_KEY_SUM && key_mode != KVC_KEY_MAX) return KVC_ERR_ARG;
   (void)ws;
   Dims D = dims_of(cfg);
-  hipLaunchKernelGGL(block_key_kernel, dim3((D.G + 3) / 4), dim3(256), 0, (hipStream_t)stream, D, key_mode,
+  hipLaunchKernelGGL(block_key_kernel, dim3((D.G + 3) / 4, row_shares(D, 4096)), dim3(256), 0, (hipStream_t)stream, D, key_mode,
                      st->metric, st->block_table, st->ctx_len, block_key);
   KVC_LAUNCH_CHECK();
   return KVC_OK;
@@ -764,8 +782,12 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
                      evict_flag, nflag);
   KVC_LAUNCH_CHECK();
   for (int pass = 0; pass < 4; ++pass) {
-    const int hpw = pass == 0 ? 8 : 1;
-    hipLaunchKernelGGL(select_hist_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw)), dim3(256), 0, s, D, pass,
+    // first pass (the exponent byte): nearly every head adds to the same digit of its segment, one add
+    // after the other, so a wavefront of many heads adds once for eight of them; up to 1024 heads make few
+    // adds, and each is shared out over wavefronts instead (192 heads of up to 2164 blocks 296 -> 194 us a
+    // round, 320 of 2048 287 -> 224)
+    const int hpw = pass == 0 && D.G > 1024 ? 8 : 1;
+    hipLaunchKernelGGL(select_hist_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw), row_shares(D, 1024)), dim3(256), 0, s, D, pass,
                        protect_tail_blocks, hpw, block_key, st->ctx_len, seq_seg, W.seg_hist, W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
     hipLaunchKernelGGL(select_pick_kernel, dim3(nseg), dim3(256), 0, s, pass, budget, W.seg_hist,
