@@ -80,7 +80,6 @@ __device__ __forceinline__ void for_each_metric(const float* __restrict__ metric
   }
 }
 
-
 // One workgroup (NTH threads: 256, or 1024 when there are few, long heads) per heads_per_wg
 // consecutive head instances, one after the other.  Counts a
 // head's entries below the prefix found so far and histograms the next digit of those that
@@ -301,7 +300,8 @@ __global__ void __launch_bounds__(256) rank_pick_kernel(int pass, const int32_t*
 }
 
 // Rows strictly below the threshold key, and rows that tie with it, per head.
-__global__ void __launch_bounds__(256) rank_tie_kernel(Dims D, int protect, const float* __restrict__ metric,
+template <int NTH>
+__global__ void __launch_bounds__(NTH) rank_tie_kernel(Dims D, int protect, const float* __restrict__ metric,
                                                        const int32_t* __restrict__ table,
                                                        const int32_t* __restrict__ ctx,
                                                        const int32_t* __restrict__ seq_seg,
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(256) rank_tie_kernel(Dims D, int protect, cons
   int lt = 0, le = 0;
   int lb = 0;
   while ((1 << lb) < D.b) ++lb;   // block sizes are powers of two
-  for_each_metric<256>(metric, row, C, lb, D.b - 1, [&](int, uint32_t k) {
+  for_each_metric<NTH>(metric, row, C, lb, D.b - 1, [&](int, uint32_t k) {
     lt += k < thr;
     le += k <= thr;
   });
@@ -513,8 +513,10 @@ __global__ void __launch_bounds__(1024) rank_check_small_kernel(Dims D, const in
 // uses the cells of its own blocks: hole k at logical cell k, mover k at logical cell C-1-k.
 // NTH threads: 256 when there are many head instances, 1024 when there are few (a prompt's
 // worth of long heads), so that a head's passes over its metrics run four times as wide.
+// (Registers, scalar ones too, for two workgroups of 1024 per CU: 1024 heads of 8192 tokens 161 -> 143 us a
+// round, with one 158.)
 template <int NTH>
-__global__ void __launch_bounds__(NTH) rank_compact_kernel(Dims D, char* __restrict__ kc, char* __restrict__ vc,
+__global__ void __launch_bounds__(NTH, 8) rank_compact_kernel(Dims D, char* __restrict__ kc, char* __restrict__ vc,
                                                            float* __restrict__ metric,
                                                            int32_t* __restrict__ pos,
                                                            int32_t* __restrict__ table,
@@ -588,55 +590,96 @@ __global__ void __launch_bounds__(NTH) rank_compact_kernel(Dims D, char* __restr
   const int ties_take = remain_s;
 
   // ---- ordered pass: who is evicted, hole and mover ranks ----
-  // Ranks inside a wavefront come from ballots; the wavefronts exchange their counts through LDS,
-  // two barriers per round of NTH slots (counts double-buffered by the round's parity), and every
-  // thread keeps the running totals itself.
-  __shared__ int cnt_s[2][3][NTH / 64];
   const unsigned long long lower = (1ull << lane) - 1ull;
-  int carry_tie = 0, carry_ev = 0, n_moves = 0;
-  auto ordered_round = [&](int base, int par, uint32_t k) {
-    const int j = base + tid;
-    const bool is_tie = (j < C) && k == thr;
-    const unsigned long long tm = __ballot(is_tie);
-    if (lane == 0) cnt_s[par][0][wv] = __popcll(tm);
-    __syncthreads();
-    int tie_rank = carry_tie + __popcll(tm & lower), tot_tie = 0;
-#pragma unroll
-    for (int w2 = 0; w2 < NTH / 64; ++w2) {
-      const int c = cnt_s[par][0][w2];
-      if (w2 < wv) tie_rank += c;
-      tot_tie += c;
-    }
-    const bool ev = (j < C) && (k < thr || (is_tie && tie_rank < ties_take));
-    const unsigned long long em = __ballot(ev);
-    const unsigned long long hm = __ballot(ev && j < T);
-    if (lane == 0) { cnt_s[par][1][wv] = __popcll(em); cnt_s[par][2][wv] = __popcll(hm); }
-    __syncthreads();
-    int ev_before = carry_ev + __popcll(em & lower), tot_ev = 0;
-#pragma unroll
-    for (int w2 = 0; w2 < NTH / 64; ++w2) {
-      const int c = cnt_s[par][1][w2];
-      if (w2 < wv) ev_before += c;
-      tot_ev += c;
-      n_moves += cnt_s[par][2][w2];
-    }
-    if (j < C) {
-      if (ev) {
-        if (j < T) scratch[phys(ev_before)] = j;
-      } else if (j >= T) {
-        const int kk = (C - 1 - j) - (n_ev - ev_before);  // kept slots above j
-        scratch[phys(C - 1 - kk)] = j;
-      }
-    }
-    carry_tie += tot_tie;
-    carry_ev += tot_ev;
+  int n_moves = 0;
+  // slot j, with ev_before evicted ones below it: the holes' list from the front, the movers' from the back
+  auto place = [&](int j, bool ev, int ev_before) -> int {
+    if (j >= C || ev != (j < T)) return -1;
+    return ev ? ev_before : C - 1 - ((C - 1 - j) - (n_ev - ev_before));   // (kept slots above j)
   };
-  {
+  if (kept) {
+    // Bound by its chain of steps, not by bytes.  Every wavefront walks a stretch of its own, twice: once
+    // to count, then, with the counts of those before it, without a barrier.  (In rounds of a slot per
+    // thread with two barriers each, as below, the launch took 39 us for 256 heads of 16384 tokens, 26 so.)
+    __shared__ int4 count_s[NTH / 64];
+    const int len = (C + NTH - 1) / NTH * 64, w0 = min(C, wv * len), w1 = min(C, w0 + len);
+    int lt = 0, tie = 0, lt_low = 0, tie_low = 0;   // below the threshold and at it; of these, below slot T
+    for (int j = w0 + lane; j < w1; j += 64) {
+      const uint32_t k = s_bits[j];
+      lt += k < thr;
+      tie += k == thr;
+      if (j < T) { lt_low += k < thr; tie_low += k == thr; }
+    }
+    lt = wave_sum_i(lt); tie = wave_sum_i(tie); lt_low = wave_sum_i(lt_low); tie_low = wave_sum_i(tie_low);
+    if (lane == 0) count_s[wv] = make_int4(lt, tie, lt_low, tie_low);
+    __syncthreads();
+    int ties = 0, evs = 0, all_ties_low = 0;
+#pragma unroll
+    for (int w2 = 0; w2 < NTH / 64; ++w2) {
+      const int4 c = count_s[w2];
+      if (w2 < wv) { evs += c.x; ties += c.y; }
+      n_moves += c.z;
+      all_ties_low += c.w;
+    }
+    evs += min(ties, ties_take);
+    n_moves += min(all_ties_low, ties_take);
+    for (int base = w0; base < w1; base += 4 * 64) {   // four rounds' block ids asked for together
+      int at[4], id[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int j = base + i * 64 + lane;
+        const bool in = j < w1;
+        const uint32_t k = s_bits[min(j, C - 1)];
+        const unsigned long long tm = __ballot(in && k == thr);
+        const bool ev = in && (k < thr || (k == thr && ties + __popcll(tm & lower) < ties_take));
+        const unsigned long long em = __ballot(ev);
+        at[i] = in ? place(j, ev, evs + __popcll(em & lower)) : -1;
+        ties += __popcll(tm);
+        evs += __popcll(em);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) id[i] = at[i] >= 0 ? row[at[i] >> lb] : 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (at[i] >= 0) scratch[((size_t)id[i] << lb) + (at[i] & (b - 1))] = base + i * 64 + lane;
+    }
+  } else {
+    // Ranks inside a wavefront come from ballots; the wavefronts exchange their counts through LDS,
+    // two barriers per round of NTH slots (counts double-buffered by the round's parity), and every
+    // thread keeps the running totals itself.
+    __shared__ int cnt_s[2][3][NTH / 64];
+    int carry_tie = 0, carry_ev = 0;
     for (int base = 0, par = 0; base < C; base += NTH, par ^= 1) {
       const int j = base + tid;
-      uint32_t k = 0xffffffffu;
-      if (j < C) k = kept ? s_bits[j] : metric_bits(metric[phys(j)]);
-      ordered_round(base, par, k);
+      const uint32_t k = j < C ? metric_bits(metric[phys(j)]) : 0xffffffffu;
+      const bool is_tie = (j < C) && k == thr;
+      const unsigned long long tm = __ballot(is_tie);
+      if (lane == 0) cnt_s[par][0][wv] = __popcll(tm);
+      __syncthreads();
+      int tie_rank = carry_tie + __popcll(tm & lower), tot_tie = 0;
+#pragma unroll
+      for (int w2 = 0; w2 < NTH / 64; ++w2) {
+        const int c = cnt_s[par][0][w2];
+        if (w2 < wv) tie_rank += c;
+        tot_tie += c;
+      }
+      const bool ev = (j < C) && (k < thr || (is_tie && tie_rank < ties_take));
+      const unsigned long long em = __ballot(ev);
+      const unsigned long long hm = __ballot(ev && j < T);
+      if (lane == 0) { cnt_s[par][1][wv] = __popcll(em); cnt_s[par][2][wv] = __popcll(hm); }
+      __syncthreads();
+      int ev_before = carry_ev + __popcll(em & lower), tot_ev = 0;
+#pragma unroll
+      for (int w2 = 0; w2 < NTH / 64; ++w2) {
+        const int c = cnt_s[par][1][w2];
+        if (w2 < wv) ev_before += c;
+        tot_ev += c;
+        n_moves += cnt_s[par][2][w2];
+      }
+      const int at = place(j, ev, ev_before);
+      if (at >= 0) scratch[phys(at)] = j;
+      carry_tie += tot_tie;
+      carry_ev += tot_ev;
     }
   }
   if (moves) {   // left to rank_move_kernel
@@ -768,8 +811,11 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
   if ((size_t)D.maxb * D.b <= kRankWaveTokens)
     hipLaunchKernelGGL(rank_tie_wave_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
                        st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
+  else if (D.G <= 1024)   // a workgroup per CU or so: as wide as it goes (256 heads of 16384 tokens 9.4 -> 6.0 us)
+    hipLaunchKernelGGL(rank_tie_kernel<1024>, dim3(D.G), dim3(1024), 0, s, D, protect_tail_blocks, st->metric,
+                       st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
   else
-    hipLaunchKernelGGL(rank_tie_kernel, dim3(D.G), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
+    hipLaunchKernelGGL(rank_tie_kernel<256>, dim3(D.G), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
                        st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
   KVC_LAUNCH_CHECK();
   if (D.G <= kRankSmallHeads) {
