@@ -410,8 +410,10 @@ static __global__ void __launch_bounds__(256) segments_init_kernel(Dims D, const
                                                                    int32_t* __restrict__ seg_state,
                                                                    int32_t* __restrict__ per_head,
                                                                    int32_t* __restrict__ selected,
-                                                                   int32_t* __restrict__ header) {
+                                                                   int32_t* __restrict__ header,
+                                                                   int32_t* __restrict__ more_hist, int n_more) {
   const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n_more) more_hist[i] = 0;
   if (i < D.S) {
     int sg = i;
     if (seg_offsets) {  // last segment whose first sequence is <= i

@@ -775,7 +775,7 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
   }
   int n_init = D.G > nseg * 256 ? D.G : nseg * 256;
   hipLaunchKernelGGL(segments_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, s, D, seg_offsets, nseg,
-                     seq_seg, W.seg_hist, W.seg_state, evict_count, selected, W.header);
+                     seq_seg, W.seg_hist, W.seg_state, evict_count, selected, W.header, (int32_t*)nullptr, 0);
   KVC_LAUNCH_CHECK();
   const size_t nflag = (size_t)D.G * D.maxb;
   hipLaunchKernelGGL(zero_bytes_kernel, dim3((unsigned)((nflag / 16 + 256) / 256)), dim3(256), 0, s,

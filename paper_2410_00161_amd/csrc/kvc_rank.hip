@@ -80,6 +80,64 @@ __device__ __forceinline__ void for_each_metric(const float* __restrict__ metric
   }
 }
 
+// ---- digits picked by the launch that uses them ----
+// With few heads a launch of its own for the pick of a digit is all latency: five launches of 2 us and the
+// host's time for them.  There the wavefronts of the next launch each pick their segment's digit
+// themselves, from a histogram per pass (the previous one is complete when this launch starts, nobody adds to it
+// any more), and the wavefront of a segment's first head leaves what it found for the launch after: threshold
+// and remainder in one pair of words after passes 0 and 2, in another after 1 and 3, so that nobody reads
+// words that this launch writes.  (Whole rounds and prompts, picks by themselves -> so: 256 heads of 16384
+// tokens 287 -> 279 us, 1024 of 8192 147 -> 138, 672 of up to 3595 107 -> 97, 104 of up to 957 85 -> 71.)
+struct RankPicks {
+  const int32_t* hist;     // [nseg][256] of the pass before, or NULL: rank_pick_kernel has picked
+  const int32_t* budget;
+  int nseg;
+};
+struct RankKey { uint32_t prefix; int remain, take; };
+
+__device__ __forceinline__ void check_budgets(const RankPicks& P, int nth, int32_t* header) {   // by a whole workgroup
+  bool neg = false;
+  for (int i = threadIdx.x; i < P.nseg; i += nth) neg |= P.budget[i] < 0;
+  const int any = __syncthreads_or(neg);
+  if (threadIdx.x != 0) return;
+  if (any) header[HW_SCRATCH0] |= EB_ARG;
+  settle_status(header);   // keys and budgets checked: before any output is written
+}
+
+// The threshold of segment sg as launch `pass` of the schedule (4: the ties) needs it; for all lanes.
+__device__ __forceinline__ RankKey rank_key(const RankPicks& P, int pass, int sg, int32_t* seg_state, bool leave) {
+  int32_t* stt = seg_state + sg * 8;
+  if (pass == 0) return RankKey{0u, 0, 1};
+  if (!P.hist) return RankKey{(uint32_t)stt[RS_PREFIX], stt[RS_REMAIN], stt[RS_TAKE]};
+  const int lane = threadIdx.x & 63;
+  const int from = pass & 1 ? 0 : 6, to = pass & 1 ? 6 : 0;   // (RS_PREFIX, RS_REMAIN, or the last two words)
+  RankKey key;
+  key.take = pass == 1 ? min(max(P.budget[sg], 0), stt[RS_CAND]) : stt[RS_TAKE];
+  key.prefix = pass == 1 ? 0u : (uint32_t)stt[from];
+  key.remain = pass == 1 ? key.take : stt[from + 1];
+  const int4 c = ((const int4*)(P.hist + (size_t)sg * 256))[lane];
+  const int mine = c.x + c.y + c.z + c.w;
+  int ex = wave_prefix_i(mine) - mine, digit = -1, left = 0;
+  const int c4[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (ex < key.remain && key.remain <= ex + c4[q]) { digit = 4 * lane + q; left = key.remain - ex; }
+    ex += c4[q];
+  }
+  const unsigned long long hit = __ballot(digit >= 0);   // one lane, where the segment takes anything
+  if (key.take > 0 && hit) {
+    const int src = __ffsll((long long)hit) - 1;
+    key.prefix = (key.prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
+    key.remain = __builtin_amdgcn_readlane(left, src);
+  }
+  if (leave && lane == 0) {
+    if (pass == 1) stt[RS_TAKE] = key.take;
+    stt[to] = (int32_t)key.prefix;
+    stt[to + 1] = key.remain;
+  }
+  return key;
+}
+
 // One workgroup (NTH threads: 256, or 1024 when there are few, long heads) per heads_per_wg
 // consecutive head instances, one after the other.  Counts a
 // head's entries below the prefix found so far and histograms the next digit of those that
@@ -93,9 +151,8 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
                                                         const int32_t* __restrict__ table,
                                                         const int32_t* __restrict__ ctx,
                                                         const int32_t* __restrict__ seq_seg,
-                                                        int32_t* __restrict__ seg_hist,
-                                                        int32_t* __restrict__ seg_state,
-                                                        int32_t* __restrict__ header) {
+                                                        int32_t* __restrict__ seg_hist, RankPicks picks,
+                                                        int32_t* seg_state, int32_t* header) {
   __shared__ int hist[256];
   __shared__ int below_s;
   __shared__ int smem[NTH / 64 + 1];
@@ -106,6 +163,7 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
   int lb = 0;
   while ((1 << lb) < D.b) ++lb;   // block sizes are powers of two
   int cur_sg = -1, rows_acc = 0, cand_acc = 0;
+  if (picks.hist && pass == 1 && blockIdx.x == 0) check_budgets(picks, NTH, header);
   auto flush = [&]() {
     if (cur_sg < 0) return;
     if (tid < 256 && rows_acc) atomicAdd(&seg_hist[cur_sg * 256 + tid], rows_acc);
@@ -120,12 +178,12 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
     const int nb = (C + D.b - 1) / D.b;
     const int ncand = max(0, nb - protect);
     cand_acc += ncand;
-    if (ncand == 0) continue;
-    if (pass > 0 && seg_state[sg * 8 + RS_TAKE] <= 0) continue;
+    const RankKey key = rank_key(picks, pass, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
+    if (ncand == 0 || key.take <= 0) continue;
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) below_s = 0;
     __syncthreads();
-    const uint32_t prefix = (uint32_t)seg_state[sg * 8 + RS_PREFIX];
+    const uint32_t prefix = key.prefix;
     const int32_t* row = table + (size_t)g * D.maxb;
     int below = 0;
     bool bad = false;
@@ -161,9 +219,8 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
                                                              const int32_t* __restrict__ table,
                                                              const int32_t* __restrict__ ctx,
                                                              const int32_t* __restrict__ seq_seg,
-                                                             int32_t* __restrict__ seg_hist,
-                                                             int32_t* __restrict__ seg_state,
-                                                             int32_t* __restrict__ header) {
+                                                             int32_t* __restrict__ seg_hist, RankPicks picks,
+                                                             int32_t* seg_state, int32_t* header) {
   __shared__ __align__(16) int hist_all[4][256];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int* hist = hist_all[wv];   // this wavefront's own: its LDS accesses happen in program order
@@ -174,6 +231,7 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
   while ((1 << lb) < D.b) ++lb;   // block sizes are powers of two
   const int bmask = D.b - 1;
   int cur_sg = -1, cand_acc = 0;
+  if (picks.hist && pass == 1 && blockIdx.x == 0) check_budgets(picks, 256, header);
   int rows_acc[4] = {0, 0, 0, 0};   // digits 4 lane .. 4 lane + 3
   bool bad = false;
   auto flush = [&]() {
@@ -193,10 +251,10 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
     const int nb = (C + D.b - 1) / D.b;
     const int ncand = max(0, nb - protect);
     cand_acc += ncand;
-    if (ncand == 0) continue;
-    if (pass > 0 && seg_state[sg * 8 + RS_TAKE] <= 0) continue;
+    const RankKey key = rank_key(picks, pass, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
+    if (ncand == 0 || key.take <= 0) continue;
     *(int4*)(hist + 4 * lane) = make_int4(0, 0, 0, 0);
-    const uint32_t prefix = (uint32_t)seg_state[sg * 8 + RS_PREFIX];
+    const uint32_t prefix = key.prefix;
     const int32_t* row = table + (size_t)g * D.maxb;
     int below = 0;
     auto count = [&](uint32_t k) {
@@ -305,7 +363,7 @@ __global__ void __launch_bounds__(NTH) rank_tie_kernel(Dims D, int protect, cons
                                                        const int32_t* __restrict__ table,
                                                        const int32_t* __restrict__ ctx,
                                                        const int32_t* __restrict__ seq_seg,
-                                                       const int32_t* __restrict__ seg_state,
+                                                       RankPicks picks, int32_t* seg_state,
                                                        int32_t* __restrict__ rows_lt,
                                                        int32_t* __restrict__ rows_tie) {
   __shared__ int lt_s, le_s;
@@ -314,13 +372,14 @@ __global__ void __launch_bounds__(NTH) rank_tie_kernel(Dims D, int protect, cons
   const int C = ctx[g];
   const int nb = (C + D.b - 1) / D.b;
   const int ncand = max(0, nb - protect);
-  if (ncand == 0 || seg_state[sg * 8 + RS_TAKE] <= 0) {
+  const RankKey key = rank_key(picks, 4, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
+  if (ncand == 0 || key.take <= 0) {
     if (tid == 0) { rows_lt[g] = 0; rows_tie[g] = 0; }
     return;
   }
   if (tid == 0) { lt_s = 0; le_s = 0; }
   __syncthreads();
-  const uint32_t thr = (uint32_t)seg_state[sg * 8 + RS_PREFIX];
+  const uint32_t thr = key.prefix;
   const int32_t* row = table + (size_t)g * D.maxb;
   int lt = 0, le = 0;
   int lb = 0;
@@ -351,7 +410,7 @@ __global__ void __launch_bounds__(256) rank_tie_wave_kernel(Dims D, int protect,
                                                             const int32_t* __restrict__ table,
                                                             const int32_t* __restrict__ ctx,
                                                             const int32_t* __restrict__ seq_seg,
-                                                            const int32_t* __restrict__ seg_state,
+                                                            RankPicks picks, int32_t* seg_state,
                                                             int32_t* __restrict__ rows_lt,
                                                             int32_t* __restrict__ rows_tie) {
   const int lane = threadIdx.x & 63;
@@ -361,11 +420,12 @@ __global__ void __launch_bounds__(256) rank_tie_wave_kernel(Dims D, int protect,
   const int C = ctx[g];
   const int nb = (C + D.b - 1) / D.b;
   const int ncand = max(0, nb - protect);
-  if (ncand == 0 || seg_state[sg * 8 + RS_TAKE] <= 0) {
+  const RankKey key = rank_key(picks, 4, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
+  if (ncand == 0 || key.take <= 0) {
     if (lane == 0) { rows_lt[g] = 0; rows_tie[g] = 0; }
     return;
   }
-  const uint32_t thr = (uint32_t)seg_state[sg * 8 + RS_PREFIX];
+  const uint32_t thr = key.prefix;
   const int32_t* row = table + (size_t)g * D.maxb;
   int lt = 0, le = 0;
   int lb = 0;
@@ -778,9 +838,17 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
   Workspace W = carve(D, ws);
   hipStream_t s = (hipStream_t)stream;
   int32_t* seq_seg = W.held;
-  const int n_init = D.G > nseg * 256 ? D.G : nseg * 256;
+  // up to 1024 heads: digits picked by the launch that uses them (the histograms of passes 1 to 3 in words that
+  // only a decode uses, where the pool has that many)
+  const size_t hist_words = (size_t)nseg * 256;
+  const bool fused = D.G <= 1024 && 3 * hist_words <= (size_t)D.N * D.b * D.r;
+  int32_t* const hists[4] = {W.seg_hist, fused ? (int32_t*)W.stash : W.seg_hist,
+                             fused ? (int32_t*)W.stash + hist_words : W.seg_hist,
+                             fused ? (int32_t*)W.stash + 2 * hist_words : W.seg_hist};
+  const int n_more = fused ? (int)(3 * hist_words) : 0;
+  const int n_init = std::max(std::max(D.G, nseg * 256), n_more);
   hipLaunchKernelGGL(segments_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, s, D, seg_offsets, nseg, seq_seg,
-                     W.seg_hist, W.seg_state, evict_rows, selected, W.header);
+                     W.seg_hist, W.seg_state, evict_rows, selected, W.header, (int32_t*)W.stash, n_more);
   KVC_LAUNCH_CHECK();
   for (int pass = 0; pass < 4; ++pass) {
     // first pass (the exponent byte): nearly every head lands on the same digit of its segment's
@@ -788,18 +856,20 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
     // (up to 1024 heads, whose adds are few, a wavefront each: 72 heads of 12421 tokens 324 -> 254 us a
     // round, 1024 of 8192 183 -> 163)
     const int hpw = pass == 0 && D.G > 1024 ? 4 : 1;
+    const RankPicks picks = {fused && pass > 0 ? hists[pass - 1] : nullptr, budget, nseg};
     if ((size_t)D.maxb * D.b <= kRankWaveTokens)
       hipLaunchKernelGGL(rank_hist_wave_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw)), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, W.seg_hist, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
     else if (D.G <= 1024)
       hipLaunchKernelGGL(rank_hist_kernel<1024>, dim3(D.G), dim3(1024), 0, s, D, pass, protect_tail_blocks, 1,
-                         st->metric, st->block_table, st->ctx_len, seq_seg, W.seg_hist, W.seg_state, W.header);
+                         st->metric, st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
     else
       hipLaunchKernelGGL(rank_hist_kernel<256>, dim3((D.G + hpw - 1) / hpw), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, W.seg_hist, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
+    if (fused) continue;
     hipLaunchKernelGGL(rank_pick_kernel, dim3(nseg), dim3(256), 0, s, pass, budget, W.seg_hist, W.seg_state,
                        W.header);
     KVC_LAUNCH_CHECK();
@@ -808,15 +878,16 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
       KVC_LAUNCH_CHECK();
     }
   }
+  const RankPicks picks = {fused ? hists[3] : nullptr, budget, nseg};
   if ((size_t)D.maxb * D.b <= kRankWaveTokens)
     hipLaunchKernelGGL(rank_tie_wave_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
-                       st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
+                       st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);
   else if (D.G <= 1024)   // a workgroup per CU or so: as wide as it goes (256 heads of 16384 tokens 9.4 -> 6.0 us)
     hipLaunchKernelGGL(rank_tie_kernel<1024>, dim3(D.G), dim3(1024), 0, s, D, protect_tail_blocks, st->metric,
-                       st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
+                       st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);
   else
     hipLaunchKernelGGL(rank_tie_kernel<256>, dim3(D.G), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
-                       st->block_table, st->ctx_len, seq_seg, W.seg_state, evict_rows, W.off_b);
+                       st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);
   KVC_LAUNCH_CHECK();
   if (D.G <= kRankSmallHeads) {
     hipLaunchKernelGGL(rank_grant_small_kernel, dim3(1), dim3(1024), 0, s, D, seq_seg, W.seg_state, W.off_b, evict_rows,
