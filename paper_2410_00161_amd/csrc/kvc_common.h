@@ -437,6 +437,64 @@ static __global__ void __launch_bounds__(256) segments_init_kernel(Dims D, const
   if (i < D.G) per_head[i] = 0;
 }
 
+// ---- digits picked by the launch that uses them ----
+// With few heads a launch of its own for the pick of a digit is all latency: five launches of 2 us and the
+// host's time for them.  There the wavefronts of the next launch each pick their segment's digit
+// themselves, from a histogram per pass (the previous one is complete when this launch starts, nobody adds to it
+// any more), and the wavefront of a segment's first head leaves what it found for the launch after: threshold
+// and remainder in one pair of words after passes 0 and 2, in another after 1 and 3, so that nobody reads
+// words that this launch writes.  (Rank rounds and prompts, picks by themselves -> so: 256 heads of 16384
+// tokens 287 -> 279 us, 1024 of 8192 147 -> 138, 672 of up to 3595 107 -> 97, 104 of up to 957 85 -> 71.)
+struct SegPicks {
+  const int32_t* hist;     // [nseg][256] of the pass before, or NULL: a launch of its own has picked
+  const int32_t* budget;
+  int nseg;
+};
+struct SegKey { uint32_t prefix; int remain, take; };
+
+__device__ __forceinline__ void check_budgets(const SegPicks& P, int nth, int32_t* header) {   // by a whole workgroup
+  bool neg = false;
+  for (int i = threadIdx.x; i < P.nseg; i += nth) neg |= P.budget[i] < 0;
+  const int any = __syncthreads_or(neg);
+  if (threadIdx.x != 0) return;
+  if (any) header[HW_SCRATCH0] |= EB_ARG;
+  settle_status(header);   // keys and budgets checked: before any output is written
+}
+
+// The threshold of segment sg as launch `pass` of a selection (4: the ties) needs it; for all lanes.
+__device__ __forceinline__ SegKey seg_key(const SegPicks& P, int pass, int sg, int32_t* seg_state, bool leave) {
+  int32_t* stt = seg_state + sg * 8;
+  if (pass == 0) return SegKey{0u, 0, 1};
+  if (!P.hist) return SegKey{(uint32_t)stt[SEG_PREFIX], stt[SEG_REMAIN], stt[SEG_TAKE]};
+  const int lane = threadIdx.x & 63;
+  const int from = pass & 1 ? 0 : 6, to = pass & 1 ? 6 : 0;   // (SEG_PREFIX, SEG_REMAIN, or the last two words)
+  SegKey key;
+  key.take = pass == 1 ? min(max(P.budget[sg], 0), stt[SEG_CAND]) : stt[SEG_TAKE];
+  key.prefix = pass == 1 ? 0u : (uint32_t)stt[from];
+  key.remain = pass == 1 ? key.take : stt[from + 1];
+  const int4 c = ((const int4*)(P.hist + (size_t)sg * 256))[lane];
+  const int mine = c.x + c.y + c.z + c.w;
+  int ex = wave_prefix_i(mine) - mine, digit = -1, left = 0;
+  const int c4[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (ex < key.remain && key.remain <= ex + c4[q]) { digit = 4 * lane + q; left = key.remain - ex; }
+    ex += c4[q];
+  }
+  const unsigned long long hit = __ballot(digit >= 0);   // one lane, where the segment takes anything
+  if (key.take > 0 && hit) {
+    const int src = __ffsll((long long)hit) - 1;
+    key.prefix = (key.prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
+    key.remain = __builtin_amdgcn_readlane(left, src);
+  }
+  if (leave && lane == 0) {
+    if (pass == 1) stt[SEG_TAKE] = key.take;
+    stt[to] = (int32_t)key.prefix;
+    stt[to + 1] = key.remain;
+  }
+  return key;
+}
+
 // The end of a head's moves when several workgroups of 256 threads share them: the last of the `expected`
 // ones gives the tail blocks back and sets the new length T (was C).  By all threads; the workgroup's
 // reads of the head's row and length are done.

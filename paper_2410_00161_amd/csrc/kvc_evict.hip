@@ -92,12 +92,12 @@ __global__ void __launch_bounds__(256) select_hist_kernel(Dims D, int pass, int 
                                                           const float* __restrict__ key,
                                                           const int32_t* __restrict__ ctx,
                                                           const int32_t* __restrict__ seq_seg,
-                                                          int32_t* __restrict__ seg_hist,
-                                                          int32_t* __restrict__ seg_state,
-                                                          int32_t* __restrict__ header) {
+                                                          int32_t* __restrict__ seg_hist, SegPicks picks,
+                                                          int32_t* seg_state, int32_t* header) {
   __shared__ int hist[4][256];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int* my = hist[wid];   // written and read by this wavefront only
+  if (picks.hist && pass == 1 && blockIdx.x == 0 && blockIdx.y == 0) check_budgets(picks, 256, header);
   for (int i = lane; i < 256; i += 64) my[i] = 0;
   const int g_first = (blockIdx.x * 4 + wid) * heads_per_wave;
   const int g_end = min(D.G, g_first + heads_per_wave);
@@ -119,10 +119,10 @@ __global__ void __launch_bounds__(256) select_hist_kernel(Dims D, int pass, int 
     const int C = ctx[g];
     const int ncand = max(0, (C + D.b - 1) / D.b - protect);
     cand_acc += ncand;
-    const uint32_t prefix = (uint32_t)seg_state[sg * 8 + SS_PREFIX];
-    const bool live = pass == 0 || seg_state[sg * 8 + SS_TAKE] > 0;
+    const SegKey seg = seg_key(picks, pass, sg, seg_state, blockIdx.y == 0 && g == seg_state[sg * 8 + SS_FIRSTG]);
+    const uint32_t prefix = seg.prefix;
     const float* krow = key + (size_t)g * D.maxb;
-    if (live) {
+    if (seg.take > 0) {
       for (int u = blockIdx.y * 64 + lane; u < ncand; u += 64 * gridDim.y) {
         const uint32_t k = key_bits(krow[u]);
         if (pass == 0) bad |= k >= 0x7f800000u;
@@ -172,15 +172,16 @@ __global__ void __launch_bounds__(256) select_tie_count_kernel(Dims D, int prote
                                                                const float* __restrict__ key,
                                                                const int32_t* __restrict__ ctx,
                                                                const int32_t* __restrict__ seq_seg,
-                                                               const int32_t* __restrict__ seg_state,
+                                                               SegPicks picks, int32_t* seg_state,
                                                                int32_t* __restrict__ tie_cnt) {
   const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (g >= D.G) return;
   const int lane = threadIdx.x & 63;
   const int sg = seq_seg[g / (D.Lyr * D.Hk)];
   int n = 0;
-  if (seg_state[sg * 8 + SS_TAKE] > 0) {
-    const uint32_t thr = (uint32_t)seg_state[sg * 8 + SS_PREFIX];
+  const SegKey seg = seg_key(picks, 4, sg, seg_state, g == seg_state[sg * 8 + SS_FIRSTG]);
+  if (seg.take > 0) {
+    const uint32_t thr = seg.prefix;
     const int ncand = max(0, (ctx[g] + D.b - 1) / D.b - protect);
     const float* krow = key + (size_t)g * D.maxb;
     for (int u = lane; u < ncand; u += 64) n += key_bits(krow[u]) == thr;
@@ -199,6 +200,7 @@ __global__ void __launch_bounds__(256) select_mark_kernel(Dims D, int protect, c
                                                           const int32_t* __restrict__ seq_seg,
                                                           const int32_t* __restrict__ seg_state,
                                                           const int32_t* __restrict__ tie_off,
+                                                          const int32_t* __restrict__ tie_cnt,
                                                           uint8_t* __restrict__ flag,
                                                           int32_t* __restrict__ evict_count,
                                                           int32_t* __restrict__ selected,
@@ -216,7 +218,13 @@ __global__ void __launch_bounds__(256) select_mark_kernel(Dims D, int protect, c
   // ties granted to this head: those whose rank inside the segment is below SS_REMAIN (a segment
   // that takes every key at its threshold has no ranks to look up)
   const bool all_ties = stt[SS_ALLTIES] != 0;
-  int ties_before = all_ties ? 0 : tie_off[g] - tie_off[stt[SS_FIRSTG]];
+  int ties_before = 0;
+  if (tie_cnt) {   // few heads: the segment's counts before this head's, added up here
+    for (int i = stt[SS_FIRSTG] + lane; i < g; i += 64) ties_before += tie_cnt[i];
+    ties_before = wave_sum_i(ties_before);
+  } else if (!all_ties) {
+    ties_before = tie_off[g] - tie_off[stt[SS_FIRSTG]];
+  }
   const int want = all_ties ? 0x7fffffff : stt[SS_REMAIN];
   const int ncand = max(0, (ctx[g] + D.b - 1) / D.b - protect);
   const float* krow = key + (size_t)g * D.maxb;
@@ -768,14 +776,21 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
     hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(64), 0, s, W.header);
     KVC_LAUNCH_CHECK();
     hipLaunchKernelGGL(select_mark_kernel, dim3(gw), dim3(256), 0, s, D, protect_tail_blocks, block_key,
-                       st->ctx_len, (const int32_t*)nullptr, W.seg_state, W.off_a, evict_flag, evict_count, selected,
+                       st->ctx_len, (const int32_t*)nullptr, W.seg_state, W.off_a, (const int32_t*)nullptr, evict_flag, evict_count, selected,
                        W.header);
     KVC_LAUNCH_CHECK();
     return (flags & KVC_ASYNC) ? KVC_OK : finish_sync(W, s);
   }
-  int n_init = D.G > nseg * 256 ? D.G : nseg * 256;
+  // up to 1024 heads: digits picked by the launch that uses them, ties ranked where they are marked (the
+  // histograms of passes 1 to 3 in words that only a decode uses, where the pool has that many): eight launches
+  // fewer (192 heads of up to 2164 blocks 193 -> 177 us a round, 80 of 1235 196 -> 178, 320 of 2048 226 -> 211)
+  const size_t hist_words = (size_t)nseg * 256;
+  const bool fused = D.G <= 1024 && 3 * hist_words <= (size_t)D.N * D.b * D.r;
+  const int n_more = fused ? (int)(3 * hist_words) : 0;
+  auto hist_of = [&](int pass) { return fused && pass > 0 ? (int32_t*)W.stash + (pass - 1) * hist_words : W.seg_hist; };
+  const int n_init = std::max(std::max(D.G, nseg * 256), n_more);
   hipLaunchKernelGGL(segments_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, s, D, seg_offsets, nseg,
-                     seq_seg, W.seg_hist, W.seg_state, evict_count, selected, W.header, (int32_t*)nullptr, 0);
+                     seq_seg, W.seg_hist, W.seg_state, evict_count, selected, W.header, (int32_t*)W.stash, n_more);
   KVC_LAUNCH_CHECK();
   const size_t nflag = (size_t)D.G * D.maxb;
   hipLaunchKernelGGL(zero_bytes_kernel, dim3((unsigned)((nflag / 16 + 256) / 256)), dim3(256), 0, s,
@@ -788,8 +803,10 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
     // round, 320 of 2048 287 -> 224)
     const int hpw = pass == 0 && D.G > 1024 ? 8 : 1;
     hipLaunchKernelGGL(select_hist_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw), row_shares(D, 1024)), dim3(256), 0, s, D, pass,
-                       protect_tail_blocks, hpw, block_key, st->ctx_len, seq_seg, W.seg_hist, W.seg_state, W.header);
+                       protect_tail_blocks, hpw, block_key, st->ctx_len, seq_seg, hist_of(pass),
+                       SegPicks{fused && pass > 0 ? hist_of(pass - 1) : nullptr, budget, nseg}, W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
+    if (fused) continue;
     hipLaunchKernelGGL(select_pick_kernel, dim3(nseg), dim3(256), 0, s, pass, budget, W.seg_hist,
                        W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
@@ -799,13 +816,15 @@ int kvc_evict_select(const kvc_config* cfg, const kvc_state* st, const float* bl
     }
   }
   hipLaunchKernelGGL(select_tie_count_kernel, dim3(gw), dim3(256), 0, s, D, protect_tail_blocks, block_key,
-                     st->ctx_len, seq_seg, W.seg_state, W.off_b);
+                     st->ctx_len, seq_seg, SegPicks{fused ? hist_of(3) : nullptr, budget, nseg}, W.seg_state, W.off_b);
   KVC_LAUNCH_CHECK();
-  rc = device_exclusive_scan(TieFn{W.off_b}, D.G, W.tile_sums, W.off_a, nullptr, s);
-  if (rc != KVC_OK) return rc;
+  if (!fused) {
+    rc = device_exclusive_scan(TieFn{W.off_b}, D.G, W.tile_sums, W.off_a, nullptr, s);
+    if (rc != KVC_OK) return rc;
+  }
   hipLaunchKernelGGL(select_mark_kernel, dim3(gw), dim3(256), 0, s, D, protect_tail_blocks, block_key,
-                     st->ctx_len, seq_seg, W.seg_state, W.off_a, evict_flag, evict_count, selected,
-                     W.header);
+                     st->ctx_len, seq_seg, W.seg_state, W.off_a, fused ? W.off_b : (const int32_t*)nullptr, evict_flag,
+                     evict_count, selected, W.header);
   KVC_LAUNCH_CHECK();
   return (flags & KVC_ASYNC) ? KVC_OK : finish_sync(W, s);
 }

@@ -80,64 +80,6 @@ __device__ __forceinline__ void for_each_metric(const float* __restrict__ metric
   }
 }
 
-// ---- digits picked by the launch that uses them ----
-// With few heads a launch of its own for the pick of a digit is all latency: five launches of 2 us and the
-// host's time for them.  There the wavefronts of the next launch each pick their segment's digit
-// themselves, from a histogram per pass (the previous one is complete when this launch starts, nobody adds to it
-// any more), and the wavefront of a segment's first head leaves what it found for the launch after: threshold
-// and remainder in one pair of words after passes 0 and 2, in another after 1 and 3, so that nobody reads
-// words that this launch writes.  (Whole rounds and prompts, picks by themselves -> so: 256 heads of 16384
-// tokens 287 -> 279 us, 1024 of 8192 147 -> 138, 672 of up to 3595 107 -> 97, 104 of up to 957 85 -> 71.)
-struct RankPicks {
-  const int32_t* hist;     // [nseg][256] of the pass before, or NULL: rank_pick_kernel has picked
-  const int32_t* budget;
-  int nseg;
-};
-struct RankKey { uint32_t prefix; int remain, take; };
-
-__device__ __forceinline__ void check_budgets(const RankPicks& P, int nth, int32_t* header) {   // by a whole workgroup
-  bool neg = false;
-  for (int i = threadIdx.x; i < P.nseg; i += nth) neg |= P.budget[i] < 0;
-  const int any = __syncthreads_or(neg);
-  if (threadIdx.x != 0) return;
-  if (any) header[HW_SCRATCH0] |= EB_ARG;
-  settle_status(header);   // keys and budgets checked: before any output is written
-}
-
-// The threshold of segment sg as launch `pass` of the schedule (4: the ties) needs it; for all lanes.
-__device__ __forceinline__ RankKey rank_key(const RankPicks& P, int pass, int sg, int32_t* seg_state, bool leave) {
-  int32_t* stt = seg_state + sg * 8;
-  if (pass == 0) return RankKey{0u, 0, 1};
-  if (!P.hist) return RankKey{(uint32_t)stt[RS_PREFIX], stt[RS_REMAIN], stt[RS_TAKE]};
-  const int lane = threadIdx.x & 63;
-  const int from = pass & 1 ? 0 : 6, to = pass & 1 ? 6 : 0;   // (RS_PREFIX, RS_REMAIN, or the last two words)
-  RankKey key;
-  key.take = pass == 1 ? min(max(P.budget[sg], 0), stt[RS_CAND]) : stt[RS_TAKE];
-  key.prefix = pass == 1 ? 0u : (uint32_t)stt[from];
-  key.remain = pass == 1 ? key.take : stt[from + 1];
-  const int4 c = ((const int4*)(P.hist + (size_t)sg * 256))[lane];
-  const int mine = c.x + c.y + c.z + c.w;
-  int ex = wave_prefix_i(mine) - mine, digit = -1, left = 0;
-  const int c4[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (ex < key.remain && key.remain <= ex + c4[q]) { digit = 4 * lane + q; left = key.remain - ex; }
-    ex += c4[q];
-  }
-  const unsigned long long hit = __ballot(digit >= 0);   // one lane, where the segment takes anything
-  if (key.take > 0 && hit) {
-    const int src = __ffsll((long long)hit) - 1;
-    key.prefix = (key.prefix << 8) | (uint32_t)__builtin_amdgcn_readlane(digit, src);
-    key.remain = __builtin_amdgcn_readlane(left, src);
-  }
-  if (leave && lane == 0) {
-    if (pass == 1) stt[RS_TAKE] = key.take;
-    stt[to] = (int32_t)key.prefix;
-    stt[to + 1] = key.remain;
-  }
-  return key;
-}
-
 // One workgroup (NTH threads: 256, or 1024 when there are few, long heads) per heads_per_wg
 // consecutive head instances, one after the other.  Counts a
 // head's entries below the prefix found so far and histograms the next digit of those that
@@ -151,7 +93,7 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
                                                         const int32_t* __restrict__ table,
                                                         const int32_t* __restrict__ ctx,
                                                         const int32_t* __restrict__ seq_seg,
-                                                        int32_t* __restrict__ seg_hist, RankPicks picks,
+                                                        int32_t* __restrict__ seg_hist, SegPicks picks,
                                                         int32_t* seg_state, int32_t* header) {
   __shared__ int hist[256];
   __shared__ int below_s;
@@ -178,7 +120,7 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
     const int nb = (C + D.b - 1) / D.b;
     const int ncand = max(0, nb - protect);
     cand_acc += ncand;
-    const RankKey key = rank_key(picks, pass, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
+    const SegKey key = seg_key(picks, pass, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
     if (ncand == 0 || key.take <= 0) continue;
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) below_s = 0;
@@ -219,7 +161,7 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
                                                              const int32_t* __restrict__ table,
                                                              const int32_t* __restrict__ ctx,
                                                              const int32_t* __restrict__ seq_seg,
-                                                             int32_t* __restrict__ seg_hist, RankPicks picks,
+                                                             int32_t* __restrict__ seg_hist, SegPicks picks,
                                                              int32_t* seg_state, int32_t* header) {
   __shared__ __align__(16) int hist_all[4][256];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -251,7 +193,7 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
     const int nb = (C + D.b - 1) / D.b;
     const int ncand = max(0, nb - protect);
     cand_acc += ncand;
-    const RankKey key = rank_key(picks, pass, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
+    const SegKey key = seg_key(picks, pass, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
     if (ncand == 0 || key.take <= 0) continue;
     *(int4*)(hist + 4 * lane) = make_int4(0, 0, 0, 0);
     const uint32_t prefix = key.prefix;
@@ -363,7 +305,7 @@ __global__ void __launch_bounds__(NTH) rank_tie_kernel(Dims D, int protect, cons
                                                        const int32_t* __restrict__ table,
                                                        const int32_t* __restrict__ ctx,
                                                        const int32_t* __restrict__ seq_seg,
-                                                       RankPicks picks, int32_t* seg_state,
+                                                       SegPicks picks, int32_t* seg_state,
                                                        int32_t* __restrict__ rows_lt,
                                                        int32_t* __restrict__ rows_tie) {
   __shared__ int lt_s, le_s;
@@ -372,7 +314,7 @@ __global__ void __launch_bounds__(NTH) rank_tie_kernel(Dims D, int protect, cons
   const int C = ctx[g];
   const int nb = (C + D.b - 1) / D.b;
   const int ncand = max(0, nb - protect);
-  const RankKey key = rank_key(picks, 4, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
+  const SegKey key = seg_key(picks, 4, sg, seg_state, tid < 64 && g == seg_state[sg * 8 + RS_FIRSTG]);
   if (ncand == 0 || key.take <= 0) {
     if (tid == 0) { rows_lt[g] = 0; rows_tie[g] = 0; }
     return;
@@ -410,7 +352,7 @@ __global__ void __launch_bounds__(256) rank_tie_wave_kernel(Dims D, int protect,
                                                             const int32_t* __restrict__ table,
                                                             const int32_t* __restrict__ ctx,
                                                             const int32_t* __restrict__ seq_seg,
-                                                            RankPicks picks, int32_t* seg_state,
+                                                            SegPicks picks, int32_t* seg_state,
                                                             int32_t* __restrict__ rows_lt,
                                                             int32_t* __restrict__ rows_tie) {
   const int lane = threadIdx.x & 63;
@@ -420,7 +362,7 @@ __global__ void __launch_bounds__(256) rank_tie_wave_kernel(Dims D, int protect,
   const int C = ctx[g];
   const int nb = (C + D.b - 1) / D.b;
   const int ncand = max(0, nb - protect);
-  const RankKey key = rank_key(picks, 4, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
+  const SegKey key = seg_key(picks, 4, sg, seg_state, g == seg_state[sg * 8 + RS_FIRSTG]);
   if (ncand == 0 || key.take <= 0) {
     if (lane == 0) { rows_lt[g] = 0; rows_tie[g] = 0; }
     return;
@@ -842,9 +784,7 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
   // only a decode uses, where the pool has that many)
   const size_t hist_words = (size_t)nseg * 256;
   const bool fused = D.G <= 1024 && 3 * hist_words <= (size_t)D.N * D.b * D.r;
-  int32_t* const hists[4] = {W.seg_hist, fused ? (int32_t*)W.stash : W.seg_hist,
-                             fused ? (int32_t*)W.stash + hist_words : W.seg_hist,
-                             fused ? (int32_t*)W.stash + 2 * hist_words : W.seg_hist};
+  auto hist_of = [&](int pass) { return fused && pass > 0 ? (int32_t*)W.stash + (pass - 1) * hist_words : W.seg_hist; };
   const int n_more = fused ? (int)(3 * hist_words) : 0;
   const int n_init = std::max(std::max(D.G, nseg * 256), n_more);
   hipLaunchKernelGGL(segments_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, s, D, seg_offsets, nseg, seq_seg,
@@ -856,18 +796,18 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
     // (up to 1024 heads, whose adds are few, a wavefront each: 72 heads of 12421 tokens 324 -> 254 us a
     // round, 1024 of 8192 183 -> 163)
     const int hpw = pass == 0 && D.G > 1024 ? 4 : 1;
-    const RankPicks picks = {fused && pass > 0 ? hists[pass - 1] : nullptr, budget, nseg};
+    const SegPicks picks = {fused && pass > 0 ? hist_of(pass - 1) : nullptr, budget, nseg};
     if ((size_t)D.maxb * D.b <= kRankWaveTokens)
       hipLaunchKernelGGL(rank_hist_wave_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw)), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
     else if (D.G <= 1024)
       hipLaunchKernelGGL(rank_hist_kernel<1024>, dim3(D.G), dim3(1024), 0, s, D, pass, protect_tail_blocks, 1,
-                         st->metric, st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
+                         st->metric, st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
     else
       hipLaunchKernelGGL(rank_hist_kernel<256>, dim3((D.G + hpw - 1) / hpw), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, hists[pass], picks, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
     KVC_LAUNCH_CHECK();
     if (fused) continue;
     hipLaunchKernelGGL(rank_pick_kernel, dim3(nseg), dim3(256), 0, s, pass, budget, W.seg_hist, W.seg_state,
@@ -878,7 +818,7 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
       KVC_LAUNCH_CHECK();
     }
   }
-  const RankPicks picks = {fused ? hists[3] : nullptr, budget, nseg};
+  const SegPicks picks = {fused ? hist_of(3) : nullptr, budget, nseg};
   if ((size_t)D.maxb * D.b <= kRankWaveTokens)
     hipLaunchKernelGGL(rank_tie_wave_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
                        st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);

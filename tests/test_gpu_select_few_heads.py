@@ -45,3 +45,32 @@ def test_shared_rows(S, Lyr, Hk, ties):
         np.testing.assert_array_equal(got[1].cpu().numpy().reshape(-1), count)
         np.testing.assert_array_equal(got[2].cpu().numpy(), sel)
         compare(sess, st, sess.compact(), O.compact(st, flag, count))
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("longest,Lyr", [(900, 1), (12, 1), (60, 80)])   # 12 heads, in a pool too small for the histograms too, and 960
+def test_empty_segments(longest, Lyr, ties):
+    from paper_2410_00161_amd.session import KvcSession
+    S, off = 6, [0, 0, 1, 4, 4, 6]
+    lengths = [int(x) for x in torch.randint(0, longest, (S * Lyr * 2,), generator=torch.Generator().manual_seed(3))]
+    shape, cache, _ = make(S, Lyr, 2, 1, 8, 2, lengths, "bf16", 0)
+    assert (shape.num_blocks * 2 < 3 * 256 * 5) == (longest == 12)
+    if ties:
+        cache.metric = torch.randint(0, 3, cache.metric.shape, generator=torch.Generator().manual_seed(5)).float()
+    st = oracle_state(cache)
+    sess = KvcSession(cache)
+    seg = torch.tensor(off, dtype=torch.int32)
+    for share in ((0.0, 0.4, 0.0, 0.0, 0.7), (0.0, 9.0, 0.5, 0.0, 0.0)):
+        nb = (-(-st.lens() // 2)).reshape(S, -1).sum(1)
+        budget = np.array([int(nb[a:e].sum() * f) for a, e, f in zip(off, off[1:], share)], dtype=np.int64)
+        sess.metric_reduce()
+        flag, count, sel = O.evict_select(st, O.block_keys(st)[0], budget, seg_offsets=np.array(off), protect_tail_blocks=1)
+        wrong = torch.from_numpy(budget).int()
+        wrong[3] = -1   # of an empty segment
+        with pytest.raises(B.KvcError):
+            sess.evict_select(wrong, seg)
+        got = sess.evict_select(torch.from_numpy(budget).int(), seg)
+        np.testing.assert_array_equal(got[0].cpu().numpy().reshape(flag.shape), flag)
+        np.testing.assert_array_equal(got[1].cpu().numpy().reshape(-1), count)
+        np.testing.assert_array_equal(got[2].cpu().numpy(), sel)
+        compare(sess, st, sess.compact(), O.compact(st, flag, count))
