@@ -549,10 +549,14 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
         float4 pe = *(const float4*)(my_e + (rho & (R - 1)) * 16 + 4 * kap);
         if (R < 8 && (rho % PROWS >= R || part >= PARTS)) pe = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // rows without a head or a part
         auto top16 = [](float p) { return __uint_as_float(__float_as_uint(p) & 0xffff0000u); };
+        // With three parts of 16-bit rows, one that is zero (a probability of few bits) goes in as the least
+        // normal number: zero times an infinite value would be NaN, where the plain product is infinite.
+        // Next to the finite ones it adds 2^-126 of a value, nothing.
+        auto live_part = [](float p) { return PARTS == 3 && ESZ == 2 ? fmaxf(p, 0x1p-126f) : p; };
         auto part_of = [&](float p) {   // a float whose upper 16 bits are this row's part of p
           const float mid = p - top16(p);   // exact
           if (PROWS == 4) return part == 0 ? p : part == 1 ? mid : mid - top16(mid);
-          return part == 0 ? p : mid;
+          return live_part(part == 0 ? p : mid);
         };
         auto pack = [](float p0, float p1, float p2, float p3) {
           const uint2 u = make_uint2(__builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u),
@@ -563,7 +567,7 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
         // the third part of eight heads does not fit: a second operand, the same rows
         i16x4_t aop3 = {0, 0, 0, 0};
         if constexpr (PARTS == 3 && R == 8) {
-          auto last = [&](float p) { const float mid = p - top16(p); return part == 0 ? mid - top16(mid) : 0.0f; };
+          auto last = [&](float p) { const float mid = p - top16(p); return live_part(part == 0 ? mid - top16(mid) : 0.0f); };
           aop3 = pack(last(pe.x), last(pe.y), last(pe.z), last(pe.w));
         }
         // B operand of dimension tile dt: lane = (column lane % 16, tokens 4 (lane / 16) .. + 3).

@@ -46,3 +46,29 @@ def test_outputs_near_64_bits(r, d, b, dtype, chunk):
     m = sess.cache.metric.cpu().numpy().astype(np.float64)
     np.testing.assert_allclose(m[real], st.metric[real], rtol=0, atol=r * 2.0 ** -15)
     np.testing.assert_array_equal(m[~real], before[~real])
+
+
+@pytest.mark.parametrize("r,d,b", [(8, 64, 16), (8, 64, 8), (8, 128, 8), (8, 128, 1)])
+@pytest.mark.parametrize("chunk", [0, 128, 2048])
+def test_infinite_values_stay_infinite(r, d, b, chunk):
+    """An infinite value times a probability, however few bits that has, is infinite; the other dimensions
+    and the metric do not notice.  (8-bit floats have no infinities.)"""
+    from paper_2410_00161_amd.session import KvcSession
+    shape, cache, real = make(2, 2, 4, r, d, b, LENGTHS, "bf16", 0)
+    clean = cache.clone()
+    table = cache.block_table.reshape(shape.G, -1)
+    sign = np.zeros((shape.G, d))
+    for g, j, k, x in ((0, 0, 7, 1), (3, 7, 5, 1), (3, 15, 6, -1), (8, 62, 9, 1), (12, 1000, 3, -1), (12, 40, 3, -1), (15, 511, 0, 1)):
+        cache.v_cache[int(table[g, j // b]), j % b, k] = x * float("inf")
+        sign[g, k] = x
+    q = W.make_query(shape, 3)
+    B.kvc_set_decode_chunk(chunk)
+    try:
+        sess, ref = KvcSession(cache), KvcSession(clean)
+        got, want = (s.paged_decode(q.to(s.device)).cpu().numpy().reshape(shape.G, r, d) for s in (sess, ref))
+    finally:
+        B.kvc_set_decode_chunk(0)
+    hit = np.broadcast_to((sign != 0)[:, None], got.shape)
+    np.testing.assert_array_equal(got[hit], (np.broadcast_to(sign[:, None], got.shape)[hit] * np.inf).astype(np.float32))
+    np.testing.assert_array_equal(got[~hit], want[~hit])
+    np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), ref.cache.metric.cpu().numpy())
