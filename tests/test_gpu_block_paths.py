@@ -227,3 +227,28 @@ def test_a_streamed_block_of_some_layers():
     got = sess.cache.metric.double().view(-1)
     assert float(((got - want) / want).abs().max()) <= 4e-6
     assert torch.equal(got[want == before], before[want == before])
+
+
+@pytest.mark.parametrize("d,b", [(128, 16), (64, 8)])
+def test_infinite_keys(d, b):
+    """A query row with a logit of +inf: NaN at that key, nothing added anywhere else by that row (its
+    denominator is infinite).  Over three chunks, the keys in different lanes."""
+    from paper_2410_00161_amd.session import KvcSession
+    cache = prompt(1, 1, 4, 4, d, b, [3000], "bf16", 33)
+    w, first = 256, 2700
+    assert streamed_chunk(cache.shape, w, first, False) == 1024
+    rows, table = cache.k_cache.view(-1, d), cache.block_table.view(4, -1).long()
+    for g, j in ((0, 0), (1, 7), (1, 2047), (2, 1030), (2, 2990)):
+        rows[table[g, j // b] * b + j % b, (5 * j) % d] = (-1) ** g * float("inf")
+    cache.metric.zero_()
+    q = queries(cache.shape, w)
+    row_lse = torch.empty((1, 1, 16, w), device=DEV)
+    for g, _, _, lse in in_64_bits(cache, q, w, first, 0):
+        row_lse.view(4, 4, w)[g] = torch.where(torch.isfinite(lse), lse, torch.inf).float()
+    got = []
+    for lse in (None, row_lse):
+        sess = KvcSession(cache.clone())
+        sess.query_block_metric(q, w, first, 0, row_lse=lse)
+        got.append(sess.cache.metric.cpu())
+    assert int(torch.isnan(got[1]).sum()) >= 4 and not bool(torch.isinf(got[1]).any())
+    torch.testing.assert_close(got[0], got[1], rtol=1e-4, atol=1e-4 * float(got[1].nan_to_num().max()), equal_nan=True)

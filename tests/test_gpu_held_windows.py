@@ -87,3 +87,28 @@ def test_long_runs_sampled(Lyr, Hk, r, w, d, b, dtype, L):
     for i in range(len(heads)):
         n, o = O.slots_of(st, i)
         close(after.metric.double().numpy()[n, o], st.metric[n, o], np.ones(len(n), dtype=bool))
+
+
+@pytest.mark.parametrize("r,w,d,b,dtype,lengths", [
+    (4, 8, 128, 16, "bf16", LENGTHS), (2, 32, 64, 4, "bf16", LENGTHS), (4, 32, 64, 16, "bf16", LENGTHS),
+])
+def test_infinite_keys(r, w, d, b, dtype, lengths):
+    """A query row with a logit of +inf, wherever among the lanes and runs of a head that key lies: NaN at
+    that key, nothing added anywhere else by that row (its denominator is infinite)."""
+    from paper_2410_00161_amd.session import KvcSession
+    shape, cache, real = make(2, 2, 4, r, d, b, lengths, dtype, 0)
+    table = cache.block_table.reshape(shape.G, -1)
+    for g, j in ((3, 7), (9, 62), (12, 900), (10, 40), (10, 2040), (14, 500), (15, 0), (15, 639)):
+        cache.k_cache[int(table[g, j // b]), j % b, (5 * j) % d] = (-1) ** g * float("inf")
+    st = oracle_state(cache)
+    q = queries(shape, w)
+    with np.errstate(all="ignore"):
+        given = row_lse(st, q.double().numpy(), w)
+    given[~np.isfinite(given)] = np.inf
+    got = []
+    for lse in (None, torch.from_numpy(given)):
+        sess = KvcSession(cache.clone())
+        sess.window_metric(q.to(sess.device), w, 1, row_lse=None if lse is None else lse.to(sess.device))
+        got.append(sess.cache.metric.double().cpu().numpy())
+    assert np.isnan(got[1][real]).sum() >= 4 and not np.isinf(got[1][real]).any()
+    np.testing.assert_allclose(got[0][real], got[1][real], rtol=1e-4, atol=1e-4 * np.nanmax(got[1][real]))
