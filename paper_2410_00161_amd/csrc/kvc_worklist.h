@@ -248,8 +248,11 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   }
   if (tid == 0) header[HW_CHUNK_T] = T;
   if (tid < A.gsel) {
-    nfull = C / T;
-    rem = C - nfull * T;
+    // (A full head planned one token longer: its row ends in front of that token.  Its records, which a
+    // decode looks up in the row before it compares the length, end there too.)
+    const int listed = PLAN ? (int)min((long long)C, (long long)A.D.maxb * A.D.b) : C;
+    nfull = listed / T;
+    rem = listed - nfull * T;
     nch = nfull + (rem ? 1 : 0);
     cls = rem ? size_class(rem, T) : 0;
     if (rem) atomicAdd(&bins[cls], 1);

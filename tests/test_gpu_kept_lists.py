@@ -67,3 +67,42 @@ def test_rows_with_far_more_room_are_refused():
     with pytest.raises(B.KvcError) as e:
         sess.decode_plan()
     assert e.value.code == B.KVC_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("row", [512, 1000, 64])
+def test_no_record_reaches_past_a_full_row(row):
+    """Full heads, the cache's last one among them, planned one token longer: what the list holds ends
+    with the row (a decode reads a record's block ids before it compares the length).  The append is
+    refused, the decode from the list leaves the heads alone and says so."""
+    from paper_2410_00161_amd.session import KvcSession
+    S, Hk, b = 2, 8, 16
+    row = -(-row // b) * b
+    ctx = torch.tensor([row if g in (3, S * Hk - 1) else g * row // 20 for g in range(S * Hk)], dtype=torch.int32)
+    shape = W.Shape(S, 1, Hk, 4, 128, b, W.pool_size(ctx, b, 1.2, 40), row // b, "bf16")
+    cache = W.make_cache(shape, ctx, 3, placement="fragmented", init_metric="prefill")
+    sess = KvcSession(cache)
+    sess.decode_plan(ctx_plus=1)
+    torch.cuda.synchronize()
+    # the workspace: header, the layer's header block, tile sums, two scans over the heads, blocks held, then the records
+    ws = sess.ws.view(torch.uint8).cpu()
+    at = 512 + 512
+    for words in (max(shape.num_blocks, shape.G) // 2048 + 3, shape.G + 1, shape.G + 1, shape.G):
+        at += -(-4 * words // 256) * 256
+    n = int(ws[512:1024].view(torch.int32)[3])
+    records = ws[at:at + 32 * n].view(torch.int32).view(n, 8).numpy()
+    assert sorted(set(records[:, 0])) == list(range(S * Hk)) and set(records[records[:, 0] == 3][:, 5]) == {row + 1}
+    ends = records[:, 1] + records[:, 2]
+    assert ends.max() == row and (records[:, 1] >= 0).all() and (records[:, 2] > 0).all()
+    for g in range(S * Hk):
+        assert ends[records[:, 0] == g].max() == min(int(ctx[g]) + 1, row)
+    k, v = (t.to(sess.device) for t in W.make_new_kv(shape, 3))
+    with pytest.raises(B.KvcError) as e:
+        sess.append(k, v)
+    assert e.value.code == B.KVC_ERR_TABLE_FULL
+    sess.out.fill_(5.0)
+    sess.paged_decode_planned(W.make_query(shape, 3).to(sess.device), 0)
+    torch.cuda.synchronize()
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_ERR_ARG
+    written = (sess.out.view(S * Hk, -1) != 5.0).any(1).cpu()
+    assert written.nonzero().view(-1).tolist() == [0]        # (nothing in it, a row of zeros)
+    np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), cache.metric.cpu().numpy())
