@@ -124,6 +124,16 @@ def test_entry_points_reject_bad_arguments_on_the_host():
     assert L.kvc_stream_read_probe(one, 100, one, 512, None) == B.KVC_ERR_ARG                      # bytes not a multiple of 16
 
 
+@pytest.mark.parametrize("w,pool,lse", [(8, 7, None), (8, 1, 4096), (32, 7, 4096), (64, 33, None)])
+def test_windows_over_rows_too_long_to_be_pooled_are_refused(w, pool, lse):
+    """More than 65535 tiles of 2048 positions a row, whichever kernels a shorter row would take."""
+    L = B.lib()
+    st = B.kvc_state(4096, 8192, 4096, None, 4096, 4096, 4096)   # never dereferenced
+    cfg = good_cfg(num_seqs=1, num_layers=1, num_kv_heads=1, max_blocks_per_head=65535 * 128 + 1)
+    one = C.c_void_p(4096)
+    assert L.kvc_window_metric(C.byref(cfg), C.byref(st), one, C.c_void_p(lse), w, pool, 0, 0, 1, one, None) == B.KVC_ERR_UNSUPPORTED
+
+
 def test_binding_refuses_wrong_dtypes_and_strides():
     t = torch.zeros(4, 4)
     with pytest.raises(TypeError):
