@@ -140,3 +140,45 @@ def test_pool_of_sums_that_are_no_numbers(pool, b):
             want[j] = np.fmax.reduce(raw[n, o][max(0, j - pool // 2):min(P, j + pool // 2 + 1)])
         np.testing.assert_allclose(got[n, o], want, rtol=1e-6, atol=0)
     assert np.isnan(got[real]).any()
+
+
+def sampled(sess, q, r, w, d, pool, heads):
+    """A window over a cache too large for the host, looked at in some heads."""
+    sh = sess.shape
+    small, _ = W.gather_heads(sess.cache, heads)
+    st = oracle_state(small)
+    O.window_metric(st, q.reshape(sh.G, r, w, d)[heads].double().cpu().numpy().reshape(st.S, st.Lyr, st.Hk * r, w, d), w, pool)
+    sess.window_metric(q, w, pool)
+    torch.cuda.synchronize()
+    after, _ = W.gather_heads(sess.cache, heads)
+    for i in range(len(heads)):
+        n, o = O.slots_of(st, i)
+        if len(n):
+            close(after.metric.double().numpy()[n, o], st.metric[n, o], np.ones(len(n), dtype=bool))
+
+
+@pytest.mark.parametrize("b,rounds", [(1, 2), (2, 1)])
+def test_rounds_of_workgroups(b, rounds):
+    """Runs are bounded by the block ids a wavefront keeps: blocks of a token make more runs than the chip
+    holds wavefronts."""
+    from paper_2410_00161_amd.session import KvcSession
+    Lyr, Hk, r, w, d, L = 32, 8, 4, 8, 64, 3000
+    ctx = torch.full((Lyr * Hk,), L, dtype=torch.int32)
+    ctx[2::5] -= 1900
+    shape = W.Shape(1, Lyr, Hk, r, d, b, W.pool_size(ctx, b, 1.0, 5), L // b, "fp8")
+    units = shape.num_blocks * b // 64 + 4 * shape.G   # tiles of 64 tokens, one that is short and three for a start per head
+    assert -(-units // (2048 * (511 * b // 64 - 2))) == rounds
+    cache = W.make_cache(shape, ctx, 29, device="cuda:0", placement="fragmented")
+    sampled(KvcSession(cache), queries(shape, w).cuda(), r, w, d, 7, [0, 1, 2, 7, 100, 127, 128, 254, 255])
+
+
+@pytest.mark.parametrize("S", [16, 18])   # 4096 and 4608 heads
+def test_many_short_heads(S):
+    from paper_2410_00161_amd.session import KvcSession
+    Lyr, Hk, r, w, d, b = 32, 8, 2, 16, 64, 8
+    ctx = torch.randint(0, 90, (S * Lyr * Hk,), generator=torch.Generator().manual_seed(4)).int()
+    ctx[5::7] = 0
+    ctx[1000:1300] += 400
+    shape = W.Shape(S, Lyr, Hk, r, d, b, W.pool_size(ctx, b, 1.0, 5), 64, "bf16")
+    cache = W.make_cache(shape, ctx, 31, device="cuda:0", placement="fragmented")
+    sampled(KvcSession(cache), queries(shape, w).cuda(), r, w, d, 5, list(range(0, shape.G, 211)) + [shape.G - 1])
