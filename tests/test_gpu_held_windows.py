@@ -182,3 +182,17 @@ def test_many_short_heads(S):
     shape = W.Shape(S, Lyr, Hk, r, d, b, W.pool_size(ctx, b, 1.0, 5), 64, "bf16")
     cache = W.make_cache(shape, ctx, 31, device="cuda:0", placement="fragmented")
     sampled(KvcSession(cache), queries(shape, w).cuda(), r, w, d, 5, list(range(0, shape.G, 211)) + [shape.G - 1])
+
+
+@pytest.mark.parametrize("r,w,d,dtype,L", [
+    (8, 16, 64, "fp8", 4000), (8, 16, 64, "fp8", 4100),                               # 64 heads, tiles of 64 tokens: 4096 tiles
+    (8, 16, 64, "bf16", 2000), (8, 16, 64, "bf16", 2100), (8, 16, 64, "bf16", 12300),  # tiles of 32: 4096 and 24576 tiles
+])
+def test_sizes_around_the_lines(r, w, d, dtype, L):
+    """Enough tiles for the products to outweigh the reads, and enough again for the starts not to count."""
+    from paper_2410_00161_amd.session import KvcSession
+    ctx = torch.full((64,), L, dtype=torch.int32)
+    ctx[::9] -= 5
+    shape = W.Shape(1, 8, 8, r, d, 16, W.pool_size(ctx, 16, 1.0, 5), -(-L // 16), dtype)
+    cache = W.make_cache(shape, ctx, 37, device="cuda:0", placement="fragmented")
+    sampled(KvcSession(cache), queries(shape, w).cuda(), r, w, d, 7, [0, 9, 31, 63])
