@@ -225,8 +225,13 @@ __host__ __device__ inline size_t decode_lds_bytes(int T, int R, int HD, int b, 
 // A.Ts tokens) are latency-bound, a chain of dependent loads (item, block table, K and V) in
 // front of a few groups of arithmetic: they get a launch of their own with NW = 1, small LDS
 // and fewer registers, so that a CU holds many of those chains at once.
-template <int ESZ, int HD, int R, bool B16, int NW>
-__global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
+// Long chunks of 8-bit rows with four query heads in blocks shorter than 16 tokens: by itself the compiler takes
+// 170 registers, two below which a third workgroup fits a CU (4096 heads of up to 120 tokens 70 us, 56 with
+// it; of up to 1000 177 and 153).
+constexpr int decode_waves(int esz, int HD, int R, bool b16, int nw) { return esz == 1 && HD == 128 && R == 4 && !b16 && nw == 4 ? 3 : 1; }
+
+template <int ESZ, int HD, int R, bool B16, int NW, bool MF = decode_uses_mfma(ESZ, R, HD)>
+__global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) decode_chunk_kernel(DecodeArgs A) {
   constexpr int NT = NW * 64;
   constexpr int DEPTH = decode_depth(ESZ, R, HD, NW);
   constexpr int EPL = Row<ESZ>::EPL;
@@ -246,7 +251,6 @@ __global__ void __launch_bounds__(NW * 64) decode_chunk_kernel(DecodeArgs A) {
   // order through 4 KiB of LDS, cells XOR-swizzled so that neither side has a bank conflict.
   // Head h sits in operand row 4 (h % 4) + h / 4, which leaves lane 16 a + t with the logits of
   // token t against heads a and a + 4.
-  constexpr bool MF = decode_uses_mfma(ESZ, R, HD);
   constexpr int RW = MF ? 8 : R;      // output rows a wavefront's LDS region has room for
   constexpr int NVH = (R + 3) / 4;     // MF: logits per lane
   constexpr int OWN = MF ? NVH : PER;
@@ -1007,6 +1011,12 @@ template <int ESZ, int HD, int R>
 static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_short, hipStream_t s) {
   auto kern = (A.D.b % 16 == 0) ? decode_chunk_kernel<ESZ, HD, R, true, 4> : decode_chunk_kernel<ESZ, HD, R, false, 4>;
   auto kern_short = (A.D.b % 16 == 0) ? decode_chunk_kernel<ESZ, HD, R, true, 1> : decode_chunk_kernel<ESZ, HD, R, false, 1>;
+  bool mf_short = decode_uses_mfma(ESZ, R, HD);
+  if constexpr (ESZ == 1 && HD == 128 && R == 4)
+    // short items in blocks of one token keep the plain ALUs, where a fourth wavefront fits a SIMD (152 registers
+    // against 119; 16384 heads of up to 120 tokens 132 us and 117, of up to 300 243 and 229).  In blocks of two to
+    // eight they are slower by a tenth up to 30 tokens only, and faster by 1 to 9 % from 300 on.
+    if (A.D.b == 1) { kern_short = decode_chunk_kernel<ESZ, HD, R, false, 1, false>; mf_short = false; }
   ProfilePair* pp = claim_profile_pair();
   if (pp) KVC_HIP(hipEventRecord(pp->a0, s));
   {  // above the default cap the kernel must be told how much it may take (per instantiation and device)
@@ -1019,7 +1029,7 @@ static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_shor
   if (pp) { KVC_HIP(hipEventRecord(pp->a1, s)); KVC_HIP(hipEventRecord(pp->s0, s)); }
   if (A.short_class < 16) {
     hipLaunchKernelGGL(kern_short, dim3(grid_short), dim3(64),
-                       decode_lds_bytes(A.Ts, R, HD, A.D.b, 1, decode_uses_mfma(ESZ, R, HD)), s, A);
+                       decode_lds_bytes(A.Ts, R, HD, A.D.b, 1, mf_short), s, A);
     KVC_LAUNCH_CHECK();
   }
   if (pp) { KVC_HIP(hipEventRecord(pp->s1, s)); KVC_HIP(hipEventRecord(pp->b0, s)); }

@@ -49,3 +49,17 @@ def test_window_sums_leave_room_for_their_workgroups():
         assert k[".vgpr_count"] <= most, (name, k[".vgpr_count"])
         assert k[".vgpr_spill_count"] == 0, name
     assert seen == 32
+
+
+def test_short_block_decodes_leave_room_for_their_workgroups():
+    """8-bit rows, d = 128, four query heads, blocks shorter than 16 tokens: 168 registers let three workgroups
+    of four wavefronts share a CU; 128 let four one-wavefront items share a SIMD (blocks of one token)."""
+    seen = 0
+    for name, k in kernels().items():
+        m = re.search(r"decode_chunk_kernelILi1ELi128ELi4ELb0ELi(\d)ELb(\d)E", name)
+        if not m or m[1] + m[2] == "11":
+            continue
+        seen += 1
+        assert k[".vgpr_count"] <= (168 if m[1] == "4" else 128), (name, k[".vgpr_count"])
+        assert k[".vgpr_spill_count"] == 0, name
+    assert seen == 2
