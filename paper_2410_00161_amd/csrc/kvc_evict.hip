@@ -64,7 +64,10 @@ __global__ void __launch_bounds__(256) block_key_kernel(Dims D, int key_mode, co
 // Wavefronts that share a head's row in the passes over keys and metrics: so many that few heads make
 // `want` of them in all, none with less than one load of 64 blocks.  (80 heads of up to 1235 blocks, one
 // wavefront a head: keys 19.9 us, the first digit's histogram, eight heads to a wavefront then, 50.7; shared
-// 4.8 and 7.6.  Twice as many heads as wavefronts wanted, or more: one share, as before.)
+// 4.8 and 7.6.  From more than want / 2 heads on, one share.)
+// Keys: above some 2500 wavefronts the lines of one, 64 blocks of 64 bytes, push those of the others out of the
+// caches before they are read to the end: 1024 heads of 512 blocks 19.2 us by one wavefront a head, 19.1 by two,
+// 25.8 by four, 2048 heads 31.8 and 49.2 by two; 512 heads 18.2 by one, 12.3 by five, 14.3 by eight.
 static inline unsigned row_shares(const Dims& D, int want) {
   return (unsigned)std::max(1, std::min(want / std::max(D.G, 1), (D.maxb + 63) / 64));
 }
@@ -737,7 +740,7 @@ int kvc_metric_reduce(const kvc_config* cfg, const kvc_state* st, float* block_k
   if (key_mode != KVC_KEY_SUM && key_mode != KVC_KEY_MAX) return KVC_ERR_ARG;
   (void)ws;
   Dims D = dims_of(cfg);
-  hipLaunchKernelGGL(block_key_kernel, dim3((D.G + 3) / 4, row_shares(D, 4096)), dim3(256), 0, (hipStream_t)stream, D, key_mode,
+  hipLaunchKernelGGL(block_key_kernel, dim3((D.G + 3) / 4, row_shares(D, 2560)), dim3(256), 0, (hipStream_t)stream, D, key_mode,
                      st->metric, st->block_table, st->ctx_len, block_key);
   KVC_LAUNCH_CHECK();
   return KVC_OK;
