@@ -515,10 +515,11 @@ __global__ void __launch_bounds__(1024) rank_check_small_kernel(Dims D, const in
 // uses the cells of its own blocks: hole k at logical cell k, mover k at logical cell C-1-k.
 // NTH threads: 256 when there are many head instances, 1024 when there are few (a prompt's
 // worth of long heads), so that a head's passes over its metrics run four times as wide.
-// (Registers, scalar ones too, for two workgroups of 1024 per CU: 1024 heads of 8192 tokens 161 -> 143 us a
-// round, with one 158.)
-template <int NTH>
-__global__ void __launch_bounds__(NTH, 8) rank_compact_kernel(Dims D, char* __restrict__ kc, char* __restrict__ vc,
+// WAVES: 8 bounds the registers, scalar ones too, for two workgroups of 1024 per CU (1024 heads of 8192 tokens
+// 161 -> 143 us a round, with one 158); up to 256 heads, a workgroup per CU, need no such bound and lose by it
+// (8 to 256 heads of 200 to 700 tokens 16.5 us, 17.5 with it).
+template <int NTH, int WAVES = 8>
+__global__ void __launch_bounds__(NTH, WAVES) rank_compact_kernel(Dims D, char* __restrict__ kc, char* __restrict__ vc,
                                                            float* __restrict__ metric,
                                                            int32_t* __restrict__ pos,
                                                            int32_t* __restrict__ table,
@@ -877,9 +878,10 @@ int kvc_compact_rank(const kvc_config* cfg, const kvc_state* st, const int32_t* 
     const int slice = (int)std::min((size_t)1024, std::max((size_t)64, (most_moves * D.G / 8192 + 31) / 32 * 32));
     const bool sliced = D.G <= 512 && head_tokens >= 2048 && (most_moves + slice - 1) / slice <= 65535;
     static LdsLimit limit;
-    const int rc2 = limit.need((size_t)36864 * 4, rank_compact_kernel<1024>);
+    const int rc2 = limit.need((size_t)36864 * 4, rank_compact_kernel<1024, 4>, rank_compact_kernel<1024>);
     if (rc2 != KVC_OK) return rc2;
-    hipLaunchKernelGGL(rank_compact_kernel<1024>, dim3(D.G), dim3(1024), (size_t)lds_tokens * 4, s, D, (char*)st->k_cache,
+    const auto lists = D.G <= 256 ? rank_compact_kernel<1024, 4> : rank_compact_kernel<1024>;
+    hipLaunchKernelGGL(lists, dim3(D.G), dim3(1024), (size_t)lds_tokens * 4, s, D, (char*)st->k_cache,
                        (char*)st->v_cache, st->metric, st->pos, st->block_table, st->ctx_len, st->free_map, evict_rows,
                        (int32_t*)W.stash, W.header, lds_tokens, sliced ? W.off_a : nullptr, W.off_b);
     if (sliced) {
