@@ -794,9 +794,10 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
   for (int pass = 0; pass < 4; ++pass) {
     // first pass (the exponent byte): nearly every head lands on the same digit of its segment's
     // histogram, and four heads per workgroup (a quarter of the adds) measured fastest
-    // (up to 1024 heads, whose adds are few, a wavefront each: 72 heads of 12421 tokens 324 -> 254 us a
-    // round, 1024 of 8192 183 -> 163)
-    const int hpw = pass == 0 && D.G > 1024 ? 4 : 1;
+    // (up to 1024 heads in segments of at most 256, whose adds are few, a wavefront each: 72 heads of 12421 tokens
+    // 324 -> 254 us a round, 1024 of 8192 183 -> 163.  In longer ones they meet on one word: one segment of 1024
+    // heads of 700 tokens 89 us, 68 with two heads a wavefront, 61 with four; of 8192 tokens 214, 205, 226)
+    const int hpw = pass > 0 ? 1 : D.G > 1024 ? 4 : D.G > 256 * nseg ? 2 : 1;
     const SegPicks picks = {fused && pass > 0 ? hist_of(pass - 1) : nullptr, budget, nseg};
     if ((size_t)D.maxb * D.b <= kRankWaveTokens)
       hipLaunchKernelGGL(rank_hist_wave_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw)), dim3(256), 0, s, D, pass,
@@ -873,8 +874,11 @@ int kvc_compact_rank(const kvc_config* cfg, const kvc_state* st, const int32_t* 
     const int lds_tokens = (int)(head_tokens < 36864 ? head_tokens : 36864);
     // (holes lie below the new length and movers at or above it: at most half the row's tokens move)
     const size_t most_moves = head_tokens / 2 + 1;
-    // The moves apart, in slices that make about 8192 workgroups, up to 512 heads (1024 of 1024 tokens,
-    // a tenth of their rows: 180 us in the heads' own workgroups, 193 apart; shorter rows level).
+    // The moves apart, in slices that make about 8192 workgroups, up to 512 heads, in rows of 2048 tokens or more.
+    // They cost a launch, which shows where little moves, and gain where much does: in the heads' own workgroups
+    // and apart, 128 heads of 2100 tokens that lose 2 % of their blocks 21 and 24 us, 30 % 51 and 39; 512 heads
+    // of 4096 tokens on average, up to 16384, 61 and 77, 283 and 226.  With 640 heads, where two workgroups
+    // share a CU, 63 and 80, 308 and 272 (16384 tokens each 131 and 147, 773 and 696; 2100 each 34 and 39, 121 and 117).
     const int slice = (int)std::min((size_t)1024, std::max((size_t)64, (most_moves * D.G / 8192 + 31) / 32 * 32));
     const bool sliced = D.G <= 512 && head_tokens >= 2048 && (most_moves + slice - 1) / slice <= 65535;
     static LdsLimit limit;
