@@ -857,13 +857,16 @@ int kvc_compact(const kvc_config* cfg, const kvc_state* st, const uint8_t* evict
   // 120 us, 4096 225 -> 211; 104 heads of 480, 6 KB of moves each, 68 both ways), and where tables are
   // sized for more than 65536 tokens a head, which no longer fit the LDS several times over.  Else the empty
   // workgroups of the slice grid cost more than the slices gain (65536 heads with tables for 32768
-  // tokens: 0.70 ms per head-sized workgroup against 1.36 ms sliced; 16384 heads level).
+  // tokens: 0.70 ms per head-sized workgroup against 1.36 ms sliced; 16384 heads level).  A call that moves
+  // little pays a microsecond or two for it (128 heads of 1000 tokens that lose 2 % of their blocks 20.6 us in
+  // one workgroup each, 21.7 sliced; that lose 30 % 44.9 and 36.6), which many short heads never win back (4096
+  // of 1000 tokens 44.6 and 49.6, 248 and 245; 3072 of 1500 level).
   constexpr size_t kSlicedWgs = 8192;
   const size_t row_tokens = (size_t)D.maxb * D.b;
   const int slice = row_tokens > 65536 ? kSlice
                                        : (int)std::min((size_t)kSlice, std::max((size_t)256, (row_tokens * D.G / kSlicedWgs + 63) / 64 * 64));
   const size_t slices = (row_tokens + slice - 1) / slice;
-  const bool few = D.G <= 4096 && row_tokens >= 512 && slices * D.G <= 4 * kSlicedWgs;
+  const bool few = D.G <= 4096 && row_tokens >= (D.G > 2048 ? 1536 : 512) && slices * D.G <= 4 * kSlicedWgs;
   if ((row_tokens > 65536 || few) && slices <= 65535) {
     hipLaunchKernelGGL(compact_move_sliced_kernel, dim3(D.G, (unsigned)slices), dim3(256), 0, s, D, kcp, vcp, st->metric,
                        st->pos, st->block_table, st->ctx_len, st->free_map, evict_count, W.flag_scan, W.off_a, W.header, slice);
