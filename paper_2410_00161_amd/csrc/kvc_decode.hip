@@ -259,8 +259,8 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   extern __shared__ __align__(16) char smem_raw[];
   DecodeItem it;
   int Tc;                                // tokens the work list was cut at (<= A.T)
-  const int T = NW > 1 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
-  if (NW > 1 && A.self_list) {
+  const int T = NW == 4 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
+  if (NW == 4 && A.self_list) {
     SelfList sl;
     const bool found = self_item(A, blockIdx.x, false, sl);
     // heads without a KV (lane = head, the same in every wavefront): the first workgroup writes their zero rows
@@ -277,8 +277,8 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     const int short_items = A.header[HW_SHORT_ITEMS];
     const bool placed = A.plan && A.plan_stride == 0;
     const int base = placed ? A.header[HW_PLAN_BASE] : 0;
-    if (NW > 1 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
-    if (NW > 1 && A.plan && (int)blockIdx.x < A.gsel) {
+    if (NW == 4 && blockIdx.x == 0 && tid < HW_DEC_END - HW_DEC_BINS) A.header[HW_DEC_BINS + tid] = 0;  // work-list block back to zero
+    if (NW == 4 && A.plan && (int)blockIdx.x < A.gsel) {
       // a list kept from kvc_decode_plan was made without the output at hand: the zero rows of a
       // head that holds no KV are written here, by the workgroup with the head's index
       const int ge = sel_to_g(A.D, A.l0, A.nl, blockIdx.x);
@@ -289,13 +289,13 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     // (A long item's record is where the workgroup's index says: in a small call asked for together with the
     // header words.  In a large one the workgroups beyond the last item pay more for it than the others
     // gain, 64 x 8192 tokens at 8x 1451 us against 1445.)
-    const bool early = NW > 1 && A.adapt_T && !placed;
+    const bool early = NW == 4 && A.adapt_T && !placed;
     if (early && (int)blockIdx.x < A.cap) it = A.items[blockIdx.x];
     if (total_items > A.cap || short_items < 0 || short_items > total_items) return;
     const int n_long = total_items - short_items;
-    if ((int)blockIdx.x >= (NW > 1 ? n_long : short_items)) return;
+    if ((int)blockIdx.x >= (NW == 4 ? n_long : short_items)) return;
     if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
-    if (!early) it = A.items[base + (NW > 1 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
+    if (!early) it = A.items[base + (NW == 4 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
   }
   const int g = it.g, t0 = it.t0, n_tok = it.n_tok, nch = it.nch;
   if ((unsigned)g >= (unsigned)A.D.G || n_tok <= 0 || n_tok > T || t0 < 0 || nch <= 0 || Tc < 64 || Tc > A.T ||
