@@ -245,12 +245,13 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   constexpr size_t ROWB = (size_t)HD * ESZ;
   constexpr size_t QROWB = (size_t)HD * Row<ESZ>::QSZ;
   static_assert(LPT >= 4 && LPT <= 32 && (16 % TPI) == 0, "row geometry");
-  // Q K^T of a 16-token group on the matrix cores (v_mfma_f32_16x16x32_bf16: rows = query heads,
-  // columns = tokens, four steps of 32 dimensions).  K still arrives by contiguous 1 KiB loads
-  // (a load shaped like the operand is 12 % slower); a wavefront turns its tile into operand
-  // order through 4 KiB of LDS, cells XOR-swizzled so that neither side has a bank conflict.
-  // Head h sits in operand row 4 (h % 4) + h / 4, which leaves lane 16 a + t with the logits of
-  // token t against heads a and a + 4.
+  // Q K^T of a 16-token group on the matrix cores (rows = query heads, columns = tokens): d = 128 in blocks of 16
+  // tokens or more by v_mfma_f32_16x16x32_bf16, four steps of 32 dimensions in one chain; the other shapes by
+  // v_mfma_f32_16x16x16_bf16, products of 16 dimensions added up in pairs.  K still arrives by contiguous loads
+  // (a load shaped like the operand is 12 % slower); a wavefront turns its tile into operand order through 32 d
+  // bytes of LDS (16 tokens of d 16-bit elements), cells XOR-swizzled so that neither side has a bank conflict.
+  // Head h sits in operand row 4 (h % 4) + h / 4, which leaves lane 16 a + t with the logits of token t against
+  // head a, and with eight heads a + 4.
   constexpr int RW = MF ? 8 : R;      // output rows a wavefront's LDS region has room for
   constexpr int NVH = (R + 3) / 4;     // MF: logits per lane
   constexpr int OWN = MF ? NVH : PER;
@@ -304,9 +305,10 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   const int C_now = A.plan ? A.ctx[g] : 0;   // (looked at below, behind the other loads)
   const int b = A.D.b, lb = A.log2b;
 
-  uint4* s_kt = (uint4*)smem_raw;                      // MF: [waves][16 tokens][16 cells of 16 bytes]
-  // [waves][R][HD]; on the matrix-core path a wavefront's 4 KiB of it are its operand tile until
-  // its main loop ends (R * HD * 4 = 16 * HD * 2 there, so no wavefront touches another's tile)
+  uint4* s_kt = (uint4*)smem_raw;                      // MF: [waves][16 tokens][HD / 8 cells of 16 bytes]
+  // [waves][RW][HD]; on the matrix-core path, where eight rows have room (RW * HD * 4 = 16 * HD * 2 bytes, also
+  // with four heads), a wavefront's part of it is its operand tile until its main loop ends, so that no
+  // wavefront touches another's tile
   float* s_acc = (float*)smem_raw;
   constexpr int PARTS = HD == 128 && B16 ? 2 : 3;   // MF: parts of 16 bits of a probability (see P V)
   constexpr int PROWS = R == 4 && PARTS == 3 ? 4 : 8;   // MF: operand rows between a head's parts

@@ -196,3 +196,86 @@ def test_sizes_around_the_lines(r, w, d, dtype, L):
     shape = W.Shape(1, 8, 8, r, d, 16, W.pool_size(ctx, 16, 1.0, 5), -(-L // 16), dtype)
     cache = W.make_cache(shape, ctx, 37, device="cuda:0", placement="fragmented")
     sampled(KvcSession(cache), queries(shape, w).cuda(), r, w, d, 7, [0, 9, 31, 63])
+
+
+def with_growing_keys(cache):
+    """Keys grow along the sequence and shrink again, over 2^8.5, in one head later than in the next: the
+    references of a row move many times, and runs of one head end with very different ones."""
+    shape = cache.shape
+    b, d = shape.block_size, shape.head_dim
+    rows, table = cache.k_cache.view(-1, d), cache.block_table.reshape(shape.G, -1).long()
+    for g, C in enumerate(cache.ctx_len.reshape(-1).tolist()):
+        j = torch.arange(C, device=rows.device)
+        top = 200 + 311 * (g % 5)
+        grow = torch.exp2(torch.where(j < top, 4.5 - (top - j) / 60.0, 4.5 - (j - top) / 95.0).clamp(-4.0, 4.5))
+        slots = table[g, j // b] * b + j % b
+        if shape.kv_dtype == "fp8":   # 8-bit floats are moved as bytes
+            old = rows.view(torch.uint8)[slots].view(torch.float8_e4m3fn).float()
+            rows.view(torch.uint8)[slots] = (old * grow.view(-1, 1)).to(rows.dtype).view(torch.uint8)
+        else:
+            rows[slots] = (rows[slots].float() * grow.view(-1, 1)).to(rows.dtype)
+
+
+def in_64_bits(st, g, q, w):
+    """Metric increments [C] of head g and its rows' largest log-sum-exp, from plain matrix products."""
+    n, o = O.slots_of(st, g)
+    C, r = len(n), st.r
+    x = np.einsum("hid,jd->hij", q.reshape(st.G, r, w, -1)[g], st.k_cache[n, o]) / np.sqrt(st.d)
+    x[:, np.arange(C)[None, :] > (C - w + np.arange(w))[:, None]] = -np.inf
+    top = x.max(2, keepdims=True)
+    with np.errstate(all="ignore"):
+        lse = top + np.log(np.exp(x - top).sum(2, keepdims=True))
+        p = np.where(np.isfinite(lse), np.exp(x - lse), 0.0)
+    return n, o, (p * p).sum((0, 1)), np.abs(lse[np.isfinite(lse)]).max(initial=0.0)
+
+
+@pytest.mark.parametrize("r,w,d,b,dtype", [
+    (4, 8, 128, 16, "bf16"), (4, 16, 128, 8, "bf16"), (2, 32, 128, 16, "fp8"), (1, 30, 128, 2, "fp8"),
+    (4, 8, 64, 16, "bf16"), (8, 8, 64, 32, "fp8"), (8, 16, 64, 16, "bf16"), (4, 30, 64, 4, "bf16"), (8, 16, 64, 16, "fp8"),
+])
+def test_references_follow_the_logits(r, w, d, b, dtype):
+    from paper_2410_00161_amd.session import KvcSession
+    lengths = [2500, 40, 1300, 700, 0, 1501, 129, 900, 2049, 16, 300, 1800, 64, 1000, 513, 2200]
+    shape, cache, real = make(2, 2, 4, r, d, b, lengths, dtype, 0)
+    with_growing_keys(cache)
+    st = oracle_state(cache)
+    q = queries(shape, w)
+    sess = KvcSession(cache)
+    sess.window_metric(q.to(sess.device), w, 1)
+    m = sess.cache.metric.double().cpu().numpy()
+    largest = 0.0
+    for g, C in enumerate(lengths):
+        if C == 0:
+            continue
+        n, o, want, lse = in_64_bits(st, g, q.double().numpy(), w)
+        # a row's constant and an exp's argument are each rounded to half a last bit at the size of the largest
+        # logits, twice where a sum has been carried over to a new reference; the square doubles it
+        bound = 2 * 2 * 0.6931 * 1.4427 * max(lse, 1.0) * 2.0 ** -23
+        assert np.linalg.norm(m[n, o] - want) <= bound * np.linalg.norm(want), g
+        largest = max(largest, 1.4427 * lse)
+    assert largest > 60
+
+
+@pytest.mark.parametrize("Lyr,r,w,dtype", [(36, 4, 32, "bf16"), (68, 8, 16, "fp8")])
+def test_references_follow_the_logits_of_128_rows(Lyr, r, w, dtype):
+    """128 rows of d = 128 without the log-sum-exp: at least 65536 tiles; sampled heads."""
+    from paper_2410_00161_amd.session import KvcSession
+    L = 4200
+    ctx = torch.full((Lyr * 8,), L, dtype=torch.int32)
+    ctx[1::3] -= 777
+    shape = W.Shape(1, Lyr, 8, r, 128, 16, W.pool_size(ctx, 16, 1.0, 5), -(-L // 16) + 1, dtype)
+    tile = 16 if dtype == "bf16" else 32
+    assert min(shape.G * shape.max_blocks_per_head, shape.num_blocks) * 16 // tile + shape.G >= 65536 - 1
+    cache = W.make_cache(shape, ctx, 23, device="cuda:0", placement="fragmented", init_metric="prefill")
+    with_growing_keys(cache)
+    q = queries(shape, w).cuda()
+    sess = KvcSession(cache)
+    sess.window_metric(q, w, 1)
+    heads = [0, 1, 2, 3, 4, shape.G // 2, shape.G - 1]
+    small, _ = W.gather_heads(sess.cache, heads)
+    st = oracle_state(small)
+    q_small = q.reshape(shape.G, r, w, 128)[heads].double().cpu().numpy()
+    for i in range(len(heads)):
+        n, o, want, lse = in_64_bits(st, i, q_small, w)
+        bound = 2 * 2 * 0.6931 * 1.4427 * lse * 2.0 ** -23
+        assert lse > 40 and np.linalg.norm(small.metric.double().numpy()[n, o] - want) <= bound * np.linalg.norm(want), heads[i]

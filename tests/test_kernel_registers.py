@@ -63,3 +63,19 @@ def test_short_block_decodes_leave_room_for_their_workgroups():
         assert k[".vgpr_count"] <= (168 if m[1] == "4" else 128), (name, k[".vgpr_count"])
         assert k[".vgpr_spill_count"] == 0, name
     assert seen == 2
+
+
+def test_held_windows_leave_room_for_their_workgroups():
+    """256 registers let two workgroups of four wavefronts share a CU, as many as the LDS holds.  With 128 rows
+    of d = 128 held in 128 of them the statistics spill a few (the constants of the groups that are done over),
+    the sums of 16-bit keys one."""
+    seen = 0
+    for name, k in kernels().items():
+        m = re.search(r"window_held_(stats|sum)_kernelILi(\d)ELi(\d+)ELi(\d)E", name)
+        if not m:
+            continue
+        seen += 1
+        spills = {("stats", "2"): 24, ("stats", "1"): 8, ("sum", "2"): 1}.get(m.groups()[:2], 0) if m[3] + m[4] == "1288" else 0
+        assert k[".vgpr_count"] <= 256, (name, k[".vgpr_count"])
+        assert k[".vgpr_spill_count"] <= spills, (name, k[".vgpr_spill_count"])
+    assert seen == 36
