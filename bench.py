@@ -350,9 +350,9 @@ def run_decode_config(spec, dev, keep_session=False):
 
     # Between two compression rounds every head grows by exactly one KV per step, so the
     # lengths each decode saw follow from the snapshot taken at the start of the period.
-    # A head of C tokens is cut into chunks of chunk_T; a last chunk (or whole head) of at most
-    # short_T tokens runs in the short-item launch, everything else in the long-item launch.  A
-    # head of one chunk gets its metric from the launch that streams it, others from the combine.
+    # A head of C tokens is cut into chunks of chunk_T; heads of at most short_T tokens run in the
+    # short-item launch, everything else in the long-item launch.  A head gets its metric from the
+    # launch that streams it.
     chunk_T = B.kvc_get_decode_chunk(sess.cfg)
     short_T = B.kvc_get_decode_short(sess.cfg)
     kv_per_step, long_kv, long_single, short_single = [], [], [], []
@@ -361,10 +361,9 @@ def run_decode_config(spec, dev, keep_session=False):
         s0 = max(k for k in keys if k <= i)
         c = snaps[s0].to(torch.int64) + (i - s0)
         if chunk_T > 0:
-            rem = c % chunk_T
-            in_short = rem * ((rem > 0) & (rem <= short_T))
-            long_single.append(float((c * ((c <= chunk_T) & (c > short_T))).sum()))
-            short_single.append(float((c * (c <= min(short_T, chunk_T))).sum()))
+            in_short = c * (c <= short_T)
+            long_single.append(float((c - in_short).sum()))
+            short_single.append(float(in_short.sum()))
         else:               # fallback kernel: one launch, every head whole
             in_short = torch.zeros_like(c)
             long_single.append(float(c.sum()))
@@ -378,7 +377,7 @@ def run_decode_config(spec, dev, keep_session=False):
     ms_step = ms_total / steps
 
     # dominant kernel: decode_chunk_kernel over the long items (four wavefronts per item): streams
-    # their K and V once, metric RMW for heads of one chunk
+    # their K and V once, and their metric read and written
     per_kv = 2 * shape.head_dim * shape.kv_bytes + 4.0 / shape.block_size
     chunk_alg = long_kv * per_kv + 8.0 * long_single
     short_alg = (kv_per_step - long_kv) * per_kv + 8.0 * short_single

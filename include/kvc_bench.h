@@ -18,9 +18,9 @@ extern "C" {
 #endif
 
 /* kvc_profile_begin(n) makes the next n calls of kvc_paged_decode record HIP event pairs on
- * their stream around each of its three launches: the chunk kernel over the long items (it
- * streams nearly all of K and V), the same kernel over the short items, and the combine kernel;
- * n = 0 switches recording off and releases the events.  At most 4096 calls.              */
+ * their stream around each of its launches: the chunk kernel over the long items (it streams
+ * nearly all of K and V) and the same kernel over the short items; the third pair stands for a launch that
+ * combined the chunks of a head, which they now do themselves (nothing is between its events).  n = 0 switches recording off and releases the events.  At most 4096 calls.              */
 int kvc_profile_begin(int n);
 
 /* Pauses (0) or resumes (non-zero) the recording without releasing anything, so that a

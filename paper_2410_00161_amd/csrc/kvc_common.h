@@ -32,11 +32,14 @@ enum HeaderWord {
   HW_PLAN_BASE = 11,   // a kept work list's first record
   // decode work-list block: item counts per size class, per-class cursors, cursor of the
   // per-chunk partial results.  All zero between calls (the chunk kernel clears it).
-  HW_DEC_BINS = 32,    // [16]
-  HW_DEC_CUR = 48,     // [16]
-  HW_DEC_PCUR = 64,    // [1]
-  HW_DEC_PTOT = 65,    // [1] partial-result slots wanted, counted in pass 1
-  HW_DEC_END = 66,
+  HW_DEC_BINS = 12,    // [16]
+  HW_DEC_CUR = 28,     // [16]
+  HW_DEC_PCUR = 44,    // [1]
+  HW_DEC_PTOT = 45,    // [1] partial-result slots wanted, counted in pass 1
+  HW_DEC_END = 46,
+  // meeting words of the heads of a decode that keeps no work list (chunks started and arrived).
+  // Zero between calls.
+  HW_MEET = 64,        // [64]
   HW_WORDS = 128
 };
 
@@ -68,10 +71,10 @@ struct Workspace {
   int32_t* off_b;      // [G + 1]
   int32_t* held;       // [G]      blocks held per head instance
   int32_t* items;      // [max_items][8]      decode work items (see DecodeItem)
-  int32_t* slot_item;  // [max_items]         work item of every partial-result slot in use
+  int32_t* slot_word;  // [max_items]         a word per partial-result slot: where a split head's chunks meet
   float*   part_ml;    // [max_items][r][2]   chunk max and sum per query head
   float*   part_acc;   // [max_items][r][d]   chunk un-normalised output
-  float*   stash;      // [N*b][r]            chunk-relative exp of every logit
+  float*   stash;      // [N*b][r]            chunk-relative exp of every logit of a chunk that left its head (see kMeetBits)
   int32_t* seg_hist;   // [S][256]            radix histograms per segment; in an append, what its workgroups counted ([kAppendWgs][3])
   int32_t* seg_state;  // [S][8]              prefix, remaining, ties wanted, ...
   int32_t* flag_scan;  // [G][maxb]           per-head prefix count of flagged blocks
@@ -99,7 +102,7 @@ inline Workspace carve(const Dims& D, void* base) {
   w.held = (int32_t*)take((size_t)D.G * 4);
   size_t items = max_items_of(D);
   w.items = (int32_t*)take(items * 32);
-  w.slot_item = (int32_t*)take(items * 4);
+  w.slot_word = (int32_t*)take(items * 4);
   w.part_ml = (float*)take(items * D.r * 2 * 4);
   w.part_acc = (float*)take(items * D.r * D.d * 4);
   w.stash = (float*)take((size_t)D.N * D.b * D.r * 4);
@@ -161,6 +164,12 @@ __device__ __forceinline__ void publish_i32(int32_t* p, int32_t v) {
 }
 __device__ __forceinline__ int32_t published_i32(const int32_t* p) {
   return __hip_atomic_load(const_cast<int32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_u64(void* p, uint64_t v) {   // (8-byte aligned)
+  __hip_atomic_store((uint64_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t published_u64(const void* p) {
+  return __hip_atomic_load((uint64_t*)const_cast<void*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void publish_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -9,9 +9,9 @@
 // into chunks of T tokens; one workgroup owns one chunk, keeps the chunk's r x T
 // logits in LDS between its pass over K and its pass over V, and therefore
 // reads every key and value exactly once.  A head that fits one chunk is
-// finished inside that workgroup (output and metric written directly).  A longer
-// head leaves per-chunk (max, sum, un-normalised output) and the chunk-relative
-// exp of every logit in the workspace; a second, light kernel combines them.
+// finished inside that workgroup (output and metric written directly).  The chunks of
+// a longer head leave their (max, sum, un-normalised output) in the workspace, wait for one
+// another and finish the head together (see kMeetBits).
 //
 // Data movement.  A KV row (d elements) is 256 bytes at d = 128 / bf16; a lane
 // reads 16 bytes, so LPT = row_bytes / 16 lanes cover one token and a wavefront
@@ -138,41 +138,50 @@ template <> struct Row<1> {  // OCP e4m3: 8 elements in 8 bytes, facing 8 bf16 q
   }
 };
 
-// A head of more than one chunk leaves, for every KV and query head, e = exp2(logit - chunk
-// max) in [0, 1] for the combine kernel.  It is kept as 16-bit fixed point: the error of e, and
-// so of the probability it turns into (p = e * weight, weight <= 1), is at most 2^-17, which
-// moves a metric increment (sum over r heads of p^2 or p) by at most r * 2^-16.
+// The exp of every logit against its group's running max, e in [0, 1], is kept in LDS as 16-bit fixed
+// point: the error of e, and so of the probability it turns into (p = e * weight, weight <= 1), is at
+// most 2^-17, which moves a metric increment (sum over r heads of p^2 or p) by at most r * 2^-16.
 __device__ __forceinline__ uint32_t q16(float e) { return (uint32_t)(e * 65535.0f + 0.5f); }
-__device__ __forceinline__ float unq16(uint32_t q) { return (float)q * (1.0f / 65535.0f); }
 
+// What a chunk that does not wait for the rest of its head (see kMeetBits) leaves of a KV: its exps
+// against the chunk's max, as the chunk itself would go on with them, so that the metric has the same bits
+// whoever adds it.
 template <int R>
-__device__ __forceinline__ void stash_store(float* stash, size_t slot, const float* e) {
-  uint16_t* base = (uint16_t*)stash + slot * R;
-  if constexpr (R == 1) {
-    *base = (uint16_t)q16(e[0]);
-  } else {
-    uint32_t wds[R / 2];
+__device__ __forceinline__ void exps_publish(float* stash, size_t slot, const float (&e)[R]) {
+  if constexpr (R == 1) publish_i32((int32_t*)stash + slot, __float_as_int(e[0]));
+  else
 #pragma unroll
-    for (int i = 0; i < R / 2; ++i) wds[i] = q16(e[2 * i]) | (q16(e[2 * i + 1]) << 16);
-    if constexpr (R == 2) __builtin_nontemporal_store(wds[0], (uint32_t*)base);
-    else if constexpr (R == 4) { typedef unsigned int u2 __attribute__((ext_vector_type(2))); u2 t = {wds[0], wds[1]}; __builtin_nontemporal_store(t, (u2*)base); }
-    else { typedef unsigned int u4 __attribute__((ext_vector_type(4))); u4 t = {wds[0], wds[1], wds[2], wds[3]}; __builtin_nontemporal_store(t, (u4*)base); }
-  }
+    for (int i = 0; i < R; i += 2) publish_u64(stash + slot * R + i, (uint64_t)__float_as_uint(e[i]) | (uint64_t)__float_as_uint(e[i + 1]) << 32);
 }
 template <int R>
-__device__ __forceinline__ void stash_load(const float* stash, size_t slot, float* e) {
-  const uint16_t* base = (const uint16_t*)stash + slot * R;
-  if constexpr (R == 1) {
-    e[0] = unq16(*base);
-  } else {
-    uint32_t wds[R / 2];
-    if constexpr (R == 2) wds[0] = __builtin_nontemporal_load((const uint32_t*)base);
-    else if constexpr (R == 4) { typedef unsigned int u2 __attribute__((ext_vector_type(2))); const u2 t = __builtin_nontemporal_load((const u2*)base); wds[0] = t.x; wds[1] = t.y; }
-    else { const uint4 t = load_stream16(base); wds[0] = t.x; wds[1] = t.y; wds[2] = t.z; wds[3] = t.w; }
+__device__ __forceinline__ void exps_published(const float* stash, size_t slot, float (&e)[R]) {
+  if constexpr (R == 1) e[0] = __int_as_float(published_i32((const int32_t*)stash + slot));
+  else
 #pragma unroll
-    for (int i = 0; i < R / 2; ++i) { e[2 * i] = unq16(wds[i] & 0xffffu); e[2 * i + 1] = unq16(wds[i] >> 16); }
-  }
+    for (int i = 0; i < R; i += 2) {
+      const uint64_t t = published_u64(stash + slot * R + i);
+      e[i] = __uint_as_float((uint32_t)t); e[i + 1] = __uint_as_float((uint32_t)(t >> 32));
+    }
 }
+
+// The chunks of a head of more than one finish it themselves.  Each leaves its max, sum and
+// un-normalised output and then needs the head's max and sum, for the metric of its own tokens (their exps are
+// still in its LDS) and for its share of the head's output.  It counts itself as started when it begins and
+// as arrived when its part is out, and waits for the others only if all of them have started by
+// then: a chunk that has started runs, and arrives without waiting for anybody, so every wait ends.  A
+// chunk that finds some not started leaves its exps and ends; those that waited (one at least, the one
+// that started last) share out what is left of it.  The last one to arrive sets the counts back and
+// calls the others, each at a word of its own: a hundred of them looking at the word that they add to keep
+// the adds waiting, ~10 ns each (one layer of 8 ragged heads, up to 107 chunks: 22.4 us a layer so, 18.2 with
+// words of their own, 19.1 as a launch for the chunks and one that combined them).
+// Before, chunks left 2 r bytes of exps per KV and a second launch combined them: 4 x 131072 tokens at 8x, r = 8
+// 4015 -> 3490 us (the exps were 16 of 528 bytes a KV; what is written costs this chip ten times what is
+// read does), 16 sequences layer by layer 1174 -> 1080, a step of two sequences of 512 tokens 25 -> 21.7.
+// Started and arrived are halves of one header word per head in a call without a work list, else two
+// words where the list keeps the head's partial-result slots.
+constexpr int kMeetBits = 16, kMeetMost = (1 << kMeetBits) - 1;   // of a half
+constexpr int kMeetLooks = 1 << 19;   // for the call, ~0.5 us each: a workspace never reset, or in use by two calls at once
+constexpr int kMeetStarts = 6;        // for the last chunk to start, ~1 us each: one that does soon is worth the wait
 
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / 64;
@@ -261,9 +270,11 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   DecodeItem it;
   int Tc;                                // tokens the work list was cut at (<= A.T)
   const int T = NW == 4 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
+  int32_t* slot_words = A.slot_word;     // of this list
+  int rec = 0;                           // record of this item
   if (NW == 4 && A.self_list) {
     SelfList sl;
-    const bool found = self_item(A, blockIdx.x, false, sl);
+    const bool found = self_item(A, blockIdx.x, sl);
     // heads without a KV (lane = head, the same in every wavefront): the first workgroup writes their zero rows
     if (blockIdx.x == 0)
       for (unsigned long long empty = __ballot(sl.g >= 0 && sl.C == 0); empty; empty &= empty - 1) {
@@ -273,6 +284,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     if (!found) return;
     it = sl.it;
     Tc = sl.T;
+    rec = blockIdx.x;   // (no list: the records' room serves the heads that meet)
   } else {
     const int total_items = A.header[HW_TOTAL_ITEMS];
     const int short_items = A.header[HW_SHORT_ITEMS];
@@ -296,9 +308,17 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     const int n_long = total_items - short_items;
     if ((int)blockIdx.x >= (NW == 4 ? n_long : short_items)) return;
     if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
+    slot_words += base;
+    rec = base + blockIdx.x;
     if (!early) it = A.items[base + (NW == 4 ? blockIdx.x : n_long + blockIdx.x)];   // the short items end the list
   }
-  const int g = it.g, t0 = it.t0, n_tok = it.n_tok, nch = it.nch;
+  // (the same in every lane: in scalar registers)
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  const int g = uniform(it.g), t0 = uniform(it.t0), n_tok = uniform(it.n_tok), nch = uniform(it.nch);
+  it.pbase = uniform(it.pbase);
+  it.pad[0] = uniform(it.pad[0]);
+  it.pad[1] = uniform(it.pad[1]);
+  Tc = uniform(Tc);
   if ((unsigned)g >= (unsigned)A.D.G || n_tok <= 0 || n_tok > T || t0 < 0 || nch <= 0 || Tc < 64 || Tc > A.T ||
       (nch > 1 && (it.pbase < 0 || it.pbase + nch > A.cap)))
     return;  // not a record this call wrote
@@ -352,6 +372,15 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   if (A.plan && C_now != it.pad[0]) {
     if (tid == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
     return;
+  }
+  const bool single = nch == 1;
+  int32_t* const arrived = A.self_list ? A.header + HW_MEET + it.pad[1] : slot_words + it.pbase;
+  int32_t* const started = arrived + (A.self_list ? 0 : 1);
+  const int one_started = A.self_list ? 1 << kMeetBits : 1;
+  int32_t* const call = &A.items[rec].pad[2];    // where this chunk is called, when all of its head have arrived
+  if (!single && tid == 0) {
+    publish_i32(call, 0);
+    __hip_atomic_fetch_add(started, one_started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
 
@@ -706,10 +735,19 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
         for (int k = 0; k < EPL; ++k) s_acc[(w * RW + hh) * HD + seg * EPL + k] = acc[hh][k];
     }
   }
+  // (the first wavefront's exps have been used: its place serves for a word to all)
+  int* s_say = (int*)s_e;
+  if (!single && tid == 0) {
+    bool all = false;
+    for (int looks = 0; looks < kMeetStarts && !all; ++looks) {
+      const uint32_t n = (uint32_t)published_i32(started);
+      all = (int)(A.self_list ? n >> kMeetBits : n) == nch;
+    }
+    s_say[0] = all;
+  }
   __syncthreads();
 
   // chunk max and sum per head from the wavefronts' pairs
-  const bool single = nch == 1;
   float cm[R], cl[R], wsc[NW][R];
 #pragma unroll
   for (int hh = 0; hh < R; ++hh) {
@@ -725,198 +763,227 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     cm[hh] = m;
     cl[hh] = l;
   }
-  const size_t pslot = (size_t)it.pbase + (size_t)(t0 / Tc);  // partial-result slot of this chunk
+  const int ci = t0 / Tc;                                // this chunk of the head,
+  const size_t pslot = (size_t)it.pbase + (size_t)ci;    // and its partial-result slot
+  const bool waits = !single && s_say[0];
 #pragma unroll
   for (int hh = 0; hh < R; ++hh) {
+    if (!single) {
+      for (int k = 2 * tid; k < HD; k += 2 * NT) {
+        float s[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) {
+          const float2 v = *(const float2*)&s_acc[(ww * RW + hh) * HD + k];
+          s[0] += v.x * wsc[ww][hh];
+          s[1] += v.y * wsc[ww][hh];
+        }
+        publish_u64(&A.part_acc[(pslot * R + hh) * HD + k], (uint64_t)__float_as_uint(s[0]) | (uint64_t)__float_as_uint(s[1]) << 32);
+      }
+      continue;
+    }
     for (int k = tid; k < HD; k += NT) {
       float s = 0.0f;
 #pragma unroll
       for (int ww = 0; ww < NW; ++ww) s += s_acc[(ww * RW + hh) * HD + k] * wsc[ww][hh];
-      if (single) __builtin_nontemporal_store(s / cl[hh], &A.out[((size_t)g * R + hh) * HD + k]);
-      else __builtin_nontemporal_store(s, &A.part_acc[(pslot * R + hh) * HD + k]);
+      __builtin_nontemporal_store(s / cl[hh], &A.out[((size_t)g * R + hh) * HD + k]);
     }
   }
   if (!single && tid == 0) {
 #pragma unroll
-    for (int hh = 0; hh < R; ++hh) {
-      A.part_ml[(pslot * R + hh) * 2 + 0] = cm[hh];
-      A.part_ml[(pslot * R + hh) * 2 + 1] = cl[hh];
-    }
+    for (int hh = 0; hh < R; ++hh)   // (the sum's sign says that the chunk does not wait)
+      publish_u64(&A.part_ml[(pslot * R + hh) * 2], (uint64_t)__float_as_uint(cm[hh]) |
+                                                        (uint64_t)((__float_as_uint(cl[hh]) & 0x7fffffffu) | (waits ? 0u : 0x80000000u)) << 32);
   }
-  if (!A.accumulate) return;
+  if (single && !A.accumulate) return;
   // The stored 16-bit value of a KV times 2^(its group's running max - chunk max) is the exp of
   // its logit against the chunk max; for a head of one chunk, divided by the sum, its
   // probability.  That factor is the same for the 16 tokens of a group: formed once, in place.
-  for (int i = tid; i < ngroups * R; i += NT) {
-    const int hh = i % R;
-    float f = 0.0f;
-#pragma unroll
-    for (int h2 = 0; h2 < R; ++h2)
-      if (h2 == hh) f = __builtin_amdgcn_exp2f(s_gm[i] - cm[h2]) * (single ? 1.0f / cl[h2] : 1.0f) * (1.0f / 65535.0f);
-    s_gm[i] = f;
-  }
-  __syncthreads();
-  for (int tok = tid; tok < n_tok; tok += NT) {
-    const size_t slot = ((size_t)s_tab[tok >> lb] << lb) + (tok & (b - 1));
-    float e[R];
-#pragma unroll
-    for (int hh = 0; hh < R; ++hh) e[hh] = (float)s_q[tok * R + hh] * s_gm[(tok >> 4) * R + hh];
-    if (single) {
-      float inc = 0.0f;
-#pragma unroll
-      for (int hh = 0; hh < R; ++hh) inc += A.D.mode == KVC_L2 ? e[hh] * e[hh] : e[hh];
-      // one writer per slot in a launch, so the hardware add gives the same bits as load-add-store
-      unsafeAtomicAdd(&A.metric[slot], inc);
-    } else {
-      stash_store<R>(A.stash, slot, e);
-    }
-  }
-}
-
-// Second kernel, heads of more than one chunk only.  Every chunk's workgroup
-// rebuilds the head's max and sum from the per-chunk pairs (a wavefront per query head, lane =
-// chunk), adds the metric increments of its own tokens and adds up its share of the head's
-// output: pieces of four dimensions, the chunks' partial rows spread over the threads that share a
-// piece.  (The first chunk's workgroup alone walking all the partial rows, and one thread per head
-// walking all the pairs, took 16 us for a layer with a head of 48 chunks; 6.5 now.)
-template <int R>
-__global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs A) {
-  // one workgroup per partial-result slot in use, i.e. per chunk of a head of more than one chunk
-  const int p = blockIdx.x;
-  DecodeItem it;
-  int Tc;                                    // tokens the work list was cut at
-  if (A.self_list) {
-    SelfList sl;
-    if (!self_item(A, p, true, sl)) return;
-    it = sl.it;
-    Tc = sl.T;
-  } else {
-    const bool placed = A.plan && A.plan_stride == 0;
-    if (p >= A.cap) return;
-    const int total_items = A.header[HW_TOTAL_ITEMS], total_partials = A.header[HW_TOTAL_PARTIALS];
-    const int base = placed ? A.header[HW_PLAN_BASE] : 0;
-    Tc = A.header[HW_CHUNK_T];
-    int item = placed ? 0 : A.slot_item[p];   // (asked for together with the header words)
-    if (p >= total_partials || p >= total_items) return;
-    if (placed && (base < 0 || base > A.plan_cap - total_items)) return;
-    if (placed) item = A.slot_item[base + p];
-    if (item < 0 || item >= total_items || item >= A.cap) return;
-    it = A.items[base + item];
-  }
-  const int nch = it.nch;
-  if (nch <= 1) return;
-  if ((unsigned)it.g >= (unsigned)A.D.G || it.n_tok <= 0 || it.n_tok > A.T || it.t0 < 0 || it.pbase < 0 ||
-      it.pbase + nch > A.cap)
-    return;  // not a record this call wrote
-  const int g = it.g, t0 = it.t0, n_tok = it.n_tok;
-  if (Tc < 64 || Tc > A.T) return;
-  const int C_now = A.plan ? A.ctx[g] : 0;   // (looked at below, behind the other loads)
-  const int c = t0 / Tc;
-  if (c >= nch) return;
-  const int first = it.pbase;                // partial-result slots first .. first + nch - 1
-  const int b = A.D.b, lb = A.log2b, HD = A.D.d;
-  constexpr int kMaxCh = 64;                 // chunk weights kept in LDS; longer heads recompute
-  __shared__ float s_m[R], s_il[R], s_w[R], s_wc[kMaxCh][R];
-  __shared__ float4 s_part[256];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int32_t* row = A.table + (size_t)g * A.D.maxb;
-  for (int hh = wv; hh < R; hh += 4) {
-    const float2* ml = (const float2*)A.part_ml + (size_t)first * R + hh;
-    float m = -INFINITY;
-    for (int c0 = 0; c0 < nch; c0 += 64)
-      if (c0 + lane < nch) m = fmaxf(m, ml[(size_t)(c0 + lane) * R].x);
-    m = wave_max_f(m);
-    float l = 0.0f, mine = 0.0f;
-    for (int c0 = 0; c0 < nch; c0 += 64) {
-      const int cc = c0 + lane;
-      if (cc >= nch) break;
-      const float2 v = ml[(size_t)cc * R];
-      const float wgt = __builtin_amdgcn_exp2f(v.x - m);
-      if (cc < kMaxCh) s_wc[cc][hh] = wgt;
-      if (cc == c) mine = wgt;
-      l += v.y * wgt;
-    }
-    l = wave_sum_f(l);
-    mine = wave_max_f(mine);   // the one lane's weight
-    if (lane == 0) {
-      s_m[hh] = m;
-      s_il[hh] = 1.0f / l;
-      s_w[hh] = mine / l;
-    }
-  }
-  if (A.plan && C_now != it.pad[0]) return;   // a kept list that no longer fits the head: its chunks did nothing either
-  __syncthreads();
   if (A.accumulate) {
-    float wv_h[R];
+    for (int i = tid; i < ngroups * R; i += NT) {
+      const int hh = i % R;
+      float f = 0.0f;
 #pragma unroll
-    for (int hh = 0; hh < R; ++hh) wv_h[hh] = s_w[hh];
-    // Four tokens per thread at a time, their block ids asked for together and then their exps: a
-    // token by itself is a chain of two dependent loads in front of one add.  (The first four asked
-    // for ahead of the pairs, or the output formed ahead of the metric: 177 and 200 us against 170
-    // at 4 x 131072 tokens, r = 8.)
-    for (int tok0 = tid; tok0 < n_tok; tok0 += 4 * 256) {
-      int id[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) id[u] = row[(t0 + min(tok0 + u * 256, n_tok - 1)) >> lb];
-      size_t slot[4];
-      float e[4][R];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = t0 + min(tok0 + u * 256, n_tok - 1);
-        slot[u] = ((size_t)id[u] << lb) + (j & (b - 1));
-        stash_load<R>(A.stash, slot[u], e[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (tok0 + u * 256 >= n_tok) break;
-        float inc = 0.0f;
-#pragma unroll
-        for (int hh = 0; hh < R; ++hh) {
-          const float pr = e[u][hh] * wv_h[hh];
-          inc += A.D.mode == KVC_L2 ? pr * pr : pr;
-        }
-        unsafeAtomicAdd(&A.metric[slot[u]], inc);
-      }
+      for (int h2 = 0; h2 < R; ++h2)
+        if (h2 == hh) f = __builtin_amdgcn_exp2f(s_gm[i] - cm[h2]) * (single ? 1.0f / cl[h2] : 1.0f) * (1.0f / 65535.0f);
+      s_gm[i] = f;
     }
+    __syncthreads();
   }
-  // output pieces e0 .. e1 - 1 of this chunk's workgroup; np threads (a power of two) side by side on
-  // pieces, 256 / np sharing the chunks of each
-  const int pieces = R * HD / 4;
-  const int e0 = (int)((long long)pieces * c / nch), e1 = (int)((long long)pieces * (c + 1) / nch);
-  for (int ebase = e0; ebase < e1; ebase += 256) {
-    const int ne = min(256, e1 - ebase);
-    int lnp = 0;
-    while ((1 << lnp) < ne) ++lnp;
-    const int np = 1 << lnp, q = tid & (np - 1), sub = tid >> lnp, subs = 256 >> lnp;
-    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (q < ne) {
-      const int i = (ebase + q) * 4, hh = i / HD;
-      const float* src = A.part_acc + (size_t)first * R * HD + i;
-#pragma unroll 4
-      for (int cc = sub; cc < nch; cc += subs) {
-        const float4 v = *(const float4*)(src + (size_t)cc * R * HD);
-        const float wgt = cc < kMaxCh ? s_wc[cc][hh]
-                                      : __builtin_amdgcn_exp2f(A.part_ml[((size_t)(first + cc) * R + hh) * 2] - s_m[hh]);
-        s.x = fmaf(v.x, wgt, s.x); s.y = fmaf(v.y, wgt, s.y); s.z = fmaf(v.z, wgt, s.z); s.w = fmaf(v.w, wgt, s.w);
+  auto each_token = [&](auto use) {
+    for (int tok = tid; tok < n_tok; tok += NT) {
+      const size_t slot = ((size_t)s_tab[tok >> lb] << lb) + (tok & (b - 1));
+      float e[R];
+#pragma unroll
+      for (int hh = 0; hh < R; ++hh) e[hh] = (float)s_q[tok * R + hh] * s_gm[(tok >> 4) * R + hh];
+      use(slot, e);
+    }
+  };
+  auto add = [&](size_t slot, float (&e)[R]) {
+    float inc = 0.0f;
+#pragma unroll
+    for (int hh = 0; hh < R; ++hh) inc += A.D.mode == KVC_L2 ? e[hh] * e[hh] : e[hh];
+    // one writer per slot in a launch, so the hardware add gives the same bits as load-add-store
+    unsafeAtomicAdd(&A.metric[slot], inc);
+  };
+  if (single) {
+    each_token(add);
+    return;
+  }
+  if constexpr (NW == 4) {   // (a short item is a whole head)
+    if (A.accumulate && !waits) each_token([&](size_t slot, float (&e)[R]) { exps_publish<R>(A.stash, slot, e); });
+    publish_wait();
+    __syncthreads();
+    if (w == 0) {
+      int was = 0;
+      if (lane == 0) was = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      was = __builtin_amdgcn_readfirstlane(was);
+      if (A.self_list) was &= kMeetMost;
+      bool go = waits;
+      if (was == nch - 1) {
+        for (int c = lane; c < nch; c += 64)
+          if (c != ci) publish_i32(call + (c - ci) * (int)(sizeof(DecodeItem) / 4), 1);
+        if (lane == 0) {
+          __hip_atomic_fetch_add(arrived, -nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_fetch_add(started, -nch * one_started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else if (waits) {
+        for (int looks = 0; !published_i32(call); ++looks) {
+          if (looks == kMeetLooks) {
+            go = false;
+            if (lane == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
+            break;
+          }
+        }
+      }
+      if (lane == 0) s_say[1] = go;
+    }
+    __syncthreads();
+    if (!s_say[1]) return;   // (its part is out: the others see to it)
+    // ---- every chunk of the head has arrived ----
+    const float* ml = A.part_ml + (size_t)it.pbase * R * 2;
+    const float* accs = A.part_acc + (size_t)it.pbase * R * HD;
+    // A chunk's share of the head's output, in pairs of dimensions: a wavefront has at most 64 of them (the
+    // head has two chunks at least), lanes on pairs, the chunks spread over the lanes that share one.
+    // The first four of a lane are asked for ahead of the max and sum.
+    constexpr int PAIRS = R * HD / 2, AHEAD = 4;
+    static_assert((PAIRS + 1) / 2 <= 64 * NW, "a wavefront's share of the output");
+    struct Share { int i, hh, ne, lnp; uint64_t v[AHEAD]; };
+    auto share_ask = [&](int c, Share& o) {
+      const int e0 = (int)((unsigned)(PAIRS * c) / (unsigned)nch), e1 = (int)((unsigned)(PAIRS * (c + 1)) / (unsigned)nch);
+      const int per = (e1 - e0 + NW - 1) / NW, w0 = e0 + w * per;
+      o.ne = max(0, min(per, e1 - w0));
+      o.lnp = o.ne > 1 ? 32 - __builtin_clz(o.ne - 1) : 0;
+      o.i = min(2 * (w0 + min(lane & ((1 << o.lnp) - 1), max(o.ne, 1) - 1)), 2 * PAIRS - 2);
+      o.hh = o.i / HD;
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        const int cc = (lane >> o.lnp) + k * (64 >> o.lnp);
+        o.v[k] = o.ne && cc < nch ? published_u64(accs + (size_t)cc * R * HD + o.i) : 0;
+      }
+    };
+    Share own;
+    share_ask(ci, own);
+    // The chunks' pairs go into LDS (a word of a line that every chunk of the head reads costs each of them
+    // ~5 ns: no wavefront asks for one that another has), and the head's max and sum come from there, a
+    // wavefront per query head, lane = chunk.  The chunks that have left are shared out among those that
+    // waited (one at least: the chunk that started last).
+    constexpr int kPairs = NW * RW * HD / 2;   // pairs that the wavefronts' outputs leave room for
+    uint64_t* s_ml = (uint64_t*)s_acc;
+    float* s_m = s_red;                     // [R] max, [R] 1 / sum
+    int* s_who = s_say + 2;                 // chunks that waited: in front of this one, and in all
+    float m_all[(R + NW - 1) / NW], l_all[(R + NW - 1) / NW];
+    int rank = 0, stay = 0;
+    constexpr int kRoom = kPairs / R;       // chunks at a time
+    for (int base = 0; base < nch; base += kRoom) {
+      const int n = min(kRoom, nch - base);
+      if (base) __syncthreads();
+      for (int i = tid; i < n * R; i += NT) s_ml[i] = published_u64(ml + ((size_t)base * R + i) * 2);
+      __syncthreads();
+#pragma unroll
+      for (int z = 0; z < (R + NW - 1) / NW; ++z) {
+        const int hh = w + z * NW;
+        if (hh >= R) break;
+        float m = base ? m_all[z] : -INFINITY, l = base ? l_all[z] : 0.0f;
+        for (int c0 = 0; c0 < n; c0 += 64) {
+          const int cc = c0 + lane;
+          const uint64_t v = cc < n ? s_ml[cc * R + hh] : (uint64_t)0xff800000u;
+          const float vm = __uint_as_float((uint32_t)v), vl = __uint_as_float((uint32_t)(v >> 32) & 0x7fffffffu);
+          const float nm = fmaxf(m, wave_max_f(vm));
+          l = (base + c0 ? l * __builtin_amdgcn_exp2f(m - nm) : 0.0f) + wave_sum_f(cc < n ? vl * __builtin_amdgcn_exp2f(vm - nm) : 0.0f);
+          m = nm;
+          if (hh == 0) {
+            const unsigned long long in = __ballot(cc < n && !(v >> 63));
+            const int to = ci - base - c0;   // this chunk's lane
+            stay += __popcll(in);
+            rank += to >= 64 ? __popcll(in) : to > 0 ? __popcll(in & ((1ull << to) - 1ull)) : 0;
+          }
+        }
+        m_all[z] = m;
+        l_all[z] = l;
       }
     }
-    for (int o = np; o < 64; o <<= 1) {   // lanes of a wavefront that share a piece
-      s.x += __shfl_xor(s.x, o); s.y += __shfl_xor(s.y, o); s.z += __shfl_xor(s.z, o); s.w += __shfl_xor(s.w, o);
-    }
-    const int in_wave = min(np, 64), parts = np < 64 ? 4 : subs;   // partial sums of a piece that are left: np apart
-    if (lane < in_wave) s_part[np < 64 ? wv * np + lane : tid] = s;
+#pragma unroll
+    for (int z = 0; z < (R + NW - 1) / NW; ++z)
+      if (lane == 0 && w + z * NW < R) { s_m[w + z * NW] = m_all[z]; s_m[R + w + z * NW] = 1.0f / l_all[z]; }
+    if (tid == 0) { s_who[0] = rank; s_who[1] = stay; }
     __syncthreads();
-    if (tid < ne) {
-      float4 t = s_part[tid];
-      for (int k = 1; k < parts; ++k) {
-        const float4 v = s_part[k * np + tid];
-        t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+    rank = s_who[0];
+    stay = s_who[1];
+    const bool kept = nch <= kRoom;         // every pair is still in LDS
+    auto max_of = [&](int c, int hh) {
+      return kept ? __uint_as_float((uint32_t)s_ml[c * R + hh]) : __int_as_float(published_i32((const int32_t*)ml + ((size_t)c * R + hh) * 2));
+    };
+    auto share_put = [&](const Share& o) {
+      if (!o.ne) return;
+      const float top = s_m[o.hh], il = s_m[R + o.hh];
+      float s0 = 0.0f, s1 = 0.0f;
+      auto term = [&](int cc, uint64_t v) {
+        const float wt = __builtin_amdgcn_exp2f(max_of(cc, o.hh) - top);
+        s0 = fmaf(__uint_as_float((uint32_t)v), wt, s0);
+        s1 = fmaf(__uint_as_float((uint32_t)(v >> 32)), wt, s1);
+      };
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        const int cc = (lane >> o.lnp) + k * (64 >> o.lnp);
+        if (cc < nch) term(cc, o.v[k]);
       }
-      const int i = (ebase + tid) * 4;
-      const float il = s_il[i / HD];
-      *(float4*)&A.out[(size_t)g * R * HD + i] = make_float4(t.x * il, t.y * il, t.z * il, t.w * il);
+      for (int cc = (lane >> o.lnp) + AHEAD * (64 >> o.lnp); cc < nch; cc += 64 >> o.lnp)
+        term(cc, published_u64(accs + (size_t)cc * R * HD + o.i));
+      for (int k = 1 << o.lnp; k < 64; k <<= 1) { s0 += __shfl_xor(s0, k); s1 += __shfl_xor(s1, k); }
+      if (lane < o.ne) *(float2*)&A.out[(size_t)g * R * HD + o.i] = make_float2(s0 * il, s1 * il);
+    };
+    float wgt[R];
+    auto weigh = [&](size_t slot, float (&e)[R]) {
+#pragma unroll
+      for (int hh = 0; hh < R; ++hh) e[hh] *= wgt[hh];
+      add(slot, e);
+    };
+    if (A.accumulate) {
+#pragma unroll
+      for (int hh = 0; hh < R; ++hh) wgt[hh] = __builtin_amdgcn_exp2f(cm[hh] - s_m[hh]) * s_m[R + hh];
+      each_token(weigh);
     }
-    __syncthreads();
+    share_put(own);
+    if (stay == nch) return;
+    // chunks that did not wait: every stay-th of them from this one's rank on
+    const int C = A.ctx[g];
+    int left = 0;
+    for (int c = 0; c < nch; ++c) {
+      if (published_i32((const int32_t*)ml + (size_t)c * R * 2 + 1) >= 0) continue;
+      if (left++ % stay != rank) continue;
+      share_ask(c, own);
+      share_put(own);
+      if (!A.accumulate) continue;
+      const int32_t* row = A.table + (size_t)g * A.D.maxb;
+#pragma unroll
+      for (int hh = 0; hh < R; ++hh) wgt[hh] = __builtin_amdgcn_exp2f(max_of(c, hh) - s_m[hh]) * s_m[R + hh];
+      for (int j = c * Tc + tid; j < min(C, c * Tc + Tc); j += NT) {
+        const size_t slot = ((size_t)row[j >> lb] << lb) + (j & (b - 1));
+        float e[R];
+        exps_published<R>(A.stash, slot, e);
+        weigh(slot, e);
+      }
+    }
   }
 }
 
@@ -1035,13 +1102,6 @@ static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_shor
     KVC_LAUNCH_CHECK();
   }
   if (pp) { KVC_HIP(hipEventRecord(pp->s1, s)); KVC_HIP(hipEventRecord(pp->b0, s)); }
-  // heads of more than one chunk hold more than T tokens each: at most N b / T of them, and their
-  // chunks number at most tokens / T plus one per head (a chunk length picked on the device: the
-  // bound on the work items serves)
-  const size_t split_bound = A.adapt_T ? (size_t)grid : 2 * ((size_t)A.D.N * A.D.b / A.T) + 1;
-  const int grid_combine = (size_t)grid < split_bound ? grid : (int)split_bound;
-  hipLaunchKernelGGL(decode_combine_kernel<R>, dim3(grid_combine), dim3(256), 0, s, A);
-  KVC_LAUNCH_CHECK();
   if (pp) KVC_HIP(hipEventRecord(pp->b1, s));
   return KVC_OK;
 }
@@ -1236,7 +1296,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   A.all_partials = 0;
   A.rotate_chunks = 0;
   A.cap = (int)(max_items_of(D) < 0x7fffffffull ? max_items_of(D) : 0x7fffffffull);
-  A.items = (DecodeItem*)W.items; A.slot_item = W.slot_item; A.part_ml = W.part_ml; A.part_acc = W.part_acc; A.stash = W.stash;
+  A.items = (DecodeItem*)W.items; A.slot_word = W.slot_word; A.part_ml = W.part_ml; A.part_acc = W.part_acc; A.stash = W.stash;
   A.header = W.header;
   A.status = W.header;
   A.plan = 0; A.plan_stride = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
@@ -1297,8 +1357,8 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     }
     A.header += (size_t)layer_begin * HW_WORDS;
     A.items += (size_t)layer_begin * A.plan_stride;
-    A.slot_item += (size_t)layer_begin * A.plan_stride;
-  } else if (small_call && A.gsel <= kSelfListHeads) {
+    A.slot_word += (size_t)layer_begin * A.plan_stride;
+  } else if (small_call && A.gsel <= kSelfListHeads && (size_t)D.maxb * D.b / kMinChunk < (size_t)kMeetMost) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {
     hipLaunchKernelGGL(decode_worklist_small_kernel<false>, dim3(1), dim3(1024), 0, s, A);

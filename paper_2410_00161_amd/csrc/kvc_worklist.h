@@ -13,7 +13,8 @@ struct DecodeItem {   // 32 bytes
   int n_tok;    // tokens in the chunk
   int nch;      // chunks of the head
   int pbase;    // first partial-result slot of the head (heads of more than one chunk)
-  int pad[3];   // [0]: the head's length the list was made for (lists kept by kvc_decode_plan)
+  int pad[3];   // [0]: the head's length the list was made for (lists kept by kvc_decode_plan); [1]: without a list, the
+                // head's meeting word; [2]: where a chunk of a head that meets is called
 };
 
 struct DecodeArgs {
@@ -30,17 +31,18 @@ struct DecodeArgs {
   int adapt_T;            // the one-launch work list picks the chunk length from the lengths it sees (see there)
   int log2b;              // block size is a power of two on the tiled path
   int cap;                // item records and partial-result slots the workspace holds
-  int all_partials;       // give every head a partial-result slot range, not only split heads
+  int all_partials;       // give every head a partial-result slot range, not only split heads (else the chunks of a split
+                          // head are listed side by side, its last and shorter one too: they meet, see kMeetBits)
   int rotate_chunks;      // a head's full chunks take their places rotated by the head's index (see decode_items_kernel)
   int short_class, Ts;    // size classes from short_class up (at most Ts tokens) are "short" items; 16 = none
   DecodeItem* items;
-  int32_t* slot_item;     // work item of partial-result slot p (heads of more than one chunk): what the combine kernel runs over
+  int32_t* slot_word;     // a word per partial-result slot: those of a head's first two are where its chunks meet
   float* part_ml;
   float* part_acc;
   float* stash;
   int32_t* header;
   // Work lists kept from one launch for every layer (kvc_decode_plan): layer l has its own header
-  // block at header + l * HW_WORDS and its own stretch of the records of items / slot_item.
+  // block at header + l * HW_WORDS and its own stretch of the records of items / slot_word.
   int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
   int plan_stride;        // records of a layer's stretch; 0: it starts where its header block says
   int plan_cap;           // records of all layers the workspace holds
@@ -76,8 +78,9 @@ static __global__ void __launch_bounds__(256) decode_count_kernel(DecodeArgs A) 
     const int C = A.ctx[sel_to_g(A.D, A.l0, A.nl, gi)];
     const int nfull = C / A.T, rem = C - nfull * A.T;
     const int nch = nfull + (rem ? 1 : 0);
-    if (nfull) atomicAdd(&bins[0], nfull);
-    if (rem) atomicAdd(&bins[size_class(rem, A.T)], 1);
+    const bool together = !A.all_partials && nch > 1;
+    if (nfull) atomicAdd(&bins[0], together ? nch : nfull);
+    if (rem && !together) atomicAdd(&bins[size_class(rem, A.T)], 1);
     if (nch > 1 || (A.all_partials && nch > 0)) atomicAdd(&bins[16], nch);
   }
   __syncthreads();
@@ -123,6 +126,7 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     nfull = C / T;
     rem = C - nfull * T;
     nch = nfull + (rem ? 1 : 0);
+    if (!A.all_partials && nch > 1) { nfull = nch; rem = 0; }   // side by side, in the class of full chunks
     cls = rem ? size_class(rem, T) : 0;
     if (nfull) my_full = atomicAdd(&want[0], nfull);
     if (rem) my_rem = atomicAdd(&want[cls], 1);       // class 0 never holds a remainder
@@ -149,10 +153,10 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     const int at = base[0] + got[0] + my_full;
     if (at < 0 || at + nfull > A.cap) return;
     for (int c = 0; c < nfull; ++c) {
-      DecodeItem it = {g, c * T, T, nch, pbase, {0, 0, 0}};
+      DecodeItem it = {g, c * T, min(T, C - c * T), nch, pbase, {0, 0, 0}};
       const int place = at + (A.rotate_chunks ? (c + g) % nfull : c);
       A.items[place] = it;
-      if (slotted) A.slot_item[pbase + c] = place;
+      if (slotted && c < 2) A.slot_word[pbase + c] = 0;
     }
   }
   if (rem) {
@@ -160,7 +164,6 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     if (at < 0 || at >= A.cap) return;
     DecodeItem it = {g, nfull * T, rem, nch, pbase, {0, 0, 0}};
     A.items[at] = it;
-    if (slotted) A.slot_item[pbase + nfull] = at;
   }
 }
 
@@ -202,13 +205,13 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   const int layer = PLAN ? (int)blockIdx.x : 0;
   int32_t* header = A.header + (size_t)layer * (PLAN ? HW_WORDS : 0);
   DecodeItem* items = A.items + (size_t)layer * A.plan_stride;
-  int32_t* slot_item = A.slot_item + (size_t)layer * A.plan_stride;
+  int32_t* slot_word = A.slot_word + (size_t)layer * A.plan_stride;
   int cap = A.cap;
   if (tid == 0) { ptot = 0; tokens = 0; live = 0; longest = 0; before = 0; }
   if (tid < 16) bins[tid] = 0;
   if (tid < 17) cur[tid] = 0;
   __syncthreads();
-  int g = 0, C = 0, nfull = 0, rem = 0, nch = 0, cls = 0;
+  int g = 0, C = 0, listed = 0, nfull = 0, rem = 0, nch = 0, cls = 0;
   if (tid < A.gsel) {
     g = sel_to_g(A.D, A.l0 + layer, A.nl, tid);
     C = A.ctx[g] + A.ctx_plus;
@@ -242,7 +245,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     const unsigned long long at = before / kSmallCallChunk + (unsigned long long)layer * A.gsel;
     const int start = (int)(at < (unsigned long long)A.plan_cap ? at : (unsigned long long)A.plan_cap);
     items += start;
-    slot_item += start;
+    slot_word += start;
     cap = min(cap, A.plan_cap - start);
     if (tid == 0) header[HW_PLAN_BASE] = start;
   }
@@ -250,10 +253,11 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   if (tid < A.gsel) {
     // (A full head planned one token longer: its row ends in front of that token.  Its records, which a
     // decode looks up in the row before it compares the length, end there too.)
-    const int listed = PLAN ? (int)min((long long)C, (long long)A.D.maxb * A.D.b) : C;
+    listed = PLAN ? (int)min((long long)C, (long long)A.D.maxb * A.D.b) : C;
     nfull = listed / T;
     rem = listed - nfull * T;
     nch = nfull + (rem ? 1 : 0);
+    if (!A.all_partials && nch > 1) { nfull = nch; rem = 0; }   // side by side, in the class of full chunks
     cls = rem ? size_class(rem, T) : 0;
     if (rem) atomicAdd(&bins[cls], 1);
   }
@@ -294,10 +298,10 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     const int at = base[0] + full_at;
     if (at < 0 || at + nfull > cap) return;
     for (int c = 0; c < nfull; ++c) {
-      DecodeItem it = {g, c * T, T, nch, pbase, {C, 0, 0}};
+      DecodeItem it = {g, c * T, min(T, listed - c * T), nch, pbase, {C, 0, 0}};
       const int place = at + (A.rotate_chunks ? (c + g) % nfull : c);
       items[place] = it;
-      if (slotted) slot_item[pbase + c] = place;
+      if (slotted && c < 2) slot_word[pbase + c] = 0;
     }
   }
   if (rem) {
@@ -305,21 +309,19 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     if (at < 0 || at >= cap) return;
     DecodeItem it = {g, nfull * T, rem, nch, pbase, {C, 0, 0}};
     items[at] = it;
-    if (slotted) slot_item[pbase + nfull] = at;
   }
 }
 
 // A call over at most kSelfListHeads head instances (a layer of one or a few sequences) keeps no
 // work list: every wavefront (lane = head instance) reads the lengths, repeats the cut and picks
 // its workgroup's item, one load and a few cross-lane scans in place of a launch (~7 us) and two
-// dependent loads.  Item x: the full chunks of all heads first, then the heads' remainders; or,
-// with `partial`, chunk x of the heads of more than one chunk.  Returns false when there is no
-// item x.  (Not for more heads, four a lane or one a thread: without the list's order by size long
+// dependent loads.  Item x: the chunks of the heads of more than one chunk, head by head, then the
+// heads of one.  Returns false when there is no item x.  (Not for more heads, four a lane or one a thread: without the list's order by size long
 // remainders meet on one CU, 256 ragged heads of 2048 KVs on average 62 -> 77 us; and at 512 heads
 // the prologue of every workgroup, empty ones too, costs what the launch does.)
 constexpr int kSelfListHeads = 64;
 struct SelfList { DecodeItem it; int T; int C; int g; };   // item, chunk length; this lane's head and length (g = -1: none)
-__device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, bool partial, SelfList& out) {
+__device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, SelfList& out) {
   const int lane = threadIdx.x & 63;
   int g = -1, C = 0;
   if (lane < A.gsel) {
@@ -330,25 +332,23 @@ __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, bool parti
   if (A.adapt_T) {
     T = small_call_chunk(A.T, wave_sum_long(C), __popcll(__ballot(C > 0)), wave_max(C));
   }
-  const int nfull = C / T, rem = C - nfull * T, nch = nfull + (rem ? 1 : 0);
+  const int nch = C / T + (C % T ? 1 : 0);
   const int split = nch > 1 ? nch : 0;
-  const int fi = wave_prefix_i(nfull), si = wave_prefix_i(split);   // inclusive
-  const int F = __builtin_amdgcn_readlane(fi, 63);
-  const unsigned long long rm = __ballot(rem > 0);
+  const int si = wave_prefix_i(split);   // inclusive
+  const int P = __builtin_amdgcn_readlane(si, 63);
+  const unsigned long long whole = __ballot(nch == 1);
   int t0 = -1;   // the item's first token, in the lane of its head
-  if (partial) {
+  if (x < P) {
     if (x >= si - split && x < si) t0 = (x - (si - split)) * T;
-  } else if (x < F) {
-    if (x >= fi - nfull && x < fi) t0 = (x - (fi - nfull)) * T;
-  } else if (rem && x - F == __popcll(rm & ((1ull << lane) - 1ull))) {
-    t0 = nfull * T;
+  } else if (nch == 1 && x - P == __popcll(whole & ((1ull << lane) - 1ull))) {
+    t0 = 0;
   }
   out.T = T; out.C = C; out.g = g;
   const unsigned long long has = __ballot(t0 >= 0);
   if (has == 0) return false;
   const int src = __builtin_ctzll(has);
   out.it = DecodeItem{__builtin_amdgcn_readlane(g, src), __builtin_amdgcn_readlane(t0, src), 0,
-                      __builtin_amdgcn_readlane(nch, src), __builtin_amdgcn_readlane(si - split, src), {0, 0, 0}};
+                      __builtin_amdgcn_readlane(nch, src), __builtin_amdgcn_readlane(si - split, src), {0, src, 0}};
   out.it.n_tok = min(T, __builtin_amdgcn_readlane(C, src) - out.it.t0);
   return true;
 }

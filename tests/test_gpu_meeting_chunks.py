@@ -1,0 +1,81 @@
+"""Heads of several chunks, whose workgroups wait for one another and finish the head together: few and
+many chunks, more than their pairs' room in LDS, more than the chip runs at once (the first ones then
+leave their exps, and the last ones finish for them), from every kind of list; the same bits each time."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvc_oracle as O
+from paper_2410_00161_amd import binding as B
+from paper_2410_00161_amd import workloads as W
+from helpers import oracle_state
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # chunk length, shape, lengths
+    ("two_chunks_each", 64, dict(S=1, Lyr=1, Hk=4, r=8, d=128, kv_dtype="bf16"), [65, 128, 64, 127]),
+    ("around_64_chunks", 64, dict(S=1, Lyr=1, Hk=3, r=4, d=128, kv_dtype="fp8"), [64 * 64, 64 * 64 + 1, 63 * 64 + 5]),
+    ("pairs_beyond_lds", 64, dict(S=1, Lyr=1, Hk=2, r=1, d=64, kv_dtype="bf16"), [64 * 300 + 9, 64 * 128]),
+    ("more_than_run_at_once_r1", 64, dict(S=1, Lyr=1, Hk=2, r=1, d=64, kv_dtype="bf16"), [64 * 2600 + 3, 700]),
+    ("more_than_run_at_once_r4", 64, dict(S=1, Lyr=1, Hk=1, r=4, d=64, kv_dtype="f32"), [64 * 2100]),
+    ("more_than_run_at_once_r2_b4", 64, dict(S=1, Lyr=1, Hk=1, r=2, d=64, kv_dtype="fp8", b=4), [64 * 2600 - 1]),
+    ("picked_on_the_device", 0, dict(S=3, Lyr=2, Hk=8, r=4, d=128, kv_dtype="bf16"), None),
+    ("two_pass_list", 512, dict(S=40, Lyr=4, Hk=8, r=2, d=64, kv_dtype="bf16"), None),
+]
+
+
+@pytest.mark.parametrize("name,chunk,kw,lengths", CASES, ids=[c[0] for c in CASES])
+def test_split_heads(name, chunk, kw, lengths):
+    from paper_2410_00161_amd.session import KvcSession
+    b, G = kw.get("b", 16), kw["S"] * kw["Lyr"] * kw["Hk"]
+    g0 = torch.Generator().manual_seed(4)
+    ctx = torch.tensor(lengths, dtype=torch.int32) if lengths else (1 + 2500 * torch.rand(G, generator=g0) ** 3).to(torch.int32)
+    shape = W.Shape(kw["S"], kw["Lyr"], kw["Hk"], kw["r"], kw["d"], b, W.pool_size(ctx, b, 1.1, 3), -(-int(ctx.max()) // b) + 1,
+                    kw["kv_dtype"])
+    cache = W.make_cache(shape, ctx, 13, placement="fragmented")
+    st = oracle_state(cache)
+    q = W.make_query(shape, 13)
+    want = O.paged_decode(st, q.double().numpy())
+    live = st.free_map == 0
+    first = None
+    B.kvc_set_decode_chunk(chunk)
+    try:
+        for turn in range(3):
+            sess = KvcSession(cache.clone())
+            out = sess.paged_decode(q.to(sess.device))
+            assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+            again = sess.paged_decode(q.to(sess.device), accumulate_metric=False, out=torch.empty_like(out))
+            torch.cuda.synchronize()
+            got, metric = out.cpu().numpy(), sess.cache.metric.cpu().numpy()
+            np.testing.assert_array_equal(again.cpu().numpy(), got)   # (the counts are back at zero, the list is gone)
+            if turn == 0:
+                first = got, metric
+                # f32 sums (3e-7 measured); where two 16-bit parts of a probability go into a matrix product, the 16 bits
+                # that they carry move an output by up to 2^-16 of the values' weighted mean
+                parts = kw["d"] == 128 and b >= 16 and (kw["r"] == 8 or kw["kv_dtype"] == "fp8")
+                assert np.linalg.norm(got - want.reshape(got.shape)) <= (2.0 ** -16 if parts else 2e-6) * np.linalg.norm(want)
+                np.testing.assert_allclose(metric[live], st.metric[live], rtol=0, atol=kw["r"] * 2.0 ** -15)   # exps of 16 bits
+            # whoever finished a chunk, the bits are the same
+            np.testing.assert_array_equal(got, first[0])
+            np.testing.assert_array_equal(metric, first[1])
+    finally:
+        B.kvc_set_decode_chunk(0)
+
+
+def test_kept_lists_meet_again():
+    """A layer's kept list serves any number of decodes: its meeting words are back at zero after each."""
+    from paper_2410_00161_amd.session import KvcSession
+    ctx = torch.tensor([3000, 1, 900, 129, 4000, 128, 2000, 640] * 4, dtype=torch.int32)
+    shape = W.Shape(2, 2, 8, 4, 128, 16, W.pool_size(ctx, 16, 1.1, 3), 260, "bf16")
+    cache = W.make_cache(shape, ctx, 5)
+    q = W.make_query(shape, 5)
+    plain, sess = KvcSession(cache.clone()), KvcSession(cache.clone())
+    sess.decode_plan()
+    for turn in range(3):
+        for layer in range(2):
+            want = plain.paged_decode(q.to(plain.device), layer_begin=layer, layer_end=layer + 1)
+            got = sess.paged_decode_planned(q.to(sess.device), layer)
+        np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+        np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), plain.cache.metric.cpu().numpy())
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
