@@ -668,6 +668,9 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
       }
     }
   }
+  // (the first look for chunks that have not started: on its way while the wavefronts merge)
+  uint32_t seen = 0;
+  if (!single && tid == 0) seen = (uint32_t)published_i32(started);
   // ---- merge: token groups of one wavefront, then the wavefronts ----
   if constexpr (MF) {
 #pragma unroll
@@ -737,14 +740,6 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   }
   // (the first wavefront's exps have been used: its place serves for a word to all)
   int* s_say = (int*)s_e;
-  if (!single && tid == 0) {
-    bool all = false;
-    for (int looks = 0; looks < kMeetStarts && !all; ++looks) {
-      const uint32_t n = (uint32_t)published_i32(started);
-      all = (int)(A.self_list ? n >> kMeetBits : n) == nch;
-    }
-    s_say[0] = all;
-  }
   __syncthreads();
 
   // chunk max and sum per head from the wavefronts' pairs
@@ -765,40 +760,40 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   }
   const int ci = t0 / Tc;                                // this chunk of the head,
   const size_t pslot = (size_t)it.pbase + (size_t)ci;    // and its partial-result slot
-  const bool waits = !single && s_say[0];
+  // a wavefront per query head
 #pragma unroll
   for (int hh = 0; hh < R; ++hh) {
-    if (!single) {
-      for (int k = 2 * tid; k < HD; k += 2 * NT) {
-        float s[2] = {0.0f, 0.0f};
+    if (NW > 1 && hh % NW != w) continue;
+    for (int k = 2 * lane; k < HD; k += 128) {
+      float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-          const float2 v = *(const float2*)&s_acc[(ww * RW + hh) * HD + k];
-          s[0] += v.x * wsc[ww][hh];
-          s[1] += v.y * wsc[ww][hh];
-        }
-        publish_u64(&A.part_acc[(pslot * R + hh) * HD + k], (uint64_t)__float_as_uint(s[0]) | (uint64_t)__float_as_uint(s[1]) << 32);
+      for (int ww = 0; ww < NW; ++ww) {
+        const float2 v = *(const float2*)&s_acc[(ww * RW + hh) * HD + k];
+        s0 += v.x * wsc[ww][hh];
+        s1 += v.y * wsc[ww][hh];
       }
-      continue;
-    }
-    for (int k = tid; k < HD; k += NT) {
-      float s = 0.0f;
-#pragma unroll
-      for (int ww = 0; ww < NW; ++ww) s += s_acc[(ww * RW + hh) * HD + k] * wsc[ww][hh];
-      __builtin_nontemporal_store(s / cl[hh], &A.out[((size_t)g * R + hh) * HD + k]);
+      if (single) {
+        const f32x2_t o = {s0 / cl[hh], s1 / cl[hh]};
+        __builtin_nontemporal_store(o, (f32x2_t*)&A.out[((size_t)g * R + hh) * HD + k]);
+      } else {
+        publish_u64(&A.part_acc[(pslot * R + hh) * HD + k], (uint64_t)__float_as_uint(s0) | (uint64_t)__float_as_uint(s1) << 32);
+      }
     }
   }
   if (!single && tid == 0) {
+    auto all = [&]() { return (int)(A.self_list ? seen >> kMeetBits : seen) == nch; };
+    for (int looks = 1; looks < kMeetStarts && !all(); ++looks) seen = (uint32_t)published_i32(started);
+    s_say[0] = all();
 #pragma unroll
     for (int hh = 0; hh < R; ++hh)   // (the sum's sign says that the chunk does not wait)
       publish_u64(&A.part_ml[(pslot * R + hh) * 2], (uint64_t)__float_as_uint(cm[hh]) |
-                                                        (uint64_t)((__float_as_uint(cl[hh]) & 0x7fffffffu) | (waits ? 0u : 0x80000000u)) << 32);
+                                                        (uint64_t)((__float_as_uint(cl[hh]) & 0x7fffffffu) | (all() ? 0u : 0x80000000u)) << 32);
   }
   if (single && !A.accumulate) return;
   // The stored 16-bit value of a KV times 2^(its group's running max - chunk max) is the exp of
   // its logit against the chunk max; for a head of one chunk, divided by the sum, its
   // probability.  That factor is the same for the 16 tokens of a group: formed once, in place.
-  if (A.accumulate) {
+  if (A.accumulate || !single) {
     for (int i = tid; i < ngroups * R; i += NT) {
       const int hh = i % R;
       float f = 0.0f;
@@ -830,6 +825,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     return;
   }
   if constexpr (NW == 4) {   // (a short item is a whole head)
+    const bool waits = s_say[0];
     if (A.accumulate && !waits) each_token([&](size_t slot, float (&e)[R]) { exps_publish<R>(A.stash, slot, e); });
     publish_wait();
     __syncthreads();
