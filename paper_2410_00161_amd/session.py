@@ -74,7 +74,7 @@ class KvcSession:
         nseg = budget.numel()
         if seg_offsets is not None:
             seg_offsets = seg_offsets.to(self.device, torch.int32).contiguous()
-        selected = torch.zeros((nseg,), dtype=torch.int32, device=self.device)
+        selected = torch.empty((nseg,), dtype=torch.int32, device=self.device)   # (every selection writes or clears it)
         key = self.block_key if block_key is None else block_key
         B.kvc_evict_select(self.cfg, self.st, key, seg_offsets, budget, nseg, protect_tail_blocks,
                            self.evict_flag, self.evict_count, selected, self.ws, flags=flags)
@@ -91,7 +91,7 @@ class KvcSession:
         nseg = budget.numel()
         if seg_offsets is not None:
             seg_offsets = seg_offsets.to(self.device, torch.int32).contiguous()
-        selected = torch.zeros((nseg,), dtype=torch.int32, device=self.device)
+        selected = torch.empty((nseg,), dtype=torch.int32, device=self.device)   # (every selection writes or clears it)
         B.kvc_evict_rank_select(self.cfg, self.st, seg_offsets, budget, nseg, protect_tail_blocks,
                                 self.evict_count, selected, self.ws, flags=flags)
         return self.evict_count, selected
