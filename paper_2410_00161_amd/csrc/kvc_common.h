@@ -141,6 +141,12 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
   const u32x4 t = __builtin_nontemporal_load((const u32x4*)p);
   return make_uint4(t.x, t.y, t.z, t.w);
 }
+// 16-byte store of data that this launch does not read again, with the same hint.
+__device__ __forceinline__ void store_stream16(void* p, const uint4& v) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 t = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(t, (u32x4*)p);
+}
 __device__ __forceinline__ uint2 load_stream8(const void* p) {
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
   const u32x2 t = __builtin_nontemporal_load((const u32x2*)p);
@@ -172,6 +178,52 @@ __device__ __forceinline__ uint64_t published_u64(const void* p) {
   return __hip_atomic_load((uint64_t*)const_cast<void*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void publish_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// ---- KVs moved by a compaction ----
+// By the 16 lanes of a group, one or two of them: the rows of both are asked for before the first is stored.
+// What moves is not looked at again by its launch, so the stores pass the caches by, and in large pools the
+// loads do.  Block compactions of 1024 heads of 500 tokens to 16384 of 1024 (0.3 to 8.6 GB of KVs) that lose 10
+// or 30 % of their blocks, on caches filled with something else: one KV at a time with plain accesses 71 (128 x 4
+// x 8 heads of 400 tokens), 150 (64 x 32 x 8 of 300), 423 and 953 us (64 x 32 x 8 of 1024); two at a time with
+// plain ones 70, 147, 416 and 929; stores with the hint 69, 150, 412 and 890; both 58, 119, 372 and 731.  Where
+// most of what moves is still in the 256 MB behind the L2s, loads with the hint lose: 512 heads of 1005
+// tokens run again on the same cache 43, 46, 41 and 52 us, 2048 of 1024 80, 76, 60 and 81, 16384 of 300 (2.5 GB) 120, 118, 111 and 117.
+struct Pool { char* kc; char* vc; float* metric; int32_t* pos; size_t row_bytes; bool large; };
+constexpr size_t kLargePool = (size_t)2 << 30;
+__device__ __forceinline__ Pool pool_of(const Dims& D, char* kc, char* vc, float* metric, int32_t* pos) {
+  const size_t rb = (size_t)D.d * kv_esz(D.dtype);
+  return Pool{kc, vc, metric, pos, rb, 2 * rb * (size_t)D.b * (size_t)D.N >= kLargePool};
+}
+template <bool LARGE>
+__device__ __forceinline__ void move_rows(const Pool& P, int gl, bool two, size_t s0, size_t d0, size_t s1, size_t d1) {
+  const size_t rb = P.row_bytes;
+  auto load = [](const char* p) { return LARGE ? load_stream16(p) : *(const uint4*)p; };
+  if (two) {
+    for (size_t c = gl * 16; c < rb; c += 256) {
+      const uint4 k0 = load(P.kc + s0 * rb + c), v0 = load(P.vc + s0 * rb + c);
+      const uint4 k1 = load(P.kc + s1 * rb + c), v1 = load(P.vc + s1 * rb + c);
+      store_stream16(P.kc + d0 * rb + c, k0);
+      store_stream16(P.vc + d0 * rb + c, v0);
+      store_stream16(P.kc + d1 * rb + c, k1);
+      store_stream16(P.vc + d1 * rb + c, v1);
+    }
+  } else {
+    for (size_t c = gl * 16; c < rb; c += 256) {
+      const uint4 k0 = load(P.kc + s0 * rb + c), v0 = load(P.vc + s0 * rb + c);
+      store_stream16(P.kc + d0 * rb + c, k0);
+      store_stream16(P.vc + d0 * rb + c, v0);
+    }
+  }
+}
+__device__ __forceinline__ void move_kvs(const Pool& P, int gl, bool two, size_t s0, size_t d0, size_t s1, size_t d1) {
+  if (P.large) move_rows<true>(P, gl, two, s0, d0, s1, d1);
+  else move_rows<false>(P, gl, two, s0, d0, s1, d1);
+  if (gl < 1 + two) {
+    const size_t src = gl ? s1 : s0, dst = gl ? d1 : d0;
+    P.metric[dst] = P.metric[src];
+    if (P.pos) P.pos[dst] = P.pos[src];
+  }
+}
 
 // ---- across the lanes of a wavefront ----
 // Without LDS: a shuffle is an LDS access of ~110 clocks, and a reduction is a chain of six.  Lanes of

@@ -555,13 +555,13 @@ __global__ void __launch_bounds__(256) compact_move_kernel(Dims D, char* __restr
   // evicted real KVs: flagged blocks are full except possibly the last one
   const int n_ev = e * b - (last_flag ? nb * b - C : 0);
   const int T = C - n_ev;
-  const size_t row_bytes = (size_t)D.d * kv_esz(D.dtype);
-  const int pieces = (int)(row_bytes / 16);
+  const Pool P = pool_of(D, kc, vc, metric, pos);
   const int grp = threadIdx.x >> 4, gl = threadIdx.x & 15;
-  for (int j = T + grp; j < C; j += 16) {
+  auto route = [&](int j, size_t& src, size_t& dst) -> bool {
+    if (j >= C) return false;
     const int uj = j >> lb;
     const int before = uj ? pi[uj - 1] : 0;
-    if (pi[uj] != before) continue;  // its block is flagged: evicted, nothing to keep
+    if (pi[uj] != before) return false;  // its block is flagged: evicted, nothing to keep
     // evicted real slots in [0, j+1): whole flagged blocks before block uj (uj itself is kept)
     const int ev_below = before << lb;
     const int k = (C - 1 - j) - (n_ev - ev_below);  // kept slots above j = rank among movers
@@ -569,16 +569,16 @@ __global__ void __launch_bounds__(256) compact_move_kernel(Dims D, char* __restr
     const int want = (k >> lb) + 1;
     int lo = 0, hi = nb - 1;  // smallest u with pi[u] >= want
     while (lo < hi) { int mid = (lo + hi) >> 1; if (pi[mid] >= want) hi = mid; else lo = mid + 1; }
-    const size_t src = ((size_t)ids[uj] << lb) + (j & (b - 1));
-    const size_t dst = ((size_t)ids[lo] << lb) + (k & (b - 1));
-    for (int c = gl; c < pieces; c += 16) {
-      ((uint4*)(kc + dst * row_bytes))[c] = ((const uint4*)(kc + src * row_bytes))[c];
-      ((uint4*)(vc + dst * row_bytes))[c] = ((const uint4*)(vc + src * row_bytes))[c];
-    }
-    if (gl == 0) {
-      metric[dst] = metric[src];
-      if (pos) pos[dst] = pos[src];
-    }
+    src = ((size_t)ids[uj] << lb) + (j & (b - 1));
+    dst = ((size_t)ids[lo] << lb) + (k & (b - 1));
+    return true;
+  };
+  for (int j = T + grp; j < C; j += 32) {
+    size_t s0 = 0, d0 = 0, s1 = 0, d1 = 0;
+    const bool one = route(j, s0, d0), two = route(j + 16, s1, d1);
+    if (!one && !two) continue;
+    if (!one) { s0 = s1; d0 = d1; }
+    move_kvs(P, gl, one && two, s0, d0, s1, d1);
   }
   __syncthreads();  // all moves of this head read the table before it shrinks
   const int nb2 = (T + b - 1) >> lb;
@@ -679,8 +679,7 @@ __global__ void __launch_bounds__(256) compact_move_sliced_kernel(Dims D, char* 
     if (last > r_hi) break;       // the same for every thread
   }
   __syncthreads();
-  const size_t row_bytes = (size_t)D.d * kv_esz(D.dtype);
-  const int pieces = (int)(row_bytes / 16);
+  const Pool P = pool_of(D, kc, vc, metric, pos);
   const int grp = tid >> 4, gl = tid & 15;
   auto route = [&](int j, size_t& src, size_t& dst) {
     if (j >= j_hi) return false;
@@ -691,36 +690,12 @@ __global__ void __launch_bounds__(256) compact_move_sliced_kernel(Dims D, char* 
     dst = ((size_t)s_hole[(k >> lb) - r_lo] << lb) + (k & (b - 1));   // k-th hole: offset k % b of the (k / b)-th flagged block
     return true;
   };
-  // two KVs of a group at a time: a KV is a chain of loads and stores
   for (int j = j_lo + grp; j < j_hi; j += 32) {
     size_t s0 = 0, d0 = 0, s1 = 0, d1 = 0;
     const bool one = route(j, s0, d0), two = route(j + 16, s1, d1);
     if (!one && !two) continue;
     if (!one) { s0 = s1; d0 = d1; }
-    if (one && two) {
-      for (int c = gl; c < pieces; c += 16) {
-        const uint4 k0 = ((const uint4*)(kc + s0 * row_bytes))[c], v0 = ((const uint4*)(vc + s0 * row_bytes))[c];
-        const uint4 k1 = ((const uint4*)(kc + s1 * row_bytes))[c], v1 = ((const uint4*)(vc + s1 * row_bytes))[c];
-        ((uint4*)(kc + d0 * row_bytes))[c] = k0;
-        ((uint4*)(vc + d0 * row_bytes))[c] = v0;
-        ((uint4*)(kc + d1 * row_bytes))[c] = k1;
-        ((uint4*)(vc + d1 * row_bytes))[c] = v1;
-      }
-    } else {
-      for (int c = gl; c < pieces; c += 16) {
-        const uint4 k0 = ((const uint4*)(kc + s0 * row_bytes))[c], v0 = ((const uint4*)(vc + s0 * row_bytes))[c];
-        ((uint4*)(kc + d0 * row_bytes))[c] = k0;
-        ((uint4*)(vc + d0 * row_bytes))[c] = v0;
-      }
-    }
-    if (gl == 0) {
-      metric[d0] = metric[s0];
-      if (pos) pos[d0] = pos[s0];
-      if (one && two) {
-        metric[d1] = metric[s1];
-        if (pos) pos[d1] = pos[s1];
-      }
-    }
+    move_kvs(P, gl, one && two, s0, d0, s1, d1);
   }
   }
   finish_head(D, table, ctx, free_map, arrived, g, expected, C, T);

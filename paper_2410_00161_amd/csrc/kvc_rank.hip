@@ -691,20 +691,14 @@ __global__ void __launch_bounds__(NTH, WAVES) rank_compact_kernel(Dims D, char* 
   }
   __syncthreads();   // the lists are complete (and in memory) before anyone reads them back
 
-  const size_t row_bytes = (size_t)D.d * kv_esz(D.dtype);
-  const int pieces = (int)(row_bytes / 16);
+  const Pool P = pool_of(D, kc, vc, metric, pos);
   const int grp = tid >> 4, gl = tid & 15;
-  for (int kk = grp; kk < n_moves; kk += NTH / 16) {
-    const size_t dst = phys(scratch[phys(kk)]);
-    const size_t src = phys(scratch[phys(C - 1 - kk)]);
-    for (int c = gl; c < pieces; c += 16) {
-      ((uint4*)(kc + dst * row_bytes))[c] = ((const uint4*)(kc + src * row_bytes))[c];
-      ((uint4*)(vc + dst * row_bytes))[c] = ((const uint4*)(vc + src * row_bytes))[c];
-    }
-    if (gl == 0) {
-      metric[dst] = metric[src];
-      if (pos) pos[dst] = pos[src];
-    }
+  for (int kk = grp; kk < n_moves; kk += NTH / 8) {
+    const int k2 = kk + NTH / 16;
+    const bool two = k2 < n_moves;
+    const int d0 = scratch[phys(kk)], s0 = scratch[phys(C - 1 - kk)];
+    const int d1 = scratch[phys(two ? k2 : kk)], s1 = scratch[phys(C - 1 - (two ? k2 : kk))];
+    move_kvs(P, gl, two, phys(s0), phys(d0), phys(s1), phys(d1));
   }
   __syncthreads();
   const int nb2 = nb - e;
@@ -737,28 +731,14 @@ __global__ void __launch_bounds__(256) rank_move_kernel(Dims D, char* __restrict
   const int C = ctx[g], T = (((C + D.b - 1) >> lb) - e) << lb;
   const int32_t* row = table + (size_t)g * D.maxb;
   auto phys = [&](int j) -> size_t { return ((size_t)row[j >> lb] << lb) + (j & (D.b - 1)); };
-  const size_t row_bytes = (size_t)D.d * kv_esz(D.dtype);
-  const int pieces = (int)(row_bytes / 16);
+  const Pool P = pool_of(D, kc, vc, metric, pos);
   const int grp = tid >> 4, gl = tid & 15;
   const int k1 = min(n_moves, ((int)blockIdx.y + 1) * slice);
-  // two moves of a group at a time (a last odd one twice): a move is a chain of five loads
-  for (int k = (int)blockIdx.y * slice + grp; k < k1; k += 32) {
-    const int k2 = k + 16 < k1 ? k + 16 : k;
+  for (int k = (int)blockIdx.y * slice + grp; k < k1; k += 32) {   // (a move is a chain of five loads)
+    const bool two = k + 16 < k1;
+    const int k2 = two ? k + 16 : k;
     const int j0 = scratch[phys(k)], j1 = scratch[phys(k2)], i0 = scratch[phys(C - 1 - k)], i1 = scratch[phys(C - 1 - k2)];
-    const size_t d0 = phys(j0), d1 = phys(j1), s0 = phys(i0), s1 = phys(i1);
-    for (int c = gl; c < pieces; c += 16) {
-      const uint4 a0 = ((const uint4*)(kc + s0 * row_bytes))[c], v0 = ((const uint4*)(vc + s0 * row_bytes))[c];
-      const uint4 a1 = ((const uint4*)(kc + s1 * row_bytes))[c], v1 = ((const uint4*)(vc + s1 * row_bytes))[c];
-      ((uint4*)(kc + d0 * row_bytes))[c] = a0;
-      ((uint4*)(vc + d0 * row_bytes))[c] = v0;
-      ((uint4*)(kc + d1 * row_bytes))[c] = a1;
-      ((uint4*)(vc + d1 * row_bytes))[c] = v1;
-    }
-    if (gl < 2) {
-      const size_t src = gl ? s1 : s0, dst = gl ? d1 : d0;
-      metric[dst] = metric[src];
-      if (pos) pos[dst] = pos[src];
-    }
+    move_kvs(P, gl, two, phys(i0), phys(j0), phys(i1), phys(j1));
   }
   finish_head(D, table, ctx, free_map, arrived, g, expected, C, T);
 }
