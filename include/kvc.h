@@ -215,7 +215,7 @@ int kvc_paged_decode(const kvc_config* cfg, const kvc_state* st, const void* q, 
  * Covers what kvc_paged_decode runs on its tiled kernels with at most 1024 head instances per
  * layer and the library's own chunk length, unless the rows have far more room than the pool can
  * fill: with H = num_seqs * num_kv_heads heads a layer, num_layers * min(H * ceil(row tokens / 256),
- * H + max(410, pool tokens of one layer / longest chunk)) items have to fit the
+ * H + max(410, pool tokens / 6144, or 3456 with eight query heads)) items have to fit the
  * num_blocks * block_size / 64 + heads + 1 that the workspace has.  Else KVC_ERR_UNSUPPORTED.
  * Asynchronous.                                                                          */
 int kvc_decode_plan(const kvc_config* cfg, const kvc_state* st, int ctx_plus, void* ws, void* stream);

@@ -236,8 +236,23 @@ __host__ __device__ inline size_t decode_lds_bytes(int T, int R, int HD, int b, 
 // and fewer registers, so that a CU holds many of those chains at once.
 // Long chunks of 8-bit rows with four query heads in blocks shorter than 16 tokens: by itself the compiler takes
 // 170 registers, two below which a third workgroup fits a CU (4096 heads of up to 120 tokens 70 us, 56 with
-// it; of up to 1000 177 and 153).
-constexpr int decode_waves(int esz, int HD, int R, bool b16, int nw) { return esz == 1 && HD == 128 && R == 4 && !b16 && nw == 4 ? 3 : 1; }
+// it; of up to 1000 177 and 153).  With eight and blocks of 16 it takes 172, and a third workgroup is worth three
+// registers spilt (see decode_groups).
+constexpr int decode_waves(int esz, int HD, int R, bool b16, int nw) {
+  return esz == 1 && HD == 128 && nw == 4 && (R == 4 ? !b16 : R == 8 && b16) ? 3 : 1;
+}
+
+// Workgroups of four wavefronts that should share a CU, where the registers let more than two: the default chunk
+// is then the longest that leaves each its part of the LDS (what a chunk keeps grows with its tokens).  Over
+// 32 x 8192, 4 x 65536 and 64 x 2048 tokens at 8x, 8 KV heads, two workgroups (3456 or 6144 tokens) and so, us:
+// d = 64: 16-bit rows with eight query heads 984, 895, 497 and 849, 809, 466 (2368 tokens), with four 808, 773,
+// 464 and 794, 765, 436 (5120); 8-bit rows with eight 1619, 1456, 795 and 1141, 1089, 621 (1664), with four
+// 1180, 1215, 703 and 1037, 964, 571 (3840); d = 128, 8-bit rows with eight 1066, 971, 551 and 959, 929, 509 (1920).
+// Not where nothing comes of it: 8-bit rows of d = 128 with four (3456 tokens 849, 812; 6144 849, 806), 16-bit ones
+// with two (168 registers 751, 758, 392; 170 739, 740, 394).
+constexpr int decode_groups(int esz, int HD, int R, bool b16) {
+  return HD == 64 && R >= 4 ? (esz == 1 ? 4 : esz == 2 ? 3 : 2) : esz == 1 && HD == 128 && R == 8 && b16 ? 3 : 2;
+}
 
 template <int ESZ, int HD, int R, bool B16, int NW, bool MF = decode_uses_mfma(ESZ, R, HD)>
 __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) decode_chunk_kernel(DecodeArgs A) {
@@ -1114,6 +1129,10 @@ static int launch_tiled_r(const DecodeArgs& A, int grid, size_t lds, int grid_sh
 }
 
 constexpr size_t kLdsLimit = 160 * 1024;  // gfx950: 160 KiB of LDS per workgroup
+constexpr size_t kLdsUnit = 1280, kLdsUnits = kLdsLimit / kLdsUnit;   // handed out in these
+
+// Chunk length of large calls, before the LDS of a CU is shared out among more than two workgroups.
+static int default_chunk(const Dims& D) { return D.r >= 8 ? 3456 : 6144; }
 
 // Whether the tiled kernels cover this shape, and with which chunk length and LDS size.
 static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, bool* small_call = nullptr,
@@ -1127,9 +1146,14 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
                tpi >= 1 && 64 % D.b == 0;
   if (!tiled) return false;
   // default: a chunk that lets two workgroups share a CU (at r = 8, d = 128, 16-bit rows: 3456
-  // tokens x 16 bytes of exps + the rest = 81 764 of the 81 920 bytes a half CU has)
+  // tokens x 16 bytes of exps + the rest = 81 764 of the 81 920 bytes a half CU has), or as many as
+  // decode_groups says
   const int knob = g_chunk_tokens.load(std::memory_order_relaxed);
-  int T = knob ? knob : (D.r >= 8 ? 3456 : 6144);
+  const bool mf = decode_uses_mfma(esz, D.r, D.d);   // a per-wavefront operand tile in LDS
+  const int groups = decode_groups(esz, D.d, D.r, D.b % 16 == 0);
+  int T = knob ? knob : default_chunk(D);
+  if (!knob && groups > 2)
+    while (T > 1024 && decode_lds_bytes(T, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsUnits / groups * kLdsUnit) T -= 64;
   const int T_default = T;
   bool shrunk = false, device_side = false;
   if (!knob) {
@@ -1144,7 +1168,6 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
     // just what the tables have room for, and picks the length (at most the default) on the device
     if (shrunk && gsel <= kSmallWorklistHeads) { T = T_default; device_side = true; }
   }
-  const bool mf = decode_uses_mfma(esz, D.r, D.d);   // a per-wavefront operand tile in LDS
   // the default is sized so that two workgroups share a CU's LDS with blocks of 16 tokens; shorter
   // blocks put more block ids next to the exps (eight heads, d = 128, blocks of 8: 82 628 bytes): a shorter
   // chunk keeps the second workgroup on the CU
@@ -1338,7 +1361,10 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     // Rows with far more room than the pool can fill have no lists: every layer's launch is as large as
     // full rows would need, and nearly all of it would be empty.  (Lists of chunks of kPlanRowChunk for
     // all layers' full rows have to fit the records that the workspace has.)
-    if (items_of_rows(kPlanRowChunk) * (size_t)D.Lyr > (size_t)A.cap) return KVC_ERR_UNSUPPORTED;
+    // (counted in chunks of the length that two workgroups leave each other)
+    const size_t bound_accept = std::max(most_tokens / default_chunk(D), (size_t)410) + (size_t)A.gsel;
+    const size_t full_rows = (size_t)A.gsel * (((size_t)D.maxb * D.b + kPlanRowChunk - 1) / kPlanRowChunk);
+    if (std::min(bound_accept, full_rows) * (size_t)D.Lyr > (size_t)A.cap) return KVC_ERR_UNSUPPORTED;
     A.plan = 1;
     A.plan_cap = A.cap;
     A.plan_stride = grid * (size_t)D.Lyr <= (size_t)A.cap ? (int)grid : 0;   // (a start of its own costs every launch a dependent load)

@@ -65,6 +65,27 @@ def test_short_block_decodes_leave_room_for_their_workgroups():
     assert seen == 2
 
 
+def test_decodes_leave_room_for_as_many_workgroups_as_share_the_lds():
+    """Chunks sized for four workgroups a CU (8-bit rows of d = 64 with four or eight query heads) need 128
+    registers, for three (16-bit ones; 8-bit rows of d = 128 with eight, which spill three) 168."""
+    seen = 0
+    for name, k in kernels().items():
+        m = re.search(r"decode_chunk_kernelILi(\d)ELi(\d+)ELi([48])ELb(\d)ELi4E", name)
+        if not m:
+            continue
+        shape = m.groups()
+        if shape[1] == "64" and shape[0] in "12":
+            most, spills = 128 if shape[0] == "1" else 168, 0
+        elif shape == ("1", "128", "8", "1"):
+            most, spills = 168, 3
+        else:
+            continue
+        seen += 1
+        assert k[".vgpr_count"] <= most, (name, k[".vgpr_count"])
+        assert k[".vgpr_spill_count"] <= spills, (name, k[".vgpr_spill_count"])
+    assert seen == 9
+
+
 def test_held_windows_leave_room_for_their_workgroups():
     """256 registers let two workgroups of four wavefronts share a CU, as many as the LDS holds.  With 128 rows
     of d = 128 held in 128 of them the statistics spill a few (the constants of the groups that are done over),
