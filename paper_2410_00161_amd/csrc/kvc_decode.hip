@@ -283,7 +283,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   const int tid = threadIdx.x, lane = tid & 63, w = NW == 1 ? 0 : tid >> 6;
   extern __shared__ __align__(16) char smem_raw[];
   DecodeItem it;
-  int Tc;                                // tokens the work list was cut at (<= A.T)
+  int word = 0;                          // meeting word of the head in a call without a list
   const int T = NW == 4 ? A.T : A.Ts;    // tokens this launch sizes its LDS arrays for
   int32_t* slot_words = A.slot_word;     // of this list
   int rec = 0;                           // record of this item
@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
       }
     if (!found) return;
     it = sl.it;
-    Tc = sl.T;
+    word = sl.word;
     rec = blockIdx.x;   // (no list: the records' room serves the heads that meet)
   } else {
     const int total_items = A.header[HW_TOTAL_ITEMS];
@@ -313,7 +313,6 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
       if (A.ctx[ge] == 0)
         for (int i = tid; i < R * HD; i += NT) A.out[(size_t)ge * R * HD + i] = 0.0f;
     }
-    Tc = A.header[HW_CHUNK_T];
     // (A long item's record is where the workgroup's index says: in a small call asked for together with the
     // header words.  In a large one the workgroups beyond the last item pay more for it than the others
     // gain, 64 x 8192 tokens at 8x 1451 us against 1445.)
@@ -332,9 +331,8 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   const int g = uniform(it.g), t0 = uniform(it.t0), n_tok = uniform(it.n_tok), nch = uniform(it.nch);
   it.pbase = uniform(it.pbase);
   it.pad[0] = uniform(it.pad[0]);
-  it.pad[1] = uniform(it.pad[1]);
-  Tc = uniform(Tc);
-  if ((unsigned)g >= (unsigned)A.D.G || n_tok <= 0 || n_tok > T || t0 < 0 || nch <= 0 || Tc < 64 || Tc > A.T ||
+  const int Tc = uniform(it.pad[1]);     // tokens of the head's chunks but the last
+  if ((unsigned)g >= (unsigned)A.D.G || n_tok <= 0 || n_tok > T || t0 < 0 || nch <= 0 || Tc < 16 || Tc > A.T ||
       (nch > 1 && (it.pbase < 0 || it.pbase + nch > A.cap)))
     return;  // not a record this call wrote
   const int C_now = A.plan ? A.ctx[g] : 0;   // (looked at below, behind the other loads)
@@ -389,7 +387,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     return;
   }
   const bool single = nch == 1;
-  int32_t* const arrived = A.self_list ? A.header + HW_MEET + it.pad[1] : slot_words + it.pbase;
+  int32_t* const arrived = A.self_list ? A.header + HW_MEET + uniform(word) : slot_words + it.pbase;
   int32_t* const started = arrived + (A.self_list ? 0 : 1);
   const int one_started = A.self_list ? 1 << kMeetBits : 1;
   int32_t* const call = &A.items[rec].pad[2];    // where this chunk is called, when all of its head have arrived

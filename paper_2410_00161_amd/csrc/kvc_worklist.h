@@ -13,8 +13,8 @@ struct DecodeItem {   // 32 bytes
   int n_tok;    // tokens in the chunk
   int nch;      // chunks of the head
   int pbase;    // first partial-result slot of the head (heads of more than one chunk)
-  int pad[3];   // [0]: the head's length the list was made for (lists kept by kvc_decode_plan); [1]: without a list, the
-                // head's meeting word; [2]: where a chunk of a head that meets is called
+  int pad[3];   // [0]: the head's length the list was made for (lists kept by kvc_decode_plan); [1]: tokens of the head's
+                // chunks but the last; [2]: where a chunk of a head that meets is called
 };
 
 struct DecodeArgs {
@@ -68,6 +68,16 @@ __device__ __forceinline__ int size_class(int n, int T) {
   return cls;
 }
 
+// Tokens of the chunks of a head of C, cut to at most T: as many chunks as full ones would make (or fewer), all
+// of one length but the last.  The chunks of a head wait for one another, so one that is much shorter would
+// hold its place on a CU for nothing (3256 heads of 395 tokens in 32-bit rows, cut at 384: 384 and 11 tokens
+// 385 us, 208 and 187 313; 310 when chunks did not wait and a second launch combined them).
+__device__ __forceinline__ int cut_tokens(int C, int T, int b) {
+  if (C <= T) return T;
+  const int nch = (C + T - 1) / T, g = max(16, b);   // (chunks start on blocks and on groups of 16 tokens; T is a multiple of 64)
+  return ((C + nch - 1) / nch + g - 1) & ~(g - 1);
+}
+
 // Pass 1 of the work list: number of items per size class.
 static __global__ void __launch_bounds__(256) decode_count_kernel(DecodeArgs A) {
   __shared__ int bins[17];   // [16] = partial-result slots wanted
@@ -78,10 +88,15 @@ static __global__ void __launch_bounds__(256) decode_count_kernel(DecodeArgs A) 
     const int C = A.ctx[sel_to_g(A.D, A.l0, A.nl, gi)];
     const int nfull = C / A.T, rem = C - nfull * A.T;
     const int nch = nfull + (rem ? 1 : 0);
-    const bool together = !A.all_partials && nch > 1;
-    if (nfull) atomicAdd(&bins[0], together ? nch : nfull);
-    if (rem && !together) atomicAdd(&bins[size_class(rem, A.T)], 1);
-    if (nch > 1 || (A.all_partials && nch > 0)) atomicAdd(&bins[16], nch);
+    if (!A.all_partials && nch > 1) {
+      const int Th = cut_tokens(C, A.T, A.D.b), n = (C + Th - 1) / Th;
+      atomicAdd(&bins[0], n);
+      atomicAdd(&bins[16], n);
+    } else {
+      if (nfull) atomicAdd(&bins[0], nfull);
+      if (rem) atomicAdd(&bins[size_class(rem, A.T)], 1);
+      if (A.all_partials && nch > 0) atomicAdd(&bins[16], nch);
+    }
   }
   __syncthreads();
   if (threadIdx.x < 16 && bins[threadIdx.x]) atomicAdd(&A.header[HW_DEC_BINS + threadIdx.x], bins[threadIdx.x]);
@@ -117,7 +132,7 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
   }
   __syncthreads();
   const int gi = blockIdx.x * 256 + tid;
-  const int T = A.T;
+  int T = A.T;   // (of the head's chunks, below)
   int g = 0, C = 0, nfull = 0, rem = 0, nch = 0, cls = 0;
   int my_full = 0, my_rem = 0, my_p = 0;  // offsets inside this workgroup's claims
   if (gi < A.gsel) {
@@ -126,7 +141,11 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     nfull = C / T;
     rem = C - nfull * T;
     nch = nfull + (rem ? 1 : 0);
-    if (!A.all_partials && nch > 1) { nfull = nch; rem = 0; }   // side by side, in the class of full chunks
+    if (!A.all_partials && nch > 1) {   // side by side, in the class of full chunks
+      T = cut_tokens(C, T, A.D.b);
+      nfull = nch = (C + T - 1) / T;
+      rem = 0;
+    }
     cls = rem ? size_class(rem, T) : 0;
     if (nfull) my_full = atomicAdd(&want[0], nfull);
     if (rem) my_rem = atomicAdd(&want[cls], 1);       // class 0 never holds a remainder
@@ -153,7 +172,7 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     const int at = base[0] + got[0] + my_full;
     if (at < 0 || at + nfull > A.cap) return;
     for (int c = 0; c < nfull; ++c) {
-      DecodeItem it = {g, c * T, min(T, C - c * T), nch, pbase, {0, 0, 0}};
+      DecodeItem it = {g, c * T, min(T, C - c * T), nch, pbase, {0, T, 0}};
       const int place = at + (A.rotate_chunks ? (c + g) % nfull : c);
       A.items[place] = it;
       if (slotted && c < 2) A.slot_word[pbase + c] = 0;
@@ -162,7 +181,7 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
   if (rem) {
     const int at = base[cls] + got[cls] + my_rem;
     if (at < 0 || at >= A.cap) return;
-    DecodeItem it = {g, nfull * T, rem, nch, pbase, {0, 0, 0}};
+    DecodeItem it = {g, nfull * T, rem, nch, pbase, {0, T, 0}};
     A.items[at] = it;
   }
 }
@@ -257,7 +276,11 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     nfull = listed / T;
     rem = listed - nfull * T;
     nch = nfull + (rem ? 1 : 0);
-    if (!A.all_partials && nch > 1) { nfull = nch; rem = 0; }   // side by side, in the class of full chunks
+    if (!A.all_partials && nch > 1) {   // side by side, in the class of full chunks
+      T = cut_tokens(listed, T, A.D.b);
+      nfull = nch = (listed + T - 1) / T;
+      rem = 0;
+    }
     cls = rem ? size_class(rem, T) : 0;
     if (rem) atomicAdd(&bins[cls], 1);
   }
@@ -298,7 +321,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     const int at = base[0] + full_at;
     if (at < 0 || at + nfull > cap) return;
     for (int c = 0; c < nfull; ++c) {
-      DecodeItem it = {g, c * T, min(T, listed - c * T), nch, pbase, {C, 0, 0}};
+      DecodeItem it = {g, c * T, min(T, listed - c * T), nch, pbase, {C, T, 0}};
       const int place = at + (A.rotate_chunks ? (c + g) % nfull : c);
       items[place] = it;
       if (slotted && c < 2) slot_word[pbase + c] = 0;
@@ -307,7 +330,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   if (rem) {
     const int at = base[cls] + atomicAdd(&cur[cls], 1);
     if (at < 0 || at >= cap) return;
-    DecodeItem it = {g, nfull * T, rem, nch, pbase, {C, 0, 0}};
+    DecodeItem it = {g, nfull * T, rem, nch, pbase, {C, T, 0}};
     items[at] = it;
   }
 }
@@ -320,7 +343,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
 // remainders meet on one CU, 256 ragged heads of 2048 KVs on average 62 -> 77 us; and at 512 heads
 // the prologue of every workgroup, empty ones too, costs what the launch does.)
 constexpr int kSelfListHeads = 64;
-struct SelfList { DecodeItem it; int T; int C; int g; };   // item, chunk length; this lane's head and length (g = -1: none)
+struct SelfList { DecodeItem it; int word; int C; int g; };   // item, its head's meeting word; this lane's head and length (g = -1: none)
 __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, SelfList& out) {
   const int lane = threadIdx.x & 63;
   int g = -1, C = 0;
@@ -332,7 +355,8 @@ __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, SelfList& 
   if (A.adapt_T) {
     T = small_call_chunk(A.T, wave_sum_long(C), __popcll(__ballot(C > 0)), wave_max(C));
   }
-  const int nch = C / T + (C % T ? 1 : 0);
+  T = cut_tokens(C, T, A.D.b);
+  const int nch = (C + T - 1) / T;
   const int split = nch > 1 ? nch : 0;
   const int si = wave_prefix_i(split);   // inclusive
   const int P = __builtin_amdgcn_readlane(si, 63);
@@ -343,13 +367,15 @@ __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, SelfList& 
   } else if (nch == 1 && x - P == __popcll(whole & ((1ull << lane) - 1ull))) {
     t0 = 0;
   }
-  out.T = T; out.C = C; out.g = g;
+  out.C = C; out.g = g;
   const unsigned long long has = __ballot(t0 >= 0);
   if (has == 0) return false;
   const int src = __builtin_ctzll(has);
+  const int Th = __builtin_amdgcn_readlane(T, src);
+  out.word = src;
   out.it = DecodeItem{__builtin_amdgcn_readlane(g, src), __builtin_amdgcn_readlane(t0, src), 0,
-                      __builtin_amdgcn_readlane(nch, src), __builtin_amdgcn_readlane(si - split, src), {0, src, 0}};
-  out.it.n_tok = min(T, __builtin_amdgcn_readlane(C, src) - out.it.t0);
+                      __builtin_amdgcn_readlane(nch, src), __builtin_amdgcn_readlane(si - split, src), {0, Th, 0}};
+  out.it.n_tok = min(Th, __builtin_amdgcn_readlane(C, src) - out.it.t0);
   return true;
 }
 
