@@ -80,6 +80,8 @@ __device__ __forceinline__ void for_each_metric(const float* __restrict__ metric
   }
 }
 
+// `rows` (the last pass, few heads): the head's rows in front of every digit and at it, which are those below the
+// threshold and at it once the segment's digit is known.
 // One workgroup (NTH threads: 256, or 1024 when there are few, long heads) per heads_per_wg
 // consecutive head instances, one after the other.  Counts a
 // head's entries below the prefix found so far and histograms the next digit of those that
@@ -94,7 +96,7 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
                                                         const int32_t* __restrict__ ctx,
                                                         const int32_t* __restrict__ seq_seg,
                                                         int32_t* __restrict__ seg_hist, SegPicks picks,
-                                                        int32_t* seg_state, int32_t* header) {
+                                                        int32_t* seg_state, int32_t* header, int2* __restrict__ rows) {
   __shared__ int hist[256];
   __shared__ int below_s;
   __shared__ int smem[NTH / 64 + 1];
@@ -145,7 +147,11 @@ __global__ void __launch_bounds__(NTH) rank_hist_kernel(Dims D, int pass, int pr
     __syncthreads();
     const int c = tid < 256 ? hist[tid] : 0;
     const int ex = block_exclusive_scan<NTH>(c, smem, nullptr) + below_s;
-    if (tid < 256) rows_acc += min(ncand, (ex + c) >> lb) - min(ncand, ex >> lb);
+    const int lt = min(ncand, ex >> lb), here = min(ncand, (ex + c) >> lb) - lt;
+    if (tid < 256) {
+      rows_acc += here;
+      if (rows) rows[(size_t)g * 256 + tid] = make_int2(lt, here);
+    }
     __syncthreads();   // hist and below_s are reused by the next head
   }
   flush();
@@ -162,7 +168,7 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
                                                              const int32_t* __restrict__ ctx,
                                                              const int32_t* __restrict__ seq_seg,
                                                              int32_t* __restrict__ seg_hist, SegPicks picks,
-                                                             int32_t* seg_state, int32_t* header) {
+                                                             int32_t* seg_state, int32_t* header, int2* __restrict__ rows) {
   __shared__ __align__(16) int hist_all[4][256];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int* hist = hist_all[wv];   // this wavefront's own: its LDS accesses happen in program order
@@ -257,7 +263,9 @@ __global__ void __launch_bounds__(256) rank_hist_wave_kernel(Dims D, int pass, i
     const int cc[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      rows_acc[k] += min(ncand, (ex + cc[k]) >> lb) - min(ncand, ex >> lb);
+      const int lt = min(ncand, ex >> lb), here = min(ncand, (ex + cc[k]) >> lb) - lt;
+      rows_acc[k] += here;
+      if (rows) rows[(size_t)g * 256 + 4 * lane + k] = make_int2(lt, here);
       ex += cc[k];
     }
   }
@@ -451,28 +459,48 @@ __global__ void __launch_bounds__(256) rank_grant_kernel(Dims D, const int32_t* 
 }
 
 // Ranks of the ties and the grant in one workgroup, for at most 1024 head instances (a prompt's):
-// one launch in place of the three of a device-wide scan and one more, ~4.5 us each.
+// one launch in place of the three of a device-wide scan and one more, ~4.5 us each.  With `rows` the
+// last digit is picked here too, and a head's rows below the threshold and at it are looked up where the last
+// pass left them for every digit: a launch less that read every metric once more (256 heads of 16384
+// tokens 255 -> 250 us a prompt; rounds of 40 heads of 1379 tokens 74.9 -> 70.5, 48 of 8334 87.5 -> 82.5, 112 of 1212
+// 73.4 -> 68.9, 1024 of 4096 219.6 -> 210.9).
 constexpr int kRankSmallHeads = 1024;
-__global__ void __launch_bounds__(1024) rank_grant_small_kernel(Dims D, const int32_t* __restrict__ seq_seg,
-                                                                const int32_t* __restrict__ seg_state,
+__global__ void __launch_bounds__(1024) rank_grant_small_kernel(Dims D, int protect, const int32_t* __restrict__ ctx,
+                                                                const int32_t* __restrict__ seq_seg, SegPicks picks,
+                                                                int32_t* seg_state, const int2* __restrict__ rows,
                                                                 const int32_t* __restrict__ rows_tie,
                                                                 int32_t* __restrict__ evict_rows,
                                                                 int32_t* __restrict__ selected,
                                                                 const int32_t* __restrict__ header) {
   __shared__ int smem[1024 / 64 + 1];
   __shared__ int off[kRankSmallHeads];
-  const int g = threadIdx.x;
-  const int ties = g < D.G ? rows_tie[g] : 0;
+  __shared__ int take_s[kRankSmallHeads], remain_s[kRankSmallHeads], digit_s[kRankSmallHeads];   // per segment, of which there are no more than heads
+  const int g = threadIdx.x, sg = g < D.G ? seq_seg[g / (D.Lyr * D.Hk)] : 0;
+  for (int i = threadIdx.x >> 6; i < picks.nseg; i += 1024 / 64) {
+    const SegKey key = seg_key(picks, 4, i, seg_state, false);   // (the histogram's digit picked, or a launch has)
+    if ((threadIdx.x & 63) == 0) { take_s[i] = key.take; remain_s[i] = key.remain; digit_s[i] = (int)(key.prefix & 255u); }
+  }
+  __syncthreads();
+  int ties = 0, below = 0;
+  if (g < D.G) {
+    if (rows) {
+      if (max(0, (ctx[g] + D.b - 1) / D.b - protect) > 0 && take_s[sg] > 0) {
+        const int2 r = rows[(size_t)g * 256 + digit_s[sg]];
+        below = r.x;
+        ties = r.y;
+      }
+    } else {
+      below = evict_rows[g];
+      ties = rows_tie[g];
+    }
+  }
   off[g] = block_exclusive_scan<1024>(ties, smem, nullptr);
   __syncthreads();
   if (g >= D.G) return;
   if (header[HW_STATUS] != KVC_OK) { evict_rows[g] = 0; return; }
-  const int sg = seq_seg[g / (D.Lyr * D.Hk)];
-  const int32_t* stt = seg_state + sg * 8;
-  const int take = stt[RS_TAKE];
-  if (g == stt[RS_FIRSTG]) selected[sg] = take;
-  if (take <= 0) { evict_rows[g] = 0; return; }
-  evict_rows[g] += max(0, min(ties, stt[RS_REMAIN] - (off[g] - off[stt[RS_FIRSTG]])));   // rows below the threshold are there
+  const int take = take_s[sg], first = seg_state[sg * 8 + RS_FIRSTG];
+  if (g == first) selected[sg] = take;
+  evict_rows[g] = take <= 0 ? 0 : below + max(0, min(ties, remain_s[sg] - (off[g] - off[first])));
 }
 
 // ---------------------------------------------------------------------------
@@ -767,6 +795,8 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
   const bool fused = D.G <= 1024 && 3 * hist_words <= (size_t)D.N * D.b * D.r;
   auto hist_of = [&](int pass) { return fused && pass > 0 ? (int32_t*)W.stash + (pass - 1) * hist_words : W.seg_hist; };
   const int n_more = fused ? (int)(3 * hist_words) : 0;
+  // ... and behind them, of every head and digit of the last pass, the rows
+  int2* rows = fused && 3 * hist_words + (size_t)D.G * 512 <= (size_t)D.N * D.b * D.r ? (int2*)((int32_t*)W.stash + 3 * hist_words) : nullptr;
   const int n_init = std::max(std::max(D.G, nseg * 256), n_more);
   hipLaunchKernelGGL(segments_init_kernel, dim3((n_init + 255) / 256), dim3(256), 0, s, D, seg_offsets, nseg, seq_seg,
                      W.seg_hist, W.seg_state, evict_rows, selected, W.header, (int32_t*)W.stash, n_more);
@@ -782,14 +812,15 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
     if ((size_t)D.maxb * D.b <= kRankWaveTokens)
       hipLaunchKernelGGL(rank_hist_wave_kernel, dim3((D.G + 4 * hpw - 1) / (4 * hpw)), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header, pass == 3 ? rows : nullptr);
     else if (D.G <= 1024)
       hipLaunchKernelGGL(rank_hist_kernel<1024>, dim3(D.G), dim3(1024), 0, s, D, pass, protect_tail_blocks, 1,
-                         st->metric, st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
+                         st->metric, st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header,
+                         pass == 3 ? rows : nullptr);
     else
       hipLaunchKernelGGL(rank_hist_kernel<256>, dim3((D.G + hpw - 1) / hpw), dim3(256), 0, s, D, pass,
                          protect_tail_blocks, hpw, st->metric,
-                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header);
+                         st->block_table, st->ctx_len, seq_seg, hist_of(pass), picks, W.seg_state, W.header, nullptr);
     KVC_LAUNCH_CHECK();
     if (fused) continue;
     hipLaunchKernelGGL(rank_pick_kernel, dim3(nseg), dim3(256), 0, s, pass, budget, W.seg_hist, W.seg_state,
@@ -801,7 +832,9 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
     }
   }
   const SegPicks picks = {fused ? hist_of(3) : nullptr, budget, nseg};
-  if ((size_t)D.maxb * D.b <= kRankWaveTokens)
+  if (rows) {
+    // (nothing more to read: the last pass has left what the grant needs)
+  } else if ((size_t)D.maxb * D.b <= kRankWaveTokens)
     hipLaunchKernelGGL(rank_tie_wave_kernel, dim3((D.G + 3) / 4), dim3(256), 0, s, D, protect_tail_blocks, st->metric,
                        st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);
   else if (D.G <= 1024)   // a workgroup per CU or so: as wide as it goes (256 heads of 16384 tokens 9.4 -> 6.0 us)
@@ -812,8 +845,9 @@ int kvc_evict_rank_select(const kvc_config* cfg, const kvc_state* st, const int3
                        st->block_table, st->ctx_len, seq_seg, picks, W.seg_state, evict_rows, W.off_b);
   KVC_LAUNCH_CHECK();
   if (D.G <= kRankSmallHeads) {
-    hipLaunchKernelGGL(rank_grant_small_kernel, dim3(1), dim3(1024), 0, s, D, seq_seg, W.seg_state, W.off_b, evict_rows,
-                       selected, W.header);
+    // (the ties' launch has picked the last digit, where there was one)
+    hipLaunchKernelGGL(rank_grant_small_kernel, dim3(1), dim3(1024), 0, s, D, protect_tail_blocks, st->ctx_len, seq_seg,
+                       SegPicks{rows ? picks.hist : nullptr, budget, nseg}, W.seg_state, rows, W.off_b, evict_rows, selected, W.header);
   } else {
     rc = device_exclusive_scan(RowTieFn{W.off_b}, D.G, W.tile_sums, W.off_a, nullptr, s);
     if (rc != KVC_OK) return rc;
