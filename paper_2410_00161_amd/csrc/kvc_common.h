@@ -27,16 +27,13 @@ enum HeaderWord {
   HW_SCRATCH1 = 6,
   HW_ARRIVED = 7,     // workgroups of an append's first launch that are done (its last one sets it back to zero)
   HW_SHORT_ITEMS = 8,  // decode work items short enough for the one-wavefront launch
-  HW_TOTAL_PARTIALS = 9,  // per-chunk partial-result slots in use = chunks of heads of more than one chunk
-  HW_CHUNK_T = 10,     // chunk length the work list in place was cut with (tokens)
   HW_PLAN_BASE = 11,   // a kept work list's first record
   // decode work-list block: item counts per size class, per-class cursors, cursor of the
   // per-chunk partial results.  All zero between calls (the chunk kernel clears it).
   HW_DEC_BINS = 12,    // [16]
   HW_DEC_CUR = 28,     // [16]
   HW_DEC_PCUR = 44,    // [1]
-  HW_DEC_PTOT = 45,    // [1] partial-result slots wanted, counted in pass 1
-  HW_DEC_END = 46,
+  HW_DEC_END = 45,
   // meeting words of the heads of a decode that keeps no work list (chunks started and arrived).
   // Zero between calls.
   HW_MEET = 64,        // [64]

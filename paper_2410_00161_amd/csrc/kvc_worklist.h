@@ -80,8 +80,8 @@ __device__ __forceinline__ int cut_tokens(int C, int T, int b) {
 
 // Pass 1 of the work list: number of items per size class.
 static __global__ void __launch_bounds__(256) decode_count_kernel(DecodeArgs A) {
-  __shared__ int bins[17];   // [16] = partial-result slots wanted
-  if (threadIdx.x < 17) bins[threadIdx.x] = 0;
+  __shared__ int bins[16];
+  if (threadIdx.x < 16) bins[threadIdx.x] = 0;
   __syncthreads();
   const int gi = blockIdx.x * 256 + threadIdx.x;
   if (gi < A.gsel) {
@@ -91,16 +91,13 @@ static __global__ void __launch_bounds__(256) decode_count_kernel(DecodeArgs A) 
     if (!A.all_partials && nch > 1) {
       const int Th = cut_tokens(C, A.T, A.D.b), n = (C + Th - 1) / Th;
       atomicAdd(&bins[0], n);
-      atomicAdd(&bins[16], n);
     } else {
       if (nfull) atomicAdd(&bins[0], nfull);
       if (rem) atomicAdd(&bins[size_class(rem, A.T)], 1);
-      if (A.all_partials && nch > 0) atomicAdd(&bins[16], nch);
     }
   }
   __syncthreads();
   if (threadIdx.x < 16 && bins[threadIdx.x]) atomicAdd(&A.header[HW_DEC_BINS + threadIdx.x], bins[threadIdx.x]);
-  if (threadIdx.x == 16 && bins[16]) atomicAdd(&A.header[HW_DEC_PTOT], bins[16]);
 }
 
 // Pass 2: every head instance claims its places and writes its items; a head that holds no
@@ -126,8 +123,6 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
     if (blockIdx.x == 0) {
       A.header[HW_TOTAL_ITEMS] = run;
       A.header[HW_SHORT_ITEMS] = shorts;
-      A.header[HW_TOTAL_PARTIALS] = A.header[HW_DEC_PTOT];
-      A.header[HW_CHUNK_T] = A.T;
     }
   }
   __syncthreads();
@@ -215,7 +210,7 @@ __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long to
 constexpr int kSmallWorklistHeads = 1024;
 template <bool PLAN>
 static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(DecodeArgs A) {
-  __shared__ int bins[16], base[16], cur[17], ptot;
+  __shared__ int bins[16], base[16], cur[17];
   __shared__ unsigned long long tokens;
   __shared__ int live, longest;
   __shared__ unsigned long long before;
@@ -226,7 +221,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   DecodeItem* items = A.items + (size_t)layer * A.plan_stride;
   int32_t* slot_word = A.slot_word + (size_t)layer * A.plan_stride;
   int cap = A.cap;
-  if (tid == 0) { ptot = 0; tokens = 0; live = 0; longest = 0; before = 0; }
+  if (tid == 0) { tokens = 0; live = 0; longest = 0; before = 0; }
   if (tid < 16) bins[tid] = 0;
   if (tid < 17) cur[tid] = 0;
   __syncthreads();
@@ -268,7 +263,6 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     cap = min(cap, A.plan_cap - start);
     if (tid == 0) header[HW_PLAN_BASE] = start;
   }
-  if (tid == 0) header[HW_CHUNK_T] = T;
   if (tid < A.gsel) {
     // (A full head planned one token longer: its row ends in front of that token.  Its records, which a
     // decode looks up in the row before it compares the length, end there too.)
@@ -291,7 +285,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   int full_at = 0, slots_at = 0;
   if (lane == 63) {
     if (full_to) { atomicAdd(&bins[0], full_to); full_at = atomicAdd(&cur[0], full_to); }
-    if (slots_to) { atomicAdd(&ptot, slots_to); slots_at = atomicAdd(&cur[16], slots_to); }
+    if (slots_to) slots_at = atomicAdd(&cur[16], slots_to);
   }
   full_at = __builtin_amdgcn_readlane(full_at, 63) + full_to - nfull;
   const int pbase = slotted ? __builtin_amdgcn_readlane(slots_at, 63) + slots_to - nch : 0;
@@ -301,7 +295,6 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     if (tid < 16) base[tid] = to - n;
     const int run = __builtin_amdgcn_readlane(to, 63), longs = A.short_class > 0 ? __builtin_amdgcn_readlane(to, A.short_class - 1) : 0;
     if (tid == 0) {
-      header[HW_TOTAL_PARTIALS] = ptot;
       // (a list that does not fit, which lengths the pool can hold never make, is one no decode takes)
       header[HW_TOTAL_ITEMS] = PLAN && run > cap ? 0x7fffffff : run;
       header[HW_SHORT_ITEMS] = run - longs;
