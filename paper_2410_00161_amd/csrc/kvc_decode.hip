@@ -1150,21 +1150,26 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
   const bool mf = decode_uses_mfma(esz, D.r, D.d);   // a per-wavefront operand tile in LDS
   const int groups = decode_groups(esz, D.d, D.r, D.b % 16 == 0);
   int T = knob ? knob : default_chunk(D);
+  const int T_two = T;
+  int T_fits = T;
   if (!knob && groups > 2)
-    while (T > 1024 && decode_lds_bytes(T, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsUnits / groups * kLdsUnit) T -= 64;
-  const int T_default = T;
+    while (T_fits > 1024 && decode_lds_bytes(T_fits, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsUnits / groups * kLdsUnit) T_fits -= 64;
   bool shrunk = false, device_side = false;
   if (!knob) {
     // a call over few head instances (one layer at a time) has too few long chunks to fill the
     // chip: shorten them until full rows would give a few thousand work items
+    // (counted from the length that two workgroups leave each other, also where more share a CU: counted
+    // from the shorter one, 960 heads of 1250 KVs and rows of 20000, r = 8, d = 128, fp8, took the two
+    // launches of a large call, 121 us where one takes 80)
     const long long want_items = 6144;
     // (halved and rounded up to whole 64-token strips: a chunk starts on a block boundary)
     while (T > 256 && (long long)gsel * (((long long)D.maxb * D.b + T - 1) / T) < want_items)
       T = ((T / 2) + 63) & ~63;
-    shrunk = T < T_default;
+    shrunk = T < T_two;
+    T = T < T_fits ? T : T_fits;
     // ... unless the one-launch work list serves the call: it sees the lengths themselves, not
     // just what the tables have room for, and picks the length (at most the default) on the device
-    if (shrunk && gsel <= kSmallWorklistHeads) { T = T_default; device_side = true; }
+    if (shrunk && gsel <= kSmallWorklistHeads) { T = T_fits; device_side = true; }
   }
   // the default is sized so that two workgroups share a CU's LDS with blocks of 16 tokens; shorter
   // blocks put more block ids next to the exps (eight heads, d = 128, blocks of 8: 82 628 bytes): a shorter

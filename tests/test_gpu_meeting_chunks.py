@@ -79,3 +79,25 @@ def test_kept_lists_meet_again():
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
         np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), plain.cache.metric.cpu().numpy())
     assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+
+
+@pytest.mark.parametrize("r,d,dtype", [(8, 64, "bf16"), (8, 128, "fp8"), (4, 64, "fp8")])
+def test_few_heads_are_counted_in_the_same_chunks_everywhere(r, d, dtype):
+    """Whether a call has few heads for the room of its rows, and can have a kept list, does not depend on how
+    many workgroups share a CU: rows of five chunks, 1024 heads a layer."""
+    from paper_2410_00161_amd.session import KvcSession
+    two = 3456 if r == 8 else 6144
+    maxb = 5 * two // 16   # 1024 rows of five chunks are few, of the ten or more shorter ones they would not be
+    ctx = torch.full((1024,), 40, dtype=torch.int32)
+    ctx[7], ctx[500], ctx[1023] = 9000, 0, 3000
+    shape = W.Shape(128, 1, 8, r, d, 16, W.pool_size(ctx, 16, 1.1, 3), maxb, dtype)
+    cache = W.make_cache(shape, ctx, 5)
+    q = W.make_query(shape, 5)
+    plain, sess = KvcSession(cache.clone()), KvcSession(cache.clone())
+    assert B.kvc_get_decode_chunk(sess.cfg) < two
+    sess.decode_plan()   # (refused: an exception)
+    want = plain.paged_decode(q.to(plain.device))
+    got = sess.paged_decode_planned(q.to(sess.device), 0)
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+    np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), plain.cache.metric.cpu().numpy())
