@@ -1163,7 +1163,10 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
     // launches of a large call, 121 us where one takes 80)
     const long long want_items = 6144;
     // (halved and rounded up to whole 64-token strips: a chunk starts on a block boundary)
-    while (T > 256 && (long long)gsel * (((long long)D.maxb * D.b + T - 1) / T) < want_items)
+    // (over a thousand heads fill the chip whole: their chunks only have to even out unequal lengths, and
+    // shorter ones have to meet.  2990 heads of 609 KVs, r = 4, 16-bit rows: 317 us in chunks of 192, whole 173)
+    const int least = gsel > kSmallWorklistHeads ? 768 : 256;
+    while (T > least && (long long)gsel * (((long long)D.maxb * D.b + T - 1) / T) < want_items)
       T = ((T / 2) + 63) & ~63;
     shrunk = T < T_two;
     T = T < T_fits ? T : T_fits;

@@ -188,9 +188,13 @@ static __global__ void __launch_bounds__(256) decode_items_kernel(DecodeArgs A) 
 // Where that leaves every head whole there is nothing to combine and it stays (256 heads of 2048
 // KVs: 54 us, 67 when cut in two); heads that are cut anyway are cut to 1/512, so that the two
 // workgroups a CU has room for even out what the other leaves (256 ragged heads of up to 16384
-// KVs, 2048 on average: 77 -> 71 us; 1/384, 1/768 and 1/1024: 77, 74 and 74).  Cutting costs (the
-// exps of a split head go through the workspace), so nothing shorter than 128 tokens (8 heads of
-// 1000 KVs: 18.2 us at 256, 15.8 at 128 and at 64).
+// KVs, 2048 on average: 77 -> 71 us; 1/384, 1/768 and 1/1024: 77, 74 and 74).  Cutting costs: the
+// chunks of a head meet, which takes longer the more there are, so they stay at 512 tokens as long as
+// that is no more than 1/256 (8 heads of 8786 KVs, r = 8, 16-bit rows: 25 us in chunks of 192, 19 in
+// 384; 12 of 5082 on average, the longest of far more, r = 1: 25 and 16; 64 of 3093, fp8: 24 in 512,
+// 28 in 1024), and nothing is shorter than 128 (8 heads of 1000 KVs: 18.2 us at 256, 15.8 at 128 and
+// at 64, with a second launch that combined them).
+constexpr int kMeetingChunk = 512;
 constexpr int kSmallCallChunk = 128;
 __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long tokens, int live, int longest) {
   const unsigned long long want = tokens + tokens / 4;
@@ -201,7 +205,7 @@ __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long to
     return min(T_max, max(kSmallCallChunk, t64));
   };
   const int T = length(min(512, max(256, live)));
-  return longest <= T ? T : length(512);
+  return longest <= T ? T : max(length(512), min(length(256), min(kMeetingChunk, T_max)));
 }
 
 // Both passes in one workgroup, for calls over at most kSmallWorklistHeads head instances (one
