@@ -35,7 +35,7 @@ enum HeaderWord {
   HW_DEC_PCUR = 44,    // [1]
   HW_DEC_END = 45,
   // meeting words of the heads of a decode that keeps no work list (chunks started and arrived).
-  // Zero between calls.
+  // Zero between calls, here and in the layers' blocks (see meet_word).
   HW_MEET = 64,        // [64]
   HW_WORDS = 128
 };

@@ -101,3 +101,27 @@ def test_few_heads_are_counted_in_the_same_chunks_everywhere(r, d, dtype):
     assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
     np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
     np.testing.assert_array_equal(sess.cache.metric.cpu().numpy(), plain.cache.metric.cpu().numpy())
+
+
+@pytest.mark.parametrize("layers", [1, 2, 5, 70])
+def test_meeting_words_beside_kept_lists(layers):
+    """Decodes without a list meet in the header blocks of the layers' kept lists: neither disturbs the other."""
+    from paper_2410_00161_amd.session import KvcSession
+    ctx = torch.tensor([1500, 1, 900, 129, 2000, 128, 640, 300], dtype=torch.int32).repeat(layers)
+    shape = W.Shape(2, layers, 4, 4, 64, 16, W.pool_size(ctx, 16, 1.1, 3), 130, "bf16")
+    cache = W.make_cache(shape, ctx, 5)
+    q = W.make_query(shape, 5)
+    plain, sess = KvcSession(cache.clone()), KvcSession(cache.clone())
+    sess.decode_plan()
+    for layer in {0, layers // 2, layers - 1}:
+        want = plain.paged_decode(q.to(plain.device), layer_begin=layer, layer_end=layer + 1, accumulate_metric=False).clone()
+        for turn in range(2):
+            got = torch.zeros_like(want)
+            sess.paged_decode_planned(q.to(sess.device), layer, accumulate_metric=False, out=got)
+            again = torch.zeros_like(want)
+            sess.paged_decode(q.to(sess.device), layer_begin=layer, layer_end=layer + 1, accumulate_metric=False, out=again)
+            rows = slice(None), slice(layer, layer + 1)
+            view = (2, layers, -1)
+            np.testing.assert_array_equal(got.view(view)[rows].cpu().numpy(), want.view(view)[rows].cpu().numpy())
+            np.testing.assert_array_equal(again.view(view)[rows].cpu().numpy(), want.view(view)[rows].cpu().numpy())
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
