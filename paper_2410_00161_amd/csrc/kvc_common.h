@@ -34,8 +34,9 @@ enum HeaderWord {
   HW_DEC_CUR = 28,     // [16]
   HW_DEC_PCUR = 44,    // [1]
   HW_DEC_END = 45,
-  // meeting words of the heads of a decode that keeps no work list (chunks started and arrived).
-  // Zero between calls, here and in the layers' blocks (see meet_word).
+  // meeting words of the heads of a decode that keeps no work list (chunks started and arrived): in this block and in
+  // the next one, the first layer's, which every config has in the same place.  Zero between calls of any
+  // config (see meet_word).
   HW_MEET = 64,        // [64]
   HW_WORDS = 128
 };

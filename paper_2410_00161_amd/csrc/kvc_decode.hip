@@ -387,7 +387,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     return;
   }
   const bool single = nch == 1;
-  int32_t* const arrived = A.self_list ? A.header + meet_word(A, uniform(word)) : slot_words + it.pbase;
+  int32_t* const arrived = A.self_list ? A.status + meet_word(uniform(word)) : slot_words + it.pbase;
   int32_t* const started = arrived + (A.self_list ? 0 : 1);
   const int one_started = A.self_list ? 1 << kMeetBits : 1;
   int32_t* const call = &A.items[rec].pad[2];    // where this chunk is called, when all of its head have arrived
@@ -1325,8 +1325,6 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   A.header = W.header;
   A.status = W.header;
   A.plan = 0; A.plan_stride = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
-  A.meet_mask = 0;   // (the header and one block per layer behind it)
-  while (A.meet_mask < kSelfListHeads - 1 && 2 * A.meet_mask + 2 <= 1 + D.Lyr) A.meet_mask = 2 * A.meet_mask + 1;
   A.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D.d));
 
   int T = 0;
@@ -1456,10 +1454,10 @@ int kvc_paged_decode_static(const kvc_config* cfg, const kvc_state* st, const vo
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
   if (rc != KVC_OK) return rc;
-  // The array keeps what the last call left, possibly a call with another config: the header words
-  // (item counts, work-list cursors) start from zero again.  A fill kernel, not a memset, so that
+  // The array keeps what the last call left, possibly a call that was cut short: the header words (item counts,
+  // work-list cursors) and the meeting words start from zero again.  A fill kernel, not a memset, so that
   // the call may be recorded into a HIP graph.
-  const int words = HW_WORDS * (1 + cfg->num_layers);   // (the layers' header blocks too: chunks meet there, see meet_word)
+  const int words = 2 * HW_WORDS;   // (chunks meet in the first layer's block too, see meet_word)
   hipLaunchKernelGGL(zero_words_kernel, dim3((words + 63) / 64), dim3(64), 0, (hipStream_t)stream, (int32_t*)ws, words);
   KVC_LAUNCH_CHECK();
   return paged_decode_impl(cfg, st, q, out, layer_begin, layer_end, accumulate_metric, ws, stream);

@@ -41,7 +41,6 @@ struct DecodeArgs {
   float* part_acc;
   float* stash;
   int32_t* header;
-  int meet_mask;          // see meet_word
   // Work lists kept from one launch for every layer (kvc_decode_plan): layer l has its own header
   // block at header + l * HW_WORDS and its own stretch of the records of items / slot_word.
   int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
@@ -341,12 +340,14 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
 // remainders meet on one CU, 256 ragged heads of 2048 KVs on average 62 -> 77 us; and at 512 heads
 // the prologue of every workgroup, empty ones too, costs what the launch does.)
 constexpr int kSelfListHeads = 64;
-// Where the chunks of head x meet without a list: a word of the header block or of the blocks that the layers'
-// kept lists have behind it (no list uses those words; they are zero between calls).  Atomics on one line are run
-// one after the other, so heads are spread over as many blocks as there are (64 heads of 55075 KVs, 8-bit rows,
-// r = 8, d = 64: 190 us with all words on two lines, 137 spread; a layer of 8 heads of 2048: 17.7 us a layer, 17.1).
-__device__ __forceinline__ int meet_word(const DecodeArgs& A, int x) {
-  return (x & A.meet_mask) * HW_WORDS + HW_MEET + (x & ~A.meet_mask);
+// Where the chunks of head x meet without a list: a word (from the workspace's first on) of the header block or of
+// the first layer's behind it, whose other words serve kept lists.  Nothing but these calls writes it, whatever
+// configs the calls on a workspace have, and every config's reset clears it; further blocks are another config's
+// tables and records.  Atomics on one line are run one after the other, so heads are dealt out to the four lines of
+// 128 bytes that the two blocks have free, then to the second halves of these.
+static_assert(HW_DEC_END <= HW_MEET && HW_MEET + kSelfListHeads <= HW_WORDS && kSelfListHeads == 8 * 8, "room for the meeting words");
+__device__ __forceinline__ int meet_word(int x) {
+  return (x & 1) * HW_WORDS + HW_MEET + (x & 2) * 16 + (x & 4) * 4 + (x >> 3);
 }
 struct SelfList { DecodeItem it; int word; int C; int g; };   // item, its head's meeting word; this lane's head and length (g = -1: none)
 __device__ __forceinline__ bool self_item(const DecodeArgs& A, int x, SelfList& out) {
