@@ -197,7 +197,10 @@ int kvc_append(const kvc_config* cfg, const kvc_state* st, const void* k_new,
  * attended slot's metric grows by the sum over the r query heads of its group
  * ("Query Group Compression") of p^2 ("Squared Attention Metric"; p with
  * KVC_L1), p being the normalised probability ("Continual Compression").
- * Asynchronous; no device-side error exists for this call.                     */
+ * Asynchronous.  A workspace that was never reset, or that two calls used at once, can leave
+ * KVC_ERR_ARG in the status word (kvc_poll_status): output rows and metrics of that call and
+ * of the later ones are then not to be trusted (keys, values and tables are not touched)
+ * until kvc_workspace_reset, and a new plan for kept lists.                      */
 int kvc_paged_decode(const kvc_config* cfg, const kvc_state* st, const void* q, float* out,
                      int layer_begin, int layer_end, int accumulate_metric,
                      void* ws, void* stream);
@@ -229,7 +232,8 @@ int kvc_paged_decode_planned(const kvc_config* cfg, const kvc_state* st, const v
  * holds one until the process ends).  KVC_ERR_UNSUPPORTED when kvc_workspace_bytes(cfg) exceeds
  * that size - such caches go through kvc_paged_decode with a caller's workspace.  Allocates
  * nothing and calls no allocating routine.  All calls on one GPU share the array: two calls
- * that overlap there (different streams, different threads) race; order them.  Asynchronous. */
+ * that overlap there (different streams, different threads) race; order them (no status tells:
+ * every call starts the array's header afresh).  Asynchronous.                   */
 #define KVC_STATIC_SCRATCH_BYTES (32u << 20)
 int kvc_paged_decode_static(const kvc_config* cfg, const kvc_state* st, const void* q, float* out,
                             int layer_begin, int layer_end, int accumulate_metric, void* stream);

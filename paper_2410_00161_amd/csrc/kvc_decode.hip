@@ -177,10 +177,13 @@ __device__ __forceinline__ void exps_published(const float* stash, size_t slot, 
 // Before, chunks left 2 r bytes of exps per KV and a second launch combined them: 4 x 131072 tokens at 8x, r = 8
 // 4015 -> 3490 us (the exps were 16 of 528 bytes a KV; what is written costs this chip ten times what is
 // read does), 16 sequences layer by layer 1174 -> 1080, a step of two sequences of 512 tokens 25 -> 21.7.
-// Started and arrived are halves of one header word per head in a call without a work list, else two
-// words where the list keeps the head's partial-result slots.
+// Started and arrived are halves of one word per head: a header word in a call without a work list, else one
+// where the list keeps the head's partial-result slots (the first two, in rows of so many chunks that a half could run over).
+// The words are zero between calls.  Where they are not (a workspace never reset, or in use by two calls at
+// once) too few or too many chunks seem to have come: a count beyond the head's chunks, an arrival ahead of its start,
+// chunks that all left or a call that does not come say so in the status.
 constexpr int kMeetBits = 16, kMeetMost = (1 << kMeetBits) - 1;   // of a half
-constexpr int kMeetLooks = 1 << 19;   // for the call, ~0.5 us each: a workspace never reset, or in use by two calls at once
+constexpr int kMeetLooks = 1 << 19;   // for the call, ~0.5 us each
 constexpr int kMeetStarts = 6;        // for the last chunk to start, ~1 us each: one that does soon is worth the wait
 
 constexpr int kDecodeThreads = 256;
@@ -382,14 +385,15 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
   }
   // A head of a kept list must still be as long as the plan took it to be (the record carries that length).
   // A stale plan is an argument error, found here and left in the status word.
+  auto argument_error = [&]() { if (A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG; };
   if (A.plan && C_now != it.pad[0]) {
-    if (tid == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
+    if (tid == 0) argument_error();
     return;
   }
   const bool single = nch == 1;
   int32_t* const arrived = A.self_list ? A.status + meet_word(uniform(word)) : slot_words + it.pbase;
-  int32_t* const started = arrived + (A.self_list ? 0 : 1);
-  const int one_started = A.self_list ? 1 << kMeetBits : 1;
+  int32_t* const started = arrived + (A.packed ? 0 : 1);
+  const int one_started = A.packed ? 1 << kMeetBits : 1;
   int32_t* const call = &A.items[rec].pad[2];    // where this chunk is called, when all of its head have arrived
   if (!single && tid == 0) {
     publish_i32(call, 0);
@@ -794,8 +798,10 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     }
   }
   if (!single && tid == 0) {
-    auto all = [&]() { return (int)(A.self_list ? seen >> kMeetBits : seen) == nch; };
+    auto count = [&]() { return A.packed ? seen >> kMeetBits : seen; };
+    auto all = [&]() { return count() == (uint32_t)nch; };
     for (int looks = 1; looks < kMeetStarts && !all(); ++looks) seen = (uint32_t)published_i32(started);
+    if (count() > (uint32_t)nch) argument_error();
     s_say[0] = all();
 #pragma unroll
     for (int hh = 0; hh < R; ++hh)   // (the sum's sign says that the chunk does not wait)
@@ -842,32 +848,38 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     if (A.accumulate && !waits) each_token([&](size_t slot, float (&e)[R]) { exps_publish<R>(A.stash, slot, e); });
     publish_wait();
     __syncthreads();
+    // (what the first wavefront finds on its way is looked at in the end, away from those that wait)
+    uint32_t was = 0, begun = 1;
+    bool came = true;
     if (w == 0) {
-      int was = 0;
-      if (lane == 0) was = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      was = __builtin_amdgcn_readfirstlane(was);
-      if (A.self_list) was &= kMeetMost;
+      if (lane == 0) was = (uint32_t)__hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      was = (uint32_t)__builtin_amdgcn_readfirstlane((int)was);
+      begun = A.packed ? was >> kMeetBits : (uint32_t)nch;
+      if (A.packed) was &= kMeetMost;
       bool go = waits;
-      if (was == nch - 1) {
+      if (was == (uint32_t)nch - 1) {
         for (int c = lane; c < nch; c += 64)
           if (c != ci) publish_i32(call + (c - ci) * (int)(sizeof(DecodeItem) / 4), 1);
         if (lane == 0) {
-          __hip_atomic_fetch_add(arrived, -nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_fetch_add(started, -nch * one_started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (!A.packed) __hip_atomic_fetch_add(arrived, -nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_fetch_add(started, A.packed ? -nch * (one_started + 1) : -nch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!waits) {   // somebody has to
+          bool one = false;
+          for (int c = lane; c < nch; c += 64) one |= published_i32((const int32_t*)A.part_ml + ((size_t)it.pbase + c) * R * 2 + 1) >= 0;
+          came = __any(one);
         }
       } else if (waits) {
-        for (int looks = 0; !published_i32(call); ++looks) {
-          if (looks == kMeetLooks) {
-            go = false;
-            if (lane == 0 && A.status[HW_STATUS] == KVC_OK) A.status[HW_STATUS] = KVC_ERR_ARG;
-            break;
-          }
-        }
+        for (int looks = 0; !published_i32(call); ++looks)
+          if (looks == kMeetLooks) { go = came = false; break; }
       }
       if (lane == 0) s_say[1] = go;
     }
     __syncthreads();
-    if (!s_say[1]) return;   // (its part is out: the others see to it)
+    auto look_back = [&]() {
+      if (w == 0 && (was >= begun || begun > (uint32_t)nch || !came)) argument_error();
+    };
+    if (!s_say[1]) { look_back(); return; }   // (its part is out: the others see to it)
     // ---- every chunk of the head has arrived ----
     const float* ml = A.part_ml + (size_t)it.pbase * R * 2;
     const float* accs = A.part_acc + (size_t)it.pbase * R * HD;
@@ -973,6 +985,7 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
       each_token(weigh);
     }
     share_put(own);
+    look_back();
     if (stay == nch) return;
     // chunks that did not wait: every stay-th of them from this one's rank on
     const int C = A.ctx[g];
@@ -1325,6 +1338,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   A.header = W.header;
   A.status = W.header;
   A.plan = 0; A.plan_stride = 0; A.plan_cap = 0; A.ctx_plus = 0; A.self_list = 0;
+  A.packed = (size_t)D.maxb * D.b / kMinChunk < (size_t)kMeetMost;
   A.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D.d));
 
   int T = 0;
@@ -1386,7 +1400,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     A.header += (size_t)layer_begin * HW_WORDS;
     A.items += (size_t)layer_begin * A.plan_stride;
     A.slot_word += (size_t)layer_begin * A.plan_stride;
-  } else if (small_call && A.gsel <= kSelfListHeads && (size_t)D.maxb * D.b / kMinChunk < (size_t)kMeetMost) {
+  } else if (small_call && A.gsel <= kSelfListHeads && A.packed) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {
     hipLaunchKernelGGL(decode_worklist_small_kernel<false>, dim3(1), dim3(1024), 0, s, A);

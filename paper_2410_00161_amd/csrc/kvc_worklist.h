@@ -46,6 +46,7 @@ struct DecodeArgs {
   int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
   int plan_stride;        // records of a layer's stretch; 0: it starts where its header block says
   int plan_cap;           // records of all layers the workspace holds
+  int packed;             // rows of fewer than kMeetMost chunks: a head's counts of chunks are halves of one word
   int self_list;          // no work list: every workgroup finds its own item from the lengths (at most kSelfListHeads heads)
   int ctx_plus;           // the plan is made for heads ctx_plus tokens longer than they are now
   int32_t* status;        // the workspace's own header (status word), whatever `header` points at

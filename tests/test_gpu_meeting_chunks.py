@@ -125,3 +125,53 @@ def test_meeting_words_beside_kept_lists(layers):
             np.testing.assert_array_equal(got.view(view)[rows].cpu().numpy(), want.view(view)[rows].cpu().numpy())
             np.testing.assert_array_equal(again.view(view)[rows].cpu().numpy(), want.view(view)[rows].cpu().numpy())
     assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+
+
+@pytest.mark.parametrize("kept", [False, True], ids=["no_list", "kept_list"])
+@pytest.mark.parametrize("word", [1 << 16, 3 << 16, 1, 2, 0x10001, 0x20002, 0x50003, 7 << 16, -1, -(1 << 16), 0x5a5a5a5a], ids=hex)
+def test_words_that_are_not_zero_are_reported(word, kept):
+    """Counts left by something else, as in a workspace that was never reset or that two calls at once have used: never
+    an unfinished head with the status OK.  A reset (and, of a kept list, a new plan) makes the workspace good again."""
+    from paper_2410_00161_amd.session import KvcSession
+    ctx = torch.tensor([3000, 1, 900, 1290, 4000, 128, 2000, 640], dtype=torch.int32)   # (up to 32 chunks)
+    shape = W.Shape(1, 1, 8, 4, 128, 16, W.pool_size(ctx, 16, 1.1, 3), 260, "bf16")
+    cache = W.make_cache(shape, ctx, 5)
+    q = W.make_query(shape, 5)
+    sess = KvcSession(cache)
+
+    def call():
+        out = torch.full_like(sess.out, 7.0)
+        if kept:
+            return sess.paged_decode_planned(q.to(sess.device), 0, accumulate_metric=False, out=out).cpu().numpy()
+        return sess.paged_decode(q.to(sess.device), accumulate_metric=False, out=out).cpu().numpy()
+
+    if kept:
+        sess.decode_plan()
+    want = call()
+    words = sess.ws.view(torch.int32)
+    if kept:   # the words of the list's partial-result slots, in the workspace behind its records
+        tokens, items = shape.num_blocks * 16, shape.num_blocks * 16 // 64 + 8 + 1
+        up = lambda n: -(-n // 256) * 256  # noqa: E731
+        tiles = max(shape.num_blocks, 8) // 2048 + 2   # (one more block than there are, in tiles of 2048)
+        at = (up(512) + up(512) + up(4 * tiles) + 2 * up(4 * 9) + up(4 * 8) + up(32 * items)) // 4
+        n = items
+    else:      # the second halves of the header block and of the first layer's
+        at, n = 64, 192
+    planted = words[at:at + n].clone()
+    if kept:
+        planted += word
+    else:
+        planted[:64] += word
+        planted[128:] += word
+    words[at:at + n] = planted
+    for turn in range(2):
+        got = call()
+        reported = B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_ERR_ARG
+        assert reported or np.array_equal(got, want)
+        assert reported or turn == 0
+        words[0] = 0   # (the status alone)
+    B.kvc_workspace_reset(sess.cfg, sess.ws)
+    if kept:
+        sess.decode_plan()
+    np.testing.assert_array_equal(call(), want)
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
