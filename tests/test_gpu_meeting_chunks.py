@@ -127,6 +127,64 @@ def test_meeting_words_beside_kept_lists(layers):
     assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
 
 
+def _words_of(shape):
+    """Where the temporaries of a decode begin in the workspace, in 32-bit words."""
+    S, Lyr, G = shape.num_seqs, shape.num_layers, shape.G
+    items = shape.num_blocks * shape.block_size // 64 + G + 1
+    sizes = dict(header=512, plan_hdr=512 * Lyr, tile_sums=4 * ((max(shape.num_blocks, G) + 1) // 2048 + 2), off_a=4 * (G + 1),
+                 off_b=4 * (G + 1), held=4 * G, items=32 * items, slot_word=4 * items, part_ml=8 * shape.group_size * items)
+    at, out = 0, {}
+    for name, n in sizes.items():
+        out[name] = at // 4
+        at += -(-n // 256) * 256
+    return out
+
+
+def test_chunks_that_leave_in_calls_of_few_heads():
+    """More chunks than the chip has places for, at the library's own chunk length: without a list and from a kept one
+    some chunks leave, the others finish for them, twice in a row and with the same bits."""
+    from paper_2410_00161_amd.session import KvcSession
+    S, Hk, r, d = 2, 4, 8, 64   # (8-bit rows: chunks of 1664 tokens, 1024 places; a head of 1322 chunks among shorter ones)
+    ctx = torch.tensor([70000, 2200003, 1665, 40, 3329, 90017, 1664, 130000], dtype=torch.int32)
+    shape = W.Shape(S, 1, Hk, r, d, 16, W.pool_size(ctx, 16, 1.01, 3), -(-int(ctx.max()) // 16) + 1, "fp8")
+    cache = W.make_cache(shape, ctx, 21, device="cuda:0")
+    q = W.make_query(shape, 21).cuda()
+    want, p2 = torch.empty(S * Hk, r, d, dtype=torch.float64), torch.zeros(shape.num_blocks, 16, dtype=torch.float64, device="cuda:0")
+    for g in range(S * Hk):
+        C, ids = int(ctx[g]), cache.block_table.view(S * Hk, -1)[g]
+        ids = ids[ids >= 0].long()
+        k, v = ((t.view(torch.uint8)[ids].view(torch.float8_e4m3fn).to(torch.float64).reshape(-1, d)[:C]) for t in (cache.k_cache, cache.v_cache))
+        p = torch.softmax(q.view(S * Hk, r, d)[g].double() @ k.t().contiguous() / d ** 0.5, dim=1)
+        want[g] = (p @ v).cpu()
+        sq = torch.zeros(ids.numel() * 16, dtype=torch.float64, device="cuda:0")
+        sq[:C] = (p * p).sum(0)
+        p2[ids] = sq.view(-1, 16)
+    first = None
+    for kept in (False, True):
+        sess = KvcSession(cache.clone())
+        if kept:
+            sess.decode_plan()
+        marks = sess.ws.view(torch.int32)[_words_of(shape)["part_ml"]:][:sum(n for n in (-(-int(c) // 1664) for c in ctx) if n > 1) * r * 2].view(-1, r, 2)
+        for turn in range(2):
+            marks.zero_()
+            out = sess.paged_decode_planned(q, 0) if kept else sess.paged_decode(q)
+            left = int((marks[:, 0, 1] < 0).sum())
+            print(f"[case] kept={kept} turn={turn}: {left} of {marks.shape[0]} chunks left", flush=True)
+            assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+            assert 0 < left < marks.shape[0] and bool((marks[:, :, 1] != 0).all())
+            got, metric = out.cpu().numpy().reshape(S * Hk, r, d), sess.cache.metric.double()
+            assert np.linalg.norm(got - want.numpy()) <= 2e-6 * np.linalg.norm(want.numpy())   # f32 sums
+            # exps of 16 bits: an increment is off by a few of their halves at most, and the sum over a head by what these cancel to
+            assert float((metric - (turn + 1) * p2).norm() / p2.norm()) <= (turn + 1) * 2.0 ** -12
+            np.testing.assert_allclose(metric.cpu().numpy(), (turn + 1) * p2.cpu().numpy(), rtol=0, atol=(turn + 1) * r * 2.0 ** -15)
+            bits = got, metric.cpu().numpy() / (turn + 1)
+            first = bits if first is None else first
+            np.testing.assert_array_equal(bits[0], first[0])
+            if turn == 0:
+                np.testing.assert_array_equal(bits[1], first[1])
+        del sess, marks
+
+
 @pytest.mark.parametrize("kept", [False, True], ids=["no_list", "kept_list"])
 @pytest.mark.parametrize("word", [1 << 16, 3 << 16, 1, 2, 0x10001, 0x20002, 0x50003, 7 << 16, -1, -(1 << 16), 0x5a5a5a5a], ids=hex)
 def test_words_that_are_not_zero_are_reported(word, kept):
@@ -149,14 +207,8 @@ def test_words_that_are_not_zero_are_reported(word, kept):
         sess.decode_plan()
     want = call()
     words = sess.ws.view(torch.int32)
-    if kept:   # the words of the list's partial-result slots, in the workspace behind its records
-        tokens, items = shape.num_blocks * 16, shape.num_blocks * 16 // 64 + 8 + 1
-        up = lambda n: -(-n // 256) * 256  # noqa: E731
-        tiles = max(shape.num_blocks, 8) // 2048 + 2   # (one more block than there are, in tiles of 2048)
-        at = (up(512) + up(512) + up(4 * tiles) + 2 * up(4 * 9) + up(4 * 8) + up(32 * items)) // 4
-        n = items
-    else:      # the second halves of the header block and of the first layer's
-        at, n = 64, 192
+    # the words of the list's partial-result slots, or the second halves of the header block and of the first layer's
+    at, n = (_words_of(shape)["slot_word"], shape.num_blocks * 16 // 64 + 8 + 1) if kept else (64, 192)
     planted = words[at:at + n].clone()
     if kept:
         planted += word
