@@ -1193,10 +1193,12 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
     const long long want_items = 6144;
     // (halved and rounded up to whole 64-token strips: a chunk starts on a block boundary)
     // (over a thousand heads fill the chip whole: their chunks only have to even out unequal lengths, and
-    // shorter ones have to meet.  2990 heads of 609 KVs, r = 4, 16-bit rows: 317 us in chunks of 192, whole 173)
+    // shorter ones have to meet, so they stay at 768 or more (896 with eight query heads).  2990
+    // heads of 609 KVs, r = 4, 16-bit rows: 317 us in chunks of 192, whole 173; 2048 of up to 600, r = 8, 174 in
+    // chunks of 448, 129 whole, 8-bit 121 and 80; of 2000 and 4000 level)
     const int least = gsel > kSmallWorklistHeads ? 768 : 256;
-    while (T > least && (long long)gsel * (((long long)D.maxb * D.b + T - 1) / T) < want_items)
-      T = ((T / 2) + 63) & ~63;
+    auto half = [&]() { return ((T / 2) + 63) & ~63; };
+    while (half() >= least && (long long)gsel * (((long long)D.maxb * D.b + T - 1) / T) < want_items) T = half();
     shrunk = T < T_two;
     T = T < T_fits ? T : T_fits;
     // ... unless the one-launch work list serves the call: it sees the lengths themselves, not

@@ -146,3 +146,14 @@ def test_small_pools_need_no_more_workspace_than_their_block_list_did():
     """A cache at the limit of the fixed scratch array: one head, 64 blocks, a table that fills the rest."""
     cfg = good_cfg(num_seqs=1, num_layers=1, num_kv_heads=1, group_size=1, num_blocks=64, max_blocks_per_head=8383940)
     assert B.kvc_workspace_bytes(cfg) <= 33554176 < B.KVC_STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("heads,row,r,chunk", [(1032, 1024, 4, 768), (2048, 1024, 4, 768), (1032, 1024, 8, 896), (2048, 1024, 8, 896), (2048, 6144, 8, 1728),
+                                               (8192, 1024, 8, 3456), (8192, 1024, 4, 6144)])
+def test_chunks_of_more_than_a_thousand_heads_are_not_cut_short(heads, row, r, chunk):
+    """Halved while full rows would make too few of them, but not below 768 tokens, whatever length they start from."""
+    L = B.lib()
+    cfg = good_cfg(num_seqs=heads // 8, num_layers=1, num_kv_heads=8, group_size=r, num_blocks=heads * row // 16, max_blocks_per_head=row // 16)
+    got = C.c_int(-1)
+    assert L.kvc_get_decode_chunk(C.byref(cfg), C.byref(got)) == B.KVC_OK
+    assert got.value == chunk
