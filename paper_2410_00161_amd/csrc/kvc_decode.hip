@@ -186,6 +186,7 @@ constexpr int kMeetBits = 16, kMeetMost = (1 << kMeetBits) - 1;   // of a half
 constexpr int kMeetLooks = 1 << 19;   // for the call, ~0.5 us each
 constexpr int kMeetStarts = 6;        // for the last chunk to start, ~1 us each: one that does soon is worth the wait
 
+constexpr int kCus = 256;
 constexpr int kDecodeThreads = 256;
 constexpr int kDecodeWaves = kDecodeThreads / 64;
 
@@ -1114,9 +1115,40 @@ __global__ void __launch_bounds__(256) decode_generic_kernel(DecodeArgs A) {
   }
 }
 
+// What the runtime is told and says about the kernel of four wavefronts, by whether blocks are of 16 tokens or more.
+template <int ESZ, int HD, int R>
+struct TiledKernel {
+  static inline LdsLimit limit[2];
+  static inline std::atomic<uint64_t> shared[2];   // workgroups that share a CU (its last byte), and with how much LDS
+  static auto of(bool b16) { return b16 ? decode_chunk_kernel<ESZ, HD, R, true, 4> : decode_chunk_kernel<ESZ, HD, R, false, 4>; }
+  static int places(bool b16, size_t lds) {   // of the whole chip; no bound when the runtime does not say
+    uint64_t v = shared[b16].load(std::memory_order_relaxed);
+    if (v >> 8 != lds) {
+      int n = 0;
+      if (limit[b16].need(lds, of(b16)) != KVC_OK ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, of(b16), kDecodeThreads, lds) != hipSuccess || n <= 0) return 0x7fffffff;
+      v = (uint64_t)lds << 8 | (uint64_t)(n < 255 ? n : 255);
+      shared[b16].store(v, std::memory_order_relaxed);
+    }
+    return (int)(v & 255) * kCus;
+  }
+};
+
+template <int ESZ, int HD>
+static int tiled_places(const Dims& D, size_t lds) {
+  const bool b16 = D.b % 16 == 0;
+  switch (D.r) {
+    case 1: return TiledKernel<ESZ, HD, 1>::places(b16, lds);
+    case 2: return TiledKernel<ESZ, HD, 2>::places(b16, lds);
+    case 4: return TiledKernel<ESZ, HD, 4>::places(b16, lds);
+    case 8: return TiledKernel<ESZ, HD, 8>::places(b16, lds);
+  }
+  return 0x7fffffff;
+}
+
 template <int ESZ, int HD, int R>
 static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_short, hipStream_t s) {
-  auto kern = (A.D.b % 16 == 0) ? decode_chunk_kernel<ESZ, HD, R, true, 4> : decode_chunk_kernel<ESZ, HD, R, false, 4>;
+  const auto kern = TiledKernel<ESZ, HD, R>::of(A.D.b % 16 == 0);
   auto kern_short = (A.D.b % 16 == 0) ? decode_chunk_kernel<ESZ, HD, R, true, 1> : decode_chunk_kernel<ESZ, HD, R, false, 1>;
   bool mf_short = decode_uses_mfma(ESZ, R, HD);
   if constexpr (ESZ == 1 && HD == 128 && R == 4)
@@ -1127,8 +1159,7 @@ static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_shor
   ProfilePair* pp = claim_profile_pair();
   if (pp) KVC_HIP(hipEventRecord(pp->a0, s));
   {  // above the default cap the kernel must be told how much it may take (per instantiation and device)
-    static LdsLimit limit[2];
-    const int rc = limit[A.D.b % 16 == 0].need(lds, kern);
+    const int rc = TiledKernel<ESZ, HD, R>::limit[A.D.b % 16 == 0].need(lds, kern);
     if (rc != KVC_OK) return rc;
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kDecodeThreads), lds, s, A);
@@ -1390,6 +1421,12 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   // length picked on the device is T (then the first bound holds), or at least 1.25 / 512 of all
   // tokens, or the 128-token floor with under 128 * 512 / 1.25 tokens in all: at most 512 / 1.25
   // full chunks either way, and one shorter item per head.
+  A.places = 0x7fffffff;
+  if (A.adapt_T && A.gsel > kSelfListHeads) {   // (fewer heads make 410 chunks and one each, at most)
+    if (esz == 1) A.places = D.d == 64 ? tiled_places<1, 64>(D, lds) : tiled_places<1, 128>(D, lds);
+    else if (esz == 2) A.places = D.d == 64 ? tiled_places<2, 64>(D, lds) : tiled_places<2, 128>(D, lds);
+    else A.places = D.d == 64 ? tiled_places<4, 64>(D, lds) : tiled_places<4, 128>(D, lds);
+  }
   const size_t most_tokens = std::min((size_t)D.N * D.b, (size_t)A.gsel * D.maxb * D.b);   // pool, or the rows of the heads called for
   const size_t bound_pool = (A.adapt_T ? std::max(most_tokens / T, (size_t)410) : most_tokens / T) + (size_t)A.gsel;
   auto items_of_rows = [&](size_t chunk) { return std::min(bound_pool, (size_t)A.gsel * (((size_t)D.maxb * D.b + chunk - 1) / chunk)); };

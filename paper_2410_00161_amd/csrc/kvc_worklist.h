@@ -29,6 +29,7 @@ struct DecodeArgs {
   int l0, nl, gsel;       // first layer, layer count, head instances selected
   int accumulate, T;      // metric on/off, chunk tokens (the most a chunk may hold when adapt_T is set)
   int adapt_T;            // the one-launch work list picks the chunk length from the lengths it sees (see there)
+  int places;             // workgroups of four wavefronts that the chip runs at once (where a list's chunks are to fit them)
   int log2b;              // block size is a power of two on the tiled path
   int cap;                // item records and partial-result slots the workspace holds
   int all_partials;       // give every head a partial-result slot range, not only split heads (else the chunks of a split
@@ -209,13 +210,31 @@ __device__ __forceinline__ int small_call_chunk(int T_max, unsigned long long to
   return longest <= T ? T : max(length(512), min(length(256), min(kMeetingChunk, T_max)));
 }
 
+// What the fraction cannot see is whether the chunks have places at once.  A few too many run by themselves in
+// the end, each as long as what ran before (chunks longer than T / 2: shorter ones, whole heads all of them, fill gaps).
+// Then T is the shortest that has places for all the longer ones at once, if the longest chunk has.  320 heads of
+// 1650 to 8250 KVs, r = 4, d = 128, 512 places: chunks of 3328 tokens (545 long ones) 156 us, of 3648 (509) 139, of 6144
+// (380) 163; 8-bit rows 103, 81 and 108.  Not two turns of as many chunks as there are places: 120 -> 108 us
+// at the best of sizes, slower at others.
+// long_chunks(T): chunks longer than T / 2 when heads are cut at T; no more, the longer T is.
+template <class Count>
+__device__ __forceinline__ int one_turn(int T, int T_max, int places, Count long_chunks) {
+  if (T >= T_max || long_chunks(T) <= places || long_chunks(T_max) > places) return T;
+  int lo = T / 64, hi = T_max / 64;   // too short; long enough
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (long_chunks(64 * mid) <= places) hi = mid; else lo = mid;
+  }
+  return 64 * hi;
+}
+
 // Both passes in one workgroup, for calls over at most kSmallWorklistHeads head instances (one
 // layer of a model, one prompt): one launch instead of two.  Leaves the header words as the
 // two-pass pair does.  (Measured with two heads per thread, 2048 heads: no faster than the pair.)
 constexpr int kSmallWorklistHeads = 1024;
 template <bool PLAN>
 static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(DecodeArgs A) {
-  __shared__ int bins[16], base[16], cur[17];
+  __shared__ int bins[16], base[16], cur[17], tally[16];
   __shared__ unsigned long long tokens;
   __shared__ int live, longest;
   __shared__ unsigned long long before;
@@ -227,13 +246,16 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   int32_t* slot_word = A.slot_word + (size_t)layer * A.plan_stride;
   int cap = A.cap;
   if (tid == 0) { tokens = 0; live = 0; longest = 0; before = 0; }
-  if (tid < 16) bins[tid] = 0;
+  if (tid < 16) { bins[tid] = 0; tally[tid] = 0; }
   if (tid < 17) cur[tid] = 0;
   __syncthreads();
   int g = 0, C = 0, listed = 0, nfull = 0, rem = 0, nch = 0, cls = 0;
   if (tid < A.gsel) {
     g = sel_to_g(A.D, A.l0 + layer, A.nl, tid);
     C = A.ctx[g] + A.ctx_plus;
+    // (A full head planned one token longer: its row ends in front of that token.  Its records, which a
+    // decode looks up in the row before it compares the length, end there too.)
+    listed = PLAN ? (int)min((long long)C, (long long)A.D.maxb * A.D.b) : C;
   }
   // Where stretches of equal length, for what full rows hold, do not fit: the layer's records start
   // behind the most that the layers before it can need from their lengths (a full chunk holds at least
@@ -259,6 +281,15 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     if ((tid & 63) == 0 && t) { atomicAdd(&tokens, t); atomicAdd(&live, lv); atomicMax(&longest, lm); }
     __syncthreads();
     T = small_call_chunk(A.T, tokens, live, longest);
+    if (longest > T && tokens + (unsigned long long)live * T > (unsigned long long)A.places * T) {   // (tokens / T and one per head at most)
+      int step = 0;   // (nine at most: chunks are up to 8192 tokens)
+      T = one_turn(T, A.T, A.places, [&](int t) {
+        const int n = wave_sum_i(listed > t / 2 ? (listed + t - 1) / t : 0);
+        if ((tid & 63) == 0 && n) atomicAdd(&tally[step], n);
+        __syncthreads();
+        return tally[step++];
+      });
+    }
   }
   if (placed) {
     const unsigned long long at = before / kSmallCallChunk + (unsigned long long)layer * A.gsel;
@@ -269,9 +300,6 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
     if (tid == 0) header[HW_PLAN_BASE] = start;
   }
   if (tid < A.gsel) {
-    // (A full head planned one token longer: its row ends in front of that token.  Its records, which a
-    // decode looks up in the row before it compares the length, end there too.)
-    listed = PLAN ? (int)min((long long)C, (long long)A.D.maxb * A.D.b) : C;
     nfull = listed / T;
     rem = listed - nfull * T;
     nch = nfull + (rem ? 1 : 0);

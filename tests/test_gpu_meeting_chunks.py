@@ -227,3 +227,31 @@ def test_words_that_are_not_zero_are_reported(word, kept):
         sess.decode_plan()
     np.testing.assert_array_equal(call(), want)
     assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+
+
+@pytest.mark.parametrize("kept", [False, True], ids=["list", "kept_list"])
+def test_long_chunks_have_places_at_once(kept):
+    """32-bit rows of d = 128 with eight query heads leave one workgroup a CU, 256 in all: 72 heads, cut by the fraction of
+    their tokens into some 320 chunks of nearly one length, are cut longer; few short heads more or less do not count."""
+    from paper_2410_00161_amd.session import KvcSession
+    g0 = torch.Generator().manual_seed(2)
+    ctx = (1100 + 2000 * torch.rand(72, generator=g0)).to(torch.int32)
+    ctx[3], ctx[40], ctx[71] = 0, 1, 130
+    shape = W.Shape(9, 1, 8, 8, 128, 16, W.pool_size(ctx, 16, 1.1, 3), 200, "f32")
+    cache = W.make_cache(shape, ctx, 5)
+    st = oracle_state(cache)
+    q = W.make_query(shape, 5)
+    want = O.paged_decode(st, q.double().numpy())
+    sess = KvcSession(cache)
+    if kept:
+        sess.decode_plan()
+        out = sess.paged_decode_planned(q.to(sess.device), 0).cpu().numpy()
+    else:
+        out = sess.paged_decode(q.to(sess.device)).cpu().numpy()
+    assert B.kvc_poll_status(sess.cfg, sess.ws) == B.KVC_OK
+    assert np.linalg.norm(out - want.reshape(out.shape)) <= 2e-6 * np.linalg.norm(want)
+    live = st.free_map == 0
+    np.testing.assert_allclose(sess.cache.metric.cpu().numpy()[live], st.metric[live], rtol=0, atol=8 * 2.0 ** -15)
+    items = int(sess.ws.view(torch.int32)[_words_of(shape)["plan_hdr"] + 3 if kept else 3])   # items listed
+    tokens = int(ctx.sum())
+    assert -(-tokens // 512) > 256 and 72 < items <= 256 + 3
