@@ -1214,6 +1214,10 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
   int T_fits = T;
   if (!knob && groups > 2)
     while (T_fits > 1024 && decode_lds_bytes(T_fits, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsUnits / groups * kLdsUnit) T_fits -= 64;
+  // ... but not where rows then need two chunks that do not all have places, and whole ones do (512 heads of 3210 KVs,
+  // r = 8, d = 128, fp8: 105 us in halves, whole 94; 512 of 3400, d = 64, bf16: 106 and 88)
+  const long long row_tokens = (long long)D.maxb * D.b;
+  if (row_tokens > T_fits && row_tokens <= T_two && gsel <= 2 * kCus && 2 * gsel > groups * kCus) T_fits = T_two;
   bool shrunk = false, device_side = false;
   if (!knob) {
     // a call over few head instances (one layer at a time) has too few long chunks to fill the

@@ -255,3 +255,11 @@ def test_long_chunks_have_places_at_once(kept):
     items = int(sess.ws.view(torch.int32)[_words_of(shape)["plan_hdr"] + 3 if kept else 3])   # items listed
     tokens = int(ctx.sum())
     assert -(-tokens // 512) > 256 and 72 < items <= 256 + 3
+
+
+@pytest.mark.parametrize("heads,two", [(376, False), (392, True), (512, True), (520, False)])
+def test_rows_of_one_chunk_of_two_workgroups(heads, two):
+    """Rows that a chunk for two workgroups a CU holds whole, one for three does not: whole where all heads then have
+    places at once, and halves would not."""
+    cfg = B.make_config(heads // 8, 1, 8, 8, 128, 16, heads * 204, 204, "fp8")   # 3264 tokens
+    assert B.kvc_get_decode_chunk(cfg) == (3456 if two else 1920)
