@@ -345,7 +345,7 @@ def run_decode_config(spec, dev, keep_session=False):
         print(f"bench.py: device-side error {status} ({B.status_string(status)})", file=sys.stderr)
         sys.exit(1)
     ms_total = t0.elapsed_time(t1)
-    chunk_ms, short_ms, combine_ms = B.kvc_profile_collect(4096)
+    chunk_ms, short_ms, _ = B.kvc_profile_collect(4096)
     B.kvc_profile_begin(0)
 
     # Between two compression rounds every head grows by exactly one KV per step, so the
@@ -385,7 +385,6 @@ def run_decode_config(spec, dev, keep_session=False):
     if len(chunk_ms):
         chunk_ms = np.array(chunk_ms, dtype=np.float64)
         short_ms = np.array(short_ms, dtype=np.float64)
-        combine_ms = np.array(combine_ms, dtype=np.float64)
         chunk_alg_s = chunk_alg[::prof_every][:len(chunk_ms)]          # the steps that were timed
         short_alg_s = short_alg[::prof_every][:len(chunk_ms)]
         ach = float(chunk_alg_s.mean() / (chunk_ms.mean() * 1e-3) / 1e9)
@@ -400,8 +399,7 @@ def run_decode_config(spec, dev, keep_session=False):
                     "short_items_GBps": float(short_alg_s.mean() / (short_ms.mean() * 1e-3) / 1e9) if short_ms.mean() > 0 else None,
                     "short_items_max_tokens": short_T,
                     "decode_call_GBps": float((kv_per_step[::prof_every][:len(chunk_ms)] * bytes_kv).mean() /
-                                              ((chunk_ms + short_ms + combine_ms).mean() * 1e-3) / 1e9),
-                    "combine_kernel_ms": float(combine_ms.mean())}
+                                              ((chunk_ms + short_ms).mean() * 1e-3) / 1e9)}
 
     evict = None
     if evict_events:

@@ -19,8 +19,8 @@ extern "C" {
 
 /* kvc_profile_begin(n) makes the next n calls of kvc_paged_decode record HIP event pairs on
  * their stream around each of its launches: the chunk kernel over the long items (it streams
- * nearly all of K and V) and the same kernel over the short items; the third pair stands for a launch that
- * combined the chunks of a head, which they now do themselves (nothing is between its events).  n = 0 switches recording off and releases the events.  At most 4096 calls.              */
+ * nearly all of K and V) and the same kernel over the short items.  n = 0 switches recording off
+ * and releases the events.  At most 4096 calls.                                          */
 int kvc_profile_begin(int n);
 
 /* Pauses (0) or resumes (non-zero) the recording without releasing anything, so that a
@@ -29,7 +29,7 @@ int kvc_profile_enable(int on);
 
 /* Waits for the recorded events and writes up to `cap` durations in milliseconds to the host
  * arrays chunk_ms, short_ms and combine_ms (each may be NULL), returning the number of recorded
- * calls in *count (host).                                                               */
+ * calls in *count (host).  No launch combines the chunks of a head any more: combine_ms gets zeros. */
 int kvc_profile_collect(float* chunk_ms, float* short_ms, float* combine_ms, int cap, int* count);
 
 /* Bandwidth probe: reads `bytes` (a multiple of 16) of device memory at `src` once with 16-byte

@@ -34,7 +34,7 @@ namespace kvc {
 static std::atomic<int> g_chunk_tokens{0};  // 0 = default; set by kvc_set_decode_chunk
 
 // optional event pairs around the decode kernels (kvc_profile_begin / _collect)
-struct ProfilePair { hipEvent_t a0, a1, s0, s1, b0, b1; };  // long-item, short-item launches; b0 to b1 is empty (no launch combines)
+struct ProfilePair { hipEvent_t a0, a1, s0, s1; };  // long-item, short-item launches
 static std::mutex g_prof_lock;
 static ProfilePair* g_prof = nullptr;
 static int g_prof_cap = 0, g_prof_used = 0, g_prof_on = 1;
@@ -1170,8 +1170,7 @@ static int launch_tiled(const DecodeArgs& A, int grid, size_t lds, int grid_shor
                        decode_lds_bytes(A.Ts, R, HD, A.D.b, 1, mf_short), s, A);
     KVC_LAUNCH_CHECK();
   }
-  if (pp) { KVC_HIP(hipEventRecord(pp->s1, s)); KVC_HIP(hipEventRecord(pp->b0, s)); }
-  if (pp) KVC_HIP(hipEventRecord(pp->b1, s));
+  if (pp) KVC_HIP(hipEventRecord(pp->s1, s));
   return KVC_OK;
 }
 
@@ -1280,7 +1279,6 @@ int kvc_profile_begin(int n) {
     for (int i = 0; i < g_prof_cap; ++i) {
       hipEventDestroy(g_prof[i].a0); hipEventDestroy(g_prof[i].a1);
       hipEventDestroy(g_prof[i].s0); hipEventDestroy(g_prof[i].s1);
-      hipEventDestroy(g_prof[i].b0); hipEventDestroy(g_prof[i].b1);
     }
     delete[] g_prof;
     g_prof = nullptr;
@@ -1292,7 +1290,6 @@ int kvc_profile_begin(int n) {
   for (int i = 0; i < n; ++i) {
     KVC_HIP(hipEventCreate(&g_prof[i].a0)); KVC_HIP(hipEventCreate(&g_prof[i].a1));
     KVC_HIP(hipEventCreate(&g_prof[i].s0)); KVC_HIP(hipEventCreate(&g_prof[i].s1));
-    KVC_HIP(hipEventCreate(&g_prof[i].b0)); KVC_HIP(hipEventCreate(&g_prof[i].b1));
   }
   g_prof_cap = n;
   return KVC_OK;
@@ -1309,11 +1306,11 @@ int kvc_profile_collect(float* chunk_ms, float* short_ms, float* combine_ms, int
   std::lock_guard<std::mutex> hold(g_prof_lock);
   *count = g_prof_used;
   for (int i = 0; i < g_prof_used && i < cap; ++i) {
-    KVC_HIP(hipEventSynchronize(g_prof[i].b1));
+    KVC_HIP(hipEventSynchronize(g_prof[i].s1));
     float ms = 0.0f;
     if (chunk_ms) { KVC_HIP(hipEventElapsedTime(&ms, g_prof[i].a0, g_prof[i].a1)); chunk_ms[i] = ms; }
     if (short_ms) { KVC_HIP(hipEventElapsedTime(&ms, g_prof[i].s0, g_prof[i].s1)); short_ms[i] = ms; }
-    if (combine_ms) { KVC_HIP(hipEventElapsedTime(&ms, g_prof[i].b0, g_prof[i].b1)); combine_ms[i] = ms; }
+    if (combine_ms) combine_ms[i] = 0.0f;   // (no launch combines: chunks finish their heads themselves)
   }
   return KVC_OK;
 }

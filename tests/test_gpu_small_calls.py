@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from oracle import kvc_oracle as O
+from paper_2410_00161_amd import binding as B
 from paper_2410_00161_amd import workloads as W
 from helpers import oracle_state
 
@@ -54,3 +55,21 @@ def test_few_heads(name, kw, lengths):
         assert (got[:, [0, 2]] == 7.0).all(), "rows of other layers were written"
         live = st.free_map == 0
         np.testing.assert_allclose(sess.cache.metric.cpu().numpy().astype(np.float64)[live], st.metric[live], rtol=0, atol=2e-3)
+
+
+def test_recorded_calls_have_no_time_for_a_launch_that_does_not_exist():
+    """Two launches are recorded, of the long items and of the short ones; the third output is zeros."""
+    from paper_2410_00161_amd.session import KvcSession
+    ctx = torch.tensor([9000, 300], dtype=torch.int32)
+    shape = W.Shape(1, 1, 2, 4, 128, 16, W.pool_size(ctx, 16, 1.1, 3), 600, "bf16")
+    sess = KvcSession(W.make_cache(shape, ctx, 3))
+    q = W.make_query(shape, 3).to(sess.device)
+    B.kvc_profile_begin(4)
+    try:
+        for _ in range(3):
+            sess.paged_decode(q)
+        chunk, short, combine = B.kvc_profile_collect(4)
+    finally:
+        B.kvc_profile_begin(0)
+    assert len(chunk) == len(short) == len(combine) == 3
+    assert min(chunk) > 0 and combine == [0.0] * 3
