@@ -355,9 +355,8 @@ int kvc_set_decode_chunk(int tokens);
  * lengths of the heads.  Host only.                                              */
 int kvc_get_decode_chunk(const kvc_config* cfg, int* tokens);
 
-/* kvc_paged_decode runs the last chunk of a head (or a whole short head) in a second launch,
- * one wavefront per item, when it holds at most this many tokens (host out-param; for a call
- * over all layers; 0 on the fallback path).  Host only.                          */
+/* kvc_paged_decode runs whole heads of at most this many tokens in a second launch, one
+ * wavefront each (host out-param; for a call over all layers; 0 on the fallback path).  Host only. */
 int kvc_get_decode_short(const kvc_config* cfg, int* tokens);
 
 #ifdef __cplusplus

@@ -181,11 +181,15 @@ __device__ __forceinline__ void publish_wait() { asm volatile("s_waitcnt vmcnt(0
 // By the 16 lanes of a group, one or two of them: the rows of both are asked for before the first is stored.
 // What moves is not looked at again by its launch, so the stores pass the caches by, and in large pools the
 // loads do.  Block compactions of 1024 heads of 500 tokens to 16384 of 1024 (0.3 to 8.6 GB of KVs) that lose 10
-// or 30 % of their blocks, on caches filled with something else: one KV at a time with plain accesses 71 (128 x 4
+// or 30 % of their blocks, on caches filled with something else (a model's weights pass through them between two rounds): one KV at a time with plain accesses 71 (128 x 4
 // x 8 heads of 400 tokens), 150 (64 x 32 x 8 of 300), 423 and 953 us (64 x 32 x 8 of 1024); two at a time with
 // plain ones 70, 147, 416 and 929; stores with the hint 69, 150, 412 and 890; both 58, 119, 372 and 731.  Where
 // most of what moves is still in the 256 MB behind the L2s, loads with the hint lose: 512 heads of 1005
 // tokens run again on the same cache 43, 46, 41 and 52 us, 2048 of 1024 80, 76, 60 and 81, 16384 of 300 (2.5 GB) 120, 118, 111 and 117.
+// The pool decides, not what it holds: the same round on other caches, right after a decode and again, with the hint
+// and without, 1024 heads of 1000 tokens (0.5 GB) 72 and 93, 68 and 69, 68 and 53 us; 4096 (1.9 GB) 107 and 143, 100
+// and 102, 102 and 92; 10240 (4.7 GB) 229 and 245, 217 and 223, 217 and 221.  A large pool with little in it loses only
+// where a compaction follows another.
 struct Pool { char* kc; char* vc; float* metric; int32_t* pos; size_t row_bytes; bool large; };
 constexpr size_t kLargePool = (size_t)2 << 30;
 __device__ __forceinline__ Pool pool_of(const Dims& D, char* kc, char* vc, float* metric, int32_t* pos) {

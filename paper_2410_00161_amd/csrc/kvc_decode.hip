@@ -1214,7 +1214,7 @@ static bool choose_chunk(const Dims& D, int gsel, int* T_out, size_t* lds_out, b
   if (!knob && groups > 2)
     while (T_fits > 1024 && decode_lds_bytes(T_fits, D.r, D.d, D.b, kDecodeWaves, mf) > kLdsUnits / groups * kLdsUnit) T_fits -= 64;
   // ... but not where rows then need two chunks that do not all have places, and whole ones do (512 heads of 3210 KVs,
-  // r = 8, d = 128, fp8: 105 us in halves, whole 94; 512 of 3400, d = 64, bf16: 106 and 88)
+  // r = 8, d = 128, fp8: 109 us in halves, whole 100; 512 of 3300, d = 64, bf16: 104 and 85)
   const long long row_tokens = (long long)D.maxb * D.b;
   if (row_tokens > T_fits && row_tokens <= T_two && gsel <= 2 * kCus && 2 * gsel > groups * kCus) T_fits = T_two;
   bool shrunk = false, device_side = false;
@@ -1359,7 +1359,7 @@ static int decode_args_check(const kvc_config* cfg, const kvc_state* st, const v
   return KVC_OK;
 }
 
-// plan_mode 0: an ordinary call (work list, chunks, combine).  1: only the work lists, one per
+// plan_mode 0: an ordinary call (work list, chunks).  1: only the work lists, one per
 // layer, kept in the workspace (q and out are not looked at).  2: layer `layer_begin` from its kept list.
 enum { PLAN_NONE = 0, PLAN_BUILD = 1, PLAN_USE = 2 };
 constexpr size_t kPlanRowChunk = 256;
@@ -1474,8 +1474,8 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
 }
 
 // ---- the decode for callers that cannot allocate --------------------------------------------
-// The temporaries of kvc_paged_decode (work items, per-chunk partial results, the 16-bit exps of
-// split heads) in a fixed array of this library's own instead of a caller's workspace.  Every
+// The temporaries of kvc_paged_decode (work items, per-chunk partial results, the exps of chunks
+// that left their head) in a fixed array of this library's own instead of a caller's workspace.  Every
 // GPU holds its own copy of the array at its own address; host code never uses the array's name
 // as an address, only what hipGetSymbolAddress returned for the device that is current.
 static __device__ __align__(256) unsigned char scratch[KVC_STATIC_SCRATCH_BYTES];

@@ -30,7 +30,7 @@ def pick_heads(ctx, chunk, n_random, seed):
 @pytest.fixture
 def forced_chunk(request):
     """0 = the library's own choice (what bench.py times); otherwise a shorter chunk so that long
-    heads are split over several workgroups and finished by the combine kernel."""
+    heads are split over several workgroups, which finish them together."""
     B.kvc_set_decode_chunk(request.param)
     yield request.param
     B.kvc_set_decode_chunk(0)
@@ -197,8 +197,8 @@ def test_llama8b_shape_rank_schedule_on_one_sequence():
 @pytest.mark.parametrize("forced_chunk", [0, 1024], indirect=True)
 def test_llama70b_shape_long_heads_sampled(forced_chunk):
     """One sequence of the 70B shape (80 layers x 8 KV heads, groups of 8 query heads, 131072
-    prompt tokens, mean 8x): heads of up to 131 K tokens are split into 52 chunks at the default
-    chunk length and into 128 with the forced one, past what the combine kernel keeps in LDS.
+    prompt tokens, mean 8x): heads of up to 131 K tokens are split into 38 chunks at the default
+    chunk length and into 128 with the forced one.
     The longest, the shortest and a few random head instances are recomputed by the oracle."""
     from paper_2410_00161_amd.session import KvcSession
     print(f"[case] llama70b shape, one sequence, chunk setting {forced_chunk}", flush=True)
