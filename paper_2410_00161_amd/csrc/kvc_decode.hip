@@ -799,10 +799,8 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     }
   }
   if (!single && tid == 0) {
-    auto count = [&]() { return A.packed ? seen >> kMeetBits : seen; };
-    auto all = [&]() { return count() == (uint32_t)nch; };
+    auto all = [&]() { return (A.packed ? seen >> kMeetBits : seen) == (uint32_t)nch; };
     for (int looks = 1; looks < kMeetStarts && !all(); ++looks) seen = (uint32_t)published_i32(started);
-    if (count() > (uint32_t)nch) argument_error();
     s_say[0] = all();
 #pragma unroll
     for (int hh = 0; hh < R; ++hh)   // (the sum's sign says that the chunk does not wait)
@@ -878,7 +876,8 @@ __global__ void __launch_bounds__(NW * 64, decode_waves(ESZ, HD, R, B16, NW)) de
     }
     __syncthreads();
     auto look_back = [&]() {
-      if (w == 0 && (was >= begun || begun > (uint32_t)nch || !came)) argument_error();
+      const uint32_t most = (uint32_t)nch;
+      if (w == 0 && (was >= begun || begun > most || (A.packed ? seen >> kMeetBits : seen) > most || !came)) argument_error();
     };
     if (!s_say[1]) { look_back(); return; }   // (its part is out: the others see to it)
     // ---- every chunk of the head has arrived ----

@@ -29,7 +29,6 @@ struct DecodeArgs {
   int l0, nl, gsel;       // first layer, layer count, head instances selected
   int accumulate, T;      // metric on/off, chunk tokens (the most a chunk may hold when adapt_T is set)
   int adapt_T;            // the one-launch work list picks the chunk length from the lengths it sees (see there)
-  int places;             // workgroups of four wavefronts that the chip runs at once (where a list's chunks are to fit them)
   int log2b;              // block size is a power of two on the tiled path
   int cap;                // item records and partial-result slots the workspace holds
   int all_partials;       // give every head a partial-result slot range, not only split heads (else the chunks of a split
@@ -47,11 +46,13 @@ struct DecodeArgs {
   int plan;               // the work-list kernel runs one workgroup per layer; a decode reads one layer's list
   int plan_stride;        // records of a layer's stretch; 0: it starts where its header block says
   int plan_cap;           // records of all layers the workspace holds
-  int packed;             // rows of fewer than kMeetMost chunks: a head's counts of chunks are halves of one word
   int self_list;          // no work list: every workgroup finds its own item from the lengths (at most kSelfListHeads heads)
   int ctx_plus;           // the plan is made for heads ctx_plus tokens longer than they are now
   int32_t* status;        // the workspace's own header (status word), whatever `header` points at
   float scale_log2;       // log2(e) / sqrt(d)
+  // (at the end: in front of the others they moved these to other lines, and a layer's call took 0.2 us more)
+  int packed;             // rows of fewer than kMeetMost chunks: a head's counts of chunks are halves of one word
+  int places;             // workgroups of four wavefronts that the chip runs at once (where a list's chunks are to fit them)
 };
 
 __device__ __forceinline__ int sel_to_g(const Dims& D, int l0, int nl, int gi) {
