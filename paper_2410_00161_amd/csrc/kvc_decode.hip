@@ -1432,6 +1432,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   auto items_of_rows = [&](size_t chunk) { return std::min(bound_pool, (size_t)A.gsel * (((size_t)D.maxb * D.b + chunk - 1) / chunk)); };
   const size_t grid = items_of_rows(A.adapt_T ? (size_t)kSmallCallChunk : (size_t)T);
   if (grid > 0x7fffffffull) return KVC_ERR_UNSUPPORTED;   // before anything is launched: the work list stays clean
+  const int list_threads = (A.gsel + 63) & ~63;   // of a one-launch list: a thread per head
   if (plan_mode != PLAN_NONE) {
     // Rows with far more room than the pool can fill have no lists: every layer's launch is as large as
     // full rows would need, and nearly all of it would be empty.  (Lists of chunks of kPlanRowChunk for
@@ -1448,7 +1449,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
     A.header = W.plan_hdr;
     if (plan_mode == PLAN_BUILD) {
       A.out = nullptr;    // (the zero rows of heads without a KV are written when the layer is decoded)
-      hipLaunchKernelGGL(decode_worklist_small_kernel<true>, dim3(D.Lyr), dim3(1024), 0, s, A);
+      hipLaunchKernelGGL(decode_worklist_small_kernel<true>, dim3(D.Lyr), dim3(list_threads), 0, s, A);
       KVC_LAUNCH_CHECK();
       return KVC_OK;
     }
@@ -1458,7 +1459,7 @@ static int paged_decode_impl(const kvc_config* cfg, const kvc_state* st, const v
   } else if (small_call && A.gsel <= kSelfListHeads && A.packed) {
     A.self_list = 1;
   } else if (A.gsel <= kSmallWorklistHeads) {
-    hipLaunchKernelGGL(decode_worklist_small_kernel<false>, dim3(1), dim3(1024), 0, s, A);
+    hipLaunchKernelGGL(decode_worklist_small_kernel<false>, dim3(1), dim3(list_threads), 0, s, A);
     KVC_LAUNCH_CHECK();
   } else {
     hipLaunchKernelGGL(decode_count_kernel, dim3((A.gsel + 255) / 256), dim3(256), 0, s, A);

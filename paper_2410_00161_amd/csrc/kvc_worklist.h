@@ -266,7 +266,7 @@ static __global__ void __launch_bounds__(1024) decode_worklist_small_kernel(Deco
   if (placed) {
     const int per = layer * A.D.Hk;
     unsigned long long t = 0;
-    for (int i = tid; i < A.D.S * per; i += 1024) {
+    for (int i = tid; i < A.D.S * per; i += (int)blockDim.x) {
       const int s = i / per;
       t += (unsigned long long)max(A.ctx[(size_t)s * A.D.Lyr * A.D.Hk + (i - s * per)] + A.ctx_plus, 0);
     }
