@@ -212,9 +212,11 @@ int kvc_paged_decode(const kvc_config* cfg, const kvc_state* st, const void* q, 
  * results as kvc_paged_decode over that layer).  ctx_plus = 0: the lists are for the heads as
  * they are now; 1: for every head one token longer than now, i.e. planned before the step's
  * kvc_append calls (layer by layer, each before its layer's decode).  The lists stay valid
- * until a context length changes in any other way (compaction, free, preemption, a second
- * append): a layer decoded from a stale list does nothing for the heads that changed and leaves
- * KVC_ERR_ARG in the status word (kvc_poll_status; the cache state is not touched).
+ * until another call makes a list of its own in the workspace (kvc_paged_decode of more than 64
+ * heads, the window and block metrics), another config uses it, or a context length changes in
+ * any other way (compaction, free, preemption, a second append).  Of changed lengths the decode
+ * can tell: it does nothing for the heads that changed and leaves KVC_ERR_ARG in the status word
+ * (kvc_poll_status; the cache state is not touched).
  * Covers what kvc_paged_decode runs on its tiled kernels with at most 1024 head instances per
  * layer and the library's own chunk length, unless the rows have far more room than the pool can
  * fill: with H = num_seqs * num_kv_heads heads a layer, num_layers * min(H * ceil(row tokens / 256),
